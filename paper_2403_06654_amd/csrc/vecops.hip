@@ -5,6 +5,7 @@
 // precision, reduce within the block in a fixed tree (wave shuffles, then
 // LDS across the four waves) and finish in a single-block kernel that adds
 // the per-block partials in block order.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include "spectral.hpp"
@@ -25,10 +26,28 @@ static int nblk(size_t n) {
   return (int)(b < 1 ? 1 : (b > (size_t)kRedBlocks ? kRedBlocks : b));
 }
 
+// v plus the value that the DPP pattern CTRL brings to this lane (0 where it
+// brings none, and in the rows that ROWS leaves out)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double add_dpp(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, true);
+  return v + __hiloint2double(hi, lo);
+}
+// Sum over the wavefront (all 64 lanes active), returned in every lane: row
+// shifts by 1, 2, 4, 8 leave each 16-lane row's sum in its last lane, two row
+// broadcasts carry them to lane 63.  A fixed tree on the vector ALU: the same
+// tree through LDS permutes costs two LDS round trips per step, which the
+// latency-bound reductions of small fields feel.
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  v = add_dpp<0x111, 0xf>(v);  // row_shr:1
+  v = add_dpp<0x112, 0xf>(v);  // row_shr:2
+  v = add_dpp<0x114, 0xf>(v);  // row_shr:4
+  v = add_dpp<0x118, 0xf>(v);  // row_shr:8
+  v = add_dpp<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+  v = add_dpp<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
+                          __builtin_amdgcn_readlane(__double2loint(v), 63));
 }
 
 // Reduce acc[0..K) across a 256-thread block; value i of block b goes to
@@ -56,15 +75,30 @@ __device__ __forceinline__ void block_store(const double* acc, int k_used, doubl
 // powers of two), so the kx = 0 test is a mask, not a 64-bit division
 __device__ __forceinline__ double spec_w(size_t e, int M) { return (e & (size_t)(M - 1)) == 0 ? 1.0 : 2.0; }
 
-// One wave per output value; lanes stride over the block partials in a
-// fixed order, then a fixed shuffle tree.  No block-wide barrier.
+// Sum of one value's nblk <= kRedBlocks block partials by one wavefront, in a
+// fixed order: lanes stride over them, then the wavefront's tree.  Every lane
+// issues all its loads before the first addition.  A loop that added each
+// partial as it arrived paid up to sixteen dependent load latencies: on 1024
+// partials of 9-16 values k_gs_prep took 6.8 us (4.5 now) and k_gs_check 9.4 us
+// (5.2 now).
+__device__ __forceinline__ double sum_partials(const double* __restrict__ p, int nblk) {
+  constexpr int Q = kRedBlocks / 64;
+  const int lane = threadIdx.x & 63;
+  double v[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) v[q] = lane + 64 * q < nblk ? p[lane + 64 * q] : 0.0;
+  double s = v[0];
+#pragma unroll
+  for (int q = 1; q < Q; ++q) s += v[q];
+  return wave_sum(s);
+}
+
+// One wave per output value (a 1024-thread block).  No block-wide barrier.
 __device__ __forceinline__ void reduce_values(const double* __restrict__ partial, int nblk, int K, double scale,
                                               double* __restrict__ out) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   for (int i = w; i < K; i += 16) {
-    double v = 0.0;
-    for (int b = lane; b < nblk; b += 64) v += partial[(size_t)i * kRedBlocks + b];
-    v = wave_sum(v);
+    const double v = sum_partials(partial + (size_t)i * kRedBlocks, nblk);
     if (lane == 0) out[i] = v * scale;
   }
 }
@@ -108,9 +142,7 @@ __global__ __launch_bounds__(1024) void k_reduce(const double* __restrict__ part
   __shared__ double val[2];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   for (int i = w; i < K; i += 16) {
-    double v = 0.0;
-    for (int b = lane; b < nblk; b += 64) v += partial[(size_t)i * kRedBlocks + b];
-    v = wave_sum(v) * scale;
+    const double v = sum_partials(partial + (size_t)i * kRedBlocks, nblk) * scale;
     if (lane == 0) {
       out[i] = v;
       if (i < 2) val[i] = v;
@@ -292,56 +324,59 @@ __global__ __launch_bounds__(1024) void k_gs_prep(DevStates S, int nv, int nb, d
   }
 }
 
-// Orthogonality check of the first pass, then the Givens rotations of GMRES
-// on the new Hessenberg column j = nv - 1 (the second pass, if any, changes
-// only w, not H).
-__global__ __launch_bounds__(1024) void k_gs_check(DevStates S, int nv, double tol, int nb, double scale) {
-  DevState* st = S.st[blockIdx.y];
-  const double* __restrict__ partial = S.partial[blockIdx.y];
-  __shared__ double val[kMaxVec + 2];
-  __shared__ double hc[kMaxVec + 1], csl[kMaxRestart], snl[kMaxRestart];
-  if (st->halt) {  // a step queued past the end of the cycle: no second pass either
-    if (threadIdx.x == 0) st->reorth = 0;
-    return;
-  }
-  reduce_values(partial, nb, nv + 1, scale, val);
-  __syncthreads();
-  if (threadIdx.x >= 64) return;  // one wavefront from here on
-  const int lane = threadIdx.x, j = nv - 1;
-  double c = 0.0, h = 0.0, v = 0.0;
-  if (lane <= nv) st->red[lane] = val[lane];
+// Orthogonality check of the first pass, taken by one wavefront with lane i on
+// basis vector i (val: the reduced dots (V_i, w') and, at nv, ||w'||^2).
+struct GsCheck {
+  double h, v;   // this lane's first-pass coefficient and vector scale
+  double csel;   // its second-pass coefficient (0: the vector passed the test)
+  double hn;     // norm of the orthogonalised vector
+  bool orth;     // no second pass needed
+  bool finite;
+};
+__device__ __forceinline__ GsCheck gs_check(const DevState* st, const double* val, int nv, double tol) {
+  const int lane = threadIdx.x & 63;
+  GsCheck k;
+  double c = 0.0;
+  k.h = k.v = 0.0;
   if (lane < nv) {
-    v = st->vs[lane];
-    h = st->hcol[lane];
-    c = v * val[lane];
+    k.v = st->vs[lane];
+    k.h = st->hcol[lane];
+    c = k.v * val[lane];
   }
+  const double n2 = val[nv];
+  const double thr = tol * sqrt(n2);
+  k.orth = n2 > 0.0 && wave_max(fabs(c)) <= thr;
+  // The second pass subtracts only the components that fail the test: the
+  // others already meet the tolerance accepted when no second pass runs.
+  // (n2 <= 0 selects every nonzero component.)
+  k.csel = (!k.orth && lane < nv && !(fabs(c) <= thr)) ? c : 0.0;
+  const double h2 = n2 - wave_sum(k.csel * k.csel);
+  // wave_max drops NaN, and a NaN norm would read as a lucky breakdown
+  k.finite = isfinite(n2) && isfinite(wave_sum(c * c));
+  k.hn = k.orth ? sqrt(n2) : (h2 > 0.0 ? sqrt(h2) : 0.0);
+  return k;
+}
+
+// The Givens rotations of GMRES on the new Hessenberg column j = nv - 1 (the
+// second pass, if any, changes only w, not H) and the stopping test of the
+// host loop, taken here so that the next step, when already queued, exits at
+// its gates.  One full wavefront; hc, csl, snl: its LDS scratch.
+__device__ __forceinline__ void gs_givens(DevState* st, const GsCheck& k, int nv, double* hc, double* csl,
+                                          double* snl) {
+  const int lane = threadIdx.x & 63, j = nv - 1;
   if (lane < j) {
     csl[lane] = st->cs[lane];
     snl[lane] = st->sn[lane];
   }
-  const double n2 = val[nv];
-  const double thr = tol * sqrt(n2);
-  const bool orth = n2 > 0.0 && wave_max(fabs(c)) <= thr;
-  // The second pass subtracts only the components that fail the test: the
-  // others already meet the tolerance accepted when no second pass runs.
-  // (n2 <= 0 selects every nonzero component.)
-  const double csel = (!orth && lane < nv && !(fabs(c) <= thr)) ? c : 0.0;
-  const double h2 = n2 - wave_sum(csel * csel);
-  // wave_max drops NaN, and a NaN norm would read as a lucky breakdown
-  const bool finite = isfinite(n2) && isfinite(wave_sum(c * c));
-  const double hn = orth ? sqrt(n2) : (h2 > 0.0 ? sqrt(h2) : 0.0);
-  if (lane < nv) {
-    st->ccol[lane] = csel;
-    st->coef[lane] = csel * v;
-    hc[lane] = h + csel;  // Hessenberg column before rotation
-  }
+  if (lane < nv) hc[lane] = k.h + k.csel;  // Hessenberg column before rotation
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   if (lane != 0) return;
-  if (!finite) st->bad = 1;
-  st->reorth = orth ? 0 : 1;
-  if (!orth) st->nreorth += 1;
+  const double hn = k.hn;
+  if (!k.finite) st->bad = 1;
+  st->reorth = k.orth ? 0 : 1;
+  if (!k.orth) st->nreorth += 1;
   st->hn = hn;
   st->vs[nv] = hn > 0.0 ? 1.0 / hn : 0.0;
   // previous rotations, in order, then the new one
@@ -368,9 +403,29 @@ __global__ __launch_bounds__(1024) void k_gs_check(DevStates S, int nv, double t
   st->g[j] = cr * gj;
   st->resid = fabs(sr * gj);
   if (!isfinite(rr) || !isfinite(sr * gj)) st->bad = 1;
-  // the stopping test of the host loop, taken here so that the next step,
-  // when already queued, exits at its gates
   if (st->bad || st->resid / st->stop_bnorm <= st->stop_rtol || j >= st->jlast) st->halt = 1;
+}
+
+__global__ __launch_bounds__(1024) void k_gs_check(DevStates S, int nv, double tol, int nb, double scale) {
+  DevState* st = S.st[blockIdx.y];
+  const double* __restrict__ partial = S.partial[blockIdx.y];
+  __shared__ double val[kMaxVec + 2];
+  __shared__ double hc[kMaxVec + 1], csl[kMaxRestart], snl[kMaxRestart];
+  if (st->halt) {  // a step queued past the end of the cycle: no second pass either
+    if (threadIdx.x == 0) st->reorth = 0;
+    return;
+  }
+  reduce_values(partial, nb, nv + 1, scale, val);
+  __syncthreads();
+  if (threadIdx.x >= 64) return;  // one wavefront from here on
+  const int lane = threadIdx.x;
+  const GsCheck k = gs_check(st, val, nv, tol);
+  if (lane <= nv) st->red[lane] = val[lane];
+  if (lane < nv) {
+    st->ccol[lane] = k.csel;
+    st->coef[lane] = k.csel * k.v;
+  }
+  gs_givens(st, k, nv, hc, csl, snl);
 }
 
 template <typename R, int NV>
@@ -454,6 +509,250 @@ __global__ __launch_bounds__(256) void k_gs_reorth(SysSet<R> S, int nv, size_t n
   }
 }
 
+// ---- The same step on small fields: three launches instead of five.
+//
+// Up to kFoldElems elements (64^3, 512^2) a step moves a few MB that sit in
+// the caches, and its time is launches and dependent load latencies.  So a
+// block takes 256 elements, its wavefronts split the vectors between them (H
+// groups of four wavefronts, NVH vectors each) and every thread has all its
+// loads in flight at once.  The blocks are few enough (kFoldBlocks) that each
+// block of the update and of the second pass reduces all the block partials
+// of the pass before it by itself, some KB from L2, instead of waiting for a
+// launch that does so: k_gs_prep runs inside k_gs_update_s, and k_gs_check
+// with the second pass inside k_gs_finish (block 0 writes the state).  Larger
+// fields keep the kernels above: they are bound by the basis stream, and their
+// up to 1024 partials per value are too many to reduce in every block.
+// The dots and the check dots alternate between two halves of each partial
+// row, because blocks of one launch read the first while others write the second.
+// Measured per launch, before -> now (rocprofv3, median over a solve):
+//   32^3 FP64, 9-16 vectors: dots 14.6 -> 4.3 us, update with k_gs_prep 12.2 +
+//     3.8 -> 5.7 us, check with second pass 4.6 + 1.7 -> 6.1 us;
+//   101 x 64 slots FP32, 5-8 vectors: 9.1 -> 3.8, 7.6 + 1.8 -> 5.0 and
+//     3.9 + 1.8 -> 4.6 us.
+constexpr size_t kFoldElems = 131072;
+constexpr int kFoldBlocks = 256;
+constexpr int kFoldHalf = kRedBlocks / 2;
+static bool folds(size_t n) { return n <= kFoldElems; }
+static int fold_blocks(size_t n) { return (int)std::min<size_t>((n + 255) / 256, kFoldBlocks); }
+
+// val[0..K) = the sums of the block partials (nb <= kFoldBlocks each), by all
+// NW wavefronts of the block; ends with a block barrier.
+template <int KMAX, int NW>
+__device__ __forceinline__ void fold_reduce(const double* __restrict__ partial, int nb, int K, double scale,
+                                            double* val) {
+  constexpr int PW = (KMAX + NW - 1) / NW, Q = kFoldBlocks / 64;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double v[PW];
+#pragma unroll
+  for (int p = 0; p < PW; ++p) {
+    v[p] = 0.0;
+    const int i = w + NW * p;
+    if (i < K) {
+      const double* src = partial + (size_t)i * kRedBlocks;
+      double t[Q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) t[q] = lane + 64 * q < nb ? src[lane + 64 * q] : 0.0;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) v[p] += t[q];
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < PW; ++p) {
+    const double t = wave_sum(v[p]);
+    if (lane == 0 && w + NW * p < K) val[w + NW * p] = t * scale;
+  }
+  __syncthreads();
+}
+
+// Dots of split h's vectors (acc), and with NORM split 0's acc[NVH], to the
+// block partials of this block (value nv: the norm).
+template <int NVH, int H, bool NORM>
+__device__ __forceinline__ void fold_store(const double* acc, int nv, double* partial) {
+  constexpr int K = NVH + (NORM ? 1 : 0);
+  __shared__ double sh[4 * H][K];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+  for (int q = 0; q < K; ++q) {
+    const double t = wave_sum(acc[q]);
+    if (lane == 0) sh[w][q] = t;
+  }
+  __syncthreads();
+  const int i = threadIdx.x;
+  if (i < nv + (NORM ? 1 : 0)) {
+    const int h = i == nv ? 0 : i / NVH, q = i == nv ? NVH : i - h * NVH;
+    const double(*p)[K] = sh + 4 * h;
+    partial[(size_t)i * kRedBlocks + blockIdx.x] = ((p[0][q] + p[1][q]) + p[2][q]) + p[3][q];
+  }
+}
+
+template <typename R, int NVH, int H>
+__global__ __launch_bounds__(256 * H) void k_mdot_s(SysSet<R> S, int nv, size_t n, int M) {
+  const int sy = blockIdx.y;
+  const int* gate = S.gate[sy];
+  if (gate && *gate) return;
+  const C2<R>* __restrict__ x = S.x[sy];
+  const int i0 = NVH * __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);  // the split's first vector
+  const void* const* V = S.V[sy].p + i0;
+  const int nvh = nv - i0;
+  double acc[NVH];
+#pragma unroll
+  for (int i = 0; i < NVH; ++i) acc[i] = 0.0;
+  for (size_t e = (size_t)blockIdx.x * 256 + (threadIdx.x & 255); e < n; e += (size_t)gridDim.x * 256) {
+    C2<R> vv[NVH];
+    const C2<R> xv = ldg(x + e);
+#pragma unroll
+    for (int i = 0; i < NVH; ++i)
+      if (i < nvh) vv[i] = ldg((const C2<R>*)V[i] + e);
+    const double w = spec_w(e, M);
+    const double xr = xv.x, xi = xv.y;
+#pragma unroll
+    for (int i = 0; i < NVH; ++i)
+      if (i < nvh) acc[i] += w * ((double)vv[i].x * xr + (double)vv[i].y * xi);
+  }
+  fold_store<NVH, H, false>(acc, nv, S.partial[sy]);
+}
+
+// w' = w - sum_i h_i v_i with its check dots; the dots of k_mdot_s are reduced
+// here.  Every split forms its part of the sum; they meet in LDS.
+template <typename R, int NVH, int H>
+__global__ __launch_bounds__(256 * H) void k_gs_update_s(SysSet<R> S, int nv, size_t n, int M, double scale) {
+  const int sy = blockIdx.y;
+  DevState* st = S.st[sy];
+  if (st->halt) return;
+  C2<R>* __restrict__ x = S.x[sy];
+  double* partial = S.partial[sy];
+  __shared__ double val[NVH * H], cl[NVH * H];
+  __shared__ C2<double> part[H > 1 ? H : 1][H > 1 ? 256 : 1];
+  const int h = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), i0 = NVH * h, te = threadIdx.x & 255;
+  const void* const* V = S.V[sy].p + i0;
+  const int nvh = nv - i0;
+  const size_t stride = (size_t)gridDim.x * 256, b0 = (size_t)blockIdx.x * 256;
+  C2<R> vv[NVH], xv;
+  auto load = [&](size_t e) {
+    xv = C2<R>{R(0), R(0)};
+#pragma unroll
+    for (int i = 0; i < NVH; ++i) vv[i] = C2<R>{R(0), R(0)};
+    if (e >= n) return;
+    xv = ldg(x + e);
+#pragma unroll
+    for (int i = 0; i < NVH; ++i)
+      if (i < nvh) vv[i] = ldg((const C2<R>*)V[i] + e);
+  };
+  load(b0 + te);  // the first elements' loads overlap the reduction
+  fold_reduce<NVH * H, 4 * H>(partial, gridDim.x, nv, scale, val);
+  if ((int)threadIdx.x < NVH * H) {
+    const int i = threadIdx.x;
+    double c = 0.0;
+    if (i < nv) {
+      const double v = st->vs[i], hh = v * val[i];
+      c = hh * v;
+      if (blockIdx.x == 0) {
+        st->red2[i] = val[i];
+        st->hcol[i] = hh;
+      }
+    }
+    cl[i] = c;
+  }
+  __syncthreads();
+  double acc[NVH + 1];
+#pragma unroll
+  for (int i = 0; i <= NVH; ++i) acc[i] = 0.0;
+  for (size_t b = b0; b < n; b += stride) {  // the same trips for every thread of the block
+    const size_t e = b + te;
+    if (b != b0) load(e);
+    double sr = 0.0, si = 0.0;
+#pragma unroll
+    for (int i = 0; i < NVH; ++i) {
+      const double c = cl[i0 + i];
+      sr += c * (double)vv[i].x;
+      si += c * (double)vv[i].y;
+    }
+    if constexpr (H > 1) {
+      if (b != b0) __syncthreads();  // the last trip's sums have been read
+      part[h][te] = C2<double>{sr, si};
+      __syncthreads();
+      sr = si = 0.0;
+#pragma unroll
+      for (int q = 0; q < H; ++q) {
+        sr += part[q][te].x;
+        si += part[q][te].y;
+      }
+    }
+    const C2<R> nx{R((double)xv.x - sr), R((double)xv.y - si)};
+    // every split has loaded this x before the barrier above
+    if (h == 0 && e < n) stg(x + e, nx);
+    const double w = spec_w(e, M);
+    const double yr = nx.x, yi = nx.y;
+#pragma unroll
+    for (int i = 0; i < NVH; ++i) acc[i] += w * ((double)vv[i].x * yr + (double)vv[i].y * yi);
+    acc[NVH] += w * (yr * yr + yi * yi);  // 0 past the end
+  }
+  fold_store<NVH, H, true>(acc, nv, partial + kFoldHalf);
+}
+
+// The orthogonality check in every block, the second pass over the vectors
+// that failed it, and in block 0 the Givens rotations and the stopping test.
+// (A block that starts after block 0 has set halt skips its part of the second
+// pass: the vector that ends a cycle is never read.)
+template <typename R, int NV>
+__global__ __launch_bounds__(256) void k_gs_finish(SysSet<R> S, int nv, size_t n, double tol, double scale) {
+  const int sy = blockIdx.y;
+  DevState* st = S.st[sy];
+  __shared__ double val[NV + 1], cl[NV];
+  __shared__ double hc[kMaxVec + 1], csl[kMaxRestart], snl[kMaxRestart];
+  __shared__ int again;
+  if (st->halt) return;
+  fold_reduce<NV + 1, 4>(S.partial[sy] + kFoldHalf, gridDim.x, nv + 1, scale, val);
+  GsCheck k{};
+  if (threadIdx.x < 64) {
+    k = gs_check(st, val, nv, tol);
+    if ((int)threadIdx.x < nv) cl[threadIdx.x] = k.csel * k.v;
+    if (threadIdx.x == 0) again = !k.orth;
+  }
+  __syncthreads();
+  if (again) {
+    C2<R>* __restrict__ x = S.x[sy];
+    const VecPtrs& V = S.V[sy];
+    for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (size_t)gridDim.x * 256) {
+      const C2<R> xv = ldg(x + e);
+      double xr = xv.x, xi = xv.y;
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        if (i < nv && cl[i] != 0.0) {
+          const C2<R> v = ldg((const C2<R>*)V.p[i] + e);
+          xr -= cl[i] * (double)v.x;
+          xi -= cl[i] * (double)v.y;
+        }
+      }
+      stg(x + e, C2<R>{R(xr), R(xi)});
+    }
+  }
+  if (blockIdx.x != 0 || threadIdx.x >= 64) return;
+  const int lane = threadIdx.x;
+  if (lane <= nv) st->red[lane] = val[lane];
+  if (lane < nv) {
+    st->ccol[lane] = k.csel;
+    st->coef[lane] = k.csel * k.v;
+  }
+  gs_givens(st, k, nv, hc, csl, snl);
+}
+
+template <typename R, int NVH, int H>
+static void launch_gs_small(const Geom& g, const SysSet<R>& S, int nsys, int nv, hipStream_t s, Prof* prof) {
+  const size_t n = nspec(g);
+  const dim3 gr(fold_blocks(n), nsys);
+  const bool pr = prof && prof->on;
+  const double fb = (double)n * sizeof(C2<R>) * nsys;
+  if (pr) prof->begin(10, s, (nv + 1) * fb);
+  hipLaunchKernelGGL((k_mdot_s<R, NVH, H>), gr, dim3(256 * H), 0, s, S, nv, n, g.M);
+  if (pr) prof->end(s);
+  if (pr) prof->begin(11, s, (nv + 2) * fb);
+  hipLaunchKernelGGL((k_gs_update_s<R, NVH, H>), gr, dim3(256 * H), 0, s, S, nv, n, g.M, g.ntot_inv);
+  if (pr) prof->end(s);
+  hipLaunchKernelGGL((k_gs_finish<R, NVH * H < kMaxVec ? NVH * H : kMaxVec>), gr, dim3(256), 0, s, S, nv, n,
+                     orth_tol<R>(), g.ntot_inv);
+}
+
 template <typename R, int NV>
 static void launch_gs(const Geom& g, const SysSet<R>& S, int nsys, int nv, int second, hipStream_t s) {
   const dim3 gr(nblk(nspec(g)), nsys);
@@ -466,6 +765,14 @@ static void launch_gs(const Geom& g, const SysSet<R>& S, int nsys, int nv, int s
 // its own halt flag is set.
 template <typename R>
 static void gs_orthogonalize_set(const Geom& g, const SysSet<R>& S, int nsys, int nv, hipStream_t s, Prof* prof) {
+  if (folds(nspec(g))) {
+    if (nv <= 4) launch_gs_small<R, 4, 1>(g, S, nsys, nv, s, prof);
+    else if (nv <= 8) launch_gs_small<R, 8, 1>(g, S, nsys, nv, s, prof);
+    else if (nv <= 16) launch_gs_small<R, 8, 2>(g, S, nsys, nv, s, prof);
+    else if (nv <= 24) launch_gs_small<R, 8, 3>(g, S, nsys, nv, s, prof);
+    else launch_gs_small<R, 9, 4>(g, S, nsys, nv, s, prof);
+    return;
+  }
   const bool pr = prof && prof->on;
   const double fb = (double)nspec(g) * sizeof(C2<R>) * nsys;
   if (pr) prof->begin(10, s, (nv + 1) * fb);
@@ -513,7 +820,10 @@ void gs_orthogonalize_batch(const Geom& g, void* const* w, const VecPtrs* V, int
 
 // ------------------------------------------------------------- lincomb
 
-template <typename R, int NV>
+// ALL: every vector's load in flight at once (small fields, latency-bound:
+// 14.8 -> 6.3 us at 32^3 FP64, 18 vectors); otherwise each load is consumed at
+// once (more wavefronts, for fields that stream from HBM).
+template <typename R, int NV, bool ALL>
 __global__ __launch_bounds__(256) void k_lincomb(C2<R>* __restrict__ z, VecPtrs V, int nv,
                                                  const double* __restrict__ coef, size_t n) {
   double c[NV];
@@ -521,10 +831,16 @@ __global__ __launch_bounds__(256) void k_lincomb(C2<R>* __restrict__ z, VecPtrs 
   for (int i = 0; i < NV; ++i) c[i] = i < nv ? coef[i] : 0.0;
   for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (size_t)gridDim.x * 256) {
     double zr = 0.0, zi = 0.0;
+    C2<R> vv[ALL ? NV : 1];
+    if constexpr (ALL) {
+#pragma unroll
+      for (int i = 0; i < NV; ++i)
+        if (i < nv) vv[i] = ldg((const C2<R>*)V.p[i] + e);
+    }
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       if (i < nv) {
-        C2<R> v = ldg((const C2<R>*)V.p[i] + e);
+        const C2<R> v = ALL ? vv[i] : ldg((const C2<R>*)V.p[i] + e);
         zr += c[i] * (double)v.x;
         zi += c[i] * (double)v.y;
       }
@@ -533,16 +849,18 @@ __global__ __launch_bounds__(256) void k_lincomb(C2<R>* __restrict__ z, VecPtrs 
   }
 }
 
+template <typename R, bool ALL>
+static void launch_lincomb(const Geom& g, void* z, const VecPtrs& V, int nv, const double* coef, hipStream_t s) {
+  const size_t n = nspec(g);
+  const dim3 gr(ALL ? (unsigned)((n + 255) / 256) : (unsigned)nblk(n)), bl(256);
+  if (nv <= 4) hipLaunchKernelGGL((k_lincomb<R, 4, ALL>), gr, bl, 0, s, (C2<R>*)z, V, nv, coef, n);
+  else if (nv <= 16) hipLaunchKernelGGL((k_lincomb<R, 16, ALL>), gr, bl, 0, s, (C2<R>*)z, V, nv, coef, n);
+  else hipLaunchKernelGGL((k_lincomb<R, kMaxVec, ALL>), gr, bl, 0, s, (C2<R>*)z, V, nv, coef, n);
+}
 template <typename R>
 void lincomb(const Geom& g, void* z, const VecPtrs& V, int nv, const double* coef, hipStream_t s) {
-  size_t n = nspec(g);
-  dim3 gr(nblk(n)), bl(256);
-  if (nv <= 4)
-    hipLaunchKernelGGL((k_lincomb<R, 4>), gr, bl, 0, s, (C2<R>*)z, V, nv, coef, n);
-  else if (nv <= 16)
-    hipLaunchKernelGGL((k_lincomb<R, 16>), gr, bl, 0, s, (C2<R>*)z, V, nv, coef, n);
-  else
-    hipLaunchKernelGGL((k_lincomb<R, kMaxVec>), gr, bl, 0, s, (C2<R>*)z, V, nv, coef, n);
+  if (folds(nspec(g))) launch_lincomb<R, true>(g, z, V, nv, coef, s);
+  else launch_lincomb<R, false>(g, z, V, nv, coef, s);
 }
 
 // ---------------------------------------------------------- elementwise
@@ -754,34 +1072,50 @@ void project_range(const Geom& g, void* spec, double* removed, hipStream_t st) {
 
 // ------------------------------------------------------- scalar kernels
 
-__global__ void k_gmres_init(DevState* st, double beta, int m, double bnorm, double rtol, int jlast) {
-  if (threadIdx.x != 0) return;
+// One wavefront (one thread clearing the 1056 entries of H took 6.8 us; 1.7 now).
+__global__ __launch_bounds__(64) void k_gmres_init(DevState* st, double beta, int m, double bnorm, double rtol,
+                                                   int jlast) {
+  const int t = threadIdx.x;
+  for (int i = t; i < (kMaxRestart + 1) * kMaxRestart; i += 64) st->H[i] = 0.0;
+  if (t <= m && t <= kMaxRestart) st->g[t] = t == 0 ? beta : 0.0;
+  if (t <= kMaxRestart) st->vs[t] = t == 0 ? 1.0 / beta : 0.0;
+  if (t != 0) return;
   st->stop_bnorm = bnorm;
   st->stop_rtol = rtol;
   st->jlast = jlast;
   st->halt = 0;
-  for (int i = 0; i < (kMaxRestart + 1) * kMaxRestart; ++i) st->H[i] = 0.0;
-  for (int i = 0; i <= m && i <= kMaxRestart; ++i) st->g[i] = 0.0;
-  st->g[0] = beta;
   st->resid = beta;
   st->bad = 0;
   st->reorth = 0;
-  for (int i = 0; i <= kMaxRestart; ++i) st->vs[i] = 0.0;
-  st->vs[0] = 1.0 / beta;
 }
 
 // Column j of the Hessenberg matrix: the Gram-Schmidt coefficients h (plus
 // the second-pass corrections c when that pass ran); subdiagonal ||w||.
-__global__ void k_gmres_backsolve(DevState* st, int k) {
-  if (threadIdx.x != 0) return;
-  const int ld = ldh();
-  for (int i = k - 1; i >= 0; --i) {
-    double s = st->g[i];
-    for (int l = i + 1; l < k; ++l) s -= st->H[i + l * ld] * st->y[l];
-    const double d = st->H[i + i * ld];
-    st->y[i] = d != 0.0 ? s / d : 0.0;
+// One wavefront, lane i on row i: the triangle goes to LDS with all loads in
+// flight, then column by column (18.8 us with one thread walking it in memory, 6.0 now,
+// at 18 columns).
+__global__ __launch_bounds__(64) void k_gmres_backsolve(DevState* st, int k) {
+  static_assert(kMaxRestart < 64, "one lane per row");
+  __shared__ double H[(kMaxRestart + 1) * kMaxRestart];
+  const int t = threadIdx.x, ld = ldh();
+#pragma unroll 17
+  for (int i = t; i < (kMaxRestart + 1) * kMaxRestart; i += 64)
+    if (i < k * ld) H[i] = st->H[i];
+  double s = t < k ? st->g[t] : 0.0;
+  const double v = t < k ? st->vs[t] : 0.0;
+  __syncthreads();
+  double y = 0.0;
+  for (int l = k - 1; l >= 0; --l) {
+    const double d = H[l + l * ld];
+    const double q = d != 0.0 ? s / d : 0.0;   // meaningful in lane l
+    const double yl = __shfl(q, l, 64);
+    if (t == l) y = yl;
+    if (t < l) s -= H[t + l * ld] * yl;
   }
-  for (int i = 0; i < k; ++i) st->coef[i] = st->y[i] * st->vs[i];  // stored basis is unnormalised
+  if (t < k) {
+    st->y[t] = y;
+    st->coef[t] = y * v;  // stored basis is unnormalised
+  }
 }
 
 __global__ void k_cg_alpha(DevState* st, const int* gate) {

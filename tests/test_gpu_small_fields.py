@@ -1,0 +1,45 @@
+"""GPU GMRES on fields around the size where its Gram-Schmidt step changes
+kernels (131072 spectral slots), against the oracle's GMRES.
+
+Sizes: fewer slots than one block of the small-field kernels holds (256), the
+largest field they take, and the smallest above it.  A density ratio of 25 makes
+the solves run past 24 basis vectors, so every split of the vectors between a
+block's wavefronts is used.  Tolerances: both sides stop at a true relative
+residual of 1e-10, so the solutions agree to 2e-10 times the condition number
+of the preconditioned system, at most the density ratio; CGS with a measured
+check and the oracle's MGS differ by rounding, so the iteration counts by at
+most one."""
+import numpy as np
+import pytest
+
+from tests.gpu_util import rel2, smooth_density, to_dev, to_host
+from oracle import krylov, operators
+from paper_2403_06654_amd import workloads
+
+pytestmark = pytest.mark.gpu
+RATIO = 25.0
+
+
+@pytest.mark.parametrize("shape", [(16, 16), (16, 64), (64, 64, 64), (64, 64, 128)])
+@pytest.mark.parametrize("precision", ["fp64", "fp32_refine"])
+def test_gmres_around_the_small_field_limit(shape, precision):
+    from paper_2403_06654_amd.api import Grid
+    rho = smooth_density(shape, 3, 1.0, RATIO)
+    f = workloads.band_limited(shape, min(shape) // 4, seed=2)
+    b, _ = operators.project_range(-f, operators.nullspace_basis(shape))
+    ref = krylov.gmres(lambda x: operators.apply_pressure(x, rho), b,
+                       lambda r: operators.precond_pressure(r, float(rho.mean())), restart=32, rtol=1e-10,
+                       max_iter=500)
+    g = Grid(shape)
+    g.set_density(to_dev(rho))
+    p, info = g.solve_pressure(to_dev(f), restart=32, precision=precision)
+    p2, _ = g.solve_pressure(to_dev(f), restart=32, precision=precision)
+    g.close()
+    x = to_host(p)
+    assert np.array_equal(x, to_host(p2))
+    rr = np.linalg.norm(operators.apply_pressure(x, rho) - b) / np.linalg.norm(b)
+    assert info["status"] == 0 and rr <= 1.01e-10
+    assert rel2(x, ref["x"]) <= 2e-10 * RATIO
+    if precision == "fp64":
+        assert ref["iterations"] > 24
+        assert abs(info["iterations"] - ref["iterations"]) <= 1
