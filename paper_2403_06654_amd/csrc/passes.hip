@@ -79,16 +79,49 @@ struct Col512 {
   static constexpr int NT = WIDE ? 1024 : (DBL && MODE == COL_P_FIRST ? 256 : 512);
 };
 
-template <int L, typename R, int MODE>
+// Small fields (SM).  Up to kSmallField slots a pass is not bound by memory but
+// by how long one wavefront takes: its dependent loads (halt flag, twiddles,
+// data) and its instructions, four cycles each with nothing else to run on the
+// SIMD (32^3 FP64: 4 to 32 blocks, 5.2-7.9 us a pass against 1.5 us for a
+// launch that returns at its gate).  So the small configuration
+//   - issues the data and twiddle loads before it waits for the halt flag,
+//   - gives a thread 8 points of a column line (4 of a row) and a block few
+//     columns (TC: at least 64 B runs),
+//   - runs the two or three transforms of a pressure pass side by side, one
+//     group of wavefronts each (NG), instead of one after another.
+// 32^3 FP64, before -> now: z-first 5.2 -> 4.4 us, y-inverse 6.3 -> 3.6,
+// x 6.2 -> 4.2, y-forward 7.9 -> 3.8, z-last 6.4 -> 4.0; x pass of a 257 x 512
+// wall grid 7.6 -> 5.5.  Larger fields keep the shapes below, which are chosen
+// for bandwidth: with the limit at 2^20 slots a 64 x 128 x 256 FP32+refine
+// solve took 3481 us instead of 3417 (128^3 FP64 K: 1888 instead of 1953).
+constexpr size_t kSmallField = 131072;
+
+constexpr int col_groups(int mode) {
+  return mode == COL_P_FIRST || mode == COL_P_LAST ? 2 : mode == COL_P_MIDINV || mode == COL_P_MIDFWD ? 3 : 1;
+}
+
+template <int L>
+struct ColSmall {
+  static constexpr int E = 8, T = L / E;
+  static constexpr int TC = L <= 64 ? 64 / T : (L == 128 ? 8 : 4);
+  static constexpr int NTG = T * TC;  // threads per group, a multiple of 64
+};
+// lengths that the small configuration is built for
+constexpr bool col_has_small(int L, int mode) { return L <= 256 || (col_groups(mode) <= 2 && L <= 1024); }
+
+template <int L, typename R, int MODE, bool SM = false>
 struct ColCfg {
+  static constexpr int NG = SM ? col_groups(MODE) : 1;
   static constexpr bool E8 = sizeof(R) == 8 && L < 512 && MODE != COL_P_LAST && MODE != COL_P_MIDFWD;
-  static constexpr int E = L == 512 ? Col512<R, MODE>::E : E8 ? (L >= 8 ? 8 : L) : (L >= 16 ? 16 : L);
+  static constexpr int E = SM ? ColSmall<L>::E
+                              : L == 512 ? Col512<R, MODE>::E : E8 ? (L >= 8 ? 8 : L) : (L >= 16 ? 16 : L);
   static constexpr int T = L / E;
-  static constexpr int NT = L == 512 ? Col512<R, MODE>::NT : 256;  // threads per block
-  static constexpr int TC = NT / T;                      // columns per tile
+  static constexpr int NTG = SM ? ColSmall<L>::NTG : L == 512 ? Col512<R, MODE>::NT : 256;
+  static constexpr int NT = NG * NTG;                    // threads per block
+  static constexpr int TC = NTG / T;                     // columns per tile
 };
 
-template <int L, typename R>
+template <int L, typename R, bool SM = false>
 struct RowCfg {
   // 8 points per thread: the x pass keeps a field's inverse and forward
   // transforms plus the half-length pre/post-processing live at once, and
@@ -96,7 +129,8 @@ struct RowCfg {
   // FP32 rows too: at 256^3 (128-point rows) 16 points per thread took the
   // pressure x pass 126 us and the Helmholtz x pass 48 us, 8 points 113 and
   // 40 us.
-  static constexpr int E = L >= 16 ? 8 : L;
+  // Small fields: 4 points per thread where the row still fits a wavefront.
+  static constexpr int E = SM && L >= 16 && L <= 256 ? 4 : L >= 16 ? 8 : L;
   static constexpr int T = L / E;
   static_assert(T <= 64, "a row must fit one wavefront");
   // A row's T threads are adjacent lanes of one wavefront and each row owns
@@ -178,19 +212,19 @@ __device__ __forceinline__ KSys* block_sys() {
   return (KSys*)(seg + offsetof(Args, sys)) + blockIdx.y;
 }
 
-template <int L, typename R, int MODE>
-__global__ __launch_bounds__((ColCfg<L, R, MODE>::NT)) void k_col(ColArgs a, const C2<R>* __restrict__ twtab) {
-  using Cf = ColCfg<L, R, MODE>;
-  constexpr int E = Cf::E, T = Cf::T, TC = Cf::TC;
+template <int L, typename R, int MODE, bool SM>
+__global__ __launch_bounds__((ColCfg<L, R, MODE, SM>::NT)) void k_col(ColArgs a, const C2<R>* __restrict__ twtab) {
+  using Cf = ColCfg<L, R, MODE, SM>;
+  constexpr int E = Cf::E, T = Cf::T, TC = Cf::TC, NTG = Cf::NTG, NG = Cf::NG, NT = Cf::NT;
   using S = Sched<L, E>;
   constexpr int R0 = S::template first_radix<false>();
   constexpr int R1 = S::template last_radix<false>();
-  constexpr int LDSN = S::npass > 1 ? TC * L : 1;
+  constexpr int LDSN = S::npass > 1 ? NG * TC * L : 1;
   // this block's system, read from the kernel-argument segment (one code
   // path for a launch of one system and a batch)
   KSys* sy = block_sys<ColArgs>();
   const int* gate = sy->gate;
-  if (gate && *gate) return;  // the flag is written before the launch
+  if (!SM && gate && *gate) return;  // the flag is written before the launch
   const void* in0 = sy->in[0];
   const void* in1 = sy->in[1];
   const void* in2 = sy->in[2];
@@ -202,24 +236,94 @@ __global__ __launch_bounds__((ColCfg<L, R, MODE>::NT)) void k_col(ColArgs a, con
   __shared__ C2<R> lds_raw[LDSN];
   // twiddle table staged in LDS (see k_row)
   __shared__ C2<R> tw_lds[L];
-  for (int i = threadIdx.x; i < L; i += blockDim.x) tw_lds[i] = twtab[L + i];
-  __syncthreads();
-  const C2<R>* tw = tw_lds;
 
-  const int tid = threadIdx.x;
+  const int grp = NG > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / NTG) : 0;
+  const int tid = NG > 1 ? threadIdx.x - grp * NTG : threadIdx.x;
   const int c = tid % TC, t = tid / TC;
   const int ob = blockIdx.x / a.ntile, tile = blockIdx.x % a.ntile;
   const int col = tile * TC + c;
   const bool ok = col < a.inner;
   const size_t base = (size_t)ob * L * a.inner + col;
-  LdsCol<R> lds{lds_raw, c, TC};
+  LdsCol<R> lds{lds_raw + (NG > 1 ? grp * TC * L : 0), c, TC};
   C2<R> reg[E];
+
+  if constexpr (SM) {
+    // every load that does not depend on another one, then the halt flag
+    constexpr int NTW = (L + NT - 1) / NT;
+    C2<R> twr[NTW];
+#pragma unroll
+    for (int i = 0; i < NTW; ++i)
+      if (i * NT + (int)threadIdx.x < L) twr[i] = ldg(twtab + L + i * NT + threadIdx.x);
+    const void* src = NG == 3 ? (MODE == COL_P_MIDINV ? (grp == 2 ? in1 : in0) : (grp == 0 ? in0 : grp == 1 ? in1 : in2))
+                      : MODE == COL_P_LAST && grp == 1 ? in1 : in0;
+    col_load<L, E, R0>(reg, (const C2<R>*)src, base, a.inner, t, ok);
+    if (gate && *gate) return;
+#pragma unroll
+    for (int i = 0; i < NTW; ++i)
+      if (i * NT + (int)threadIdx.x < L) tw_lds[i * NT + threadIdx.x] = twr[i];
+  } else {
+    for (int i = threadIdx.x; i < L; i += blockDim.x) tw_lds[i] = twtab[L + i];
+  }
+  __syncthreads();
+  const C2<R>* tw = tw_lds;
+
+  if constexpr (SM && NG > 1) {
+    // one transform per group; every group meets the same barriers
+    if constexpr (MODE == COL_P_FIRST) {
+      const int ky = col / a.g.M, kx = col % a.g.M;
+      const R sc = in_scale_of<R>(iscale);
+#pragma unroll
+      for (int s = 0; s < E; ++s) {
+        const int kz = pat_index<L, E, R0>(t, s);
+        const R m = a.precond ? mult_press<R>(kx, ky, kz, a.g, rho0) : R(1);
+        reg[s] = cscale(reg[s], m * sc);
+        if (grp == 1) reg[s] = cik(reg[s], kprime_of<R>(kz, L, R(a.g.sz)));
+      }
+      fft_line<L, E, +1, false>(reg, lds, tw, t);
+      col_store<L, E, R1>(reg, (C2<R>*)(grp ? out1 : out0), base, a.inner, t, ok);
+    } else if constexpr (MODE == COL_P_MIDINV) {
+      // in place (out0 = in0, out2 = in1): both readers of in0 have consumed
+      // their loads before the first exchange's barrier
+      static_assert(S::npass > 1, "a barrier between the loads and the stores");
+      if (grp == 1) {
+#pragma unroll
+        for (int s = 0; s < E; ++s) reg[s] = cik(reg[s], kprime_of<R>(pat_index<L, E, R0>(t, s), L, R(a.g.sy)));
+      }
+      fft_line<L, E, +1, false>(reg, lds, tw, t);
+      col_store<L, E, R1>(reg, (C2<R>*)(grp == 0 ? out0 : grp == 1 ? out1 : out2), base, a.inner, t, ok);
+    } else {
+      constexpr bool LAST = MODE == COL_P_LAST;
+      const R sk = LAST ? R(a.g.sz) : R(a.g.sy);
+      fft_line<L, E, -1, false>(reg, lds, tw, t);
+      __syncthreads();  // group 1's tile has been read
+      if (grp == 1) {
+#pragma unroll
+        for (int s = 0; s < E; ++s) {
+          const int idx = pat_index<L, E, R1>(t, s);
+          lds.st(idx, cik(reg[s], kprime_of<R>(idx, L, sk)));
+        }
+      }
+      __syncthreads();
+      if (grp == 0) {
+        const LdsCol<R> other{lds_raw + TC * L, c, TC};
+#pragma unroll
+        for (int s = 0; s < E; ++s) {
+          const C2<R> d = other.ld(pat_index<L, E, R1>(t, s));
+          reg[s] = LAST ? C2<R>{-(reg[s].x + d.x), -(reg[s].y + d.y)} : reg[s] + d;
+        }
+        col_store<L, E, R1>(reg, (C2<R>*)out0, base, a.inner, t, ok);
+      } else if (!LAST && grp == 2) {
+        col_store<L, E, R1>(reg, (C2<R>*)out1, base, a.inner, t, ok);
+      }
+    }
+    return;
+  }
 
   if constexpr (MODE == COL_FFT_FWD || MODE == COL_FFT_INV) {
     constexpr int DIR = MODE == COL_FFT_FWD ? -1 : +1;
     const int nf = a.nf;
     for (int f = 0; f < nf; ++f) {
-      col_load<L, E, R0>(reg, (const C2<R>*)(f ? a.in[f] : in0), base, a.inner, t, ok);
+      if (!SM || f) col_load<L, E, R0>(reg, (const C2<R>*)(f ? a.in[f] : in0), base, a.inner, t, ok);
       fft_line<L, E, DIR, false>(reg, lds, tw, t);
       col_store<L, E, R1>(reg, (C2<R>*)(f ? a.out[f] : out0), base, a.inner, t, ok);
     }
@@ -280,7 +384,12 @@ __global__ __launch_bounds__((ColCfg<L, R, MODE>::NT)) void k_col(ColArgs a, con
     const R sc = in_scale_of<R>(iscale);
     const C2<R>* v = (const C2<R>*)(FIRST ? in0 : in1);
     C2<R> mv[E];
-    col_load<L, E, RP>(mv, v, base, a.inner, t, ok);
+    if constexpr (SM && FIRST) {
+#pragma unroll
+      for (int s = 0; s < E; ++s) mv[s] = reg[s];
+    } else {
+      col_load<L, E, RP>(mv, v, base, a.inner, t, ok);
+    }
     const bool need_mirror = (kx == 0) && (a.precond || !FIRST);
     const int kym = (a.g.ny - ky) % a.g.ny;
     const size_t basem = (size_t)ob * L * a.inner + (size_t)kym * a.g.M;
@@ -312,7 +421,7 @@ __global__ __launch_bounds__((ColCfg<L, R, MODE>::NT)) void k_col(ColArgs a, con
       fft_line<L, E, +1, false>(mv, lds, tw, t);
       col_store<L, E, R1>(mv, (C2<R>*)out0, base, a.inner, t, ok);
     } else {
-      col_load<L, E, R0>(reg, (const C2<R>*)in0, base, a.inner, t, ok);
+      if (!SM) col_load<L, E, R0>(reg, (const C2<R>*)in0, base, a.inner, t, ok);
       fft_line<L, E, -1, false>(reg, lds, tw, t);
 #pragma unroll
       for (int s = 0; s < E; ++s) reg[s] = reg[s] + mv[s];
@@ -376,9 +485,9 @@ constexpr bool row_loop() {
   return (MODE == ROW_P && L == 256 && sizeof(R) == 8) || (MODE == ROW_H && L == 128);
 }
 
-template <int L, typename R, int MODE>
+template <int L, typename R, int MODE, bool SM>
 __global__ __launch_bounds__(64 * row_waves<MODE>()) void k_row(RowArgs a, const C2<R>* __restrict__ twtab) {
-  using Cf = RowCfg<L, R>;
+  using Cf = RowCfg<L, R, SM>;
   constexpr int E = Cf::E, T = Cf::T, RW = Cf::RW, LP = Cf::LP;
   constexpr bool WV = Cf::WAVE;
   using S = Sched<L, E>;
@@ -393,7 +502,7 @@ __global__ __launch_bounds__(64 * row_waves<MODE>()) void k_row(RowArgs a, const
   constexpr bool SYS = MODE == ROW_P || MODE == ROW_H;
   KSys* sy = SYS ? block_sys<RowArgs>() : nullptr;
   const int* gate = SYS ? sy->gate : a.gate;
-  if (gate && *gate) return;
+  if (!SM && gate && *gate) return;
   auto IN = [&](int f) -> const void* {
     if constexpr (SYS) return sy->in[f];
     else return a.in[f];
@@ -409,11 +518,6 @@ __global__ __launch_bounds__(64 * row_waves<MODE>()) void k_row(RowArgs a, const
   // twiddle tables in LDS: a load in every butterfly pass from global memory
   // (even an L1 hit) costs latency inside the transform and address registers
   __shared__ C2<R> tw_lds[2 * L];
-  for (int i = threadIdx.x; i < 2 * L; i += blockDim.x) tw_lds[i] = twtab[L + i];
-  __syncthreads();
-  const C2<R>* tw = tw_lds;       // length-L table
-  const C2<R>* twN = tw_lds + L;  // length-2L table, first L entries used
-
   // ROW_P: wavefront w handles field w of the block's rows, so the fields
   // share each coefficient row through the CU's L1 instead of re-reading it
   // from HBM, and each thread keeps only one field's transforms live.
@@ -436,6 +540,41 @@ __global__ __launch_bounds__(64 * row_waves<MODE>()) void k_row(RowArgs a, const
   LdsRow<R> lds{lds_all + (FW ? fsel * RW + rr : rr) * LP};
   const R sx = R(a.g.sx);
   C2<R> reg[E];
+  constexpr bool LOOP = !SM && row_loop<L, R, MODE>();
+  auto place = [&](int grp) {
+    const int bx = (MODE == ROW_P || MODE == ROW_H) ? ngroups - 1 - grp : grp;
+    row = bx * RB + rr;
+    ok = row < a.nrows;
+  };
+
+  // small fields: the block's row (spectral or real pairs, in natural order
+  // t + s T) and the twiddles are on their way before the halt flag is read
+  C2<R> first[SM ? E : 1];
+  if constexpr (SM) {
+    constexpr int NT = 64 * NW, NTW = (2 * L + 127) / 128;  // ROW_P may run two wavefronts
+    static_assert(NT >= 128, "at least two wavefronts");
+    place(blockIdx.x);
+    const C2<R>* src = (const C2<R>*)IN(fsel);
+#pragma unroll
+    for (int s = 0; s < E; ++s) {
+      const int k = MODE == ROW_R2C ? pat_index<L, E, RF0>(t, s) : t + s * T;
+      first[s] = ok ? ldg(src + (size_t)row * L + k) : C2<R>{R(0), R(0)};
+    }
+    C2<R> twr[NTW];
+    const int nt = blockDim.x;
+#pragma unroll
+    for (int i = 0; i < NTW; ++i)
+      if (i * nt + (int)threadIdx.x < 2 * L) twr[i] = ldg(twtab + L + i * nt + threadIdx.x);
+    if (gate && *gate) return;
+#pragma unroll
+    for (int i = 0; i < NTW; ++i)
+      if (i * nt + (int)threadIdx.x < 2 * L) tw_lds[i * nt + threadIdx.x] = twr[i];
+  } else {
+    for (int i = threadIdx.x; i < 2 * L; i += blockDim.x) tw_lds[i] = twtab[L + i];
+  }
+  __syncthreads();
+  const C2<R>* tw = tw_lds;       // length-L table
+  const C2<R>* twN = tw_lds + L;  // length-2L table, first L entries used
 
   auto pre_mult = [&](int f, int k, C2<R> X) -> C2<R> {
     if constexpr (MODE == ROW_P) {
@@ -461,7 +600,7 @@ __global__ __launch_bounds__(64 * row_waves<MODE>()) void k_row(RowArgs a, const
 #pragma unroll
     for (int s = 0; s < E; ++s) {
       int k = t + s * T;
-      C2<R> X = ok ? ldg(src + (size_t)row * L + k) : C2<R>{R(0), R(0)};
+      C2<R> X = SM ? first[SM ? s : 0] : ok ? ldg(src + (size_t)row * L + k) : C2<R>{R(0), R(0)};
       lds.st(k, pre_mult(f, k, X));
     }
     lds_sync<WV>();
@@ -528,15 +667,13 @@ __global__ __launch_bounds__(64 * row_waves<MODE>()) void k_row(RowArgs a, const
 
   // row groups: one per block, or a loop over them (row_loop)
   for (int grp = blockIdx.x; grp < ngroups; grp += gridDim.x) {
-    const int bx = (MODE == ROW_P || MODE == ROW_H) ? ngroups - 1 - grp : grp;
-    row = bx * RB + rr;
-    ok = row < a.nrows;
+    place(grp);
     if constexpr (MODE == ROW_R2C) {
       const C2<R>* src = (const C2<R>*)IN(0);  // real row viewed as complex pairs
 #pragma unroll
       for (int s = 0; s < E; ++s) {
         int m = pat_index<L, E, RF0>(t, s);
-        reg[s] = ok ? ldg(src + (size_t)row * L + m) : C2<R>{R(0), R(0)};
+        reg[s] = SM ? first[SM ? s : 0] : ok ? ldg(src + (size_t)row * L + m) : C2<R>{R(0), R(0)};
       }
       fft_line<L, E, -1, true, WV>(reg, lds, tw, t);
       forward_post(0, (C2<R>*)OUT(0), nullptr);
@@ -558,7 +695,7 @@ __global__ __launch_bounds__(64 * row_waves<MODE>()) void k_row(RowArgs a, const
       // pressure x pass: issue the coefficient row's loads before the inverse
       // transform so that their latency hides behind it (measured: 215 -> 204
       // us at 256^3 FP64; the single-field Helmholtz pass is faster without)
-      constexpr bool PREFETCH = MODE == ROW_P;
+      constexpr bool PREFETCH = MODE == ROW_P || SM;
       C2<R> qv[PREFETCH ? E : 1];
       if constexpr (PREFETCH) {
 #pragma unroll
@@ -582,7 +719,7 @@ __global__ __launch_bounds__(64 * row_waves<MODE>()) void k_row(RowArgs a, const
       fft_line<L, E, -1, true, WV>(reg, lds, tw, t);
       forward_post(f, (C2<R>*)OUT(f), (const C2<R>*)IN(0));
     }
-    if constexpr (!row_loop<L, R, MODE>()) break;  // no back edge: nothing is hoisted
+    if constexpr (!LOOP) break;  // no back edge: nothing is hoisted
   }
 }
 
@@ -658,13 +795,26 @@ static void as_systems(Args& a) {
   y.gate = a.gate;
 }
 
-template <typename R, int MODE, int L>
-static void launch_col_L(const ColArgs& a0, const void* tw, hipStream_t st) {
+static bool small_field(const Geom& g) { return (size_t)g.nz * g.ny * g.M <= kSmallField; }
+
+template <typename R, int MODE, int L, bool SM>
+static void launch_col_S(const ColArgs& a0, const void* tw, hipStream_t st) {
+  using Cf = ColCfg<L, R, MODE, SM>;
   ColArgs a = a0;
   as_systems(a);
-  a.ntile = (a.inner + ColCfg<L, R, MODE>::TC - 1) / ColCfg<L, R, MODE>::TC;
+  a.ntile = (a.inner + Cf::TC - 1) / Cf::TC;
   dim3 grid(a.outer * a.ntile, a.nb);
-  hipLaunchKernelGGL((k_col<L, R, MODE>), grid, dim3(ColCfg<L, R, MODE>::NT), 0, st, a, (const C2<R>*)tw);
+  hipLaunchKernelGGL((k_col<L, R, MODE, SM>), grid, dim3(Cf::NT), 0, st, a, (const C2<R>*)tw);
+}
+template <typename R, int MODE, int L>
+static void launch_col_L(const ColArgs& a, const void* tw, hipStream_t st) {
+  if constexpr (col_has_small(L, MODE)) {
+    if (small_field(a.g)) {
+      launch_col_S<R, MODE, L, true>(a, tw, st);
+      return;
+    }
+  }
+  launch_col_S<R, MODE, L, false>(a, tw, st);
 }
 
 template <typename R, int MODE>
@@ -684,9 +834,9 @@ static void launch_col(int L, const ColArgs& a, const void* tw, hipStream_t st) 
 // Blocks of a looping row pass (eight per CU on 256 CUs), per system.
 constexpr int kRowGridCap = 2048;
 
-template <typename R, int MODE, int L>
-static void launch_row_L(const RowArgs& a0, const void* tw, hipStream_t st) {
-  constexpr int RW = RowCfg<L, R>::RW;
+template <typename R, int MODE, int L, bool SM>
+static void launch_row_S(const RowArgs& a0, const void* tw, hipStream_t st) {
+  constexpr int RW = RowCfg<L, R, SM>::RW;
   RowArgs a = a0;
   int ny = 1;
   if constexpr (MODE == ROW_P || MODE == ROW_H) {
@@ -696,10 +846,20 @@ static void launch_row_L(const RowArgs& a0, const void* tw, hipStream_t st) {
   }
   const int rb = row_field_waves<MODE>() ? RW : row_waves<MODE>() * RW;
   const int ngroups = (a.nrows + rb - 1) / rb;
-  dim3 grid(row_loop<L, R, MODE>() && ngroups > kRowGridCap ? kRowGridCap : ngroups, ny);
+  dim3 grid(!SM && row_loop<L, R, MODE>() && ngroups > kRowGridCap ? kRowGridCap : ngroups, ny);
   // ROW_P: one wavefront per field (<= 3)
   const int waves = row_field_waves<MODE>() ? a.nf : row_waves<MODE>();
-  hipLaunchKernelGGL((k_row<L, R, MODE>), grid, dim3(64 * waves), 0, st, a, (const C2<R>*)tw);
+  hipLaunchKernelGGL((k_row<L, R, MODE, SM>), grid, dim3(64 * waves), 0, st, a, (const C2<R>*)tw);
+}
+template <typename R, int MODE, int L>
+static void launch_row_L(const RowArgs& a, const void* tw, hipStream_t st) {
+  if constexpr (MODE != ROW_P1 && MODE != ROW_H1 && L >= 16) {
+    if (small_field(a.g)) {
+      launch_row_S<R, MODE, L, true>(a, tw, st);
+      return;
+    }
+  }
+  launch_row_S<R, MODE, L, false>(a, tw, st);
 }
 
 template <typename R, int MODE>

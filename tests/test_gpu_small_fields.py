@@ -43,3 +43,22 @@ def test_gmres_around_the_small_field_limit(shape, precision):
     if precision == "fp64":
         assert ref["iterations"] > 24
         assert abs(info["iterations"] - ref["iterations"]) <= 1
+
+
+# every column length on either side of the limit, the limit itself, and a y
+# length (512) that the small configuration is not built for beside z and x
+# lengths that it is; tolerances as for the other operator parity tests
+@pytest.mark.parametrize("shape", [(16, 256, 16), (16, 64, 32), (32, 16, 512), (16, 512, 16), (64, 64, 64),
+                                   (256, 32, 32), (16, 128, 256), (128, 32, 128), (32, 256, 64), (64, 512, 16)])
+@pytest.mark.parametrize("prec,tol", [("fp64", 1e-12), ("fp32", 2e-5)])
+def test_operators_around_the_small_field_limit(shape, prec, tol):
+    from paper_2403_06654_amd.api import Grid
+    rho = smooth_density(shape, 1)
+    x = np.random.default_rng(2).standard_normal(shape)
+    g = Grid(shape)
+    g.set_density(to_dev(rho))
+    y = to_host(g.apply_operator("pressure", to_dev(x), precision=prec))
+    yh = to_host(g.apply_operator("helmholtz", to_dev(x), precision=prec, nu=0.013))
+    g.close()
+    assert rel2(y, operators.apply_pressure(x, rho)) < tol
+    assert rel2(yh, operators.apply_helmholtz(x, rho, 0.013)) < tol
