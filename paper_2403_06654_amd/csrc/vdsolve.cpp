@@ -2,9 +2,9 @@
 //
 // Krylov vectors live in HBM as packed half-spectra (see passes.hpp); the
 // scalars of each method (Hessenberg matrix, Givens rotations, CG/RMR step
-// lengths) live in a small device struct and are updated by one-thread
-// kernels, so the only host round trip per iteration is the 8-byte
-// residual estimate that decides whether to stop.
+// lengths) live in a small device struct and are updated by the kernels that
+// finish each reduction; after each step such a kernel posts the residual and
+// the stopping decision to pinned host memory, which the host polls.
 //
 // Methods (Sec. 3.1 solver list):
 //   GMRES(m)  right preconditioned (x = M^-1 V y), classical Gram-Schmidt
@@ -27,6 +27,7 @@
 #include <algorithm>
 #include <map>
 #include <new>
+#include <thread>
 #include <vector>
 
 #include "../../include/vdsolve.h"
@@ -116,15 +117,14 @@ struct vd_grid {
   bool has_rho = false;
   double rho_mean = 0, rho_min = 0, rho_max = 0;
   double* partial = nullptr;
-  double* dsmall = nullptr;   // misc device scalars
+  double* dsmall = nullptr;   // misc scalars that kernels write and the host reads (pinned host memory)
   DevState* dst = nullptr;    // device solver state
-  DevState* hst = nullptr;    // pinned host mirror
-  DevState* hslot = nullptr;  // two pinned mirrors of the state's tail, one per queued GMRES step
-  hipEvent_t slot_ev[2] = {nullptr, nullptr};
-  // the other systems of a batched solve (index 0 is dst, partial, hslot)
+  Mail* mail = nullptr;       // its mailboxes (pinned host memory)
+  unsigned long long posts = 0;  // numbers handed out for this grid's mailboxes so far
+  // the other systems of a batched solve (index 0 is dst, partial, mail)
   DevState* dstx[kMaxBatch] = {};
   double* partialx[kMaxBatch] = {};
-  DevState* hslotx[kMaxBatch] = {};
+  Mail* mailx[kMaxBatch] = {};
   std::map<int, void*> bufs;  // spectral vectors by (precision, role)
   Prof prof;
   // Chebyshev wall-normal direction (g.cheb)
@@ -249,22 +249,61 @@ static double norm_from_sq(double s) { return s < 0.0 ? 0.0 : std::sqrt(s); }
 // max that keeps a NaN of either argument
 static double max_keep_nan(double a, double b) { return (a != a || b != b) ? NAN : std::max(a, b); }
 
-void sync_state(vd_grid* G) {
-  // only the tail (resid, nrm2, bad) is read on the host
-  const size_t off = offsetof(DevState, resid);
-  ck(hipMemcpyAsync((char*)G->hst + off, (const char*)G->dst + off, sizeof(DevState) - off,
-                    hipMemcpyDeviceToHost, G->st));
-  ck(hipStreamSynchronize(G->st));
-  if (G->prof.on) G->prof.flush();
+// Waits until mailbox m holds post number seq, which work already on stream
+// st will post.  Polls the pinned memory; every few ten microseconds it also
+// asks the stream, so that a device error, or a stream that has ended without
+// posting, ends the wait.
+void wait_mail(const Mail* m, unsigned long long seq, hipStream_t st) {
+  for (unsigned spin = 1;; ++spin) {
+    if (__atomic_load_n(&m->seq, __ATOMIC_ACQUIRE) == seq) return;
+#if defined(__x86_64__)
+    __builtin_ia32_pause();
+#endif
+    if (spin % 1024) continue;
+    const hipError_t before = hipPeekAtLastError();
+    const hipError_t q = hipStreamQuery(st);
+    if (q == hipErrorNotReady) {
+      if (before == hipSuccess) (void)hipGetLastError();  // "not ready" is no error of the library's work
+      std::this_thread::yield();
+      continue;
+    }
+    ck(q);
+    if (__atomic_load_n(&m->seq, __ATOMIC_ACQUIRE) != seq) throw DevErr{};
+  }
 }
 
-double read_scalar(vd_grid* G, const double* dptr) {
-  double v = 0;
-  ck(hipMemcpyAsync(&G->hst->nrm2, dptr, sizeof(double), hipMemcpyDeviceToHost, G->st));
-  ck(hipStreamSynchronize(G->st));
-  v = G->hst->nrm2;
-  if (G->prof.on) G->prof.flush();
-  return v;
+// Posts and waits for one reduced value: `launch` enqueues, on stream st, a
+// reduction that takes the Post.
+template <typename F>
+double read_value(vd_grid* owner, DevState* dst, const Mail* mail, hipStream_t st, F&& launch) {
+  const unsigned long long seq = ++owner->posts;
+  launch(Post{POST_MAIL, dst, seq});
+  wait_mail(mail + MAIL_VALUE, seq, st);
+  return mail[MAIL_VALUE].v[0];
+}
+
+// The state that a Krylov step posted.
+struct StepState {
+  double resid = 0, nrm2 = 0;
+  bool bad = false, halt = false;
+  int nreorth = 0;
+};
+StepState wait_step(const Mail* mail, int j, unsigned long long run, hipStream_t st) {
+  const Mail& m = mail[MAIL_STEP + (j & 1)];
+  wait_mail(&m, run + j + 1, st);
+  StepState t;
+  t.resid = m.v[0];
+  t.nrm2 = m.v[1];
+  t.bad = m.flags & 1;
+  t.halt = (m.flags >> 1) & 1;
+  t.nreorth = (int)(m.flags >> 2);
+  return t;
+}
+// numbers for the steps of a cycle or run that ends after step jlast at the latest
+unsigned long long new_run(vd_grid* owner, int jlast) {
+  const unsigned long long run = owner->posts;
+  owner->posts += (unsigned long long)jlast + 1;
+  return run;
 }
 
 // ----------------------------------------------------------- solver core
@@ -367,8 +406,11 @@ struct Krylov {
   double true_resid(const void* b, const void* x, void* r) {
     void* tmp = buf(G, prec, B_TMP);
     apply(x, tmp, false);
-    sub_norm<R>(g, b, tmp, r, G->partial, &G->dst->nrm2, G->st);
-    return norm_from_sq(read_scalar(G, &G->dst->nrm2));
+    const double n2 = read_value(G, G->dst, G->mail, G->st, [&](const Post& post) {
+      sub_norm<R>(g, b, tmp, r, G->partial, &G->dst->nrm2, G->st, post);
+    });
+    if (G->prof.on) G->prof.flush();
+    return norm_from_sq(n2);
   }
 
   double copy_rhs(const void* b, void* r, double bnorm) {
@@ -377,20 +419,11 @@ struct Krylov {
   }
 
   SolveOut run(const void* b, void* x, double bnorm) {
-    ck(hipMemsetAsync(&G->dst->bad, 0, sizeof(int), G->st));
     switch (cfg.solver) {
       case VD_CG: return cg(b, x, bnorm);
       case VD_RMR: return rmr(b, x, bnorm);
       default: return gmres(b, x, bnorm);
     }
-  }
-
-  int read_nreorth() {
-    int v = 0;
-    ck(hipMemcpyAsync(&G->hst->nreorth, &G->dst->nreorth, sizeof(int), hipMemcpyDeviceToHost, G->st));
-    ck(hipStreamSynchronize(G->st));
-    v = G->hst->nreorth;
-    return v;
   }
 
   // Arnoldi step j: V[j+1] = A M^-1 v_j, Gram-Schmidt against V[0..j] and
@@ -401,22 +434,7 @@ struct Krylov {
     for (int i = 0; i <= j; ++i) P.p[i] = V[i];
     gs_orthogonalize<R>(g, V[j + 1], P, j + 1, G->dst, G->partial, G->st, &G->prof);
   }
-  // the state's tail (resid, nrm2, bad, halt) after step j into slot j % 2
-  void post_tail(int j) {
-    const size_t off = offsetof(DevState, resid);
-    ck(hipMemcpyAsync((char*)(G->hslot + (j & 1)) + off, (const char*)G->dst + off, sizeof(DevState) - off,
-                      hipMemcpyDeviceToHost, G->st));
-    ck(hipEventRecord(G->slot_ev[j & 1], G->st));
-  }
-
   SolveOut gmres(const void* b, void* x, double bnorm) {
-    const int r0 = read_nreorth();
-    SolveOut o = gmres_core(b, x, bnorm);
-    o.reorth = read_nreorth() - r0;
-    return o;
-  }
-
-  SolveOut gmres_core(const void* b, void* x, double bnorm) {
     SolveOut o;
     const int m = cfg.restart;
     std::vector<void*> V(m + 1);
@@ -438,20 +456,22 @@ struct Krylov {
       if (o.iters >= cfg.max_iter) { o.status = VD_NOT_CONVERGED; return o; }
       // the cycle ends after step jlast at the latest (restart length or iteration budget)
       const int jlast = std::min(m, cfg.max_iter - o.iters) - 1;
-      gmres_init(G->dst, beta, m, bnorm, cfg.rtol, jlast, G->st);  // v_0 = V[0] / beta via the scale vs[0]
+      const unsigned long long run = new_run(G, jlast);
+      gmres_init(G->dst, beta, m, bnorm, cfg.rtol, jlast, run, G->st);  // v_0 = V[0] / beta via the scale vs[0]
       // the step count k of this cycle: its basis size for the back-solve
-      const int k = run_queued(jlast, [&](int j, const int* gate) { arnoldi_step(V, j, gate); },
-                               [&] { return G->hst->resid / bnorm; });
+      StepState t;
+      const int k = run_queued(jlast, run, t, bnorm, [&](int j, const int* gate) { arnoldi_step(V, j, gate); });
       o.iters += k;
-      if (G->hst->bad) { o.status = VD_EBREAKDOWN; return o; }
+      o.reorth += t.nreorth;
+      if (t.bad) { o.status = VD_EBREAKDOWN; return o; }
       gmres_backsolve(G->dst, k, G->st);
       VecPtrs P{};
       for (int i = 0; i < k; ++i) P.p[i] = V[i];
       lincomb<R>(g, tmp, P, k, G->dst->coef, G->st);
       prec_axpy(x, tmp, nullptr);
       ++cycles;
-      if (cfg.inner && (G->hst->resid / bnorm <= cfg.rtol || cycles >= kInnerCycles || o.iters >= cfg.max_iter)) {
-        o.relres = G->hst->resid / bnorm;  // estimate
+      if (cfg.inner && (t.resid / bnorm <= cfg.rtol || cycles >= kInnerCycles || o.iters >= cfg.max_iter)) {
+        o.relres = t.resid / bnorm;  // estimate
         o.status = VD_OK;
         return o;
       }
@@ -482,37 +502,29 @@ struct Krylov {
   // Steps 0..jlast of a GMRES cycle or a CG/RMR run.  Step j + 1 is queued
   // before step j's state reaches the host, so the GPU never idles while the
   // host decides: step(j, gate) enqueues step j with its stopping test on the
-  // device (k_gs_check, k_rec_check), every launch gated by the halt flag, so
+  // device (gs_givens, rec_check_step), every launch gated by the halt flag, so
   // that a step queued past the end returns at once (its profile records are
-  // dropped).  history() gives the residual recorded after each step.
-  // Returns the steps that ran; G->hst holds the state after the last.
-  template <typename Step, typename Hist>
-  int run_queued(int jlast, Step&& step, Hist&& history) {
+  // dropped).  Returns the steps that ran; t: the state after the last (the
+  // history gets its resid, GMRES the Givens estimate, CG and RMR the recursive
+  // residual norm).
+  template <typename Step>
+  int run_queued(int jlast, unsigned long long run, StepState& t, double bnorm, Step&& step) {
     Prof& pf = G->prof;
     if (pf.on) pf.flush();
     const int* gate = &G->dst->halt;
     step(0, gate);
-    post_tail(0);
     size_t mark = pf.pending.size();
     int done = 0;
     for (int j = 0; j <= jlast; ++j) {
-      if (j < jlast) {
-        step(j + 1, gate);
-        post_tail(j + 1);
-      }
-      ck(hipEventSynchronize(G->slot_ev[j & 1]));
-      const DevState& t = G->hslot[j & 1];
-      G->hst->resid = t.resid;
-      G->hst->nrm2 = t.nrm2;
-      G->hst->bad = t.bad;
-      G->hst->halt = t.halt;
+      if (j < jlast) step(j + 1, gate);
+      t = wait_step(G->mail, j, run, G->st);
       if (pf.on) {
         pf.flush_front(mark);
         mark = pf.pending.size();
       }
       done = j + 1;
-      if (cfg.hist) cfg.hist->push_back(history());
-      if (G->hst->bad || G->hst->halt || !(G->hst->nrm2 == G->hst->nrm2)) break;
+      if (cfg.hist) cfg.hist->push_back(t.resid / bnorm);
+      if (t.bad || t.halt || !(t.nrm2 == t.nrm2)) break;
     }
     if (pf.on) pf.drop();
     return done;
@@ -532,19 +544,21 @@ struct Krylov {
       if (o.iters >= cfg.max_iter) { o.status = VD_NOT_CONVERGED; return o; }
       // p = M^-1 r, rz = (r, M^-1 r)
       const int jlast = cfg.max_iter - o.iters - 1;
-      rec_init(G->dst, bnorm, cfg.rtol, jlast, G->st);
+      const unsigned long long run = new_run(G, jlast);
+      rec_init(G->dst, bnorm, cfg.rtol, jlast, run, G->st);
       rz_and_p(r, p, true);
-      o.iters += run_queued(jlast, [&](int j, const int* gate) {
+      StepState t;
+      o.iters += run_queued(jlast, run, t, bnorm, [&](int j, const int* gate) {
         if (j > 0) rz_and_p(r, p, false, gate);
         apply(p, q, false, nullptr, gate);
         VecPtrs P{};
         P.p[0] = p;
         mdot<R>(g, q, P, 1, false, G->partial, G->dst->red, G->st, nullptr, gate, Post{POST_CG_ALPHA, G->dst});
         cg_xr<R>(g, x, r, p, q, G->dst, G->partial, &G->dst->nrm2, G->st, gate, Post{POST_REC_CHECK, G->dst});
-      }, [&] { return norm_from_sq(G->hst->nrm2) / bnorm; });
-      if (G->hst->bad || !(G->hst->nrm2 == G->hst->nrm2)) { o.status = VD_EBREAKDOWN; return o; }
+      });
+      if (t.bad || !(t.nrm2 == t.nrm2)) { o.status = VD_EBREAKDOWN; return o; }
       if (cfg.inner) {
-        o.relres = norm_from_sq(G->hst->nrm2) / bnorm;
+        o.relres = t.resid / bnorm;
         o.status = VD_OK;
         return o;
       }
@@ -564,8 +578,10 @@ struct Krylov {
       if (o.relres <= cfg.rtol) { o.status = VD_OK; return o; }
       if (o.iters >= cfg.max_iter) { o.status = VD_NOT_CONVERGED; return o; }
       const int jlast = cfg.max_iter - o.iters - 1;
-      rec_init(G->dst, bnorm, cfg.rtol, jlast, G->st);
-      o.iters += run_queued(jlast, [&](int, const int* gate) {
+      const unsigned long long run = new_run(G, jlast);
+      rec_init(G->dst, bnorm, cfg.rtol, jlast, run, G->st);
+      StepState t;
+      o.iters += run_queued(jlast, run, t, bnorm, [&](int, const int* gate) {
         apply(r, w, true, nullptr, gate);  // w = A M^-1 r
         VecPtrs P{};
         P.p[0] = r;
@@ -573,10 +589,10 @@ struct Krylov {
         prec_axpy(x, r, &G->dst->alpha, gate);
         axpy_norm<R>(g, r, w, &G->dst->alpha, -1.0, G->partial, &G->dst->nrm2, G->st, gate,
                      Post{POST_REC_CHECK, G->dst});
-      }, [&] { return norm_from_sq(G->hst->nrm2) / bnorm; });
-      if (G->hst->bad || !(G->hst->nrm2 == G->hst->nrm2)) { o.status = VD_EBREAKDOWN; return o; }
+      });
+      if (t.bad || !(t.nrm2 == t.nrm2)) { o.status = VD_EBREAKDOWN; return o; }
       if (cfg.inner) {
-        o.relres = norm_from_sq(G->hst->nrm2) / bnorm;
+        o.relres = t.resid / bnorm;
         o.status = VD_OK;
         return o;
       }
@@ -646,20 +662,28 @@ SolveOut solve_spectral(vd_grid* G, const vd_solve_opts& o, const OpParams& op, 
 // converges, and its result is the one it would have alone: the kernels and
 // reduction orders are those of a single system.
 
-// Device state, partials and pinned tail slots of system k (k = 0: the grid's own).
+// The pinned mailboxes of a new solver state on stream st.
+void make_mail(Mail** mail, DevState* dst, hipStream_t st) {
+  void* dev = nullptr;
+  ck(hipHostMalloc(mail, kMails * sizeof(Mail)));
+  std::memset(*mail, 0, kMails * sizeof(Mail));
+  ck(hipHostGetDevicePointer(&dev, *mail, 0));
+  set_mail(dst, (Mail*)dev, st);
+}
+
+// Device state, partials and mailboxes of system k (k = 0: the grid's own).
 void ensure_systems(vd_grid* G, int n) {
   for (int k = 1; k < n; ++k) {
     if (G->dstx[k]) continue;
     ck(hipMalloc(&G->dstx[k], sizeof(DevState)));
     ck(hipMalloc(&G->partialx[k], nred_partial() * sizeof(double)));
-    ck(hipHostMalloc(&G->hslotx[k], 2 * sizeof(DevState)));
     ck(hipMemsetAsync(G->dstx[k], 0, sizeof(DevState), G->st));
-    std::memset(G->hslotx[k], 0, 2 * sizeof(DevState));
+    make_mail(&G->mailx[k], G->dstx[k], G->st);
   }
 }
 DevState* sys_dst(vd_grid* G, int k) { return k ? G->dstx[k] : G->dst; }
 double* sys_partial(vd_grid* G, int k) { return k ? G->partialx[k] : G->partial; }
-DevState* sys_slots(vd_grid* G, int k) { return k ? G->hslotx[k] : G->hslot; }
+const Mail* sys_mail(vd_grid* G, int k) { return k ? G->mailx[k] : G->mail; }
 
 // The operator passes take all the systems in one launch only while their
 // fields fit the 256 MB Infinity Cache together: a pass then finds much of
@@ -676,7 +700,7 @@ constexpr double kBatchOpBytes = 200.0 * (1 << 20);
 
 // The systems of a lockstep solve.  System k lives in grid gs[k]: its
 // Krylov vectors are that grid's buffers under role + roff[k], and it has
-// its own device state, partials, tail slots, coefficient rows (pressure)
+// its own device state, partials, mailboxes, coefficient rows (pressure)
 // and preconditioner constant.  All run on gs[0]'s stream; the other grids
 // must be idle meanwhile.  The components of one velocity solve are systems
 // of one grid (roff[k] = k * kSysRoles); pressure solves of several grids of
@@ -687,7 +711,7 @@ struct SysGroup {
   int roff[kMaxBatch] = {};
   DevState* dst[kMaxBatch] = {};
   double* part[kMaxBatch] = {};
-  DevState* slots[kMaxBatch] = {};
+  const Mail* mail[kMaxBatch] = {};
   double rho0[kMaxBatch] = {};
 };
 
@@ -700,7 +724,7 @@ SysGroup components_of(vd_grid* G, int n, double rho0) {
     S.roff[k] = k * kSysRoles;
     S.dst[k] = sys_dst(G, k);
     S.part[k] = sys_partial(G, k);
-    S.slots[k] = sys_slots(G, k);
+    S.mail[k] = sys_mail(G, k);
     S.rho0[k] = rho0;
   }
   return S;
@@ -718,13 +742,13 @@ struct KrylovBatch {
   bool batch_ops = false;  // one launch per pass for all systems
   DevState* const* dst;
   double* const* part;
-  DevState* const* slots;
+  const Mail* const* mail;
   const void* coef[kMaxBatch];
   void* t[kMaxBatch][3];
   int max_iter[kMaxBatch];  // per system (refinement gives each its remaining budget)
 
   KrylovBatch(const SysGroup& S_, int prec_, const SolveCfg& c)
-      : S(S_), G(S_.gs[0]), prec(prec_), g(S_.gs[0]->g), cfg(c), dst(S_.dst), part(S_.part), slots(S_.slots) {
+      : S(S_), G(S_.gs[0]), prec(prec_), g(S_.gs[0]->g), cfg(c), dst(S_.dst), part(S_.part), mail(S_.mail) {
     tw = prec == 64 ? G->tw64 : G->tw32;
     helm = cfg.op.kind == OP_HELMHOLTZ;
     for (int k = 0; k < S.n; ++k) {
@@ -784,17 +808,18 @@ struct KrylovBatch {
       ob.y[q] = vec(k, B_TMP);
     }
     apply_set(ob, sys, false);
+    unsigned long long seq[kMaxBatch];
     for (int q = 0; q < ns; ++q) {
       const int k = sys[q];
-      sub_norm<R>(g, b[k], vec(k, B_TMP), r[k], part[k], &dst[k]->nrm2, G->st);
+      seq[q] = ++S.gs[k]->posts;
+      sub_norm<R>(g, b[k], vec(k, B_TMP), r[k], part[k], &dst[k]->nrm2, G->st, Post{POST_MAIL, dst[k], seq[q]});
     }
-    for (int q = 0; q < ns; ++q) rn[sys[q]] = norm_from_sq(read_scalar(G, &dst[sys[q]]->nrm2));
-  }
-
-  int read_nreorth(int k) {
-    ck(hipMemcpyAsync(&G->hst->nreorth, &dst[k]->nreorth, sizeof(int), hipMemcpyDeviceToHost, G->st));
-    ck(hipStreamSynchronize(G->st));
-    return G->hst->nreorth;
+    for (int q = 0; q < ns; ++q) {
+      const int k = sys[q];
+      wait_mail(mail[k] + MAIL_VALUE, seq[q], G->st);
+      rn[k] = norm_from_sq(mail[k][MAIL_VALUE].v[0]);
+    }
+    if (G->prof.on) G->prof.flush();
   }
 
   // Arnoldi step j of the systems sys[0..ns)
@@ -820,49 +845,33 @@ struct KrylovBatch {
     apply_set(ob, sys, true);
     gs_orthogonalize_batch<R>(g, w, V, j + 1, ds, ps, ns, G->st, &G->prof);
   }
-  void post_tails(int j, const int* sys, int ns) {
-    const size_t off = offsetof(DevState, resid);
-    for (int q = 0; q < ns; ++q) {
-      const int k = sys[q];
-      ck(hipMemcpyAsync((char*)(slots[k] + (j & 1)) + off, (const char*)dst[k] + off, sizeof(DevState) - off,
-                        hipMemcpyDeviceToHost, G->st));
-    }
-    ck(hipEventRecord(G->slot_ev[j & 1], G->st));
-  }
-
   // Steps 0..jlast of a cycle of the systems sys[0..ns), queued one step ahead
   // of the host like Krylov::run_queued; each system stops at its own halt
-  // flag.  steps[q], resid[q], bad[q]: per system at its end.
-  void run_queued(int jlast, const int* sys, int ns, int* steps, double* resid, int* bad,
+  // flag.  run[q]: the system's post numbers; steps[q], end[q]: its steps and
+  // the state after the last.
+  void run_queued(int jlast, const int* sys, int ns, const unsigned long long* run, int* steps, StepState* end,
                   std::vector<double>* hist, double hist_bnorm) {
     Prof& pf = G->prof;
     if (pf.on) pf.flush();
     step(0, sys, ns);
-    post_tails(0, sys, ns);
     size_t mark = pf.pending.size();
     bool stopped[kMaxBatch] = {};
     int nstop = 0;
     for (int j = 0; j <= jlast; ++j) {
-      if (j < jlast) {
-        step(j + 1, sys, ns);
-        post_tails(j + 1, sys, ns);
-      }
-      ck(hipEventSynchronize(G->slot_ev[j & 1]));
-      if (pf.on) {
-        pf.flush_front(mark);
-        mark = pf.pending.size();
-      }
+      if (j < jlast) step(j + 1, sys, ns);
       for (int q = 0; q < ns; ++q) {
         if (stopped[q]) continue;
-        const DevState& tt = slots[sys[q]][j & 1];
+        const StepState tt = end[q] = wait_step(mail[sys[q]], j, run[q], G->st);
         steps[q] = j + 1;
-        resid[q] = tt.resid;
-        bad[q] = tt.bad;
         if (hist && sys[q] == 0) hist->push_back(tt.resid / hist_bnorm);
         if (tt.bad || tt.halt || !(tt.nrm2 == tt.nrm2)) {
           stopped[q] = true;
           ++nstop;
         }
+      }
+      if (pf.on) {
+        pf.flush_front(mark);
+        mark = pf.pending.size();
       }
       if (nstop == ns) break;
     }
@@ -875,14 +884,9 @@ struct KrylovBatch {
              std::vector<double>* hist) {
     const int m = cfg.restart;
     double beta[kMaxBatch] = {};
-    int cycles[kMaxBatch] = {}, r0[kMaxBatch] = {};
+    int cycles[kMaxBatch] = {};
     bool active[kMaxBatch] = {};
-    for (int q = 0; q < ns; ++q) {
-      const int k = sys[q];
-      r0[k] = read_nreorth(k);
-      ck(hipMemsetAsync(&dst[k]->bad, 0, sizeof(int), G->st));
-      active[k] = true;
-    }
+    for (int q = 0; q < ns; ++q) active[sys[q]] = true;
     void* v0[kMaxBatch];
     for (int q = 0; q < ns; ++q) v0[sys[q]] = basis(sys[q], 0);
     if (cfg.inner || cfg.x_zero) {  // x = 0: r = b
@@ -913,21 +917,24 @@ struct KrylovBatch {
       }
       if (na == 0) break;
       int jlast = 0;
+      unsigned long long run[kMaxBatch];
       for (int q = 0; q < na; ++q) {
         const int k = act[q];
         const int jl = std::min(m, max_iter[k] - out[k].iters) - 1;
-        gmres_init(dst[k], beta[k], m, bnorm[k], cfg.rtol, jl, G->st);
+        run[q] = new_run(S.gs[k], jl);
+        gmres_init(dst[k], beta[k], m, bnorm[k], cfg.rtol, jl, run[q], G->st);
         jlast = std::max(jlast, jl);
       }
-      int steps[kMaxBatch] = {}, bad[kMaxBatch] = {};
-      double resid[kMaxBatch] = {};
-      run_queued(jlast, act, na, steps, resid, bad, hist, bnorm[0]);
+      int steps[kMaxBatch] = {};
+      StepState end[kMaxBatch];
+      run_queued(jlast, act, na, run, steps, end, hist, bnorm[0]);
       int nres = 0, res_sys[kMaxBatch];
       for (int q = 0; q < na; ++q) {
         const int k = act[q];
         SolveOut& o = out[k];
         o.iters += steps[q];
-        if (bad[q]) {
+        o.reorth += end[q].nreorth;
+        if (end[q].bad) {
           o.status = VD_EBREAKDOWN;
           active[k] = false;
           continue;
@@ -941,8 +948,9 @@ struct KrylovBatch {
         plain.gate = nullptr;
         precond_axpy<R>(g, plain, x[k], tmp, nullptr, 1.0, G->st);
         ++cycles[k];
-        if (cfg.inner && (resid[q] / bnorm[k] <= cfg.rtol || cycles[k] >= kInnerCycles || o.iters >= max_iter[k])) {
-          o.relres = resid[q] / bnorm[k];  // estimate
+        const double est = end[q].resid / bnorm[k];
+        if (cfg.inner && (est <= cfg.rtol || cycles[k] >= kInnerCycles || o.iters >= max_iter[k])) {
+          o.relres = est;
           o.status = VD_OK;
           active[k] = false;
           continue;
@@ -951,7 +959,6 @@ struct KrylovBatch {
       }
       if (nres) true_resid(res_sys, nres, b, x, v0, beta);
     }
-    for (int q = 0; q < ns; ++q) out[sys[q]].reorth = read_nreorth(sys[q]) - r0[sys[q]];
   }
 };
 
@@ -1068,8 +1075,11 @@ vd_status guard(vd_grid* G, vd_status (*fn)(vd_grid*, void*), void* ctx) {
 
 double host_norm_of(vd_grid* G, const void* spec64) {
   VecPtrs P{};
-  mdot<double>(G->g, spec64, P, 0, true, G->partial, &G->dst->nrm2, G->st);
-  return norm_from_sq(read_scalar(G, &G->dst->nrm2));
+  const double n2 = read_value(G, G->dst, G->mail, G->st, [&](const Post& post) {
+    mdot<double>(G->g, spec64, P, 0, true, G->partial, &G->dst->nrm2, G->st, nullptr, nullptr, post);
+  });
+  if (G->prof.on) G->prof.flush();
+  return norm_from_sq(n2);
 }
 
 // The modified pressure form's pointwise coefficient, -c = Lap(psi)/psi with
@@ -1235,14 +1245,12 @@ vd_status vd_grid_create(vd_grid** out, const vd_grid_desc* d, hipStream_t strea
     }
     fill_twiddles(G);
     ck(hipMalloc(&G->partial, nred_partial() * sizeof(double)));
-    ck(hipMalloc(&G->dsmall, 64 * sizeof(double)));
+    ck(hipHostMalloc(&G->dsmall, 64 * sizeof(double)));
     ck(hipMalloc(&G->dst, sizeof(DevState)));
-    ck(hipHostMalloc(&G->hst, sizeof(DevState)));
-    ck(hipHostMalloc(&G->hslot, 2 * sizeof(DevState)));
-    for (auto& e : G->slot_ev) ck(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    ck(hipMemset(G->dst, 0, sizeof(DevState)));
-    std::memset(G->hst, 0, sizeof(DevState));
-    std::memset(G->hslot, 0, 2 * sizeof(DevState));
+    // on the grid's stream, like everything that touches the state: a server's
+    // stream is not ordered after the null stream
+    ck(hipMemsetAsync(G->dst, 0, sizeof(DevState), stream));
+    make_mail(&G->mail, G->dst, stream);
   } catch (...) {
     vd_grid_destroy(G);
     return VD_ENOMEM;
@@ -1264,7 +1272,7 @@ vd_status vd_grid_destroy(vd_grid* G) {
   hipFree(G->a32);
   hipFree(G->rho32);
   hipFree(G->partial);
-  hipFree(G->dsmall);
+  if (G->dsmall) hipHostFree(G->dsmall);
   for (int m = 0; m < CH_NMAT; ++m) {
     hipFree(G->cd.m64[m]);
     hipFree(G->cd.m32[m]);
@@ -1281,12 +1289,9 @@ vd_status vd_grid_destroy(vd_grid* G) {
   for (int k = 1; k < kMaxBatch; ++k) {
     hipFree(G->dstx[k]);
     hipFree(G->partialx[k]);
-    if (G->hslotx[k]) hipHostFree(G->hslotx[k]);
+    if (G->mailx[k]) hipHostFree(G->mailx[k]);
   }
-  if (G->hst) hipHostFree(G->hst);
-  if (G->hslot) hipHostFree(G->hslot);
-  for (auto e : G->slot_ev)
-    if (e) hipEventDestroy(e);
+  if (G->mail) hipHostFree(G->mail);
   delete G;
   return VD_OK;
 }
@@ -1302,9 +1307,8 @@ static vd_status set_density_impl(vd_grid* G, void* ctx) {
   }
   ck(hipMemcpyAsync(G->rho, rho, G->nreal * sizeof(double), hipMemcpyDeviceToDevice, G->st));
   density_setup(G->rho, G->nreal, G->a64, G->a32, G->rho32, G->partial, G->dsmall, G->st);
-  double h[4];
-  ck(hipMemcpyAsync(h, G->dsmall, 4 * sizeof(double), hipMemcpyDeviceToHost, G->st));
   ck(hipStreamSynchronize(G->st));
+  const double* h = G->dsmall;  // pinned: written by the set-up kernel
   if (h[3] != 0.0) {
     G->has_rho = false;
     return VD_EDOMAIN;
@@ -1428,8 +1432,9 @@ double project_psi(vd_grid* G, void* b64) {
   void* psih = buf(G, 64, B_PSI);
   VecPtrs P{};
   P.p[0] = psih;
-  mdot<double>(G->g, b64, P, 1, false, G->partial, G->dsmall + 2, G->st);
-  const double dot = read_scalar(G, G->dsmall + 2);
+  const double dot = read_value(G, G->dst, G->mail, G->st, [&](const Post& post) {
+    mdot<double>(G->g, b64, P, 1, false, G->partial, &G->dst->nrm2, G->st, nullptr, nullptr, post);
+  });
   OpParams plain{};
   precond_axpy<double>(G->g, plain, b64, psih, nullptr, -dot / G->psi2, G->st);
   return std::fabs(dot) / std::sqrt(G->psi2);
@@ -1520,12 +1525,13 @@ static vd_status solve_impl(vd_grid* G, void* c) {
   for (int comp = 0; comp < s->ncomp; ++comp) {
     const double* f = s->f + (size_t)comp * G->nreal;
     double* x = s->x + (size_t)comp * G->nreal;
+    bool removed = false;  // the projection writes the removed norm to dsmall[0]
     if (G->g.cheb) {  // weak form: b = -I^T W I f, nullspace constant in z
       void* tmp = buf(G, 64, B_TMP);
       fwd_transform(G->g, f, tmp, nullptr, G->tw64, G->st);
       c2_rhs(G->g, G->cd, tmp, b64, G->st);
       c2_project(G->g, b64, G->dsmall, G->st);
-      s->info.rhs_null_norm = std::fmax(s->info.rhs_null_norm, read_scalar(G, G->dsmall));
+      removed = true;
     } else if (kform) {
       double* t = (double*)buf(G, 64, B_TMP);
       rho_sqrt_mul(G->rho, f, t, false, -1.0, G->nreal, G->st);
@@ -1537,7 +1543,7 @@ static vd_status solve_impl(vd_grid* G, void* c) {
     if (s->kind == VD_OP_PRESSURE && !G->g.cheb && !kform) {
       project_range(G->g, b64, G->dsmall, G->st);
       scale<double>(G->g, b64, nullptr, -1.0, G->st);  // A = -L_rho, b = -f
-      s->info.rhs_null_norm = std::fmax(s->info.rhs_null_norm, read_scalar(G, G->dsmall));
+      removed = true;
     }
     if (s->o.use_x0 && kform) {  // Phi_0 = phi_0 / sqrt(rho)
       double* t = (double*)buf(G, 64, B_TMP);
@@ -1550,7 +1556,8 @@ static vd_status solve_impl(vd_grid* G, void* c) {
     } else {
       ck(hipMemsetAsync(x64, 0, G->nspec * 16, G->st));
     }
-    double bnorm = host_norm_of(G, b64);
+    double bnorm = host_norm_of(G, b64);  // waits for its reduction, so for the projection before it
+    if (removed) s->info.rhs_null_norm = std::fmax(s->info.rhs_null_norm, G->dsmall[0]);
     int refin = 0;
     std::vector<double> hist;
     const bool want_hist = comp == 0 && s->o.history_cap > 0;
@@ -1652,21 +1659,22 @@ static vd_status pressure_batch_impl(vd_grid* G0, void* c) {
     S.roff[k] = 0;
     S.dst[k] = G->dst;
     S.part[k] = G->partial;
-    S.slots[k] = G->hslot;
+    S.mail[k] = G->mail;
     S.rho0[k] = std::isnan(s->o.rho0) ? G->rho_mean : s->o.rho0;
     b64[k] = buf(G, 64, B_B);
     x64[k] = buf(G, 64, B_X);
     fwd_transform(G->g, s->f[k], b64[k], nullptr, G->tw64, G->st);
     project_range(G->g, b64[k], G->dsmall, G->st);
     scale<double>(G->g, b64[k], nullptr, -1.0, G->st);  // A = -L_rho, b = -f
-    s->infos[k].rhs_null_norm = read_scalar(G, G->dsmall);
     if (s->o.use_x0) {
       fwd_transform(G->g, s->x[k], x64[k], nullptr, G->tw64, G->st);
       project_range(G->g, x64[k], G->dsmall + 1, G->st);
     } else {
       ck(hipMemsetAsync(x64[k], 0, G->nspec * 16, G->st));
     }
-    bnorm[k] = host_norm_of(G, b64[k]);  // also waits for the grid's stream
+    bnorm[k] = host_norm_of(G, b64[k]);
+    s->infos[k].rhs_null_norm = G->dsmall[0];
+    ck(hipStreamSynchronize(G->st));  // the batch runs on the first grid's stream
   }
   op.rho0 = S.rho0[0];
   SolveOut so[kMaxBatch];

@@ -103,6 +103,22 @@ __device__ __forceinline__ void reduce_values(const double* __restrict__ partial
   }
 }
 
+// Values to the host (one thread).  The release orders them, and everything
+// else this thread has written, before seq for any observer of the system.
+__device__ __forceinline__ void post_mail(Mail* m, double a, double b, unsigned long long flags,
+                                          unsigned long long seq) {
+  __hip_atomic_store(&m->v[0], a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(&m->v[1], b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(&m->flags, flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(&m->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+// The state after step j of a cycle or run (bad and halt as just decided).
+__device__ __forceinline__ void post_step(DevState* st, int j, double resid, double nrm2, bool bad, bool halt,
+                                          int nreorth) {
+  post_mail(st->mail + MAIL_STEP + (j & 1), resid, nrm2,
+            (bad ? 1ull : 0ull) | (halt ? 2ull : 0ull) | ((unsigned long long)nreorth << 2), st->run + j + 1);
+}
+
 // Scalar steps of CG and RMR, taken by one thread on the reduced values
 // (passed in: see k_reduce).
 __device__ __forceinline__ void cg_alpha_step(DevState* st, double pq) {  // alpha = rz / (p, A p)
@@ -126,7 +142,10 @@ __device__ __forceinline__ void rec_check_step(DevState* st, double n2) {
   const int j = st->step;
   st->step = j + 1;
   const double rn = n2 < 0.0 ? 0.0 : sqrt(n2);
-  if (st->bad || !(n2 == n2) || rn / st->stop_bnorm <= st->stop_rtol || j >= st->jlast) st->halt = 1;
+  const bool bad = st->bad != 0;
+  const bool halt = bad || !(n2 == n2) || rn / st->stop_bnorm <= st->stop_rtol || j >= st->jlast;
+  if (halt) st->halt = 1;
+  post_step(st, j, rn, n2, bad, halt, 0);
 }
 
 // The final reduction, optionally followed (same launch, after a block
@@ -137,7 +156,7 @@ __device__ __forceinline__ void rec_check_step(DevState* st, double n2) {
 // after those stores (the compiler may serve it from the scalar cache).
 __global__ __launch_bounds__(1024) void k_reduce(const double* __restrict__ partial, int nblk, int K, double scale,
                                                  double* __restrict__ out, const int* __restrict__ gate, int post,
-                                                 DevState* st) {
+                                                 DevState* st, unsigned long long seq) {
   if (gate && *gate) return;
   __shared__ double val[2];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -155,13 +174,15 @@ __global__ __launch_bounds__(1024) void k_reduce(const double* __restrict__ part
   else if (post == POST_CG_BETA) cg_beta_step(st, val[0]);
   else if (post == POST_RMR_ALPHA) rmr_alpha_step(st, val[0], val[1]);
   else if (post == POST_REC_CHECK) rec_check_step(st, val[0]);
+  else if (post == POST_MAIL) post_mail(st->mail + MAIL_VALUE, val[0], 0.0, 0, seq);
 }
 
 // gate (here and below): optional device flag; when nonzero the launch does
 // nothing (a Krylov step queued past the end of its run)
 static void reduce(const double* partial, int nb, int K, double scale, double* out, hipStream_t s,
                    const int* gate = nullptr, const Post& post = Post{}) {
-  hipLaunchKernelGGL(k_reduce, dim3(1), dim3(1024), 0, s, partial, nb, K, scale, out, gate, post.op, post.st);
+  hipLaunchKernelGGL(k_reduce, dim3(1), dim3(1024), 0, s, partial, nb, K, scale, out, gate, post.op, post.st,
+                     post.seq);
 }
 
 static size_t nspec(const Geom& g) { return (size_t)g.nz * g.ny * g.M; }
@@ -374,9 +395,9 @@ __device__ __forceinline__ void gs_givens(DevState* st, const GsCheck& k, int nv
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   if (lane != 0) return;
   const double hn = k.hn;
-  if (!k.finite) st->bad = 1;
+  const int nreorth = st->nreorth + (k.orth ? 0 : 1);
   st->reorth = k.orth ? 0 : 1;
-  if (!k.orth) st->nreorth += 1;
+  st->nreorth = nreorth;
   st->hn = hn;
   st->vs[nv] = hn > 0.0 ? 1.0 / hn : 0.0;
   // previous rotations, in order, then the new one
@@ -401,9 +422,13 @@ __device__ __forceinline__ void gs_givens(DevState* st, const GsCheck& k, int nv
   const double gj = st->g[j];
   st->g[j + 1] = -sr * gj;
   st->g[j] = cr * gj;
-  st->resid = fabs(sr * gj);
-  if (!isfinite(rr) || !isfinite(sr * gj)) st->bad = 1;
-  if (st->bad || st->resid / st->stop_bnorm <= st->stop_rtol || j >= st->jlast) st->halt = 1;
+  const double resid = fabs(sr * gj);
+  st->resid = resid;
+  const bool bad = st->bad || !k.finite || !isfinite(rr) || !isfinite(sr * gj);
+  const bool halt = bad || resid / st->stop_bnorm <= st->stop_rtol || j >= st->jlast;
+  if (bad) st->bad = 1;
+  if (halt) st->halt = 1;
+  post_step(st, j, resid, 0.0, bad, halt, nreorth);
 }
 
 __global__ __launch_bounds__(1024) void k_gs_check(DevStates S, int nv, double tol, int nb, double scale) {
@@ -891,10 +916,11 @@ __global__ __launch_bounds__(256) void k_sub_norm(const C2<R>* __restrict__ b, c
   block_store<1>(&acc, 1, partial + blockIdx.x);
 }
 template <typename R>
-void sub_norm(const Geom& g, const void* b, const void* q, void* r, double* partial, double* out, hipStream_t s) {
+void sub_norm(const Geom& g, const void* b, const void* q, void* r, double* partial, double* out, hipStream_t s,
+              const Post& post) {
   hipLaunchKernelGGL((k_sub_norm<R>), dim3(nblk(nspec(g))), dim3(256), 0, s, (const C2<R>*)b, (const C2<R>*)q,
                      (C2<R>*)r, nspec(g), g.M, partial);
-  reduce(partial, nblk(nspec(g)), 1, g.ntot_inv, out, s);
+  reduce(partial, nblk(nspec(g)), 1, g.ntot_inv, out, s, nullptr, post);
 }
 
 template <typename R>
@@ -1074,7 +1100,7 @@ void project_range(const Geom& g, void* spec, double* removed, hipStream_t st) {
 
 // One wavefront (one thread clearing the 1056 entries of H took 6.8 us; 1.7 now).
 __global__ __launch_bounds__(64) void k_gmres_init(DevState* st, double beta, int m, double bnorm, double rtol,
-                                                   int jlast) {
+                                                   int jlast, unsigned long long run) {
   const int t = threadIdx.x;
   for (int i = t; i < (kMaxRestart + 1) * kMaxRestart; i += 64) st->H[i] = 0.0;
   if (t <= m && t <= kMaxRestart) st->g[t] = t == 0 ? beta : 0.0;
@@ -1087,6 +1113,8 @@ __global__ __launch_bounds__(64) void k_gmres_init(DevState* st, double beta, in
   st->resid = beta;
   st->bad = 0;
   st->reorth = 0;
+  st->nreorth = 0;
+  st->run = run;
 }
 
 // Column j of the Hessenberg matrix: the Gram-Schmidt coefficients h (plus
@@ -1118,52 +1146,33 @@ __global__ __launch_bounds__(64) void k_gmres_backsolve(DevState* st, int k) {
   }
 }
 
-__global__ void k_cg_alpha(DevState* st, const int* gate) {
-  if (threadIdx.x || (gate && *gate)) return;
-  cg_alpha_step(st, st->red[0]);
-}
-__global__ void k_cg_beta(DevState* st, const int* gate) {
-  if (threadIdx.x || (gate && *gate)) return;
-  cg_beta_step(st, st->red[0]);
-}
-__global__ void k_rmr_alpha(DevState* st, const int* gate) {
-  if (threadIdx.x || (gate && *gate)) return;
-  rmr_alpha_step(st, st->red[0], st->red[1]);
-}
-
-void gmres_init(DevState* st, double beta, int m, double bnorm, double rtol, int jlast, hipStream_t s) {
-  hipLaunchKernelGGL(k_gmres_init, dim3(1), dim3(64), 0, s, st, beta, m, bnorm, rtol, jlast);
+void gmres_init(DevState* st, double beta, int m, double bnorm, double rtol, int jlast, unsigned long long run,
+                hipStream_t s) {
+  hipLaunchKernelGGL(k_gmres_init, dim3(1), dim3(64), 0, s, st, beta, m, bnorm, rtol, jlast, run);
 }
 void gmres_backsolve(DevState* st, int k, hipStream_t s) {
   hipLaunchKernelGGL(k_gmres_backsolve, dim3(1), dim3(64), 0, s, st, k);
 }
-void cg_alpha(DevState* st, hipStream_t s, const int* gate) {
-  hipLaunchKernelGGL(k_cg_alpha, dim3(1), dim3(64), 0, s, st, gate);
-}
-void cg_beta(DevState* st, hipStream_t s, const int* gate) {
-  hipLaunchKernelGGL(k_cg_beta, dim3(1), dim3(64), 0, s, st, gate);
-}
-void rmr_alpha(DevState* st, hipStream_t s, const int* gate) {
-  hipLaunchKernelGGL(k_rmr_alpha, dim3(1), dim3(64), 0, s, st, gate);
-}
 
-__global__ void k_rec_check(DevState* st, const int* gate) {
-  if (threadIdx.x || (gate && *gate)) return;
-  rec_check_step(st, st->nrm2);
-}
-__global__ void k_rec_init(DevState* st, double bnorm, double rtol, int jlast) {
+__global__ void k_rec_init(DevState* st, double bnorm, double rtol, int jlast, unsigned long long run) {
   if (threadIdx.x) return;
   st->stop_bnorm = bnorm;
   st->stop_rtol = rtol;
   st->jlast = jlast;
   st->step = 0;
   st->halt = 0;
+  st->bad = 0;
+  st->run = run;
 }
-void rec_init(DevState* st, double bnorm, double rtol, int jlast, hipStream_t s) {
-  hipLaunchKernelGGL(k_rec_init, dim3(1), dim3(64), 0, s, st, bnorm, rtol, jlast);
+void rec_init(DevState* st, double bnorm, double rtol, int jlast, unsigned long long run, hipStream_t s) {
+  hipLaunchKernelGGL(k_rec_init, dim3(1), dim3(64), 0, s, st, bnorm, rtol, jlast, run);
 }
-void rec_check(DevState* st, hipStream_t s, const int* gate) {
-  hipLaunchKernelGGL(k_rec_check, dim3(1), dim3(64), 0, s, st, gate);
+
+__global__ void k_set_mail(DevState* st, Mail* mail) {
+  if (threadIdx.x == 0) st->mail = mail;
+}
+void set_mail(DevState* st, Mail* mail, hipStream_t s) {
+  hipLaunchKernelGGL(k_set_mail, dim3(1), dim3(64), 0, s, st, mail);
 }
 
 // --------------------------------------------------------- density set-up
@@ -1291,7 +1300,8 @@ void kcoef_finish(const double* rho, const double* lap_psi, double* kc64, float*
                                     Prof*);                                                                    \
   template void gs_orthogonalize_batch<R>(const Geom&, void* const*, const VecPtrs*, int, DevState* const*,   \
                                           double* const*, int, hipStream_t, Prof*);                          \
-  template void sub_norm<R>(const Geom&, const void*, const void*, void*, double*, double*, hipStream_t);      \
+  template void sub_norm<R>(const Geom&, const void*, const void*, void*, double*, double*, hipStream_t,       \
+                            const Post&);                                                                      \
   template void precond_axpy<R>(const Geom&, const OpParams&, void*, const void*, const double*, double,       \
                                 hipStream_t);                                                                  \
   template void dot_rMr<R>(const Geom&, const OpParams&, const void*, double*, double*, hipStream_t,           \

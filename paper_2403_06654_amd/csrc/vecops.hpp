@@ -21,18 +21,34 @@ struct VecPtrs {
   const void* p[kMaxVec];
 };
 
+// What a kernel tells the waiting host: written by the kernel straight into
+// pinned host memory, values first, then seq with a system-scope release.  The
+// host polls seq for the number it expects (each is used once per mailbox).
+// A step whose state went to the host as a copy of its own, with an event to
+// wait for, cost about 10 us of the stream per Krylov step.
+struct alignas(64) Mail {
+  double v[3];
+  unsigned long long flags;  // bit 0: bad, bit 1: halt, above: second passes of this cycle
+  unsigned long long seq;
+};
+// mailboxes of a solver state: two for the Krylov steps in turn, one for
+// single reduced values
+enum { MAIL_STEP = 0, MAIL_VALUE = 2, kMails = 3 };
+
 // Solver scalars kept on the device (FP64 regardless of vector precision).
 constexpr int kMaxRestart = 32;
 struct DevState {
   double H[(kMaxRestart + 1) * kMaxRestart];  // column-major, ld = kMaxRestart + 1
   double cs[kMaxRestart], sn[kMaxRestart], g[kMaxRestart + 1], y[kMaxRestart];
   double red[kMaxVec + 2];   // outputs of the last reduction
-  double red2[kMaxVec + 2];  // outputs of the previous reduction
+  double red2[kMaxVec];      // the first-pass dots of the last Gram-Schmidt step
+  Mail* mail;                // pinned host mailboxes (device address)
+  unsigned long long run;    // step j of the current cycle or run posts run + j + 1
   double vs[kMaxRestart + 1];     // scale of each stored (unnormalised) basis vector
   double hcol[kMaxVec], ccol[kMaxVec], coef[kMaxVec];  // Gram-Schmidt coefficients
   double hn;                 // norm of the newest orthogonalised vector
   int reorth;                // second Gram-Schmidt pass ran for this step
-  int nreorth;               // second passes since the grid was created
+  int nreorth;               // second passes of the current cycle
   double alpha, beta, rz, rz_new;
   // Krylov stopping test, evaluated on the device after each step (GMRES:
   // resid / stop_bnorm <= stop_rtol on the Givens estimate; CG and RMR: on
@@ -41,7 +57,7 @@ struct DevState {
   double stop_bnorm, stop_rtol;
   int jlast;
   int step;                  // CG / RMR: steps completed in the current run
-  // mirrored to the host after each step
+  // posted to the host after each step
   double resid;              // estimated (GMRES) or recursive residual norm
   double nrm2;               // last computed squared norm
   int bad;                   // non-finite scalar seen
@@ -52,12 +68,12 @@ struct DevState {
 // takes in its own launch once the reduced value is written (st: the
 // solver's device state): alpha = rz / red[0] (CG), beta = red[0] / rz and
 // rz = red[0] (CG), alpha = red[0] / red[1] (RMR), or the stopping test on
-// nrm2 (CG and RMR; see rec_check).  The same steps exist as separate
-// launches (cg_alpha, ...).
-enum PostOp { POST_NONE = 0, POST_CG_ALPHA, POST_CG_BETA, POST_RMR_ALPHA, POST_REC_CHECK };
+// nrm2 (CG and RMR), or the reduced value posted to the host as number seq.
+enum PostOp { POST_NONE = 0, POST_CG_ALPHA, POST_CG_BETA, POST_RMR_ALPHA, POST_REC_CHECK, POST_MAIL };
 struct Post {
   int op = POST_NONE;
   DevState* st = nullptr;
+  unsigned long long seq = 0;
 };
 
 // partial[b][i] = sum_e w_e Re(conj(V_i[e]) x[e]) (i < nv), plus |x|^2 at
@@ -103,7 +119,7 @@ void scale(const Geom& g, void* v, const double* s_dev, double s_host, hipStream
 // r = b - q, and |r|^2 reduced into out[0]
 template <typename R>
 void sub_norm(const Geom& g, const void* b, const void* q, void* r, double* partial, double* out,
-              hipStream_t s);
+              hipStream_t s, const Post& post = Post{});
 
 // Gates: the kernels below that take OpParams honour p.gate; the others take
 // an explicit gate.  A nonzero *gate makes the launch do nothing.
@@ -141,20 +157,18 @@ void project_range(const Geom& g, void* spec, double* removed, hipStream_t st);
 // Zero the mean (DC) of a packed FP64 spectrum; removed Euclidean norm to *removed.
 void zero_mean(const Geom& g, void* spec, double* removed, hipStream_t st);
 
-// Scalar kernels (one thread) of the Krylov methods.
+// Scalar kernels of the Krylov methods.
+// Gives a new state its mailboxes (device address of kMails of them).
+void set_mail(DevState* st, Mail* mail, hipStream_t s);
 // Starts a GMRES cycle: H, g, the basis scales and the stopping test
-// (bnorm, rtol, last step jlast of this cycle; halt cleared).
-void gmres_init(DevState* st, double beta, int m, double bnorm, double rtol, int jlast, hipStream_t s);
+// (bnorm, rtol, last step jlast of this cycle; halt and the second-pass count
+// cleared); step j posts run + j + 1.
+void gmres_init(DevState* st, double beta, int m, double bnorm, double rtol, int jlast, unsigned long long run,
+                hipStream_t s);
 void gmres_backsolve(DevState* st, int k, hipStream_t s);  // y, and coef = y * vs
-void cg_alpha(DevState* st, hipStream_t s, const int* gate = nullptr);   // alpha = rz / red[0]
-void cg_beta(DevState* st, hipStream_t s, const int* gate = nullptr);    // beta = red[0] / rz; rz = red[0]
-void rmr_alpha(DevState* st, hipStream_t s, const int* gate = nullptr);  // alpha = red[0] / red[1]
 // Starts a CG or RMR run: its stopping test (bnorm, rtol, last step jlast),
-// step = 0, halt cleared.
-void rec_init(DevState* st, double bnorm, double rtol, int jlast, hipStream_t s);
-// After a CG or RMR step: halt on a non-finite scalar, on the recursive
-// residual sqrt(nrm2) / bnorm <= rtol, or on step jlast.
-void rec_check(DevState* st, hipStream_t s, const int* gate);
+// step = 0, halt and bad cleared; step j posts run + j + 1.
+void rec_init(DevState* st, double bnorm, double rtol, int jlast, unsigned long long run, hipStream_t s);
 
 // Density set-up: a = 1/rho and copies, min/max/sum reductions.
 void density_setup(const double* rho, size_t n, double* a64, float* a32, float* rho32, double* partial,
