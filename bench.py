@@ -730,7 +730,7 @@ def bench_ns(args):
     Krylov iterations, ||div u|| after every step up to t = pi/4; (b) errors
     at T = pi/4 for dt = T/8 .. T/64 and their orders (the temporal-error
     set-up); (c) event-timed classes over profiled steps for the roofline of
-    the FFT transforms."""
+    the FFT and fused product passes."""
     import numpy as np
     import torch
     from paper_2403_06654_amd.api import FractionalStep
@@ -758,11 +758,9 @@ def bench_ns(args):
     tr = prof["transforms"]
     ach = tr["bytes"] / (tr["ms"] * 1e-3) / 1e9
     roof = {"bound": "hbm", "achieved": round(ach, 1), "peak": 8000.0, "unit": "GB/s", "frac": round(ach / 8000.0, 4),
-            "traffic": None, "kernel": "FFT transform passes (k_row R2C/C2R, k_col FFT_FWD/FFT_INV)",
-            "per_unit": f"48 n^3 bytes per 3D transform (3 passes reading and writing the field), n = {n}; "
-                        "a launch group is one transform or three batched",
-            "launches": tr["count"], "transforms": int(round(tr["bytes"] / (48.0 * n ** 3))),
-            "avg_us_per_transform": round(1e3 * tr["ms"] / max(tr["bytes"] / (48.0 * n ** 3), 1), 2)}
+            "traffic": None, "kernel": "FFT transform passes and fused product passes (k_row, k_col, k_ns_z, k_ns_y, k_ns_*_x)",
+            "per_unit": f"8 n^3 bytes per field that a pass reads or writes, n = {n}",
+            "launch_groups": tr["count"], "fields": int(round(tr["bytes"] / (8.0 * n ** 3)))}
     ns.close()
     # (a) divergence history at dt = 0.01 up to t = pi/4
     print("bench: ns divergence history", file=sys.stderr, flush=True)

@@ -402,10 +402,11 @@ vd_status vd_ns_errors(vd_ns* h, double* err);
  * state. */
 vd_status vd_ns_project(vd_ns* h, const double* rho, const double* u, double* out, vd_solve_info* info);
 /* Optional timing of the handle's work with HIP events on its stream, by
- * class: 0 the FFT transforms (algorithmic bytes 48 n^3 each: three passes
- * reading and writing the field), 1 the pressure solves, 2 the viscous
- * solve's inner products and updates.  Enabling resets the totals; reading
- * returns milliseconds, launch counts and bytes per class. */
+ * class: 0 the FFT passes, those that form derivatives and products on the
+ * way among them (algorithmic bytes: 8 n^3 per field that a pass reads or
+ * writes), 1 the pressure solves, 2 the viscous solve's inner products and
+ * updates.  Enabling resets the totals; reading returns milliseconds, launch
+ * counts and bytes per class. */
 vd_status vd_ns_profile_enable(vd_ns* h, int on);
 vd_status vd_ns_profile_read(vd_ns* h, double* ms, long long* count, double* bytes, int nclass);
 

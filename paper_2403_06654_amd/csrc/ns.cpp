@@ -8,17 +8,23 @@
 //      viscous system u* - dt/2 zeta(rho^(n+1/2), u*) = rhs, by right-
 //      preconditioned GMRES with (I - dt/(2 Re) Lap)^-1 (eq. VDINSE.V) from u^n;
 //   5. L_rho phi = div(u*) / dt (eq. VDINSE.Lrho.num) by the pressure solver
-//      of this library (vd_solve_pressure), warm-started from the previous phi;
+//      of this library, warm-started from the previous phi;
 //   6. u^(n+1) = u* - dt grad(phi) / rho^(n+1/2) (eq. VDINSE.num.proj);
 //   7. p^(n+1/2) = p^(n-1/2) + phi - (div grad)^-1 div(dt/2 rho zeta(rho,
 //      grad(phi) / rho)) (eq. VDINSE.num.p.update, scalar form).
 // zeta is eq. VDINSE.zeta.  Derivatives are spectral (first derivatives with
-// the Nyquist mode zeroed, the Laplacian with it kept); transforms are the
-// library's FP64 FFT passes; the pointwise work runs in ns_kernels.hip.  The
-// Krylov loop of step 4 is driven from the host: its inner products are
-// block partials summed on the host in a fixed order.
+// the Nyquist mode zeroed, the Laplacian with it kept).
+//
+// Between steps the state is kept as packed spectra: linear steps (the density,
+// the divergence, the projection and the pressure update) act on them directly,
+// and a product is formed by the fused passes of ns_passes.hip, which take each
+// factor and all its derivatives to physical space in one sweep per axis.  The
+// physical fields of the state are brought up to date at the end of a call.
+// The viscous system's Krylov vectors are stacks of three spectra in the
+// Gram-Schmidt, stopping-test and mailbox machinery of the other solvers.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <initializer_list>
 #include <new>
@@ -26,41 +32,49 @@
 #include <vector>
 
 #include "../../include/vdsolve.h"
+#include "mail.hpp"
 #include "ns.hpp"
 
 using namespace vd;
 
 struct vd_ns {
   int n = 0;
-  size_t N = 0, nspec = 0;
+  size_t N = 0, ns = 0;  // grid points; slots of a packed field (N / 2)
   vd_ns_params prm{};
   hipStream_t st = nullptr;
   vd_grid* grid = nullptr;
-  Geom g{};
+  Geom g{}, g3{};  // g3: a stack of three fields as one vector of the Krylov kernels
   const void* tw = nullptr;
   std::vector<void*> allocs;
-  // state: u^n (3 fields), rho^n, p^(n-1/2), the last phi, previous advection terms
-  double *u = nullptr, *rho = nullptr, *p = nullptr, *phi = nullptr, *nu_prev = nullptr, *nr_prev = nullptr;
+  // state u^n (3 fields), rho^n, p^(n-1/2): physical, and as spectra (uh, rhoh,
+  // ph) with the last phi (phih) and the previous advection terms (the velocity's
+  // physical, nu; the density's spectral, nrh; [0] the newest)
+  double *u = nullptr, *rho = nullptr, *p = nullptr;
+  double *uh = nullptr, *rhoh = nullptr, *ph = nullptr, *phih = nullptr;
+  double* nu[2] = {};
+  double* nrh[2] = {};
   bool have_prev = false, have_state = false;
+  bool spec = false;  // the spectra hold the state (else they are built from the physical fields)
   double t = 0;
   int steps = 0;
-  // coefficients of a density: gradient (3), Hessian (00 01 02 11 12 22), 1 / (rho Re)
-  double *cg = nullptr, *ch = nullptr, *cirr = nullptr;
-  // scratch fields
-  double *rho1 = nullptr, *rh = nullptr, *f = nullptr, *S = nullptr, *advu = nullptr, *advr = nullptr;
-  double *rhs = nullptr, *ust = nullptr, *gp = nullptr, *lapb = nullptr, *d3 = nullptr, *w3 = nullptr;
-  double *e3 = nullptr, *x3 = nullptr, *sc1 = nullptr;
-  // spectral buffers: sa/sb/sc (three each) and the inverse transforms' scratch
-  void *sa[3] = {}, *sb[3] = {}, *sc[3] = {}, *wk[3] = {};
-  double* V = nullptr;  // GMRES basis, (restart + 1) vectors of 3 N
+  // coefficients of a density: its values, gradient (3), Hessian (00 01 02 11 12 22), 1 / (rho Re)
+  double *rh = nullptr, *cg = nullptr, *ch = nullptr, *cirr = nullptr;
+  // scratch: spectra of rho^(n+1) and rho^(n+1/2); rows of three components
+  // (stacks T, Tz, Tl, Ty) and of a scalar's gradient (3); stacks of three
+  double *rho1h = nullptr, *rhh = nullptr;
+  double *T = nullptr, *Tz = nullptr, *Tl = nullptr, *Ty = nullptr, *pr = nullptr;
+  double *bh = nullptr, *q3 = nullptr, *x3h = nullptr, *z3 = nullptr;
+  double *f = nullptr, *Sf = nullptr, *Sh = nullptr;  // body force (physical), mass source (physical, spectrum)
+  double* V = nullptr;  // GMRES basis, (restart + 1) stacks of three spectra
   double* part = nullptr;
-  double* dc = nullptr;
-  double* dh = nullptr;  // GMRES: the Hessenberg column being built, then ||w||^2
+  DevState* dst = nullptr;
+  Mail* mail = nullptr;
+  unsigned long long posts = 0;
   int nb = 0;
   std::vector<double> hpart;
   vd_ns_info last{};
-  // optional HIP-event timing by class: 0 FFT transforms, 1 pressure solves,
-  // 2 viscous Krylov inner products and updates
+  // optional HIP-event timing by class: 0 FFT transform passes, 1 pressure
+  // solves, 2 viscous Krylov inner products and updates
   struct Pend {
     int cls;
     double bytes;
@@ -100,14 +114,9 @@ void release(vd_ns* h) {
   }
   for (hipEvent_t e : h->spare) hipEventDestroy(e);
   for (void* p : h->allocs) hipFree(p);
+  if (h->mail) hipHostFree(h->mail);
   if (h->grid) vd_grid_destroy(h->grid);
   delete h;
-}
-
-int hidx(int i, int j) {
-  if (i > j) std::swap(i, j);
-  static const int t[3][3] = {{0, 1, 2}, {1, 3, 4}, {2, 4, 5}};
-  return t[i][j];
 }
 
 hipEvent_t ev(vd_ns* h) {
@@ -147,208 +156,256 @@ void prof_flush(vd_ns* h) {
   }
   h->pend.clear();
 }
+// Forget the records after the first n: launches that exited at their gate.
+void prof_drop(vd_ns* h, size_t n) {
+  for (size_t i = n; i < h->pend.size(); ++i) {
+    h->spare.push_back(h->pend[i].a);
+    h->spare.push_back(h->pend[i].b);
+  }
+  if (h->pend.size() > n) h->pend.resize(n, vd_ns::Pend{0, 0.0, nullptr, nullptr});
+}
 
-// One 3D transform is three passes (x rows, y and z columns), each reading
-// and writing the field once: 3 * 16 N algorithmic bytes.
-double transform_bytes(const vd_ns* h) { return 3.0 * 16.0 * (double)h->N; }
+// Algorithmic bytes of a group of passes that reads and writes `fields` fields.
+double fields_bytes(const vd_ns* h, double fields) { return 8.0 * (double)h->N * fields; }
+// One whole transform: three passes, each reading and writing the field.
+constexpr double kTransform = 6.0;
 
 void fwd(vd_ns* h, const double* phys, void* spec) {
-  timed(h, 0, transform_bytes(h), [&] { fwd_transform(h->g, phys, spec, nullptr, h->tw, h->st); });
+  timed(h, 0, fields_bytes(h, kTransform), [&] { fwd_transform(h->g, phys, spec, nullptr, h->tw, h->st); });
 }
 void inv(vd_ns* h, const void* spec, double* phys) {
-  timed(h, 0, transform_bytes(h), [&] { inv_transform(h->g, spec, phys, h->wk[0], h->tw, h->st); });
+  timed(h, 0, fields_bytes(h, kTransform), [&] { inv_transform(h->g, spec, phys, h->T, h->tw, h->st); });
 }
-// three fields at once (the column passes take all three in one launch)
-void fwd3(vd_ns* h, const double* const* phys, void* const* spec) {
-  timed(h, 0, 3 * transform_bytes(h), [&] { fwd_transform_n(h->g, phys, spec, 3, h->tw, h->st); });
+// stacks of three fields
+void fwd3(vd_ns* h, const double* phys, double* spec) {
+  const double* in[3] = {phys, phys + h->N, phys + 2 * h->N};
+  void* o[3] = {spec, spec + h->N, spec + 2 * h->N};
+  timed(h, 0, fields_bytes(h, 3 * kTransform), [&] { fwd_transform_n(h->g, in, o, 3, h->tw, h->st); });
 }
-void inv3(vd_ns* h, const void* const* spec, double* const* phys) {
-  timed(h, 0, 3 * transform_bytes(h), [&] { inv_transform_n(h->g, spec, phys, h->wk, 3, h->tw, h->st); });
+void inv3(vd_ns* h, const double* spec, double* phys) {
+  const void* in[3] = {spec, spec + h->N, spec + 2 * h->N};
+  void* wk[3] = {h->T, h->T + h->N, h->T + 2 * h->N};
+  double* o[3] = {phys, phys + h->N, phys + 2 * h->N};
+  timed(h, 0, fields_bytes(h, 3 * kTransform), [&] { inv_transform_n(h->g, in, o, wk, 3, h->tw, h->st); });
+}
+// y and z transforms of nf fields already transformed along x
+void fwd_columns(vd_ns* h, double* spec, int nf, const int* gate = nullptr) {
+  void* o[3] = {spec, spec + h->N, spec + 2 * h->N};
+  timed(h, 0, fields_bytes(h, 4.0 * nf), [&] { fwd_columns_n(h->g, o, nf, h->tw, h->st, gate); });
 }
 
-void lin(vd_ns* h, double* out, size_t n, std::initializer_list<std::pair<double, const double*>> terms,
-         std::initializer_list<std::pair<double, const double*>> dterms = {}, const double* den = nullptr,
-         const double* mul = nullptr) {
+void lin(vd_ns* h, double* out, size_t n, std::initializer_list<std::pair<double, const double*>> terms) {
   LinArgs a;
   for (auto& t : terms) {
     a.c[a.nt] = t.first;
     a.in[a.nt++] = t.second;
   }
-  for (auto& t : dterms) {
-    a.cd[a.nd] = t.first;
-    a.dv[a.nd++] = t.second;
-  }
-  a.den = den;
-  a.mul = mul;
   a.out = out;
   a.n = n;
   ns_lincomb(a, h->st);
 }
 
-// out[d] = d f / dx_d
-void grad(vd_ns* h, const double* f, double* out) {
-  fwd(h, f, h->sa[0]);
-  for (int d = 0; d < 3; ++d) ns_deriv(h->g, h->sa[0], h->sb[d], d, h->st);
-  double* o[3] = {out, out + h->N, out + 2 * h->N};
-  inv3(h, h->sb, o);
+// rows of the gradient of a scalar spectrum into pr
+void scalar_rows(vd_ns* h, const double* spec) {
+  timed(h, 0, fields_bytes(h, 8.0),
+        [&] { grad_rows(h->g, spec, h->pr, h->pr + h->N, h->pr + 2 * h->N, h->tw, h->st); });
 }
 
-void lap(vd_ns* h, const double* f, double* out) {
-  fwd(h, f, h->sa[0]);
-  lap_packed(h->g, h->sa[0], h->sb[0], h->st);
-  inv(h, h->sb[0], out);
+// rows of a stack of three components, their y and z derivatives and the y and
+// z part of their Laplacians into T, Ty, Tz, Tl; `precond`: of
+// (I - dt/(2 Re) Lap)^-1 of it, times *scale
+void vector_rows(vd_ns* h, const double* spec, bool precond = false, const double* scale = nullptr,
+                 const int* gate = nullptr) {
+  NsZArgs z{};
+  z.in = spec;
+  z.t0 = h->T;
+  z.t1 = h->Tz;
+  z.t2 = h->Tl;
+  z.stride = h->ns;
+  z.g = h->g;
+  z.nu = 0.5 * h->prm.dt / h->prm.re;
+  z.precond = precond ? 1 : 0;
+  z.in_scale = scale;
+  z.gate = gate;
+  timed(h, 0, fields_bytes(h, 12.0), [&] { ns_z_pass(z, 3, false, h->tw, h->st); });
+  NsYArgs y{};
+  y.t0 = h->T;
+  y.t1 = h->Tz;
+  y.t2 = h->Tl;
+  y.y1 = h->Ty;
+  y.stride = h->ns;
+  y.g = h->g;
+  y.gate = gate;
+  timed(h, 0, fields_bytes(h, 21.0), [&] { ns_y_pass(y, 3, false, h->tw, h->st); });
 }
 
-void div(vd_ns* h, const double* u3, double* out) {
-  const double* in[3] = {u3, u3 + h->N, u3 + 2 * h->N};
-  fwd3(h, in, h->sa);
-  for (int d = 0; d < 3; ++d) ns_deriv(h->g, h->sa[d], h->sb[d], d, h->st);
-  lin(h, (double*)h->sb[0], 2 * h->nspec,
-      {{1.0, (const double*)h->sb[0]}, {1.0, (const double*)h->sb[1]}, {1.0, (const double*)h->sb[2]}});
-  inv(h, h->sb[0], out);
+NsZetaArgs zeta_args(const vd_ns* h, double a, double b, double* out) {
+  NsZetaArgs z{};
+  z.y0 = h->T;
+  z.yy = h->Ty;
+  z.yz = h->Tz;
+  z.yl = h->Tl;
+  z.stride = h->ns;
+  z.n = h->N;
+  z.gr = h->cg;
+  z.h = h->ch;
+  z.irr = h->cirr;
+  z.a = a;
+  z.b = b;
+  z.inv_sc = 1.0 / h->prm.sc;
+  z.norm = h->g.ntot_inv;
+  z.sx = h->g.sx;
+  z.re = h->prm.re;
+  z.out = out;
+  return z;
+}
+void zeta(vd_ns* h, const NsZetaArgs& z, bool rhs, bool phys) {
+  timed(h, 0, fields_bytes(h, rhs ? 34.0 : 25.0), [&] { ns_zeta_pass(h->g, z, rhs, phys, h->tw, h->st); });
 }
 
-// gradient, Hessian and 1 / (rho Re) of a density
-void coefficients(vd_ns* h, const double* rho) {
+// out = A x (spectra): x - dt/2 zeta(rho^(n+1/2), x), of M^-1 x * *scale if precond
+void viscous_apply(vd_ns* h, const double* x, double* out, bool precond, const double* scale, const int* gate) {
+  vector_rows(h, x, precond, scale, gate);
+  NsZetaArgs z = zeta_args(h, 1.0, -0.5 * h->prm.dt, out);
+  z.gate = gate;
+  zeta(h, z, false, false);
+  fwd_columns(h, out, 3, gate);
+}
+
+// density values, gradient, Hessian and 1 / (rho Re) of a density spectrum
+void coefficients(vd_ns* h, const double* spec) {
   const size_t N = h->N;
-  fwd(h, rho, h->sa[0]);
-  for (int i = 0; i < 3; ++i) ns_deriv(h->g, h->sa[0], h->sb[i], i, h->st);
-  double* g3[3] = {h->cg, h->cg + N, h->cg + 2 * N};
-  inv3(h, h->sb, g3);
-  // Hessian entries (0,0) (0,1) (0,2), then (1,1) (1,2) (2,2)
-  for (int d = 0; d < 3; ++d) ns_deriv(h->g, h->sb[0], h->sc[d], d, h->st);
-  double* h1[3] = {h->ch + hidx(0, 0) * N, h->ch + hidx(0, 1) * N, h->ch + hidx(0, 2) * N};
-  inv3(h, h->sc, h1);
-  ns_deriv(h->g, h->sb[1], h->sc[0], 1, h->st);
-  ns_deriv(h->g, h->sb[1], h->sc[1], 2, h->st);
-  ns_deriv(h->g, h->sb[2], h->sc[2], 2, h->st);
-  double* h2[3] = {h->ch + hidx(1, 1) * N, h->ch + hidx(1, 2) * N, h->ch + hidx(2, 2) * N};
-  inv3(h, h->sc, h2);
-  ns_recip(rho, h->prm.re, h->cirr, N, h->st);
+  NsZArgs z{};
+  z.in = spec;
+  z.t0 = h->pr;
+  z.t1 = h->pr + N;
+  z.t2 = h->pr + 2 * N;
+  z.stride = h->ns;
+  z.g = h->g;
+  timed(h, 0, fields_bytes(h, 4.0), [&] { ns_z_pass(z, 1, true, h->tw, h->st); });
+  NsYArgs y{};
+  y.t0 = h->pr;
+  y.t1 = h->pr + N;
+  y.t2 = h->pr + 2 * N;
+  y.y1 = h->q3;
+  y.y2 = h->q3 + N;
+  y.y3 = h->q3 + 2 * N;
+  y.stride = h->ns;
+  y.g = h->g;
+  timed(h, 0, fields_bytes(h, 9.0), [&] { ns_y_pass(y, 1, true, h->tw, h->st); });
+  NsCoefArgs c{};
+  c.y0 = y.t0;
+  c.t1 = y.t1;
+  c.t2 = y.t2;
+  c.y1 = y.y1;
+  c.y2 = y.y2;
+  c.y3 = y.y3;
+  c.rho = h->rh;
+  c.irr = h->cirr;
+  c.gr = h->cg;
+  c.h = h->ch;
+  c.n = N;
+  c.norm = h->g.ntot_inv;
+  c.sx = h->g.sx;
+  c.re = h->prm.re;
+  timed(h, 0, fields_bytes(h, 17.0), [&] { ns_coef_pass(h->g, c, h->tw, h->st); });
 }
 
-// out = a x + b zeta(rho, x) for the density whose coefficients are loaded;
-// x and out are 3-field vectors and must not overlap.
-void zeta(vd_ns* h, const double* x, double a, double b, double* out) {
-  const size_t N = h->N;
-  const double* in[3] = {x, x + N, x + 2 * N};
-  fwd3(h, in, h->sa);
-  for (int i = 0; i < 3; ++i) {
-    lap_packed(h->g, h->sa[i], h->sb[0], h->st);
-    ns_deriv(h->g, h->sa[i], h->sb[1], 0, h->st);
-    ns_deriv(h->g, h->sa[i], h->sb[2], 1, h->st);
-    ns_deriv(h->g, h->sa[i], h->sc[0], 2, h->st);
-    double* o[3] = {h->lapb, h->d3, h->d3 + N};
-    inv3(h, h->sb, o);
-    inv(h, h->sc[0], h->d3 + 2 * N);
-    ZetaArgs z{};
-    for (int j = 0; j < 3; ++j) {
-      z.u[j] = x + j * N;
-      z.du[j] = h->d3 + j * N;
-      z.h[j] = h->ch + hidx(i, j) * N;
-      z.gr[j] = h->cg + j * N;
-    }
-    z.lap = h->lapb;
-    z.irr = h->cirr;
-    z.x = x + i * N;
-    z.a = a;
-    z.b = b;
-    z.inv_sc = 1.0 / h->prm.sc;
-    z.out = out + i * N;
-    z.n = N;
-    ns_zeta(z, h->st);
-  }
+// spectrum of (u . grad) q: u's rows are in T, q's gradient rows in pr
+void advect_scalar(vd_ns* h, double* out) {
+  NsAdvArgs a{};
+  a.y0 = h->T;
+  a.stride = h->ns;
+  a.q0 = h->pr;
+  a.qy = h->pr + h->N;
+  a.qz = h->pr + 2 * h->N;
+  a.norm = h->g.ntot_inv;
+  a.sx = h->g.sx;
+  a.out = out;
+  timed(h, 0, fields_bytes(h, 7.0), [&] { ns_advect_pass(h->g, a, h->tw, h->st); });
+  fwd_columns(h, out, 1);
 }
 
-// out = (u . grad) q for a scalar q
-void advect_scalar(vd_ns* h, const double* u3, const double* q, double* out) {
-  grad(h, q, h->d3);
-  const double* uu[3] = {u3, u3 + h->N, u3 + 2 * h->N};
-  const double* dd[3] = {h->d3, h->d3 + h->N, h->d3 + 2 * h->N};
-  ns_advect(uu, dd, out, h->N, h->st);
+// grad(q) / rho from q's gradient rows (pr) and cirr: a stack of three, spectra
+// or (phys) physical
+void grad_over_rho(vd_ns* h, double* out, bool phys) {
+  NsGradArgs a{};
+  a.q0 = h->pr;
+  a.qy = h->pr + h->N;
+  a.qz = h->pr + 2 * h->N;
+  a.irr = h->cirr;
+  a.norm = h->g.ntot_inv;
+  a.sx = h->g.sx;
+  a.re = h->prm.re;
+  a.stride = h->ns;
+  a.out = out;
+  timed(h, 0, fields_bytes(h, 7.0), [&] { ns_grad_pass(h->g, a, phys, h->tw, h->st); });
+  if (!phys) fwd_columns(h, out, 3);
 }
 
-void advect_vec(vd_ns* h, const double* u3, double* out3) {
-  for (int i = 0; i < 3; ++i) advect_scalar(h, u3, u3 + i * h->N, out3 + i * h->N);
-}
-
-// out = (I - c Lap)^-1 x, componentwise (1 or 3 fields)
-void helm_inv(vd_ns* h, const double* x, double c, double* out, int ncomp) {
-  OpParams op{};
-  op.kind = OP_HELMHOLTZ;
-  op.rho0 = 1.0;
-  op.nu = c;
-  op.precond = 1;
-  if (ncomp == 3) {
-    const double* in[3] = {x, x + h->N, x + 2 * h->N};
-    double* o[3] = {out, out + h->N, out + 2 * h->N};
-    fwd3(h, in, h->sa);
-    for (int i = 0; i < 3; ++i) precond_apply<double>(h->g, op, h->sa[i], h->sb[i], h->st);
-    inv3(h, h->sb, o);
-    return;
-  }
-  fwd(h, x, h->sa[0]);
-  precond_apply<double>(h->g, op, h->sa[0], h->sb[0], h->st);
-  inv(h, h->sb[0], out);
-}
-
-// out = (div grad)^-1 f (symbol -1 / sum_d k'_d^2, zero on its nullspace)
-void divgrad_pinv(vd_ns* h, const double* f, double* out) {
-  OpParams op{};
-  op.kind = OP_PRESSURE;
-  op.rho0 = -1.0;
-  op.precond = 1;
-  fwd(h, f, h->sa[0]);
-  precond_apply<double>(h->g, op, h->sa[0], h->sb[0], h->st);
-  inv(h, h->sb[0], out);
-}
-
-// inner products of w with V_0..V_{nv-1} (stride between vectors), summed on the host
-void dots(vd_ns* h, const double* V, size_t stride, int nv, const double* w, size_t n, double* out) {
-  timed(h, 2, 8.0 * (double)n * (nv + 1), [&] { ns_dots(V, stride, nv, w, n, h->part, h->nb, h->st); });
-  h->hpart.resize((size_t)nv * h->nb);
-  ck(hipMemcpyAsync(h->hpart.data(), h->part, h->hpart.size() * sizeof(double), hipMemcpyDeviceToHost, h->st));
-  ck(hipStreamSynchronize(h->st));
-  for (int i = 0; i < nv; ++i) {
-    double s = 0.0;
-    for (int b = 0; b < h->nb; ++b) s += h->hpart[(size_t)i * h->nb + b];
-    out[i] = s;
-  }
-}
-
+// Euclidean norm of a physical field
 double norm(vd_ns* h, const double* x, size_t n) {
-  double s;
-  dots(h, x, 0, 1, x, n, &s);
+  ns_square(x, n, h->part, h->nb, h->st);
+  h->hpart.resize(h->nb);
+  ck(hipMemcpyAsync(h->hpart.data(), h->part, h->nb * sizeof(double), hipMemcpyDeviceToHost, h->st));
+  ck(hipStreamSynchronize(h->st));
+  double s = 0.0;
+  for (int b = 0; b < h->nb; ++b) s += h->hpart[b];
   return std::sqrt(s);
 }
 
-void to_dev(vd_ns* h, const double* c, int nv) {
-  ck(hipMemcpyAsync(h->dc, c, nv * sizeof(double), hipMemcpyHostToDevice, h->st));
-  ck(hipStreamSynchronize(h->st));
+double post_value(vd_ns* h, unsigned long long seq) {
+  if (!wait_mail(h->mail + MAIL_VALUE, seq, h->st)) throw Err{VD_EDEVICE};
+  const double s = h->mail[MAIL_VALUE].v[0];
+  return s < 0.0 ? 0.0 : std::sqrt(s);  // a NaN stays NaN
+}
+// Euclidean norm of the physical values of a spectral vector of geometry g
+double norm_spec(vd_ns* h, const Geom& g, const double* x) {
+  const unsigned long long seq = ++h->posts;
+  mdot<double>(g, x, VecPtrs{}, 0, true, h->part, &h->dst->nrm2, h->st, nullptr, nullptr,
+               Post{POST_MAIL, h->dst, seq});
+  return post_value(h, seq);
+}
+// r = b - A x and its norm
+double viscous_residual(vd_ns* h, const double* b, const double* x, double* r) {
+  viscous_apply(h, x, h->q3, false, nullptr, nullptr);
+  const unsigned long long seq = ++h->posts;
+  sub_norm<double>(h->g3, b, h->q3, r, h->part, &h->dst->nrm2, h->st, Post{POST_MAIL, h->dst, seq});
+  return post_value(h, seq);
 }
 
-// Right-preconditioned GMRES(m) with classical Gram-Schmidt applied twice on
-// A x = x - dt/2 zeta(rho^(n+1/2), x) = b; x holds the initial guess.
+// Right-preconditioned GMRES(m) on A x = x - dt/2 zeta(rho^(n+1/2), x) = b
+// (stacks of three spectra); x holds the initial guess.  The steps are queued
+// one ahead of the host, as in vdsolve.cpp.
 void solve_viscous(vd_ns* h, const double* b, double* x, int& iters, int& status, double& relres) {
   const size_t n3 = 3 * h->N;
   const int m = h->prm.restart;
-  const double hdt = 0.5 * h->prm.dt, c = 0.5 * h->prm.dt / h->prm.re, rtol = h->prm.visc_rtol;
-  double* w = h->w3;
-  double* z = h->e3;
-  const double bn = norm(h, b, n3);
+  const double rtol = h->prm.visc_rtol;
+  const double vb = 8.0 * (double)n3;
   iters = 0;
   status = VD_OK;
   relres = 0.0;
+  const double bn = norm_spec(h, h->g3, b);
   if (bn == 0.0) {
     ck(hipMemsetAsync(x, 0, n3 * sizeof(double), h->st));
     return;
   }
-  double* r = h->V;  // the residual is built in V_0
-  zeta(h, x, 1.0, -hdt, w);
-  lin(h, r, n3, {{1.0, b}, {-1.0, w}});
-  std::vector<double> H((size_t)(m + 1) * m), cs(m), sn(m), g(m + 1), y(m), cf(m + 1), c2(m + 1);
+  auto vec = [&](int j) { return h->V + (size_t)j * n3; };
+  OpParams op{};
+  op.kind = OP_HELMHOLTZ;
+  op.rho0 = 1.0;
+  op.nu = 0.5 * h->prm.dt / h->prm.re;
+  op.precond = 1;
+  const int* gate = &h->dst->halt;
+  auto step = [&](int j) {
+    viscous_apply(h, vec(j), vec(j + 1), true, &h->dst->vs[j], gate);
+    VecPtrs P{};
+    for (int i = 0; i <= j; ++i) P.p[i] = vec(i);
+    timed(h, 2, vb * (2.0 * j + 5.0),
+          [&] { gs_orthogonalize<double>(h->g3, vec(j + 1), P, j + 1, h->dst, h->part, h->st); });
+  };
+  double beta = viscous_residual(h, b, x, vec(0));
   while (true) {
-    const double beta = norm(h, r, n3);
     relres = beta / bn;
     if (!(beta == beta)) {
       status = VD_EBREAKDOWN;
@@ -359,124 +416,64 @@ void solve_viscous(vd_ns* h, const double* b, double* x, int& iters, int& status
       status = VD_NOT_CONVERGED;
       return;
     }
-    lin(h, h->V, n3, {{1.0 / beta, r}});
-    std::fill(g.begin(), g.end(), 0.0);
-    g[0] = beta;
+    const int jlast = std::min(m, h->prm.max_iter - iters) - 1;
+    const unsigned long long run = h->posts;
+    h->posts += (unsigned long long)jlast + 1;
+    gmres_init(h->dst, beta, m, bn, rtol, jlast, run, h->st);
+    StepState t;
     int k = 0;
-    for (int j = 0; j < m; ++j) {
-      double* vj = h->V + (size_t)j * n3;
-      helm_inv(h, vj, c, z, 3);
-      zeta(h, z, 1.0, -hdt, w);
-      ++iters;
-      // both Gram-Schmidt passes on the device (coefficients reduced there
-      // in a fixed order), then one read of the column and ||w||^2
-      for (int pass = 0; pass < 2; ++pass) {
-        timed(h, 2, 8.0 * (double)n3 * (j + 2), [&] { ns_dots(h->V, n3, j + 1, w, n3, h->part, h->nb, h->st); });
-        ns_dsum(h->part, h->nb, j + 1, h->dc, h->dh, pass, h->st);
-        timed(h, 2, 8.0 * (double)n3 * (j + 3), [&] { ns_mupdate(h->V, n3, j + 1, h->dc, w, n3, 0, h->st); });
-      }
-      timed(h, 2, 8.0 * (double)n3 * 2, [&] { ns_dots(w, 0, 1, w, n3, h->part, h->nb, h->st); });
-      ns_dsum(h->part, h->nb, 1, h->dh + j + 1, nullptr, 0, h->st);
-      ck(hipMemcpyAsync(c2.data(), h->dh, (j + 2) * sizeof(double), hipMemcpyDeviceToHost, h->st));
-      ck(hipStreamSynchronize(h->st));
-      for (int i = 0; i <= j; ++i) cf[i] = c2[i];
-      const double hn = std::sqrt(c2[j + 1]);
-      double hj = cf[0];
-      for (int i = 0; i < j; ++i) {
-        const double hb = cf[i + 1];
-        H[(size_t)j * (m + 1) + i] = cs[i] * hj + sn[i] * hb;
-        hj = -sn[i] * hj + cs[i] * hb;
-      }
-      const double rr = std::hypot(hj, hn);
-      cs[j] = rr > 0.0 ? hj / rr : 1.0;
-      sn[j] = rr > 0.0 ? hn / rr : 0.0;
-      H[(size_t)j * (m + 1) + j] = rr;
-      g[j + 1] = -sn[j] * g[j];
-      g[j] = cs[j] * g[j];
+    step(0);
+    size_t mark = h->pend.size();
+    for (int j = 0; j <= jlast; ++j) {
+      if (j < jlast) step(j + 1);
+      if (!wait_step(h->mail, j, run, h->st, &t)) throw Err{VD_EDEVICE};
       k = j + 1;
-      if (std::fabs(g[j + 1]) / bn <= rtol || hn == 0.0 || iters >= h->prm.max_iter || !(rr == rr)) break;
-      lin(h, h->V + (size_t)(j + 1) * n3, n3, {{1.0 / hn, w}});
+      if (t.bad || t.halt) break;
+      mark = h->pend.size();
     }
-    for (int i = k - 1; i >= 0; --i) {
-      double t = g[i];
-      for (int q = i + 1; q < k; ++q) t -= H[(size_t)q * (m + 1) + i] * y[q];
-      const double d = H[(size_t)i * (m + 1) + i];
-      y[i] = d != 0.0 ? t / d : 0.0;
-    }
-    to_dev(h, y.data(), k);
-    ns_mupdate(h->V, n3, k, h->dc, w, n3, 1, h->st);
-    helm_inv(h, w, c, z, 3);
-    lin(h, x, n3, {{1.0, x}, {1.0, z}});
-    zeta(h, x, 1.0, -hdt, w);
-    lin(h, r, n3, {{1.0, b}, {-1.0, w}});
+    prof_drop(h, mark);
+    iters += k;
+    gmres_backsolve(h->dst, k, h->st);
+    VecPtrs P{};
+    for (int i = 0; i < k; ++i) P.p[i] = vec(i);
+    lincomb<double>(h->g3, h->z3, P, k, h->dst->coef, h->st);
+    for (int c = 0; c < 3; ++c)
+      precond_axpy<double>(h->g, op, x + c * h->N, h->z3 + c * h->N, nullptr, 1.0, h->st);
+    beta = viscous_residual(h, b, x, vec(0));
   }
 }
 
-// body force f and mass source S of eq. VDINSE.solexact at time t (uses the
-// coefficient buffers and the scratch fields e3, x3, sc1, rho1)
-void manufactured(vd_ns* h, double t, double* f, double* S) {
+// body force f (physical) and mass source S (spectrum Sh) of eq.
+// VDINSE.solexact at time t (uses the coefficients and the row scratch)
+void manufactured(vd_ns* h, double t) {
   const size_t N = h->N;
-  double* ue = h->x3;
-  double* pe = h->sc1;
-  double* re = h->rho1;
-  ns_tg_fields(h->n, t, h->prm.s, ue, pe, re, f, S, h->st);  // f = du/dt, S = drho/dt
-  coefficients(h, re);
-  zeta(h, ue, 0.0, -1.0, h->e3);  // e3 = -zeta(rho_e, u_e)
-  lin(h, f, 3 * N, {{1.0, f}, {1.0, h->e3}});
-  advect_vec(h, ue, h->e3);
-  lin(h, f, 3 * N, {{1.0, f}, {1.0, h->e3}});
-  grad(h, pe, h->e3);
-  for (int i = 0; i < 3; ++i) lin(h, f + i * N, N, {{1.0, f + i * N}}, {{1.0, h->e3 + i * N}}, re);
-  advect_scalar(h, ue, re, h->e3);
-  lap(h, re, h->e3 + N);
-  lin(h, S, N, {{1.0, S}, {1.0, h->e3}, {-1.0 / (h->prm.re * h->prm.sc), h->e3 + N}});
+  double *ue = h->q3, *pe = h->pr, *re = h->pr + N;
+  ns_tg_fields(h->n, t, h->prm.s, ue, pe, re, h->f, h->Sf, h->st);  // f = du/dt, Sf = drho/dt
+  fwd3(h, ue, h->bh);
+  double *peh = h->x3h, *reh = h->x3h + N, *lap = h->x3h + 2 * N;
+  fwd(h, pe, peh);
+  fwd(h, re, reh);
+  fwd(h, h->Sf, h->Sh);
+  coefficients(h, reh);
+  vector_rows(h, h->bh);
+  scalar_rows(h, peh);
+  // f = du/dt + (u . grad) u + grad p / rho - zeta(rho, u)
+  NsZetaArgs z = zeta_args(h, 0.0, -1.0, h->f);
+  z.p0 = h->pr;
+  z.py = h->pr + N;
+  z.pz = h->pr + 2 * N;
+  z.ext = h->f;
+  z.ca = z.cg = z.ce = 1.0;
+  zeta(h, z, true, true);
+  // S = drho/dt + u . grad rho - Lap rho / (Re Sc)
+  scalar_rows(h, reh);
+  advect_scalar(h, h->z3);
+  lap_packed(h->g, reh, lap, h->st);
+  lin(h, h->Sh, N, {{1.0, h->Sh}, {1.0, h->z3}, {-1.0 / (h->prm.re * h->prm.sc), lap}});
 }
 
-void step_once(vd_ns* h) {
-  const size_t N = h->N;
-  const double dt = h->prm.dt, re = h->prm.re, sc = h->prm.sc;
-  const double th = h->t + 0.5 * dt;
-  if (h->prm.s > 0.0) {
-    manufactured(h, th, h->f, h->S);
-  } else {
-    ck(hipMemsetAsync(h->f, 0, 3 * N * sizeof(double), h->st));
-    ck(hipMemsetAsync(h->S, 0, N * sizeof(double), h->st));
-  }
-  // 1. advection terms, Adams-Bashforth (N^(-1) = N^n on the first step)
-  advect_vec(h, h->u, h->advu);
-  advect_scalar(h, h->u, h->rho, h->advr);
-  if (!h->have_prev) {
-    ck(hipMemcpyAsync(h->nu_prev, h->advu, 3 * N * sizeof(double), hipMemcpyDeviceToDevice, h->st));
-    ck(hipMemcpyAsync(h->nr_prev, h->advr, N * sizeof(double), hipMemcpyDeviceToDevice, h->st));
-  }
-  // the current terms become the previous ones; the extrapolation goes to rhs/sc1
-  lin(h, h->rhs, 3 * N, {{1.5, h->advu}, {-0.5, h->nu_prev}});
-  lin(h, h->sc1, N, {{1.5, h->advr}, {-0.5, h->nr_prev}});
-  std::swap(h->advu, h->nu_prev);
-  std::swap(h->advr, h->nr_prev);
-  h->have_prev = true;
-  // 2. Crank-Nicolson density
-  const double kap = 1.0 / (re * sc);
-  lap(h, h->rho, h->e3);
-  lin(h, h->e3, N, {{1.0, h->rho}, {dt, h->S}, {-dt, h->sc1}, {0.5 * dt * kap, h->e3}});
-  helm_inv(h, h->e3, 0.5 * dt * kap, h->rho1, 1);
-  // 3. mid-step density
-  lin(h, h->rh, N, {{0.5, h->rho1}, {0.5, h->rho}});
-  // 4. intermediate velocity
-  coefficients(h, h->rh);
-  grad(h, h->p, h->gp);
-  zeta(h, h->u, 0.0, 0.5 * dt, h->e3);  // dt/2 zeta(rho^(n+1/2), u^n)
-  for (int i = 0; i < 3; ++i)
-    lin(h, h->rhs + i * N, N, {{1.0, h->u + i * N}, {-dt, h->rhs + i * N}, {1.0, h->e3 + i * N}, {dt, h->f + i * N}},
-        {{-dt, h->gp + i * N}}, h->rh);
-  ck(hipMemcpyAsync(h->ust, h->u, 3 * N * sizeof(double), hipMemcpyDeviceToDevice, h->st));
-  int vit = 0, vst = 0;
-  double vres = 0;
-  solve_viscous(h, h->rhs, h->ust, vit, vst, vres);
-  // 5. pressure equation
-  div(h, h->ust, h->sc1);
-  lin(h, h->sc1, N, {{1.0 / dt, h->sc1}});
-  if (vd_set_density(h->grid, h->rh) != VD_OK) throw Err{VD_EDOMAIN};
+// phi from the spectrum of div(u*) / dt, into phih
+vd_status solve_pressure(vd_ns* h, double* div, vd_solve_info* pi) {
   vd_solve_opts o;
   vd_default_opts(&o);
   o.solver = h->prm.pres_solver;
@@ -485,22 +482,93 @@ void step_once(vd_ns* h) {
   o.rtol = h->prm.pres_rtol;
   o.max_iter = h->prm.max_iter;
   o.use_x0 = 1;
-  vd_solve_info pi{};
   vd_status ps = VD_OK;
-  timed(h, 1, 0.0, [&] { ps = vd_solve_pressure(h->grid, h->sc1, h->phi, &o, &pi); });
+  if (h->prm.pres_form == VD_FORM_L) {
+    timed(h, 1, 0.0, [&] { ps = grid_solve_pressure_spec(h->grid, div, h->phih, &o, pi); });
+    return ps;
+  }
+  // the modified form changes the unknown in physical space
+  double *f = h->q3, *phi = h->q3 + h->N;
+  inv(h, div, f);
+  inv(h, h->phih, phi);
+  timed(h, 1, 0.0, [&] { ps = vd_solve_pressure(h->grid, f, phi, &o, pi); });
+  if (ps >= 0) fwd(h, phi, h->phih);
+  return ps;
+}
+
+void step_once(vd_ns* h) {
+  const size_t N = h->N;
+  const double dt = h->prm.dt, re = h->prm.re, sc = h->prm.sc;
+  const bool forced = h->prm.s > 0.0;
+  if (!h->spec) {  // a state was set
+    fwd3(h, h->u, h->uh);
+    fwd(h, h->rho, h->rhoh);
+    fwd(h, h->p, h->ph);
+    ck(hipMemsetAsync(h->phih, 0, N * sizeof(double), h->st));
+    h->spec = true;
+  }
+  if (forced) manufactured(h, h->t + 0.5 * dt);
+  // Adams-Bashforth weights of the new and the previous advection terms (N^(-1) = N^n on the first step)
+  const double w0 = h->have_prev ? 1.5 : 1.0, w1 = h->have_prev ? -0.5 : 0.0;
+  vector_rows(h, h->uh);
+  // 1., 2. the density's advection and Crank-Nicolson step; 3. the mid-step density
+  scalar_rows(h, h->rhoh);
+  advect_scalar(h, h->nrh[0]);
+  NsDensArgs d{};
+  d.rho = h->rhoh;
+  d.S = forced ? h->Sh : nullptr;
+  d.na = h->nrh[0];
+  d.nb = h->have_prev ? h->nrh[1] : nullptr;
+  d.c = 0.5 * dt / (re * sc);
+  d.s = dt;
+  d.sa = -dt * w0;
+  d.sb = -dt * w1;
+  d.rho1 = h->rho1h;
+  d.rhm = h->rhh;
+  d.g = h->g;
+  d.n = h->ns;
+  ns_density(d, h->st);
+  // 4. intermediate velocity
+  coefficients(h, h->rhh);
+  scalar_rows(h, h->ph);
+  NsZetaArgs z = zeta_args(h, 1.0, 0.5 * dt, h->bh);
+  z.p0 = h->pr;
+  z.py = h->pr + N;
+  z.pz = h->pr + 2 * N;
+  z.nprev = h->have_prev ? h->nu[1] : nullptr;
+  z.ext = forced ? h->f : nullptr;
+  z.ca = -dt * w0;
+  z.cp = -dt * w1;
+  z.cg = -dt;
+  z.ce = dt;
+  z.nout = h->nu[0];
+  zeta(h, z, true, false);
+  fwd_columns(h, h->bh, 3);
+  std::swap(h->nu[0], h->nu[1]);  // the current terms become the previous ones
+  std::swap(h->nrh[0], h->nrh[1]);
+  h->have_prev = true;
+  int vit = 0, vst = 0;
+  double vres = 0;
+  solve_viscous(h, h->bh, h->uh, vit, vst, vres);  // uh: u^n to u*
+  // 5. pressure equation
+  ns_div(h->g, h->uh, h->ns, 1.0 / dt, h->z3, h->st);
+  if (vd_set_density(h->grid, h->rh) != VD_OK) throw Err{VD_EDOMAIN};
+  vd_solve_info pi{};
+  const vd_status ps = solve_pressure(h, h->z3, &pi);
   if (ps < 0 && ps != VD_NOT_CONVERGED) throw Err{ps};
   // 6. projection
-  grad(h, h->phi, h->gp);
-  for (int i = 0; i < 3; ++i) lin(h, h->u + i * N, N, {{1.0, h->ust + i * N}}, {{-dt, h->gp + i * N}}, h->rh);
+  scalar_rows(h, h->phih);
+  grad_over_rho(h, h->x3h, false);
+  lin(h, h->uh, 3 * N, {{1.0, h->uh}, {-dt, h->x3h}});
   // 7. pressure update: p += phi - (div grad)^-1 div(dt/2 rho zeta(rho, grad(phi) / rho))
-  for (int i = 0; i < 3; ++i) lin(h, h->x3 + i * N, N, {}, {{1.0, h->gp + i * N}}, h->rh);
-  zeta(h, h->x3, 0.0, 0.5 * dt, h->e3);
-  for (int i = 0; i < 3; ++i) lin(h, h->e3 + i * N, N, {{1.0, h->e3 + i * N}}, {}, nullptr, h->rh);
-  div(h, h->e3, h->sc1);
-  divgrad_pinv(h, h->sc1, h->lapb);
-  lin(h, h->p, N, {{1.0, h->p}, {1.0, h->phi}, {-1.0, h->lapb}});
+  vector_rows(h, h->x3h);
+  z = zeta_args(h, 0.0, 0.5 * dt, h->q3);
+  z.wconst = 1.0 / re;  // rho times 1 / (rho Re)
+  zeta(h, z, false, false);
+  fwd_columns(h, h->q3, 3);
+  ns_pressure(h->g, h->q3, h->ns, h->phih, h->ph, h->st);
   // rho^(n+1) becomes the state
-  std::swap(h->rho, h->rho1);
+  std::swap(h->rhoh, h->rho1h);
   h->t += dt;
   ++h->steps;
   h->last.t = h->t;
@@ -512,6 +580,13 @@ void step_once(vd_ns* h) {
   h->last.pres_status = ps;
   h->last.pres_rel_residual = pi.rel_residual;
   h->last.pres_seconds = pi.seconds;
+}
+
+// the physical fields of the state from its spectra
+void state_to_physical(vd_ns* h) {
+  inv3(h, h->uh, h->u);
+  inv(h, h->rhoh, h->rho);
+  inv(h, h->ph, h->p);
 }
 
 }  // namespace
@@ -564,43 +639,45 @@ vd_status vd_ns_create(vd_ns** out, int n, const vd_ns_params* prm, hipStream_t 
     if (gs != VD_OK) throw Err{gs};
     h->g = grid_geom(h->grid);
     h->tw = grid_twiddles(h->grid);
-    h->nspec = (size_t)h->g.nz * h->g.ny * h->g.M;
-    const size_t N = h->N, ns2 = 2 * h->nspec;
+    h->ns = (size_t)h->g.nz * h->g.ny * h->g.M;
+    h->g3 = h->g;
+    h->g3.nz = 3 * h->g.nz;
+    const size_t N = h->N;  // doubles of a field, physical or packed
     h->u = dalloc(h, 3 * N);
     h->rho = dalloc(h, N);
     h->p = dalloc(h, N);
-    h->phi = dalloc(h, N);
-    h->nu_prev = dalloc(h, 3 * N);
-    h->nr_prev = dalloc(h, N);
+    h->uh = dalloc(h, 3 * N);
+    h->rhoh = dalloc(h, N);
+    h->ph = dalloc(h, N);
+    h->phih = dalloc(h, N);
+    for (int i = 0; i < 2; ++i) {
+      h->nu[i] = dalloc(h, 3 * N);
+      h->nrh[i] = dalloc(h, N);
+    }
+    h->rh = dalloc(h, N);
     h->cg = dalloc(h, 3 * N);
     h->ch = dalloc(h, 6 * N);
     h->cirr = dalloc(h, N);
-    h->rho1 = dalloc(h, N);
-    h->rh = dalloc(h, N);
+    h->rho1h = dalloc(h, N);
+    h->rhh = dalloc(h, N);
+    h->T = dalloc(h, 3 * N);
+    h->Tz = dalloc(h, 3 * N);
+    h->Tl = dalloc(h, 3 * N);
+    h->Ty = dalloc(h, 3 * N);
+    h->pr = dalloc(h, 3 * N);
+    h->bh = dalloc(h, 3 * N);
+    h->q3 = dalloc(h, 3 * N);
+    h->x3h = dalloc(h, 3 * N);
+    h->z3 = dalloc(h, 3 * N);
     h->f = dalloc(h, 3 * N);
-    h->S = dalloc(h, N);
-    h->advu = dalloc(h, 3 * N);
-    h->advr = dalloc(h, N);
-    h->rhs = dalloc(h, 3 * N);
-    h->ust = dalloc(h, 3 * N);
-    h->gp = dalloc(h, 3 * N);
-    h->lapb = dalloc(h, N);
-    h->d3 = dalloc(h, 3 * N);
-    h->w3 = dalloc(h, 3 * N);
-    h->e3 = dalloc(h, 3 * N);
-    h->x3 = dalloc(h, 3 * N);
-    h->sc1 = dalloc(h, N);
-    for (int i = 0; i < 3; ++i) {
-      h->sa[i] = dalloc(h, ns2);
-      h->sb[i] = dalloc(h, ns2);
-      h->sc[i] = dalloc(h, ns2);
-      h->wk[i] = dalloc(h, ns2);
-    }
+    h->Sf = dalloc(h, N);
+    h->Sh = dalloc(h, N);
     h->V = dalloc(h, (size_t)(p.restart + 1) * 3 * N);
     h->nb = ns_dot_blocks(3 * N);
-    h->part = dalloc(h, (size_t)(p.restart + 1) * h->nb);
-    h->dc = dalloc(h, p.restart + 1);
-    h->dh = dalloc(h, p.restart + 2);
+    h->part = dalloc(h, nred_partial());
+    h->dst = (DevState*)dalloc(h, sizeof(DevState) / sizeof(double) + 1);
+    ck(hipMemsetAsync(h->dst, 0, sizeof(DevState), stream));
+    ck(make_mail(&h->mail, h->dst, stream));
   } catch (const Err& e) {
     release(h);
     return e.s;
@@ -626,9 +703,9 @@ vd_status vd_ns_set_state(vd_ns* h, const double* u, const double* rho, const do
   if (hipMemcpyAsync(h->u, u, 3 * N * sizeof(double), hipMemcpyDeviceToDevice, h->st) != hipSuccess ||
       hipMemcpyAsync(h->rho, rho, N * sizeof(double), hipMemcpyDeviceToDevice, h->st) != hipSuccess ||
       hipMemcpyAsync(h->p, p, N * sizeof(double), hipMemcpyDeviceToDevice, h->st) != hipSuccess ||
-      hipMemsetAsync(h->phi, 0, N * sizeof(double), h->st) != hipSuccess ||
       hipStreamSynchronize(h->st) != hipSuccess)
     return VD_EDEVICE;
+  h->spec = false;
   h->t = t;
   h->steps = 0;
   h->have_prev = false;
@@ -638,12 +715,10 @@ vd_status vd_ns_set_state(vd_ns* h, const double* u, const double* rho, const do
 
 vd_status vd_ns_init_taylor_green(vd_ns* h) {
   if (!h || !(h->prm.s > 0.0)) return VD_EINVAL;
-  const size_t N = h->N;
-  ns_tg_fields(h->n, 0.0, h->prm.s, h->u, h->sc1, h->rho, nullptr, nullptr, h->st);
-  ns_tg_fields(h->n, -0.5 * h->prm.dt, h->prm.s, h->x3, h->p, h->rho1, nullptr, nullptr, h->st);
-  if (hipMemsetAsync(h->phi, 0, N * sizeof(double), h->st) != hipSuccess ||
-      hipStreamSynchronize(h->st) != hipSuccess || hipGetLastError() != hipSuccess)
-    return VD_EDEVICE;
+  ns_tg_fields(h->n, 0.0, h->prm.s, h->u, h->pr, h->rho, nullptr, nullptr, h->st);
+  ns_tg_fields(h->n, -0.5 * h->prm.dt, h->prm.s, h->q3, h->p, h->pr, nullptr, nullptr, h->st);
+  if (hipStreamSynchronize(h->st) != hipSuccess || hipGetLastError() != hipSuccess) return VD_EDEVICE;
+  h->spec = false;
   h->t = 0.0;
   h->steps = 0;
   h->have_prev = false;
@@ -662,8 +737,10 @@ vd_status vd_ns_step(vd_ns* h, int nsteps, vd_ns_info* info) {
         prof_flush(h);
       }
     }
+    if (nsteps > 0) state_to_physical(h);
     ck(hipStreamSynchronize(h->st));
     ck(hipGetLastError());
+    if (h->prof) prof_flush(h);
   } catch (const Err& e) {
     hipGetLastError();
     return e.s;
@@ -690,18 +767,21 @@ vd_status vd_ns_get_state(vd_ns* h, double* u, double* rho, double* p, double* t
 vd_status vd_ns_errors(vd_ns* h, double* err) {
   if (!h || !err || !(h->prm.s > 0.0)) return VD_EINVAL;
   const size_t N = h->N;
+  const double rn = std::sqrt((double)N);
+  double *ue = h->q3, *pe = h->pr, *re = h->pr + N;
   try {
     // exact fields at t (u, rho) and at t - dt/2 (p)
-    ns_tg_fields(h->n, h->t, h->prm.s, h->x3, h->sc1, h->rho1, nullptr, nullptr, h->st);
-    lin(h, h->x3, 3 * N, {{1.0, h->u}, {-1.0, h->x3}});
-    lin(h, h->rho1, N, {{1.0, h->rho}, {-1.0, h->rho1}});
-    err[0] = norm(h, h->x3, 3 * N) / std::sqrt((double)N);
-    err[2] = norm(h, h->rho1, N) / std::sqrt((double)N);
-    ns_tg_fields(h->n, h->t - 0.5 * h->prm.dt, h->prm.s, h->x3, h->sc1, h->rho1, nullptr, nullptr, h->st);
-    lin(h, h->sc1, N, {{1.0, h->p}, {-1.0, h->sc1}});
-    err[1] = norm(h, h->sc1, N) / std::sqrt((double)N);
-    div(h, h->u, h->sc1);
-    err[3] = norm(h, h->sc1, N) / std::sqrt((double)N);
+    ns_tg_fields(h->n, h->t, h->prm.s, ue, pe, re, nullptr, nullptr, h->st);
+    lin(h, ue, 3 * N, {{1.0, h->u}, {-1.0, ue}});
+    lin(h, re, N, {{1.0, h->rho}, {-1.0, re}});
+    err[0] = norm(h, ue, 3 * N) / rn;
+    err[2] = norm(h, re, N) / rn;
+    ns_tg_fields(h->n, h->t - 0.5 * h->prm.dt, h->prm.s, ue, pe, re, nullptr, nullptr, h->st);
+    lin(h, pe, N, {{1.0, h->p}, {-1.0, pe}});
+    err[1] = norm(h, pe, N) / rn;
+    fwd3(h, h->u, h->x3h);
+    ns_div(h->g, h->x3h, h->ns, 1.0, h->z3, h->st);
+    err[3] = norm_spec(h, h->g, h->z3) / rn;
   } catch (const Err& e) {
     hipGetLastError();
     return e.s;
@@ -714,7 +794,8 @@ vd_status vd_ns_project(vd_ns* h, const double* rho, const double* u, double* ou
   const size_t N = h->N;
   vd_status ps = VD_OK;
   try {
-    div(h, u, h->sc1);
+    fwd3(h, u, h->x3h);
+    ns_div(h->g, h->x3h, h->ns, 1.0, h->z3, h->st);
     if (vd_set_density(h->grid, rho) != VD_OK) return VD_EDOMAIN;
     vd_solve_opts o;
     vd_default_opts(&o);
@@ -722,10 +803,13 @@ vd_status vd_ns_project(vd_ns* h, const double* rho, const double* u, double* ou
     o.restart = h->prm.restart;
     o.rtol = h->prm.pres_rtol;
     o.max_iter = h->prm.max_iter;
-    ps = vd_solve_pressure(h->grid, h->sc1, h->lapb, &o, info);
+    double* phi = h->z3 + N;
+    ps = grid_solve_pressure_spec(h->grid, h->z3, phi, &o, info);
     if (ps < 0 && ps != VD_NOT_CONVERGED) return ps;
-    grad(h, h->lapb, h->gp);
-    for (int i = 0; i < 3; ++i) lin(h, out + i * N, N, {{1.0, u + i * N}}, {{-1.0, h->gp + i * N}}, rho);
+    ns_recip(rho, h->prm.re, h->cirr, N, h->st);
+    scalar_rows(h, phi);
+    grad_over_rho(h, h->q3, true);
+    lin(h, out, 3 * N, {{1.0, u}, {-1.0, h->q3}});
     ck(hipStreamSynchronize(h->st));
     ck(hipGetLastError());
   } catch (const Err& e) {

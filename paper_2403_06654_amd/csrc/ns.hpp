@@ -1,16 +1,14 @@
-// Kernels of the fractional-step driver (ns.cpp): FP64 spectral derivatives
-// on packed spectra, the pointwise parts of zeta (eq. VDINSE.zeta) and of the
-// advection terms, linear combinations, reductions and the manufactured
-// Taylor-Green fields (eq. VDINSE.solexact).
+// Kernels of the fractional-step driver (ns.cpp): fused FP64 spectral passes
+// (ns_passes.hip) and pointwise kernels, reductions and the manufactured
+// Taylor-Green fields (eq. VDINSE.solexact; ns_kernels.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>
 
 #include <cstddef>
 
+#include "../../include/vdsolve.h"
 #include "passes.hpp"
-
-struct vd_grid;
 
 namespace vd {
 
@@ -18,30 +16,111 @@ namespace vd {
 const Geom& grid_geom(const vd_grid* G);
 const void* grid_twiddles(const vd_grid* G);
 
-// y = i k'_d x on a packed FP64 spectrum (d = 0: x, 1: y, 2: z; Nyquist
-// zeroed); x == y allowed.
-void ns_deriv(const Geom& g, const void* x, void* y, int d, hipStream_t st);
+// vd_solve_pressure (direct form, Fourier grid) from and to packed spectra on
+// the grid's stream: p also holds the initial guess if opts->use_x0.
+vd_status grid_solve_pressure_spec(vd_grid* G, const void* fhat, void* phat, const vd_solve_opts* opts,
+                                   vd_solve_info* info);
 
-// out = a x + b zeta_i with
-// zeta_i = irr (lap + inv_sc (sum_j u_j h_j + sum_j gr_j du_j)),
-// where lap = Lap u_i, du_j = d u_i / dx_j, h_j = d^2 rho / dx_i dx_j,
-// gr_j = d rho / dx_j and irr = 1 / (rho Re).  x may be null when a = 0.
-struct ZetaArgs {
-  const double* u[3];
-  const double* lap;
-  const double* du[3];
-  const double* h[3];
-  const double* gr[3];
-  const double* irr;
-  const double* x;
-  double a, b, inv_sc;
-  double* out;
-  size_t n;
+// A stack is nf fields one after another, `stride` slots (one packed field)
+// apart.  Grids are n^3, n a power of two in [16, 512].  gate (optional): a
+// nonzero device flag makes the launch do nothing.
+
+// z pass of a stack: t0 = Fz^-1 v, t1 = Fz^-1 (i k'_z v), t2 = Fz^-1 (-k_z^2 v)
+// (hess: -k'_z^2), v = in * *in_scale, with precond also (I - nu Lap)^-1;
+// outputs separate from in.
+struct NsZArgs {
+  const void* in;
+  void *t0, *t1, *t2;
+  size_t stride;
+  Geom g;
+  double nu = 0;
+  int precond = 0;
+  const double* in_scale = nullptr;
+  const int* gate = nullptr;
 };
-void ns_zeta(const ZetaArgs& z, hipStream_t st);
+void ns_z_pass(const NsZArgs& a, int nf, bool hess, const void* tw, hipStream_t st);
 
-// out = sum_j u_j d_j
-void ns_advect(const double* const u[3], const double* const d[3], double* out, size_t n, hipStream_t st);
+// y pass on its output, in place: t0 -> Fy^-1 t0, t1 -> Fy^-1 t1,
+// y1 = Fy^-1 (i k'_y t0) and t2 -> Fy^-1 (t2 - k_y^2 t0); hess: t2 -> Fy^-1 t2,
+// y2 = Fy^-1 (-k'_y^2 t0), y3 = Fy^-1 (i k'_y t1).
+struct NsYArgs {
+  void *t0, *t1, *t2, *y1, *y2 = nullptr, *y3 = nullptr;
+  size_t stride;
+  Geom g;
+  const int* gate = nullptr;
+};
+void ns_y_pass(const NsYArgs& a, int nf, bool hess, const void* tw, hipStream_t st);
+
+// x pass of zeta (eq. VDINSE.zeta) on three components' rows (y0, yy, yz, yl:
+// stacks t0, y1, t1, t2 of the y pass):
+//   out_i = a u_i + b W (Lap u_i + (sum_j u_j h_ij + sum_j gr_j d_j u_i) inv_sc),
+// W = irr = 1 / (rho Re), or wconst if not zero; with rhs also
+//   + ca n_i + cp nprev_i + cg d_i p / rho + ce ext_i,  n_i = (u . grad) u_i,
+// p0, py, pz the rows of p's gradient (grad_rows), n_i written to nout; nprev,
+// ext and nout are optional.  gr, h, irr, nprev, ext, nout: physical.  out: rows
+// transformed along x, or physical.
+struct NsZetaArgs {
+  const void *y0, *yy, *yz, *yl;
+  size_t stride;  // slots per field
+  size_t n;       // grid points
+  const double *gr, *h, *irr;
+  double a, b, inv_sc, wconst = 0, norm, sx, re = 0;
+  const void *p0 = nullptr, *py = nullptr, *pz = nullptr;
+  const double *nprev = nullptr, *ext = nullptr;
+  double ca = 0, cp = 0, cg = 0, ce = 0;
+  double* nout = nullptr;
+  void* out;
+  const int* gate = nullptr;
+};
+void ns_zeta_pass(const Geom& g, const NsZetaArgs& a, bool rhs, bool phys, const void* tw, hipStream_t st);
+
+// x pass of a density's coefficients from the hess passes' rows: rho,
+// irr = 1 / (rho Re), gradient gr (3) and Hessian h (00 01 02 11 12 22).
+struct NsCoefArgs {
+  const void *y0, *t1, *t2, *y1, *y2, *y3;
+  double *rho, *irr, *gr, *h;
+  size_t n;
+  double norm, sx, re;
+};
+void ns_coef_pass(const Geom& g, const NsCoefArgs& a, const void* tw, hipStream_t st);
+
+// x pass of (u . grad) q: y0 the stack of u's rows; q0, qy, qz the rows of q's
+// gradient; out: rows transformed along x.
+struct NsAdvArgs {
+  const void* y0;
+  size_t stride;
+  const void *q0, *qy, *qz;
+  double norm, sx;
+  void* out;
+};
+void ns_advect_pass(const Geom& g, const NsAdvArgs& a, const void* tw, hipStream_t st);
+
+// x pass of grad(q) / rho (irr = 1 / (rho Re)), a stack of three; rows
+// transformed along x, or physical.
+struct NsGradArgs {
+  const void *q0, *qy, *qz;
+  const double* irr;
+  double norm, sx, re;
+  size_t stride;
+  void* out;
+};
+void ns_grad_pass(const Geom& g, const NsGradArgs& a, bool phys, const void* tw, hipStream_t st);
+
+// Spectral pointwise steps.  Crank-Nicolson density (c = dt / (2 Re Sc)):
+// rho1 = ((1 - c k^2) rho + s S + sa na + sb nb) / (1 + c k^2) (S, nb
+// optional), rhm = (rho + rho1) / 2.
+struct NsDensArgs {
+  const void *rho, *S, *na, *nb;
+  double c, s, sa, sb;
+  void *rho1, *rhm;
+  Geom g;
+  size_t n;  // slots
+};
+void ns_density(const NsDensArgs& a, hipStream_t st);
+// out = c i k' . v of a stack of three
+void ns_div(const Geom& g, const void* v, size_t stride, double c, void* out, hipStream_t st);
+// p += phi - (div grad)^-1 div v
+void ns_pressure(const Geom& g, const void* v, size_t stride, const void* phi, void* p, hipStream_t st);
 
 // out = (sum_t c_t in_t + (sum_t cd_t dv_t) / den) * mul (up to 6 and 3
 // terms; mul optional); out may alias an input.
@@ -68,18 +147,8 @@ void ns_recip(const double* x, double c, double* out, size_t n, hipStream_t st);
 void ns_tg_fields(int n, double t, double s, double* u, double* p, double* rho, double* du, double* drho,
                   hipStream_t st);
 
-// Partial inner products: part[i * nb + b] = sum over block b's share of
-// V_i . w, V_i = V + i * stride, i < nv.  Fixed order within a block.
+// part[b] = sum over block b's share of x . x, in a fixed order within a block.
 int ns_dot_blocks(size_t n);
-// c[i] = sum over blocks of part[i][b] on the device, in a fixed order;
-// hacc (optional) = c (acc = 0) or += c (acc = 1)
-void ns_dsum(const double* part, int nb, int nv, double* c, double* hacc, int acc, hipStream_t st);
-void ns_dots(const double* V, size_t stride, int nv, const double* w, size_t n, double* part, int nb,
-             hipStream_t st);
-
-// w -= sum_{i < nv} c[i] V_i (c on the device); with acc = 1 instead
-// w = sum_i c[i] V_i.
-void ns_mupdate(const double* V, size_t stride, int nv, const double* c, double* w, size_t n, int acc,
-                hipStream_t st);
+void ns_square(const double* x, size_t n, double* part, int nb, hipStream_t st);
 
 }  // namespace vd

@@ -1199,6 +1199,42 @@ void inv_transform(const Geom& g, const void* spec, double* phys, void* work, co
   launch_row<double, ROW_C2R>(g.M, r, twtab, st);
 }
 
+void fwd_columns_n(const Geom& g, void* const* spec, int nf, const void* twtab, hipStream_t st, const int* gate) {
+  ColArgs b = col_args(g, nullptr);
+  b.gate = gate;
+  b.nf = nf;
+  for (int f = 0; f < nf; ++f) b.in[f] = b.out[f] = spec[f];
+  if (g.ny > 1) {
+    b.outer = g.nz;
+    b.inner = g.M;
+    launch_col<double, COL_FFT_FWD>(g.ny, b, twtab, st);
+  }
+  if (g.nz > 1) {
+    b.outer = 1;
+    b.inner = g.ny * g.M;
+    launch_col<double, COL_FFT_FWD>(g.nz, b, twtab, st);
+  }
+}
+
+void grad_rows(const Geom& g, const void* v, void* q0, void* qy, void* qz, const void* twtab, hipStream_t st) {
+  ColArgs a = col_args(g, nullptr);
+  a.outer = 1;
+  a.inner = g.ny * g.M;
+  a.in[0] = v;
+  a.out[0] = q0;
+  a.out[1] = qz;
+  launch_col<double, COL_P_FIRST>(g.nz, a, twtab, st);
+  ColArgs b = col_args(g, nullptr);
+  b.outer = g.nz;
+  b.inner = g.M;
+  b.in[0] = q0;
+  b.in[1] = qz;
+  b.out[0] = q0;
+  b.out[1] = qy;
+  b.out[2] = qz;
+  launch_col<double, COL_P_MIDINV>(g.ny, b, twtab, st);
+}
+
 // nf <= 3 fields at once: the column passes take every field in one launch
 // (each block transforms its column of each field in turn), the x pass runs
 // per field.  work[f] are distinct spectral buffers (the inverse's scratch).
@@ -1210,23 +1246,7 @@ void fwd_transform_n(const Geom& g, const double* const* phys, void* const* spec
     r.out[0] = spec[f];
     launch_row<double, ROW_R2C>(g.M, r, twtab, st);
   }
-  if (g.cheb) return;
-  if (g.ny > 1) {
-    ColArgs b = col_args(g, nullptr);
-    b.outer = g.nz;
-    b.inner = g.M;
-    b.nf = nf;
-    for (int f = 0; f < nf; ++f) b.in[f] = b.out[f] = spec[f];
-    launch_col<double, COL_FFT_FWD>(g.ny, b, twtab, st);
-  }
-  if (g.nz > 1) {
-    ColArgs b = col_args(g, nullptr);
-    b.outer = 1;
-    b.inner = g.ny * g.M;
-    b.nf = nf;
-    for (int f = 0; f < nf; ++f) b.in[f] = b.out[f] = spec[f];
-    launch_col<double, COL_FFT_FWD>(g.nz, b, twtab, st);
-  }
+  if (!g.cheb) fwd_columns_n(g, spec, nf, twtab, st);
 }
 
 void inv_transform_n(const Geom& g, const void* const* spec, double* const* phys, void* const* work, int nf,

@@ -118,6 +118,15 @@ void fwd_transform_n(const Geom& g, const double* const* phys, void* const* spec
 void inv_transform_n(const Geom& g, const void* const* spec, double* const* phys, void* const* work, int nf,
                      const void* twtab, hipStream_t st);
 
+// The y and z passes of fwd_transform_n alone, in place on rows already
+// transformed along x; gate (optional): nonzero device flag = do nothing.
+void fwd_columns_n(const Geom& g, void* const* spec, int nf, const void* twtab, hipStream_t st,
+                   const int* gate = nullptr);
+
+// Rows of the gradient of a packed FP64 spectrum v (3D grids), everything but
+// the x transform: q0 (the x derivative is i k'_x of it), qy and qz.
+void grad_rows(const Geom& g, const void* v, void* q0, void* qy, void* qz, const void* twtab, hipStream_t st);
+
 // y = Lap x on a packed FP64 spectrum (symbol -|k|^2, Nyquist kept); x != y.
 void lap_packed(const Geom& g, const void* x, void* y, hipStream_t st);
 

@@ -27,12 +27,13 @@
 #include <algorithm>
 #include <map>
 #include <new>
-#include <thread>
 #include <vector>
 
 #include "../../include/vdsolve.h"
 #include "cheb.hpp"
 #include "cheb_ops.hpp"
+#include "mail.hpp"
+#include "ns.hpp"
 #include "passes.hpp"
 #include "vecops.hpp"
 
@@ -249,54 +250,19 @@ static double norm_from_sq(double s) { return s < 0.0 ? 0.0 : std::sqrt(s); }
 // max that keeps a NaN of either argument
 static double max_keep_nan(double a, double b) { return (a != a || b != b) ? NAN : std::max(a, b); }
 
-// Waits until mailbox m holds post number seq, which work already on stream
-// st will post.  Polls the pinned memory; every few ten microseconds it also
-// asks the stream, so that a device error, or a stream that has ended without
-// posting, ends the wait.
-void wait_mail(const Mail* m, unsigned long long seq, hipStream_t st) {
-  for (unsigned spin = 1;; ++spin) {
-    if (__atomic_load_n(&m->seq, __ATOMIC_ACQUIRE) == seq) return;
-#if defined(__x86_64__)
-    __builtin_ia32_pause();
-#endif
-    if (spin % 1024) continue;
-    const hipError_t before = hipPeekAtLastError();
-    const hipError_t q = hipStreamQuery(st);
-    if (q == hipErrorNotReady) {
-      if (before == hipSuccess) (void)hipGetLastError();  // "not ready" is no error of the library's work
-      std::this_thread::yield();
-      continue;
-    }
-    ck(q);
-    if (__atomic_load_n(&m->seq, __ATOMIC_ACQUIRE) != seq) throw DevErr{};
-  }
-}
-
 // Posts and waits for one reduced value: `launch` enqueues, on stream st, a
 // reduction that takes the Post.
 template <typename F>
 double read_value(vd_grid* owner, DevState* dst, const Mail* mail, hipStream_t st, F&& launch) {
   const unsigned long long seq = ++owner->posts;
   launch(Post{POST_MAIL, dst, seq});
-  wait_mail(mail + MAIL_VALUE, seq, st);
+  if (!wait_mail(mail + MAIL_VALUE, seq, st)) throw DevErr{};
   return mail[MAIL_VALUE].v[0];
 }
 
-// The state that a Krylov step posted.
-struct StepState {
-  double resid = 0, nrm2 = 0;
-  bool bad = false, halt = false;
-  int nreorth = 0;
-};
-StepState wait_step(const Mail* mail, int j, unsigned long long run, hipStream_t st) {
-  const Mail& m = mail[MAIL_STEP + (j & 1)];
-  wait_mail(&m, run + j + 1, st);
+StepState next_step(const Mail* mail, int j, unsigned long long run, hipStream_t st) {
   StepState t;
-  t.resid = m.v[0];
-  t.nrm2 = m.v[1];
-  t.bad = m.flags & 1;
-  t.halt = (m.flags >> 1) & 1;
-  t.nreorth = (int)(m.flags >> 2);
+  if (!wait_step(mail, j, run, st, &t)) throw DevErr{};
   return t;
 }
 // numbers for the steps of a cycle or run that ends after step jlast at the latest
@@ -517,7 +483,7 @@ struct Krylov {
     int done = 0;
     for (int j = 0; j <= jlast; ++j) {
       if (j < jlast) step(j + 1, gate);
-      t = wait_step(G->mail, j, run, G->st);
+      t = next_step(G->mail, j, run, G->st);
       if (pf.on) {
         pf.flush_front(mark);
         mark = pf.pending.size();
@@ -662,15 +628,6 @@ SolveOut solve_spectral(vd_grid* G, const vd_solve_opts& o, const OpParams& op, 
 // converges, and its result is the one it would have alone: the kernels and
 // reduction orders are those of a single system.
 
-// The pinned mailboxes of a new solver state on stream st.
-void make_mail(Mail** mail, DevState* dst, hipStream_t st) {
-  void* dev = nullptr;
-  ck(hipHostMalloc(mail, kMails * sizeof(Mail)));
-  std::memset(*mail, 0, kMails * sizeof(Mail));
-  ck(hipHostGetDevicePointer(&dev, *mail, 0));
-  set_mail(dst, (Mail*)dev, st);
-}
-
 // Device state, partials and mailboxes of system k (k = 0: the grid's own).
 void ensure_systems(vd_grid* G, int n) {
   for (int k = 1; k < n; ++k) {
@@ -678,7 +635,7 @@ void ensure_systems(vd_grid* G, int n) {
     ck(hipMalloc(&G->dstx[k], sizeof(DevState)));
     ck(hipMalloc(&G->partialx[k], nred_partial() * sizeof(double)));
     ck(hipMemsetAsync(G->dstx[k], 0, sizeof(DevState), G->st));
-    make_mail(&G->mailx[k], G->dstx[k], G->st);
+    ck(make_mail(&G->mailx[k], G->dstx[k], G->st));
   }
 }
 DevState* sys_dst(vd_grid* G, int k) { return k ? G->dstx[k] : G->dst; }
@@ -816,7 +773,7 @@ struct KrylovBatch {
     }
     for (int q = 0; q < ns; ++q) {
       const int k = sys[q];
-      wait_mail(mail[k] + MAIL_VALUE, seq[q], G->st);
+      if (!wait_mail(mail[k] + MAIL_VALUE, seq[q], G->st)) throw DevErr{};
       rn[k] = norm_from_sq(mail[k][MAIL_VALUE].v[0]);
     }
     if (G->prof.on) G->prof.flush();
@@ -861,7 +818,7 @@ struct KrylovBatch {
       if (j < jlast) step(j + 1, sys, ns);
       for (int q = 0; q < ns; ++q) {
         if (stopped[q]) continue;
-        const StepState tt = end[q] = wait_step(mail[sys[q]], j, run[q], G->st);
+        const StepState tt = end[q] = next_step(mail[sys[q]], j, run[q], G->st);
         steps[q] = j + 1;
         if (hist && sys[q] == 0) hist->push_back(tt.resid / hist_bnorm);
         if (tt.bad || tt.halt || !(tt.nrm2 == tt.nrm2)) {
@@ -1250,7 +1207,7 @@ vd_status vd_grid_create(vd_grid** out, const vd_grid_desc* d, hipStream_t strea
     // on the grid's stream, like everything that touches the state: a server's
     // stream is not ordered after the null stream
     ck(hipMemsetAsync(G->dst, 0, sizeof(DevState), stream));
-    make_mail(&G->mail, G->dst, stream);
+    ck(make_mail(&G->mail, G->dst, stream));
   } catch (...) {
     vd_grid_destroy(G);
     return VD_ENOMEM;
@@ -1422,6 +1379,7 @@ struct SolveCtx {
   int ncomp;
   const double* f;
   double* x;
+  bool spec = false;  // f and x are packed spectra (pressure, direct form, Fourier grid)
   vd_solve_opts o;
   vd_solve_info info;
 };
@@ -1537,6 +1495,8 @@ static vd_status solve_impl(vd_grid* G, void* c) {
       rho_sqrt_mul(G->rho, f, t, false, -1.0, G->nreal, G->st);
       fwd_transform(G->g, t, b64, nullptr, G->tw64, G->st);
       s->info.rhs_null_norm = std::fmax(s->info.rhs_null_norm, project_psi(G, b64));
+    } else if (s->spec) {
+      ck(hipMemcpyAsync(b64, f, G->nspec * 16, hipMemcpyDeviceToDevice, G->st));
     } else {
       fwd_transform(G->g, f, b64, nullptr, G->tw64, G->st);
     }
@@ -1550,7 +1510,8 @@ static vd_status solve_impl(vd_grid* G, void* c) {
       rho_sqrt_mul(G->rho, x, t, true, 1.0, G->nreal, G->st);
       fwd_transform(G->g, t, x64, nullptr, G->tw64, G->st);
     } else if (s->o.use_x0) {
-      fwd_transform(G->g, x, x64, nullptr, G->tw64, G->st);
+      if (s->spec) ck(hipMemcpyAsync(x64, x, G->nspec * 16, hipMemcpyDeviceToDevice, G->st));
+      else fwd_transform(G->g, x, x64, nullptr, G->tw64, G->st);
       if (G->g.cheb) c2_project(G->g, x64, G->dsmall + 1, G->st);
       else if (s->kind == VD_OP_PRESSURE) project_range(G->g, x64, G->dsmall + 1, G->st);
     } else {
@@ -1570,7 +1531,8 @@ static vd_status solve_impl(vd_grid* G, void* c) {
     // the Chebyshev preconditioner's pseudo-inverse is not Euclidean-orthogonal
     // to the nullspace: return the representative orthogonal to it
     if (G->g.cheb) c2_project(G->g, x64, G->dsmall + 1, G->st);
-    inv_transform(G->g, x64, x, buf(G, 64, B_TMP), G->tw64, G->st);
+    if (s->spec) ck(hipMemcpyAsync(x, x64, G->nspec * 16, hipMemcpyDeviceToDevice, G->st));
+    else inv_transform(G->g, x64, x, buf(G, 64, B_TMP), G->tw64, G->st);
     if (kform) {  // phi = sqrt(rho) Phi with its mean removed (a multiple of psi in Phi)
       void* t = buf(G, 64, B_T0);
       rho_sqrt_mul(G->rho, x, x, false, 1.0, G->nreal, G->st);
@@ -1604,7 +1566,7 @@ static vd_status reject(vd_solve_info* info, vd_status s) {
 }
 
 static vd_status solve_common(vd_grid* G, int kind, double nu, int ncomp, const double* f, double* x,
-                              const vd_solve_opts* opts, vd_solve_info* info) {
+                              const vd_solve_opts* opts, vd_solve_info* info, bool spec = false) {
   if (!G || !f || !x || ncomp < 1) return reject(info, VD_EINVAL);
   if (!G->has_rho) return reject(info, VD_EINVAL);
   SolveCtx c{};
@@ -1613,6 +1575,7 @@ static vd_status solve_common(vd_grid* G, int kind, double nu, int ncomp, const 
   c.ncomp = ncomp;
   c.f = f;
   c.x = x;
+  c.spec = spec;
   if (opts) c.o = *opts;
   else vd_default_opts(&c.o);
   if (!opts_ok(c.o)) return reject(info, VD_EINVAL);
@@ -1842,3 +1805,9 @@ vd_status vd_profile_read(vd_grid* G, double* ms, long long* count, double* byte
 }
 
 }  // extern "C"
+
+vd_status vd::grid_solve_pressure_spec(vd_grid* G, const void* fhat, void* phat, const vd_solve_opts* opts,
+                                       vd_solve_info* info) {
+  if (G && (G->g.cheb || (opts && opts->formulation != VD_FORM_L))) return reject(info, VD_ENOTSUP);
+  return solve_common(G, VD_OP_PRESSURE, 0.0, 1, (const double*)fhat, (double*)phat, opts, info, true);
+}
