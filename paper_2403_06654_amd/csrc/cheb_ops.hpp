@@ -12,7 +12,7 @@ enum ChebMat {
   CH_VT = 0,    // V^T                          [nz][nz]
   CH_PRE_V,     // [I V ; G V]                  [2 nz][nz]
   CH_PRE,       // [I ; G]                      [2 nz][nz]
-  CH_POST,      // [-I^T | G^T]                 [nz][2 nz]
+  CH_POST,      // [Q ; V^T Q], Q = [-I^T | G^T] [2 nz][2 nz]
   CH_V,         // V                            [nz][nz]
   CH_RHS,       // -I^T diag(h_x w_LGL) I       [nz][nz]
   CH_I,         // I (CGL -> LGL interpolation) [nz][nz]
@@ -36,6 +36,15 @@ void c2_apply(const Geom& g, const ChebDev& cd, const OpParams& p, const void* v
 template <typename R>
 void c2_precond(const Geom& g, const ChebDev& cd, double rho0, const void* r, void* z, void* wY, hipStream_t st,
                 const int* gate = nullptr);
+// CG in the eigenbasis: rt = V^T r; x = V xt; and qq = (q, V^T q) (two fields)
+// with q = A V pt (wT: two fields; gated).
+template <typename R>
+void c2_to_eigen(const Geom& g, const ChebDev& cd, const void* r, void* rt, hipStream_t st);
+template <typename R>
+void c2_from_eigen(const Geom& g, const ChebDev& cd, const void* xt, void* x, hipStream_t st);
+template <typename R>
+void c2_apply_eigen(const Geom& g, const ChebDev& cd, const void* pt, void* qq, void* wT, const void* coef,
+                    const void* twtab, hipStream_t st, Prof* prof, const int* gate);
 // b = -I^T W I f on packed-x spectra (FP64)
 void c2_rhs(const Geom& g, const ChebDev& cd, const void* fhat, void* b, hipStream_t st);
 // rho_L = I rho and the x-pass coefficient h_x w_LGL / rho_L; *bad counts non-positive values

@@ -5,7 +5,7 @@
 // z direction, B a field whose rows are z levels and whose columns are the
 // packed x spectrum viewed as reals (the z matrices are real, so complex
 // columns contract as pairs of real columns).  A block computes a 16 x 16
-// tile with v_mfma_f64_16x16x4_f64 (FP32: v_mfma_f32_16x16x4_f32), stepping
+// or 16 x 32 tile with v_mfma_f64_16x16x4_f64 (FP32: v_mfma_f32_16x16x4_f32), stepping
 // K by 4; operands are read straight from global memory (the A matrix and
 // the field each fit in L2).  Lane l feeds
 // A[l % 16][l / 16] and B[l / 16][l % 16]; accumulator r of lane l holds
@@ -55,60 +55,87 @@ struct EpiArgs {
   const int* gate;         // nonzero *gate: the launch does nothing
 };
 
-// One 512-thread block per 16 x 16 tile of C; the 8 waves split K (wave w
-// takes the k-steps w, w+8, w+16, ...), and the eight partial tiles are
-// summed through LDS before the epilogue.  The Chebyshev contractions are
-// small (M = 257 or 514 rows, N = 512 real columns, K = 257 or 514), so a
-// launch is bound by latency, not by MFMA or bandwidth: 16 x 16 tiles give
-// 544-1056 blocks for 256 CUs, and each wave loads KU k-steps before their
-// MFMAs (two independent accumulators, alternate k-steps), waiting on memory
-// once per batch.  Measured per launch (FP64, N = 512; back-to-back launches
-// with HIP events): M = 257, K = 257: 5.4 us; M = 514, K = 257: 7.8 us;
-// M = 257, K = 514: 8.7 us (4 waves with KU = 17: 6.0, 8.5, 9.7; 32 x 32
-// tiles: 7.8-10.8).  An empty kernel on the same grid takes 2.4-2.8 us, and
-// the MFMAs, reduction and stores alone (operands not loaded) 3.7-5.1 us.
+// One 512-thread block per 16 x 16 TN tile of C; the 8 waves split K (wave w
+// takes the k-steps w, w+8, w+16, ...), and the eight partial tiles are summed
+// through LDS before the epilogue.  The Chebyshev contractions are small
+// (M = 257 or 514 rows, N = 512 real columns, K = 257 or 514): a launch is bound
+// by its loads, their latency and their number, not by MFMA or HBM (at
+// M = K = 514 the loads alone take 11.5 of 13.3 us).  So the first batch of loads
+// is issued before the halt flag is read, batches are short (KU k-steps), and
+// where a 16 x 16 tiling would not fit the chip at once anyway (kGemmTiles) a
+// wave computes two column tiles from one 16 B load of B per k-step and lane:
+// lane li then holds columns 2 li and 2 li + 1.
+// Measured per launch (FP64, N = 512, back-to-back launches with HIP events; TN = 1
+// with KU = 5 / TN = 1, KU = 3 / TN = 2, KU = 3), us: M = 257, K = 257: 5.4 / 5.2 /
+// 5.3; M = 514, K = 257: 7.8 / 7.4 / 6.8; M = 257, K = 514: 8.9 / 8.2 / 8.4;
+// M = 514, K = 514: 13.3 / 12.3 / 11.2.  4 and 16 waves, 32 x 32 tiles per wave and
+// tiles staged in LDS (22-26 us at M = K = 514) are slower.
 // AT: A is stored transposed ([K][M]), so a load of 16 consecutive rows is
 // one contiguous run.
-constexpr int kGemmWaves = 8, kGemmKU = 5;
+constexpr int kGemmWaves = 8, kGemmKU = 3;
+constexpr int kGemmTiles = 512;  // two 16 x 16 tiles per CU
 
-template <typename R, bool AT>
+template <typename R, bool AT, int TN>
 __global__ __launch_bounds__(64 * kGemmWaves) void k_gemm(const R* __restrict__ A, int lda, const R* __restrict__ B,
                                                           int ldb, R* __restrict__ C, int ldc, int M, int N, int K,
                                                           EpiArgs e) {
   using MF = Mfma<R>;
-  constexpr int W = kGemmWaves, KU = kGemmKU;
-  if (e.gate && *e.gate) return;
-  __shared__ double part[W][16 * 17];
+  constexpr int W = kGemmWaves, KU = kGemmKU, TS = 16 * TN, LD = TS + 1;
+  __shared__ double part[W][16 * LD];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int r0 = blockIdx.y * 16, c0 = blockIdx.x * 16;
+  const int r0 = blockIdx.y * 16, c0 = blockIdx.x * TS;
   const int li = lane & 15, lk = lane >> 4;
-  const int ra = r0 + li, cb = c0 + li;
-  const bool rin = ra < M, cin = cb < N;
-  typename MF::V acc0{0, 0, 0, 0}, acc1{0, 0, 0, 0};
-  for (int s0 = w; 4 * s0 < K; s0 += W * KU) {
-    R a[KU], b[KU];
+  const int ra = r0 + li, cb = c0 + TN * li;
+  const bool rin = ra < M, cin = cb < N;  // TN = 2: N is even
+  typename MF::V acc[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};  // a chain per column tile, or alternate k-steps
+  R a[KU], b[KU][TN];
+  auto load = [&](int s0) {
 #pragma unroll
     for (int u = 0; u < KU; ++u) {
       const int k = 4 * (s0 + W * u) + lk;
       const bool kin = k < K;
       a[u] = (kin && rin) ? (AT ? A[(size_t)k * lda + ra] : A[(size_t)ra * lda + k]) : R(0);
-      b[u] = (kin && cin) ? B[(size_t)k * ldb + cb] : R(0);
+      if constexpr (TN == 2) {
+        const C2<R> v = (kin && cin) ? ldg((const C2<R>*)(B + (size_t)k * ldb + cb)) : C2<R>{R(0), R(0)};
+        b[u][0] = v.x;
+        b[u][1] = v.y;
+      } else {
+        b[u][0] = (kin && cin) ? B[(size_t)k * ldb + cb] : R(0);
+      }
     }
+  };
+  load(w);
+  if (e.gate && *e.gate) return;
+  for (int s0 = w;;) {
 #pragma unroll
-    for (int u = 0; u < KU; u += 2) {
-      acc0 = MF::mac(a[u], b[u], acc0);
-      if (u + 1 < KU) acc1 = MF::mac(a[u + 1], b[u + 1], acc1);
+    for (int u = 0; u < KU; ++u) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int t = TN == 2 ? j : u & 1;
+        acc[t] = MF::mac(a[u], b[u][j], acc[t]);
+      }
     }
+    s0 += W * KU;
+    if (4 * s0 >= K) break;
+    load(s0);
   }
 #pragma unroll
-  for (int r = 0; r < 4; ++r) part[w][MF::row(lk, r) * 17 + li] = (double)acc0[r] + (double)acc1[r];
+  for (int r = 0; r < 4; ++r) {
+    double* o = part[w] + MF::row(lk, r) * LD + TN * li;
+    if constexpr (TN == 2) {
+      o[0] = (double)acc[0][r];
+      o[1] = (double)acc[1][r];
+    } else {
+      o[0] = (double)acc[0][r] + (double)acc[1][r];
+    }
+  }
   __syncthreads();
-  if (threadIdx.x >= 256) return;
+  if (threadIdx.x >= 16 * TS) return;
   const double al = (e.alpha_dev ? *e.alpha_dev : 1.0) * e.alpha;
-  const int tr = threadIdx.x >> 4, tc = threadIdx.x & 15;
+  const int tr = threadIdx.x / TS, tc = threadIdx.x % TS;
   const int row = r0 + tr, col = c0 + tc;
   if (row >= M || col >= N) return;
-  const int o = tr * 17 + tc;
+  const int o = tr * LD + tc;
   double v = 0.0;
 #pragma unroll
   for (int q = 0; q < W; ++q) v += part[q][o];
@@ -125,8 +152,13 @@ __global__ __launch_bounds__(64 * kGemmWaves) void k_gemm(const R* __restrict__ 
 template <typename R, bool AT = true>
 static void gemm(const R* A, int lda, const R* B, int ldb, R* C, int ldc, int M, int N, int K, const EpiArgs& e,
                  hipStream_t s) {
-  dim3 grid((N + 15) / 16, (M + 15) / 16);
-  hipLaunchKernelGGL((k_gemm<R, AT>), grid, dim3(64 * kGemmWaves), 0, s, A, lda, B, ldb, C, ldc, M, N, K, e);
+  const dim3 grid((N + 15) / 16, (M + 15) / 16), bl(64 * kGemmWaves);
+  // pairs of columns: an even row length and pairs that sit aligned
+  const bool pairs = N % 2 == 0 && ldb % 2 == 0 && (size_t)B % (2 * sizeof(R)) == 0;
+  if (pairs && (long long)grid.x * grid.y > kGemmTiles)
+    hipLaunchKernelGGL((k_gemm<R, AT, 2>), dim3((N + 31) / 32, grid.y), bl, 0, s, A, lda, B, ldb, C, ldc, M, N, K, e);
+  else
+    hipLaunchKernelGGL((k_gemm<R, AT, 1>), grid, bl, 0, s, A, lda, B, ldb, C, ldc, M, N, K, e);
 }
 
 static EpiArgs plain(double alpha = 1.0, const double* alpha_dev = nullptr) {
@@ -182,7 +214,7 @@ void c2_apply(const Geom& g, const ChebDev& cd, const OpParams& p, const void* v
   }
   // x pass over the 2 nz rows: field 0 (I u) gets i k'_x in and out, field 1 (G u) plain
   row_pass_p2<R>(g, T, T + fs, coef, twtab, st, prof, p.gate);
-  gemm<R>(mat<R>(cd, CH_POST), nz, T, n, (R*)y, n, nz, n, 2 * nz, gated(plain()), st);  // [-I^T | G^T]
+  gemm<R>(mat<R>(cd, CH_POST), 2 * nz, T, n, (R*)y, n, nz, n, 2 * nz, gated(plain()), st);  // [-I^T | G^T]
 }
 
 template <typename R>
@@ -200,6 +232,28 @@ void c2_precond(const Geom& g, const ChebDev& cd, double rho0, const void* r, vo
   e2.gate = gate;
   gemm<R>(mat<R>(cd, CH_VT), nz, (const R*)r, n, (R*)wY, n, nz, n, nz, e, st);
   gemm<R>(mat<R>(cd, CH_V), nz, (const R*)wY, n, (R*)z, n, nz, n, nz, e2, st);
+}
+
+template <typename R>
+void c2_to_eigen(const Geom& g, const ChebDev& cd, const void* r, void* rt, hipStream_t st) {
+  const int nz = g.nz, n = 2 * g.M;
+  gemm<R>(mat<R>(cd, CH_VT), nz, (const R*)r, n, (R*)rt, n, nz, n, nz, plain(), st);
+}
+template <typename R>
+void c2_from_eigen(const Geom& g, const ChebDev& cd, const void* xt, void* x, hipStream_t st) {
+  const int nz = g.nz, n = 2 * g.M;
+  gemm<R>(mat<R>(cd, CH_V), nz, (const R*)xt, n, (R*)x, n, nz, n, nz, plain(), st);
+}
+template <typename R>
+void c2_apply_eigen(const Geom& g, const ChebDev& cd, const void* pt, void* qq, void* wT, const void* coef,
+                    const void* twtab, hipStream_t st, Prof* prof, const int* gate) {
+  const int nz = g.nz, n = 2 * g.M;
+  R* T = (R*)wT;  // [2 nz][n]
+  EpiArgs e = plain();
+  e.gate = gate;
+  gemm<R>(mat<R>(cd, CH_PRE_V), 2 * nz, (const R*)pt, n, T, n, 2 * nz, n, nz, e, st);  // [I V; G V]
+  row_pass_p2<R>(g, T, T + (size_t)nz * n, coef, twtab, st, prof, gate);
+  gemm<R>(mat<R>(cd, CH_POST), 2 * nz, T, n, (R*)qq, n, 2 * nz, n, 2 * nz, e, st);  // [Q; V^T Q]
 }
 
 void c2_rhs(const Geom& g, const ChebDev& cd, const void* fhat, void* b, hipStream_t st) {
@@ -278,6 +332,13 @@ template void c2_apply<double>(const Geom&, const ChebDev&, const OpParams&, con
                                const void*, const void*, hipStream_t, Prof*);
 template void c2_apply<float>(const Geom&, const ChebDev&, const OpParams&, const void*, void*, void*, void*,
                               const void*, const void*, hipStream_t, Prof*);
+#define VD_EIGEN(R)                                                                                      \
+  template void c2_to_eigen<R>(const Geom&, const ChebDev&, const void*, void*, hipStream_t);            \
+  template void c2_from_eigen<R>(const Geom&, const ChebDev&, const void*, void*, hipStream_t);          \
+  template void c2_apply_eigen<R>(const Geom&, const ChebDev&, const void*, void*, void*, const void*,   \
+                                  const void*, hipStream_t, Prof*, const int*);
+VD_EIGEN(double)
+VD_EIGEN(float)
 template void c2_precond<double>(const Geom&, const ChebDev&, double, const void*, void*, void*, hipStream_t,
                                  const int*);
 template void c2_precond<float>(const Geom&, const ChebDev&, double, const void*, void*, void*, hipStream_t,

@@ -166,14 +166,15 @@ inline void ck(hipError_t e) {
 size_t elem_bytes(int prec) { return prec == 32 ? 8 : 16; }
 
 // Spectral work vector of the given precision and role (allocated on first
-// use, kept until the grid is destroyed).  Role B_T1 holds two fields on
-// Chebyshev grids (the stacked interpolated values and z-derivatives).
+// use, kept until the grid is destroyed).  On Chebyshev grids roles B_T1 (the
+// stacked interpolated values and z-derivatives) and B_Q (a product and its
+// image under V^T) hold two fields.
 void* buf(vd_grid* G, int prec, int role) {
   int key = prec * 1000 + role;
   auto it = G->bufs.find(key);
   if (it != G->bufs.end()) return it->second;
   void* p = nullptr;
-  const size_t mult = (G->g.cheb && role == B_T1) ? 2 : 1;
+  const size_t mult = (G->g.cheb && (role == B_T1 || role == B_Q)) ? 2 : 1;
   if (hipMalloc(&p, mult * G->nspec * elem_bytes(prec)) != hipSuccess) throw std::bad_alloc();
   G->bufs[key] = p;
   return p;
@@ -445,26 +446,6 @@ struct Krylov {
     }
   }
 
-  // rz = (r, M^-1 r); then p = M^-1 r (restart, never gated) or
-  // p = M^-1 r + beta p
-  void rz_and_p(const void* r, void* p, bool restart, const int* gate = nullptr) {
-    const Post beta{POST_CG_BETA, G->dst};  // rz = red[0] (the reduction's launch takes the step)
-    if (dense_prec()) {
-      const void* z = materialise_prec(r, gate);
-      VecPtrs P{};
-      P.p[0] = r;
-      mdot<R>(g, z, P, 1, false, G->partial, G->dst->red, G->st, nullptr, gate, beta);
-      if (restart) ck(hipMemcpyAsync(p, z, G->nspec * elem_bytes(prec), hipMemcpyDeviceToDevice, G->st));
-      else cg_p<R>(g, ident(gate), p, z, G->dst, G->st);
-      return;
-    }
-    const OpParams op = gated(gate);
-    dot_rMr<R>(g, op, r, G->partial, G->dst->red, G->st, beta);
-    if (!restart) cg_p<R>(g, op, p, r, G->dst, G->st);
-    else if (op.precond) precond_apply<R>(g, op, r, p, G->st);
-    else ck(hipMemcpyAsync(p, r, G->nspec * elem_bytes(prec), hipMemcpyDeviceToDevice, G->st));
-  }
-
   // Steps 0..jlast of a GMRES cycle or a CG/RMR run.  Step j + 1 is queued
   // before step j's state reaches the host, so the GPU never idles while the
   // host decides: step(j, gate) enqueues step j with its stopping test on the
@@ -497,30 +478,33 @@ struct Krylov {
   }
 
   SolveOut cg(const void* b, void* x, double bnorm) {
+    if (dense_prec()) return cg_eigen(b, x, bnorm);
     SolveOut o;
     void* r = buf(G, prec, B_R);
+    void* rn = buf(G, prec, B_W);  // the residual alternates between two buffers
     void* p = buf(G, prec, B_P);
     void* q = buf(G, prec, B_Q);
-    double rn = (cfg.inner || cfg.x_zero) ? copy_rhs(b, r, bnorm) : true_resid(b, x, r);
-    if (cfg.hist) cfg.hist->push_back(rn / bnorm);
+    double res = (cfg.inner || cfg.x_zero) ? copy_rhs(b, r, bnorm) : true_resid(b, x, r);
+    if (cfg.hist) cfg.hist->push_back(res / bnorm);
     while (true) {
-      o.relres = rn / bnorm;
-      if (!(rn == rn)) { o.status = VD_EBREAKDOWN; return o; }
+      o.relres = res / bnorm;
+      if (!(res == res)) { o.status = VD_EBREAKDOWN; return o; }
       if (o.relres <= cfg.rtol) { o.status = VD_OK; return o; }
       if (o.iters >= cfg.max_iter) { o.status = VD_NOT_CONVERGED; return o; }
-      // p = M^-1 r, rz = (r, M^-1 r)
       const int jlast = cfg.max_iter - o.iters - 1;
       const unsigned long long run = new_run(G, jlast);
       rec_init(G->dst, bnorm, cfg.rtol, jlast, run, G->st);
-      rz_and_p(r, p, true);
+      // rz = (r, M^-1 r), p = M^-1 r
+      dot_rMr<R>(g, cfg.op, r, G->partial, G->dst->red, G->st, Post{POST_CG_BETA, G->dst});
+      if (cfg.op.precond) precond_apply<R>(g, cfg.op, r, p, G->st);
+      else ck(hipMemcpyAsync(p, r, G->nspec * elem_bytes(prec), hipMemcpyDeviceToDevice, G->st));
       StepState t;
       o.iters += run_queued(jlast, run, t, bnorm, [&](int j, const int* gate) {
-        if (j > 0) rz_and_p(r, p, false, gate);
+        if (j > 0) cg_p<R>(g, gated(gate), p, r, G->dst, G->st);  // p = M^-1 r + beta p
         apply(p, q, false, nullptr, gate);
-        VecPtrs P{};
-        P.p[0] = p;
-        mdot<R>(g, q, P, 1, false, G->partial, G->dst->red, G->st, nullptr, gate, Post{POST_CG_ALPHA, G->dst});
-        cg_xr<R>(g, x, r, p, q, G->dst, G->partial, &G->dst->nrm2, G->st, gate, Post{POST_REC_CHECK, G->dst});
+        dot_partials<R>(g, q, p, false, G->partial, G->st, gate);
+        rec_step<R>(g, cfg.op, false, x, r, rn, p, q, G->dst, G->partial, G->st);
+        std::swap(r, rn);
       });
       if (t.bad || !(t.nrm2 == t.nrm2)) { o.status = VD_EBREAKDOWN; return o; }
       if (cfg.inner) {
@@ -528,19 +512,68 @@ struct Krylov {
         o.status = VD_OK;
         return o;
       }
-      rn = true_resid(b, x, r);
+      res = true_resid(b, x, r);
+    }
+  }
+
+  // CG with the dense preconditioner V D V^T of a Chebyshev grid, carried out
+  // in the basis V: with rt = V^T r and p = V pt,
+  //   (r, M^-1 r) = (rt, D rt),  pt = D rt + beta pt,  (p, A p) = (pt, V^T A V pt),
+  // and x accumulates as V xt.  A step is two contractions around the x pass
+  // ([I V; G V] pt, and [Q; V^T Q] of its result with Q = [-I^T | G^T]) instead of
+  // four, and the preconditioned residual is never formed.  r itself is kept
+  // beside rt for the stopping test.
+  SolveOut cg_eigen(const void* b, void* x, double bnorm) {
+    SolveOut o;
+    void* r = buf(G, prec, B_R);
+    void* rt = buf(G, prec, B_Z);
+    void* pt = buf(G, prec, B_P);
+    void* qq = buf(G, prec, B_Q);  // two fields
+    void* xt = buf(G, prec, B_W);
+    char* qt = (char*)qq + G->nspec * elem_bytes(prec);
+    const EigDiag d{G->cd.lam, cfg.op.rho0 / G->cd.hx, g.sx};
+    double res = (cfg.inner || cfg.x_zero) ? copy_rhs(b, r, bnorm) : true_resid(b, x, r);
+    if (cfg.hist) cfg.hist->push_back(res / bnorm);
+    while (true) {
+      o.relres = res / bnorm;
+      if (!(res == res)) { o.status = VD_EBREAKDOWN; return o; }
+      if (o.relres <= cfg.rtol) { o.status = VD_OK; return o; }
+      if (o.iters >= cfg.max_iter) { o.status = VD_NOT_CONVERGED; return o; }
+      const int jlast = cfg.max_iter - o.iters - 1;
+      const unsigned long long run = new_run(G, jlast);
+      rec_init(G->dst, bnorm, cfg.rtol, jlast, run, G->st);
+      c2_to_eigen<R>(g, G->cd, r, rt, G->st);
+      eig_p<R>(g, d, pt, rt, true, G->dst, G->partial, G->st);
+      ck(hipMemsetAsync(xt, 0, G->nspec * elem_bytes(prec), G->st));
+      StepState t;
+      o.iters += run_queued(jlast, run, t, bnorm, [&](int j, const int* gate) {
+        if (j > 0) eig_p<R>(g, d, pt, rt, false, G->dst, G->partial, G->st);
+        c2_apply_eigen<R>(g, G->cd, pt, qq, work.t[1], coef, tw, G->st, &G->prof, gate);
+        dot_partials<R>(g, qt, pt, false, G->partial, G->st, gate);
+        eig_step<R>(g, d, xt, r, rt, pt, qq, G->dst, G->partial, G->st);
+      });
+      c2_from_eigen<R>(g, G->cd, xt, qq, G->st);
+      precond_axpy<R>(g, ident(), x, qq, nullptr, 1.0, G->st);
+      if (t.bad || !(t.nrm2 == t.nrm2)) { o.status = VD_EBREAKDOWN; return o; }
+      if (cfg.inner) {
+        o.relres = t.resid / bnorm;
+        o.status = VD_OK;
+        return o;
+      }
+      res = true_resid(b, x, r);
     }
   }
 
   SolveOut rmr(const void* b, void* x, double bnorm) {
     SolveOut o;
     void* r = buf(G, prec, B_R);
+    void* rn = dense_prec() ? nullptr : buf(G, prec, B_P);
     void* w = buf(G, prec, B_W);
-    double rn = (cfg.inner || cfg.x_zero) ? copy_rhs(b, r, bnorm) : true_resid(b, x, r);
-    if (cfg.hist) cfg.hist->push_back(rn / bnorm);
+    double res = (cfg.inner || cfg.x_zero) ? copy_rhs(b, r, bnorm) : true_resid(b, x, r);
+    if (cfg.hist) cfg.hist->push_back(res / bnorm);
     while (true) {
-      o.relres = rn / bnorm;
-      if (!(rn == rn)) { o.status = VD_EBREAKDOWN; return o; }
+      o.relres = res / bnorm;
+      if (!(res == res)) { o.status = VD_EBREAKDOWN; return o; }
       if (o.relres <= cfg.rtol) { o.status = VD_OK; return o; }
       if (o.iters >= cfg.max_iter) { o.status = VD_NOT_CONVERGED; return o; }
       const int jlast = cfg.max_iter - o.iters - 1;
@@ -549,6 +582,12 @@ struct Krylov {
       StepState t;
       o.iters += run_queued(jlast, run, t, bnorm, [&](int, const int* gate) {
         apply(r, w, true, nullptr, gate);  // w = A M^-1 r
+        if (!dense_prec()) {
+          dot_partials<R>(g, w, r, true, G->partial, G->st, gate);
+          rec_step<R>(g, cfg.op, true, x, r, rn, nullptr, w, G->dst, G->partial, G->st);
+          std::swap(r, rn);
+          return;
+        }
         VecPtrs P{};
         P.p[0] = r;
         mdot<R>(g, w, P, 1, true, G->partial, G->dst->red, G->st, nullptr, gate, Post{POST_RMR_ALPHA, G->dst});
@@ -562,7 +601,7 @@ struct Krylov {
         o.status = VD_OK;
         return o;
       }
-      rn = true_resid(b, x, r);
+      res = true_resid(b, x, r);
     }
   }
 };
@@ -1089,7 +1128,7 @@ bool upload_cheb(vd_grid* G, const vd_grid_desc* d) {
   M[CH_I] = cs.I;
   M[CH_PRE].resize((size_t)2 * n * n);
   M[CH_PRE_V].assign((size_t)2 * n * n, 0.0);
-  M[CH_POST].resize((size_t)2 * n * n);
+  M[CH_POST].assign((size_t)4 * n * n, 0.0);
   M[CH_RHS].assign((size_t)n * n, 0.0);
   for (int i = 0; i < n; ++i)
     for (int j = 0; j < n; ++j) {
@@ -1107,6 +1146,13 @@ bool upload_cheb(vd_grid* G, const vd_grid_desc* d) {
         M[CH_PRE_V][(size_t)(n + i) * n + j] += vg * at(cs.V, k, j);
       }
     }
+  for (int i = 0; i < n; ++i)  // V^T [-I^T | G^T] below [-I^T | G^T]
+    for (int k = 0; k < n; ++k) {
+      const double vk = at(cs.V, k, i);
+      const double* q = &M[CH_POST][(size_t)k * 2 * n];
+      double* o = &M[CH_POST][(size_t)(n + i) * 2 * n];
+      for (int j = 0; j < 2 * n; ++j) o[j] += vk * q[j];
+    }
   for (int l = 0; l < n; ++l) {  // -I^T diag(h_x w) I
     const double wv = hx * cs.wl[l];
     for (int i = 0; i < n; ++i) {
@@ -1115,8 +1161,8 @@ bool upload_cheb(vd_grid* G, const vd_grid_desc* d) {
       for (int j = 0; j < n; ++j) M[CH_RHS][(size_t)i * n + j] += a * at(cs.I, l, j);
     }
   }
-  // rows of each matrix as applied (C = A B): CH_PRE and CH_PRE_V have 2n
-  const int rows[CH_NMAT] = {n, 2 * n, 2 * n, n, n, n, n};
+  // rows of each matrix as applied (C = A B)
+  const int rows[CH_NMAT] = {n, 2 * n, 2 * n, 2 * n, n, n, n};
   for (int m = 0; m < CH_NMAT; ++m) {  // upload transposed: [K][M]
     const size_t cnt = M[m].size();
     const int R = rows[m], Kc = (int)(cnt / R);

@@ -121,10 +121,6 @@ __device__ __forceinline__ void post_step(DevState* st, int j, double resid, dou
 
 // Scalar steps of CG and RMR, taken by one thread on the reduced values
 // (passed in: see k_reduce).
-__device__ __forceinline__ void cg_alpha_step(DevState* st, double pq) {  // alpha = rz / (p, A p)
-  st->alpha = pq != 0.0 ? st->rz / pq : 0.0;
-  if (!isfinite(st->alpha) || pq <= 0.0) st->bad = 1;
-}
 __device__ __forceinline__ void cg_beta_step(DevState* st, double rzn) {  // beta = (r, M r)_new / (r, M r)
   st->beta = st->rz != 0.0 ? rzn / st->rz : 0.0;
   st->rz = rzn;
@@ -138,7 +134,7 @@ __device__ __forceinline__ void rmr_alpha_step(DevState* st, double rw, double w
 // square, also in st->nrm2), the host loop's test taken on the device: a
 // non-finite scalar, the tolerance, or the last step of the run sets halt.
 // step counts the steps.
-__device__ __forceinline__ void rec_check_step(DevState* st, double n2) {
+__device__ __forceinline__ bool rec_check_step(DevState* st, double n2) {
   const int j = st->step;
   st->step = j + 1;
   const double rn = n2 < 0.0 ? 0.0 : sqrt(n2);
@@ -146,6 +142,7 @@ __device__ __forceinline__ void rec_check_step(DevState* st, double n2) {
   const bool halt = bad || !(n2 == n2) || rn / st->stop_bnorm <= st->stop_rtol || j >= st->jlast;
   if (halt) st->halt = 1;
   post_step(st, j, rn, n2, bad, halt, 0);
+  return halt;
 }
 
 // The final reduction, optionally followed (same launch, after a block
@@ -170,10 +167,12 @@ __global__ __launch_bounds__(1024) void k_reduce(const double* __restrict__ part
   if (post == POST_NONE) return;
   __syncthreads();
   if (threadIdx.x) return;
-  if (post == POST_CG_ALPHA) cg_alpha_step(st, val[0]);
-  else if (post == POST_CG_BETA) cg_beta_step(st, val[0]);
+  if (post == POST_CG_BETA) cg_beta_step(st, val[0]);
   else if (post == POST_RMR_ALPHA) rmr_alpha_step(st, val[0], val[1]);
   else if (post == POST_REC_CHECK) rec_check_step(st, val[0]);
+  else if (post == POST_CG_STEP) {
+    if (!rec_check_step(st, val[0])) cg_beta_step(st, val[1]);
+  }
   else if (post == POST_MAIL) post_mail(st->mail + MAIL_VALUE, val[0], 0.0, 0, seq);
 }
 
@@ -963,28 +962,171 @@ void dot_rMr(const Geom& g, const OpParams& p, const void* r, double* partial, d
 }
 
 template <typename R>
-__global__ __launch_bounds__(256) void k_cg_xr(C2<R>* __restrict__ x, C2<R>* __restrict__ r,
-                                               const C2<R>* __restrict__ p, const C2<R>* __restrict__ q,
-                                               const DevState* __restrict__ st, size_t n, int M,
-                                               double* __restrict__ partial, const int* __restrict__ gate) {
-  if (gate && *gate) return;
-  const double a = st->alpha;
-  double acc = 0.0;
-  for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (size_t)gridDim.x * 256) {
-    C2<R> xv = ldg(x + e), rv = ldg(r + e), pv = ldg(p + e), qv = ldg(q + e);
-    stg(x + e, C2<R>{R(xv.x + a * pv.x), R(xv.y + a * pv.y)});
-    C2<R> nr{R(rv.x - a * qv.x), R(rv.y - a * qv.y)};
-    stg(r + e, nr);
-    acc += spec_w(e, M) * ((double)nr.x * nr.x + (double)nr.y * nr.y);
+void dot_partials(const Geom& g, const void* x, const void* v, bool want_norm, double* partial, hipStream_t s,
+                  const int* gate) {
+  VecPtrs P{};
+  P.p[0] = v;
+  mdot_partials<R>(g, x, P, 1, want_norm, partial, s, gate);
+}
+
+// alpha of a CG or RMR step from the block partials of its dots, by every block
+// for itself (a few KB from L2; one launch less than reducing them first).
+// Thread 0 of block 0 keeps the state.  Ends with a block barrier.
+template <bool RMR>
+__device__ __forceinline__ double step_alpha(DevState* st, const double* __restrict__ partial, int nb,
+                                             double scale) {
+  __shared__ double sh[2];
+  const int w = threadIdx.x >> 6;
+  if (w < (RMR ? 2 : 1)) {
+    const double v = sum_partials(partial + (size_t)w * kRedBlocks, nb) * scale;
+    if ((threadIdx.x & 63) == 0) sh[w] = v;
   }
-  block_store<1>(&acc, 1, partial + blockIdx.x);
+  __syncthreads();
+  double a;
+  bool bad;
+  if constexpr (RMR) {  // (r, w) / (w, w)
+    a = sh[1] > 0.0 ? sh[0] / sh[1] : 0.0;
+    bad = !isfinite(a);
+  } else {  // rz / (p, A p)
+    a = sh[0] != 0.0 ? st->rz / sh[0] : 0.0;
+    bad = !isfinite(a) || sh[0] <= 0.0;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->alpha = a;
+    if (bad) st->bad = 1;
+  }
+  return a;
+}
+
+// The new residual goes to another buffer: with the Helmholtz multipliers
+// (r, M^-1 r) and M^-1 r need the mirror element of kx = 0 slots, which its own
+// thread may already have updated in place.
+// In place of k_cg_xr, k_dot_rMr and two reductions of their own (128^3 FP64:
+// 15.6 + 8.4 + 2 x 4 us a step) this takes 18.6 us.
+template <typename R, bool RMR>
+__global__ __launch_bounds__(256) void k_rec_step(C2<R>* __restrict__ x, const C2<R>* __restrict__ r,
+                                                  C2<R>* __restrict__ rnew, const C2<R>* __restrict__ p,
+                                                  const C2<R>* __restrict__ q, DevState* st, Geom g, int kind,
+                                                  double rho0, double nu, size_t n, double* partial, int nb,
+                                                  double scale) {
+  if (st->halt) return;
+  const double a = step_alpha<RMR>(st, partial, nb, scale);
+  double acc[2] = {0.0, 0.0};
+  for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (size_t)gridDim.x * 256) {
+    const C2<R> xv = ldg(x + e), rv = ldg(r + e), qv = ldg(q + e);
+    const C2<R> d = RMR ? precond_at<R>(r, e, g, kind, rho0, nu) : ldg(p + e);
+    stg(x + e, C2<R>{R(xv.x + a * d.x), R(xv.y + a * d.y)});
+    const C2<R> nr{R(rv.x - a * qv.x), R(rv.y - a * qv.y)};
+    stg(rnew + e, nr);
+    const double w = spec_w(e, g.M);
+    acc[0] += w * ((double)nr.x * nr.x + (double)nr.y * nr.y);
+    if constexpr (!RMR) {
+      C2<R> z = nr;
+      if (kind >= 0) {
+        const unsigned ue = (unsigned)e, u = ue / (unsigned)g.M;
+        const int kx = (int)(ue - u * (unsigned)g.M);
+        const int ky = (int)(u % (unsigned)g.ny), kz = (int)(u / (unsigned)g.ny);
+        if (kind == OP_PRESSURE) {
+          z = cscale(nr, mult_press<R>(kx, ky, kz, g, rho0));
+        } else {
+          const HelmMult<R> h = mult_helm<R>(kx, ky, kz, g, rho0, nu, false);
+          if (kx != 0) {
+            z = cscale(nr, h.g0);
+          } else {
+            const size_t em = ((size_t)((g.nz - kz) % g.nz) * g.ny + (g.ny - ky) % g.ny) * g.M;
+            const C2<R> rm = ldg(r + em), qm = ldg(q + em);
+            z = diag_packed(nr, C2<R>{R(rm.x - a * qm.x), R(rm.y - a * qm.y)}, h.g0, h.gN);
+          }
+        }
+      }
+      acc[1] += w * ((double)nr.x * z.x + (double)nr.y * z.y);
+    }
+  }
+  block_store<2>(acc, RMR ? 1 : 2, partial + 2 * kRedBlocks + blockIdx.x);
 }
 template <typename R>
-void cg_xr(const Geom& g, void* x, void* r, const void* p, const void* q, const DevState* st, double* partial,
-           double* out, hipStream_t s, const int* gate, const Post& post) {
-  hipLaunchKernelGGL((k_cg_xr<R>), dim3(nblk(nspec(g))), dim3(256), 0, s, (C2<R>*)x, (C2<R>*)r, (const C2<R>*)p,
-                     (const C2<R>*)q, st, nspec(g), g.M, partial, gate);
-  reduce(partial, nblk(nspec(g)), 1, g.ntot_inv, out, s, gate, post);
+void rec_step(const Geom& g, const OpParams& op, bool rmr, void* x, const void* r, void* rnew, const void* p,
+              const void* q, DevState* st, double* partial, hipStream_t s) {
+  const size_t n = nspec(g);
+  const int nb = nblk(n), kind = op.precond ? op.kind : -1;
+  if (rmr)
+    hipLaunchKernelGGL((k_rec_step<R, true>), dim3(nb), dim3(256), 0, s, (C2<R>*)x, (const C2<R>*)r, (C2<R>*)rnew,
+                       (const C2<R>*)p, (const C2<R>*)q, st, g, kind, op.rho0, op.nu, n, partial, nb, g.ntot_inv);
+  else
+    hipLaunchKernelGGL((k_rec_step<R, false>), dim3(nb), dim3(256), 0, s, (C2<R>*)x, (const C2<R>*)r, (C2<R>*)rnew,
+                       (const C2<R>*)p, (const C2<R>*)q, st, g, kind, op.rho0, op.nu, n, partial, nb, g.ntot_inv);
+  reduce(partial + 2 * kRedBlocks, nb, rmr ? 1 : 2, g.ntot_inv, st->red, s, &st->halt,
+         Post{rmr ? POST_REC_CHECK : POST_CG_STEP, st});
+}
+
+// D rt at row (eigenvector) `row`, packed wavenumber slot kx
+template <typename R>
+__device__ __forceinline__ double eig_mult(const EigDiag& d, int row, int kx) {
+  const double kp = kx * d.sx;  // slot 0: k' = 0 for both halves
+  return kx == 0 && row == 0 ? 0.0 : d.scale / (kp * kp + d.lam[row]);
+}
+template <typename R>
+__global__ __launch_bounds__(256) void k_eig_step(C2<R>* __restrict__ xt, C2<R>* __restrict__ r,
+                                                  C2<R>* __restrict__ rt, const C2<R>* __restrict__ pt,
+                                                  const C2<R>* __restrict__ qq, DevState* st, EigDiag d, size_t n,
+                                                  int M, double* partial, int nb, double scale) {
+  if (st->halt) return;
+  const double a = step_alpha<false>(st, partial, nb, scale);
+  double acc[2] = {0.0, 0.0};
+  for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (size_t)gridDim.x * 256) {
+    const C2<R> xv = ldg(xt + e), pv = ldg(pt + e), rv = ldg(r + e), tv = ldg(rt + e), qv = ldg(qq + e),
+                qt = ldg(qq + n + e);
+    stg(xt + e, C2<R>{R(xv.x + a * pv.x), R(xv.y + a * pv.y)});
+    const C2<R> nr{R(rv.x - a * qv.x), R(rv.y - a * qv.y)}, nt{R(tv.x - a * qt.x), R(tv.y - a * qt.y)};
+    stg(r + e, nr);
+    stg(rt + e, nt);
+    const double w = spec_w(e, M), m = eig_mult<R>(d, (int)((unsigned)e / (unsigned)M), (int)(e & (size_t)(M - 1)));
+    acc[0] += w * ((double)nr.x * nr.x + (double)nr.y * nr.y);
+    acc[1] += w * m * ((double)nt.x * nt.x + (double)nt.y * nt.y);
+  }
+  block_store<2>(acc, 2, partial + 2 * kRedBlocks + blockIdx.x);
+}
+// Blocks of the Chebyshev CG kernels: one element per thread while the
+// partials stay within what one reduction takes.
+static int eig_blocks(size_t n) { return (int)std::min<size_t>((n + 255) / 256, kRedBlocks); }
+template <typename R>
+void eig_step(const Geom& g, const EigDiag& d, void* xt, void* r, void* rt, const void* pt, const void* qq,
+              DevState* st, double* partial, hipStream_t s) {
+  const size_t n = nspec(g);
+  const int nb = eig_blocks(n);
+  hipLaunchKernelGGL((k_eig_step<R>), dim3(nb), dim3(256), 0, s, (C2<R>*)xt, (C2<R>*)r, (C2<R>*)rt, (const C2<R>*)pt,
+                     (const C2<R>*)qq, st, d, n, g.M, partial, nblk(n), g.ntot_inv);
+  reduce(partial + 2 * kRedBlocks, nb, 2, g.ntot_inv, st->red, s, &st->halt, Post{POST_CG_STEP, st});
+}
+template <typename R>
+__global__ __launch_bounds__(256) void k_eig_p(C2<R>* __restrict__ pt, const C2<R>* __restrict__ rt, EigDiag d,
+                                               int first, const DevState* __restrict__ st, size_t n, int M,
+                                               double* __restrict__ partial) {
+  if (!first && st->halt) return;
+  const double b = first ? 0.0 : st->beta;
+  double acc = 0.0;
+  for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (size_t)gridDim.x * 256) {
+    const C2<R> tv = ldg(rt + e);
+    const double m = eig_mult<R>(d, (int)((unsigned)e / (unsigned)M), (int)(e & (size_t)(M - 1)));
+    C2<R> z{R(m * tv.x), R(m * tv.y)};
+    if (first) {
+      acc += spec_w(e, M) * ((double)tv.x * z.x + (double)tv.y * z.y);
+    } else {
+      const C2<R> pv = ldg(pt + e);
+      z = C2<R>{R(z.x + b * pv.x), R(z.y + b * pv.y)};
+    }
+    stg(pt + e, z);
+  }
+  if (first) block_store<1>(&acc, 1, partial + blockIdx.x);
+}
+template <typename R>
+void eig_p(const Geom& g, const EigDiag& d, void* pt, const void* rt, bool first, DevState* st, double* partial,
+           hipStream_t s) {
+  const size_t n = nspec(g);
+  const int nb = eig_blocks(n);
+  hipLaunchKernelGGL((k_eig_p<R>), dim3(nb), dim3(256), 0, s, (C2<R>*)pt, (const C2<R>*)rt, d, first ? 1 : 0, st, n,
+                     g.M, partial);
+  if (first) reduce(partial, nb, 1, g.ntot_inv, st->red, s, nullptr, Post{POST_CG_BETA, st});
 }
 
 template <typename R>
@@ -1306,8 +1448,13 @@ void kcoef_finish(const double* rho, const double* lap_psi, double* kc64, float*
                                 hipStream_t);                                                                  \
   template void dot_rMr<R>(const Geom&, const OpParams&, const void*, double*, double*, hipStream_t,           \
                            const Post&);                                                                       \
-  template void cg_xr<R>(const Geom&, void*, void*, const void*, const void*, const DevState*, double*,       \
-                         double*, hipStream_t, const int*, const Post&);                                       \
+  template void dot_partials<R>(const Geom&, const void*, const void*, bool, double*, hipStream_t, const int*); \
+  template void rec_step<R>(const Geom&, const OpParams&, bool, void*, const void*, void*, const void*,        \
+                            const void*, DevState*, double*, hipStream_t);                                     \
+  template void eig_step<R>(const Geom&, const EigDiag&, void*, void*, void*, const void*, const void*,        \
+                            DevState*, double*, hipStream_t);                                                  \
+  template void eig_p<R>(const Geom&, const EigDiag&, void*, const void*, bool, DevState*, double*,            \
+                         hipStream_t);                                                                         \
   template void cg_p<R>(const Geom&, const OpParams&, void*, const void*, const DevState*, hipStream_t);       \
   template void axpy_norm<R>(const Geom&, void*, const void*, const double*, double, double*, double*,         \
                              hipStream_t, const int*, const Post&);

@@ -66,10 +66,10 @@ struct DevState {
 
 // A scalar step of CG or RMR that the final reduction of a vector kernel
 // takes in its own launch once the reduced value is written (st: the
-// solver's device state): alpha = rz / red[0] (CG), beta = red[0] / rz and
-// rz = red[0] (CG), alpha = red[0] / red[1] (RMR), or the stopping test on
-// nrm2 (CG and RMR), or the reduced value posted to the host as number seq.
-enum PostOp { POST_NONE = 0, POST_CG_ALPHA, POST_CG_BETA, POST_RMR_ALPHA, POST_REC_CHECK, POST_MAIL };
+// solver's device state): beta = red[0] / rz and rz = red[0] (CG), alpha = red[0] / red[1] (RMR), or the stopping test on
+// nrm2 (CG and RMR), that test on red[0] followed by CG's beta from red[1], or
+// the reduced value posted to the host as number seq.
+enum PostOp { POST_NONE = 0, POST_CG_BETA, POST_RMR_ALPHA, POST_REC_CHECK, POST_CG_STEP, POST_MAIL };
 struct Post {
   int op = POST_NONE;
   DevState* st = nullptr;
@@ -133,10 +133,36 @@ template <typename R>
 void dot_rMr(const Geom& g, const OpParams& p, const void* r, double* partial, double* out,
              hipStream_t s, const Post& post = Post{});
 
-// CG: x += alpha p; r -= alpha q; |r|^2 -> out[0]   (alpha = st->alpha)
+// The block partials of mdot, not reduced: rec_step reduces them itself.
 template <typename R>
-void cg_xr(const Geom& g, void* x, void* r, const void* p, const void* q, const DevState* st,
-           double* partial, double* out, hipStream_t s, const int* gate = nullptr, const Post& post = Post{});
+void dot_partials(const Geom& g, const void* x, const void* v, bool want_norm, double* partial, hipStream_t s,
+                  const int* gate);
+// Second half of a CG or RMR step (rmr = false / true) after dot_partials of
+// (p, q) or of (r, w) and |w|^2:
+//   alpha = rz / (p, q)          or (r, w) / |w|^2
+//   x += alpha p                 or alpha M^-1 r
+//   rnew = r - alpha q           (q: w for RMR; rnew must be another buffer)
+// with the new |r|^2 (red[0]), for CG also (r, M^-1 r) (red[1]), the stopping
+// test and CG's beta.  Gated by st->halt.
+template <typename R>
+void rec_step(const Geom& g, const OpParams& op, bool rmr, void* x, const void* r, void* rnew, const void* p,
+              const void* q, DevState* st, double* partial, hipStream_t s);
+// CG on a Chebyshev grid with its dense preconditioner V D V^T, in the basis V
+// (rt = V^T r, p = V pt, x accumulated as V xt; qq: q and V^T q, one after the
+// other; lam, scale, sx: D as in the contraction's epilogue): after
+// dot_partials of (pt, V^T q),  xt += alpha pt, r -= alpha q,
+// rt -= alpha V^T q, then as rec_step.
+struct EigDiag {
+  const double* lam;
+  double scale, sx;
+};
+template <typename R>
+void eig_step(const Geom& g, const EigDiag& d, void* xt, void* r, void* rt, const void* pt, const void* qq,
+              DevState* st, double* partial, hipStream_t s);
+// pt = D rt + beta pt (first: pt = D rt, and (rt, D rt) reduced into rz)
+template <typename R>
+void eig_p(const Geom& g, const EigDiag& d, void* pt, const void* rt, bool first, DevState* st, double* partial,
+           hipStream_t s);
 // CG: p = M^-1 r + beta p   (beta = st->beta)
 template <typename R>
 void cg_p(const Geom& g, const OpParams& op, void* p, const void* r, const DevState* st, hipStream_t s);

@@ -1,4 +1,4 @@
-"""GPU GMRES on fields around the size where its Gram-Schmidt step changes
+"""Kernels that are chosen by size: GPU GMRES on fields around the size where its Gram-Schmidt step changes
 kernels (131072 spectral slots), against the oracle's GMRES.
 
 Sizes: fewer slots than one block of the small-field kernels holds (256), the
@@ -62,3 +62,55 @@ def test_operators_around_the_small_field_limit(shape, prec, tol):
     g.close()
     assert rel2(y, operators.apply_pressure(x, rho)) < tol
     assert rel2(yh, operators.apply_helmholtz(x, rho, 0.013)) < tol
+
+
+# odd and even wall-normal sizes from the smallest to the largest, and fields on
+# either side of the size where a contraction computes two column tiles per wave
+@pytest.mark.parametrize("nz,nx", [(9, 16), (100, 64), (513, 32), (33, 1024), (257, 512)])
+@pytest.mark.parametrize("precision", ["fp64", "fp32_refine"])
+def test_wall_cg_in_the_eigenbasis(nz, nx, precision):
+    """CG carried out in the basis of the preconditioner's eigenvectors: the
+    oracle's operator gives the returned field a true residual of 1e-10 (1% for
+    its own rounding), the field agrees with GMRES's to 2e-10 times the density
+    ratio, and a warm start and an iteration budget are honoured."""
+    from paper_2403_06654_amd.api import Grid
+    fc = operators.FourierChebyshev2D(nx=nx, m=nz - 1, lx=2.0)
+    xx, zz = fc.x[None, :], fc.z[:, None]
+    rho = np.ascontiguousarray(2.0 + np.tanh((zz - 0.2 * np.sin(np.pi * xx)) / 0.4))
+    f = np.ascontiguousarray(np.cos(np.pi * xx) * (1 + zz) + np.sin(2 * np.pi * xx) * zz ** 3)
+    b, _ = operators.project_range(fc.rhs(f), fc.nullspace_basis())
+    g = Grid((nz, nx), lengths=(2.0, 2.0), cheb=True)
+    g.set_density(to_dev(rho))
+    p, info = g.solve_pressure(to_dev(f), solver="cg", precision=precision)
+    ref, _ = g.solve_pressure(to_dev(f), solver="gmres")
+    x = to_host(p)
+    assert info["status"] == 0
+    assert rel2(fc.apply_pressure(x, rho), b) <= 1.01e-10
+    assert rel2(x, to_host(ref)) <= 2e-10 * rho.max() / rho.min()
+    warm, winfo = g.solve_pressure(to_dev(f), p=p.clone(), solver="cg", precision=precision, use_x0=True, rtol=1e-9)
+    assert winfo["status"] == 0 and winfo["iterations"] == 0
+    _, cut = g.solve_pressure(to_dev(f), solver="cg", max_iter=3)
+    assert cut["status"] == 1 and cut["iterations"] == 3
+    g.close()
+
+
+@pytest.mark.parametrize("M,N,K,shift", [(257, 513, 100, 0), (514, 514, 514, 0), (520, 530, 33, 0), (600, 512, 64, 1),
+                                         (1, 9000, 3, 0), (300, 9000, 1, 0)])
+def test_contraction_tiles(M, N, K, shift):
+    """Shapes that take the two-column-tile contraction (even N, aligned rows)
+    with partial tiles, and the same sizes where it may not be taken: an odd N,
+    and a right operand that starts in the middle of an aligned pair."""
+    import torch
+    from paper_2403_06654_amd.api import dense_matmul
+    rng = np.random.default_rng(M + N + K)
+    A, B = rng.standard_normal((M, K)), rng.standard_normal((K, N))
+    flat = torch.zeros(K * N + 1, dtype=torch.float64, device="cuda")
+    Bd = flat[shift:shift + K * N].view(K, N)
+    Bd.copy_(torch.from_numpy(B))
+    C = dense_matmul(torch.from_numpy(A).cuda(), Bd).cpu().numpy()
+    assert rel2(C, A @ B) < 1e-14
+    flat32 = torch.zeros(K * N + 1, dtype=torch.float32, device="cuda")
+    Bd32 = flat32[shift:shift + K * N].view(K, N)
+    Bd32.copy_(torch.from_numpy(B))
+    C32 = dense_matmul(torch.from_numpy(A.astype(np.float32)).cuda(), Bd32, precision="fp32").cpu().numpy()
+    assert rel2(C32.astype(np.float64), A @ B) < 2e-6
