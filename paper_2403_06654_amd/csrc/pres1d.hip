@@ -10,10 +10,10 @@ namespace vd {
 template <int OP>
 static hipError_t pres1d_dispatch(const Visc1dArgs& a, hipStream_t st) {
   switch (visc1d_tpw(a.ni)) {
-    case 1: return launch_tpw<1, OP>(a, st);
-    case 2: return launch_tpw<2, OP>(a, st);
-    case 3: return launch_tpw<3, OP>(a, st);
-    case 4: return launch_tpw<4, OP>(a, st);
+    case 1: return launch_tpw<1, 4, OP>(a, st);
+    case 2: return launch_tpw<2, 4, OP>(a, st);
+    case 3: return launch_tpw<3, 4, OP>(a, st);
+    case 4: return launch_tpw<4, 4, OP>(a, st);
     default: return pres1d_launch_large(a, st);
   }
 }

@@ -1,6 +1,5 @@
 // Batched one-dimensional pressure operators: launches for 257 to 512
-// unknowns (built with the compiler's default MFMA register forms, like the
-// large viscous systems, since these instantiations spill).
+// unknowns, split over wavefronts like the large viscous systems.
 #include "visc1d_kernel.hpp"
 
 namespace vd {
@@ -8,10 +7,10 @@ namespace vd {
 template <int OP>
 static hipError_t pres1d_large_dispatch(const Visc1dArgs& a, hipStream_t st) {
   switch (visc1d_tpw(a.ni)) {
-    case 5: return launch_tpw<5, OP>(a, st);
-    case 6: return launch_tpw<6, OP>(a, st);
-    case 7: return launch_tpw<7, OP>(a, st);
-    case 8: return launch_tpw<8, OP>(a, st);
+    case 5: return launch_tpw<2, 10, OP>(a, st);
+    case 6: return launch_tpw<3, 8, OP>(a, st);
+    case 7: return launch_tpw<4, 7, OP>(a, st);
+    case 8: return launch_tpw<4, 8, OP>(a, st);
     default: return hipErrorInvalidValue;
   }
 }

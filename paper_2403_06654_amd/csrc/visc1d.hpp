@@ -18,8 +18,7 @@ enum Visc1dSolver { VISC1D_GMRES = 0, VISC1D_CG = 1, VISC1D_RMR = 2 };
 // (eq. VDINSE.Lrho) and K_rho (eq. VDINSE.Krho), on the interior values.
 enum Visc1dOp { OP1D_VISC = 0, OP1D_PRES_L = 1, OP1D_PRES_K = 2 };
 
-// Unknowns are padded to 64 * tpw rows: tpw row tiles of 16 per wavefront,
-// four wavefronts per workgroup.
+// Unknowns are padded to 64 * tpw rows, 4 * tpw row tiles of 16.
 inline int visc1d_tpw(int ni) { return (ni + 63) / 64; }
 inline int visc1d_rows(int tpw) { return 64 * tpw; }
 

@@ -8,8 +8,8 @@
 // Every system of a batch shares the differentiation matrices and V^-1, so a
 // matrix-vector product over a group of 16 systems is a dense product
 // (unknowns x unknowns) x (unknowns x 16): one workgroup runs a group in
-// lockstep and forms those products with v_mfma_f64_16x16x4_f64, each
-// wavefront owning a quarter of the row tiles.  The 16 columns are independent
+// lockstep and forms those products with v_mfma_f64_16x16x4_f64, each of its
+// NW wavefronts owning TPW row tiles.  The 16 columns are independent
 // through every step (products, per-system reductions in a fixed order,
 // per-system scalars), so a system gives the same bits alone or in any batch;
 // a system that has converged, failed or was never present keeps computing
@@ -31,6 +31,18 @@
 //                                                      (eq. VDINSE.Krho)
 // preconditioned by the pseudo-inverse of D2 P; solutions and preconditioned
 // vectors get their wall values from the same extension.
+//
+// What bounds it: the products.  Three n x n x 16 products an iteration are
+// n^2 / 3200 us of FP64 MFMA on one CU (20.5 us at 256 rows, 46 at 384), and a
+// workgroup has to overlap the stream of the matrices from L2, the barriers and
+// the pointwise work with them.  Microseconds per RMR iteration, one group alone
+// on a CU, at 128 / 255 / 384 / 512 unknowns: 9.1 / 28.8 / 56.8 / 100.5 (10.2 /
+// 31.8 / 82.1 / 152.6 with operands copied between registers from tile to tile
+// and, above 256 unknowns, four wavefronts whose accumulators moved between the
+// two register files); 8192 systems at 255 unknowns take 56.9 us (60.0).
+// GMRES adds three reads of the basis per step, which at 4096 systems and 384
+// unknowns run at 6 TB/s: there it stays bound by them (187 us, 211 before);
+// with 500 systems a step takes 103.6 us (141.7).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -45,9 +57,9 @@ namespace {
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-constexpr int kT = 256;            // threads per workgroup (4 wavefronts)
 constexpr int kG = kVisc1dGroup;   // systems per workgroup
 constexpr int kRed = 16;           // Gram-Schmidt coefficients reduced together
+constexpr int kAhead = 8;          // loads of the serial per-system recurrences in flight together
 // GMRES: components of the new vector along the basis above this fraction of
 // its norm are removed by a second Gram-Schmidt pass (the 3D solver's FP64
 // tolerance; the residual estimate then differs from the true one by at most
@@ -56,9 +68,10 @@ constexpr double kVisc1dOrthTol = 1e-8;
 
 enum Kind { K_APPLY = 0, K_RMR = 1, K_GMRES = 2, K_CG = 3 };
 
-template <int TPW>
+// NW wavefronts of TPW row tiles (16 unknowns each)
+template <int TPW, int NW>
 struct Lay {
-  static constexpr int NP = 64 * TPW;        // padded unknowns
+  static constexpr int NP = 16 * TPW * NW;   // padded unknowns
   static constexpr int KT = NP / 16;         // k tiles of the square matrices
   static constexpr int V = NP * kG;          // doubles of one tiled vector
   static constexpr int NB = (NP + 16) * kG;  // operand buffer (one more row tile for the full-width products)
@@ -120,86 +133,123 @@ __device__ __forceinline__ double pdot(const Vec<TPW>& u, const Vec<TPW>& v) {
   return s;
 }
 
-// acc[m] = M_m B for NM matrices of kt k tiles (MFMA operand order) and the
-// operand B in the LDS buffer (tiled, 16 columns).  Component q of a lane's
-// v4d of k tile T is the operand of k step 4 T + q for both A and B.  The
-// operands of tile T + 1 are loaded before the products of tile T are issued
-// (the last tile reloads itself, in bounds), so the L2 latency of the matrix
-// stream overlaps the MFMA work.  The empty asm statements on the first tile's
-// operands keep the compiler from folding the two loads that feed the loop's
-// operand registers into one load at the top of each iteration, which would
-// expose the full latency again.
-template <int TPW, int NM>
-__device__ __forceinline__ void mv(const double* const (&M)[NM], int kt, const double* buf, const Ln& l,
+// acc[m] = M_m B for NM matrices of kt k tiles (MFMA operand order, row tiles
+// stored rs k tiles apart) and the operand B in the LDS buffer (tiled, 16
+// columns).  Component q of a lane's v4d of k tile T is the operand of k step
+// 4 T + q for both A and B.  The operands of a k tile go to one of RING register
+// sets, RING - 1 tiles before its products: a tile of one matrix is TPW * NM * 256
+// MFMA cycles, an L2 latency is 500 to 800.  The loop is unrolled over the sets,
+// so no register is copied, and the barriers to the scheduler keep the loads
+// ahead of the products.  Tiles past the last are the last again, and unused.
+template <int TPW, int NW, int NM>
+__device__ __forceinline__ void mv(const double* const (&M)[NM], int rs, int kt, const double* buf, const Ln& l,
                                    Vec<TPW> (&acc)[NM]) {
+  constexpr int RING = TPW * NM >= 3 || NW > 4 ? 2 : 4;
+  const int wv = __builtin_amdgcn_readfirstlane(l.wv);
   const v4d* bq = reinterpret_cast<const v4d*>(buf) + l.lane;
-  const v4d* ap[NM][TPW];
-  v4d av[NM][TPW];
-#pragma unroll
-  for (int m = 0; m < NM; ++m)
-#pragma unroll
-    for (int t = 0; t < TPW; ++t) {
-      ap[m][t] = reinterpret_cast<const v4d*>(M[m]) + (size_t)(l.wv * TPW + t) * kt * 64 + l.lane;
-      acc[m].t[t] = v4d{0.0, 0.0, 0.0, 0.0};
-      av[m][t] = ap[m][t][0];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        double d = av[m][t][q];
-        asm volatile("" : "+v"(d));
-        av[m][t][q] = d;
-      }
-    }
-  v4d b = bq[0];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    double d = b[q];
-    asm volatile("" : "+v"(d));
-    b[q] = d;
-  }
-#pragma unroll 1
-  for (int T = 0; T < kt; ++T) {
-    const int Tn = T + 1 < kt ? T + 1 : T;
-    v4d an[NM][TPW];
+  const v4d* ap[NM];
+  v4d av[RING][NM][TPW], bv[RING];
+  auto load = [&](int r, int T) {
 #pragma unroll
     for (int m = 0; m < NM; ++m)
 #pragma unroll
-      for (int t = 0; t < TPW; ++t) an[m][t] = ap[m][t][Tn * 64];
-    const v4d bn = bq[Tn * 64];
+      for (int t = 0; t < TPW; ++t) av[r][m][t] = (ap[m] + (size_t)(t * rs + T) * 64)[l.lane];
+    bv[r] = bq[T * 64];
+  };
+  auto mul = [&](int r) {
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
       for (int m = 0; m < NM; ++m)
 #pragma unroll
         for (int t = 0; t < TPW; ++t)
-          acc[m].t[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[m][t][q], b[q], acc[m].t[t], 0, 0, 0);
+          acc[m].t[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[r][m][t][q], bv[r][q], acc[m].t[t], 0, 0, 0);
+  };
 #pragma unroll
-    for (int m = 0; m < NM; ++m)
-#pragma unroll
-      for (int t = 0; t < TPW; ++t) av[m][t] = an[m][t];
-    b = bn;
+  for (int m = 0; m < NM; ++m) {
+    ap[m] = reinterpret_cast<const v4d*>(M[m]) + (size_t)wv * TPW * rs * 64;
+    vzero(acc[m]);
   }
+#pragma unroll
+  for (int r = 0; r < RING - 1; ++r) load(r, min(r, kt - 1));
+  int T = 0;
+#pragma unroll 1
+  for (; T + RING <= kt; T += RING) {
+#pragma unroll
+    for (int r = 0; r < RING; ++r) {
+      load((r + RING - 1) % RING, min(T + r + RING - 1, kt - 1));
+      __builtin_amdgcn_sched_barrier(0);
+      mul(r);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < RING - 1; ++r)
+    if (T + r < kt) mul(r);
 }
 
-// Sums over the unknowns of each system of NV per-lane partial values; every
-// lane returns the sums of its own system.  Fixed order: the four lanes of a
-// wavefront that hold the system by two exchanges, then the four wavefronts.
-template <int NV>
-__device__ __forceinline__ void gsum(double (&v)[NV], double* red, const Ln& l) {
+// Rows of 16 lanes exchanged between two registers without LDS: the sum of
+// the pair (a, b) over neighbouring rows (swap16) or over the two halves of the
+// wavefront (swap32); rows of even index (lower half) return a's sum, the others b's.
+__device__ __forceinline__ double swap16_add(double a, double b) {
+  const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+__device__ __forceinline__ double swap32_add(double a, double b) {
+  const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+
+// Sums over the unknowns of each system of per-lane partial values, in a fixed
+// order: the four lanes of a wavefront that hold the system by two exchanges,
+// then the NW wavefronts in order.
+template <int NW>
+__device__ __forceinline__ double wave_total(const double* p) {
+  double s = p[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) s += p[w * kG];
+  return s;
+}
+// Every lane gets the sums of its own system, at one barrier: successive sums
+// use the two halves of the scratch in turn, and the sum before the last was
+// read by every wavefront before it came to the last one's barrier.
+struct Red {
+  double* p;  // [2][2][NW][kG]
+  int ph;
+};
+template <int NV, int NW>
+__device__ __forceinline__ void gsum(double (&v)[NV], Red& rd, const Ln& l) {
+  static_assert(NV <= 2, "scratch of two values");
+  double* red = rd.p + rd.ph * 2 * NW * kG;
+  rd.ph ^= 1;
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
-    v[k] += __shfl_xor(v[k], 16, 64);
-    v[k] += __shfl_xor(v[k], 32, 64);
+    const double h = swap16_add(v[k], v[k]);
+    v[k] = swap32_add(h, h);
   }
   if (l.lq == 0) {
 #pragma unroll
-    for (int k = 0; k < NV; ++k) red[(k * 4 + l.wv) * kG + l.sl] = v[k];
+    for (int k = 0; k < NV; ++k) red[(k * NW + l.wv) * kG + l.sl] = v[k];
   }
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    const double* p = red + k * 4 * kG + l.sl;
-    v[k] = ((p[0] + p[kG]) + p[2 * kG]) + p[3 * kG];
+  for (int k = 0; k < NV; ++k) v[k] = wave_total<NW>(red + k * NW * kG + l.sl);
+}
+// The first nv of kRed sums go to out[k][system], one thread each; begins its
+// writes to out after a barrier and ends with one.  The exchanges are shared by
+// two values each, so that quad q is left with values q, q + 4, q + 8, ...
+template <int NW>
+__device__ __forceinline__ void gsum_to(const double (&v)[kRed], int nv, double* red, double* out, const Ln& l) {
+#pragma unroll
+  for (int d = 0; d < kRed / 4; ++d) {
+    const double s = swap32_add(swap16_add(v[4 * d], v[4 * d + 1]), swap16_add(v[4 * d + 2], v[4 * d + 3]));
+    red[((4 * d + l.lq) * NW + l.wv) * kG + l.sl] = s;
   }
+  __syncthreads();
+  for (int e = threadIdx.x; e < nv * kG; e += 64 * NW)
+    out[e] = wave_total<NW>(red + (e / kG) * NW * kG + (e % kG));
   __syncthreads();
 }
 
@@ -208,7 +258,7 @@ __device__ __forceinline__ void gsum(double (&v)[NV], double* red, const Ln& l) 
 // registers than both at once); z itself is read back from the buffer for
 // the pointwise terms.  Coefficients (tiled): viscous ca = a/rho, rp = rho',
 // rpp = rho''; L_rho ca = 1/rho, rp = -rho'/rho^2; K_rho rpp = c.
-template <int TPW, int OP>
+template <int TPW, int NW, int OP>
 __device__ __forceinline__ void op_buf(const Visc1dArgs& a, const double* buf, Vec<TPW>& w, const double* wca,
                                        const double* wrp, const double* wrpp, const Ln& l) {
   const v4d* zq = reinterpret_cast<const v4d*>(buf);
@@ -218,7 +268,7 @@ __device__ __forceinline__ void op_buf(const Visc1dArgs& a, const double* buf, V
   if constexpr (OP == OP1D_PRES_K) {
     Vec<TPW> d2[1];
     const double* const M2[1] = {a.D2I};
-    mv<TPW, 1>(M2, Lay<TPW>::KT, buf, l, d2);
+    mv<TPW, NW, 1>(M2, Lay<TPW, NW>::KT, (a.ni + 15) >> 4, buf, l, d2);
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
       const int i = vi4<TPW>(l, t);
@@ -230,8 +280,8 @@ __device__ __forceinline__ void op_buf(const Visc1dArgs& a, const double* buf, V
     Vec<TPW> d1[1], d2[1];
     const double* const M1[1] = {a.D1I};
     const double* const M2[1] = {a.D2I};
-    mv<TPW, 1>(M1, Lay<TPW>::KT, buf, l, d1);
-    mv<TPW, 1>(M2, Lay<TPW>::KT, buf, l, d2);
+    mv<TPW, NW, 1>(M1, Lay<TPW, NW>::KT, (a.ni + 15) >> 4, buf, l, d1);
+    mv<TPW, NW, 1>(M2, Lay<TPW, NW>::KT, (a.ni + 15) >> 4, buf, l, d2);
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
       const int i = vi4<TPW>(l, t);
@@ -249,21 +299,27 @@ __device__ __forceinline__ void op_buf(const Visc1dArgs& a, const double* buf, V
   }
 }
 
+// Wavefronts per SIMD that the registers have to leave room for: two groups on a
+// CU up to 256 unknowns (RMR, CG), one beyond that and with GMRES.
+template <int TPW, int NW, int KIND>
+constexpr int kVisc1dWaves = ((NW + 3) / 4) * (KIND == K_GMRES || TPW * NW > 16 ? 1 : 2);
+
 }  // namespace
 
-template <int TPW, int KIND, int OP>
-__global__ __launch_bounds__(kT, (KIND == K_GMRES || TPW > 4) ? 1 : 2) void k_visc1d(Visc1dArgs a) {
-  using L = Lay<TPW>;
+template <int TPW, int NW, int KIND, int OP>
+__global__ __launch_bounds__(64 * NW, (kVisc1dWaves<TPW, NW, KIND>)) void k_visc1d(Visc1dArgs a) {
+  constexpr int kT = 64 * NW;  // threads per workgroup
+  using L = Lay<TPW, NW>;
   extern __shared__ __attribute__((aligned(32))) double lds[];
   const int m = KIND == K_GMRES ? a.restart : 0;
   double* buf = lds;                  // [NB] right-hand operand of the products
-  double* red = buf + L::NB;          // [kRed][4][kG] wavefront partial sums
-  double* hco = red + kRed * 4 * kG;  // [m + 1][kG] Hessenberg column being built
+  double* red = buf + L::NB;          // GMRES: [kRed][NW][kG] wavefront partial sums
+  Red rd{red + (m ? kRed : 0) * NW * kG, 0};  // scratch of the small sums
+  double* hco = rd.p + 4 * NW * kG;   // [m + 1][kG] Hessenberg column being built
   double* cco = hco + (m + 1) * kG;   // [m + 1][kG] coefficients of the current pass, then y
   int* bad_s = reinterpret_cast<int*>(cco + (m + 1) * kG);  // [kG] density rejected
   int* stop_s = bad_s + kG;                                  // [kG] Arnoldi stop flags
-  double* thr = reinterpret_cast<double*>(stop_s + kG);      // [kG] orthogonality threshold per system
-  int* need = reinterpret_cast<int*>(thr + kG);              // [m + 1] basis vectors of the second pass
+  int* need = stop_s + kG;                                   // [m + 1] basis vectors of the second pass
   const Ln l{(int)threadIdx.x & 63, (int)threadIdx.x >> 6, (int)threadIdx.x & 15, ((int)threadIdx.x >> 4) & 3};
   const int g0 = blockIdx.x * kG;
   const int nsys = min(kG, a.batch - g0);
@@ -300,7 +356,7 @@ __global__ __launch_bounds__(kT, (KIND == K_GMRES || TPW > 4) ? 1 : 2) void k_vi
     // c = -(D2 P psi) / psi
     Vec<TPW> acc[1], c, zero;
     const double* const M[1] = {a.D2I};
-    mv<TPW, 1>(M, Lay<TPW>::KT, buf, l, acc);
+    mv<TPW, NW, 1>(M, Lay<TPW, NW>::KT, (a.ni + 15) >> 4, buf, l, acc);
     vzero(zero);
 #pragma unroll
     for (int t = 0; t < TPW; ++t)
@@ -316,7 +372,7 @@ __global__ __launch_bounds__(kT, (KIND == K_GMRES || TPW > 4) ? 1 : 2) void k_vi
   } else {
     Vec<TPW> acc[2], ca;
     const double* const M[2] = {a.D1F, a.D2F};
-    mv<TPW, 2>(M, a.kt_full, buf, l, acc);
+    mv<TPW, NW, 2>(M, a.kt_full, a.kt_full, buf, l, acc);
 #pragma unroll
     for (int t = 0; t < TPW; ++t)
 #pragma unroll
@@ -377,7 +433,7 @@ __global__ __launch_bounds__(kT, (KIND == K_GMRES || TPW > 4) ? 1 : 2) void k_vi
               wsum[1] += a.EM[i] * v.t[t][r];
             }
           }
-        gsum<2>(wsum, red, l);
+        gsum<2, NW>(wsum, rd, l);
         if (l.wv == 0 && l.lq == 0 && live) {
           a.x[(size_t)(g0 + l.sl) * np] = bad ? 0.0 : wsum[0];
           a.x[(size_t)(g0 + l.sl) * np + np - 1] = bad ? 0.0 : wsum[1];
@@ -410,19 +466,19 @@ __global__ __launch_bounds__(kT, (KIND == K_GMRES || TPW > 4) ? 1 : 2) void k_vi
       __syncthreads();
       Vec<TPW> acc[1];
       const double* const M[1] = {a.VI};
-      mv<TPW, 1>(M, L::KT, buf, l, acc);
+      mv<TPW, NW, 1>(M, L::KT, (a.ni + 15) >> 4, buf, l, acc);
       __syncthreads();
       Z = acc[0];
     } else {
       Z = R;
     }
   };
-  // Wv = V_rho Z; Z stays in the operand buffer until the next product
+  // Wv = V_rho Z; Z stays in the operand buffer until the next product.  A sum
+  // over the unknowns, with its barrier, has to come before that.
   auto apply = [&](const Vec<TPW>& Z, Vec<TPW>& Wv) {
     vst(Z, buf, l);
     __syncthreads();
-    op_buf<TPW, OP>(a, buf, Wv, wca, wrp, wrpp, l);
-    __syncthreads();
+    op_buf<TPW, NW, OP>(a, buf, Wv, wca, wrp, wrpp, l);
   };
   // R = b - V_rho X; returns ||R|| of this lane's system
   auto residual = [&](const Vec<TPW>& X, Vec<TPW>& R) -> double {
@@ -432,7 +488,7 @@ __global__ __launch_bounds__(kT, (KIND == K_GMRES || TPW > 4) ? 1 : 2) void k_vi
 #pragma unroll
     for (int t = 0; t < TPW; ++t) R.t[t] = bv.t[t] - w.t[t];
     double s[1] = {pdot(R, R)};
-    gsum<1>(s, red, l);
+    gsum<1, NW>(s, rd, l);
     return sqrt(s[0]);
   };
 
@@ -454,7 +510,7 @@ __global__ __launch_bounds__(kT, (KIND == K_GMRES || TPW > 4) ? 1 : 2) void k_vi
     double bn;
     {
       double s[1] = {pdot(B, B)};
-      gsum<1>(s, red, l);
+      gsum<1, NW>(s, rd, l);
       bn = sqrt(s[0]);
     }
     Vec<TPW> X;
@@ -487,12 +543,12 @@ __global__ __launch_bounds__(kT, (KIND == K_GMRES || TPW > 4) ? 1 : 2) void k_vi
             done = true;
           }
         }
-        if (!__syncthreads_or(!done)) break;
+        if (!__any(!done)) break;
         Vec<TPW> Z, Wv;
         prec(R, Z);
         apply(Z, Wv);
         double s2[2] = {pdot(R, Wv), pdot(Wv, Wv)};
-        gsum<2>(s2, red, l);
+        gsum<2, NW>(s2, rd, l);
         const double alpha = s2[1] > 0.0 ? s2[0] / s2[1] : 0.0;
         if (!done) {
           // z is still in the operand buffer
@@ -506,14 +562,14 @@ __global__ __launch_bounds__(kT, (KIND == K_GMRES || TPW > 4) ? 1 : 2) void k_vi
           ++it;
         }
         double s1[1] = {pdot(R, R)};
-        gsum<1>(s1, red, l);
+        gsum<1, NW>(s1, rd, l);
         if (!done) {
           rn = sqrt(s1[0]);
           record(it, rn / bn);
         }
         // the true residual now and then, against drift of the recurrence
         const bool need = !done && (rn / bn <= a.rtol || it % 50 == 0);
-        if (__syncthreads_or(need)) {
+        if (__any(need)) {
           Vec<TPW> R2, Xc;
           vld(Xc, wx, l);
           const double rn2 = residual(Xc, R2);
@@ -554,12 +610,12 @@ __global__ __launch_bounds__(kT, (KIND == K_GMRES || TPW > 4) ? 1 : 2) void k_vi
             done = true;
           }
         }
-        if (!__syncthreads_or(!done)) break;
+        if (!__any(!done)) break;
         {
           Vec<TPW> Z, P;
           prec(R, Z);
           double s1[1] = {pdot(R, Z)};
-          gsum<1>(s1, red, l);
+          gsum<1, NW>(s1, rd, l);
           if (fresh) {
             P = Z;
           } else {
@@ -581,7 +637,7 @@ __global__ __launch_bounds__(kT, (KIND == K_GMRES || TPW > 4) ? 1 : 2) void k_vi
         }
         __syncthreads();
         Vec<TPW> Q;
-        op_buf<TPW, OP>(a, buf, Q, wca, wrp, wrpp, l);
+        op_buf<TPW, NW, OP>(a, buf, Q, wca, wrp, wrpp, l);
         const v4d* pq = reinterpret_cast<const v4d*>(buf);
         double s2[1] = {0.0};
 #pragma unroll
@@ -590,7 +646,7 @@ __global__ __launch_bounds__(kT, (KIND == K_GMRES || TPW > 4) ? 1 : 2) void k_vi
 #pragma unroll
           for (int r = 0; r < 4; ++r) s2[0] += pv[r] * Q.t[t][r];
         }
-        gsum<1>(s2, red, l);
+        gsum<1, NW>(s2, rd, l);
         const double alpha = s2[0] != 0.0 ? rz / s2[0] : 0.0;
         if (!done) {
           v4d* xq = reinterpret_cast<v4d*>(wx);
@@ -602,13 +658,13 @@ __global__ __launch_bounds__(kT, (KIND == K_GMRES || TPW > 4) ? 1 : 2) void k_vi
           ++it;
         }
         double s1[1] = {pdot(R, R)};
-        gsum<1>(s1, red, l);
+        gsum<1, NW>(s1, rd, l);
         if (!done) {
           rn = sqrt(s1[0]);
           record(it, rn / bn);
         }
         const bool need = !done && rn / bn <= a.rtol;
-        if (__syncthreads_or(need)) {
+        if (__any(need)) {
           Vec<TPW> R2, Xc;
           vld(Xc, wx, l);
           const double rn2 = residual(Xc, R2);
@@ -647,7 +703,7 @@ __global__ __launch_bounds__(kT, (KIND == K_GMRES || TPW > 4) ? 1 : 2) void k_vi
           }
         }
         const bool cyc = !done;
-        if (!__syncthreads_or(cyc)) break;
+        if (!__any(cyc)) break;
         Vec<TPW> Vj;
 #pragma unroll
         for (int t = 0; t < TPW; ++t)
@@ -665,74 +721,89 @@ __global__ __launch_bounds__(kT, (KIND == K_GMRES || TPW > 4) ? 1 : 2) void k_vi
           prec(Vj, Z);
           apply(Z, Wv);
           if (!park) ++it;
-          for (int e = threadIdx.x; e < (j + 1) * kG; e += kT) hco[e] = 0.0;
           // Classical Gram-Schmidt with a measured check, as in the 3D solver:
           // h = V^T w, w' = w - V h, then c = V^T w'.  A second pass subtracts
           // only the components with |c_i| > tol ||w'|| of some system of the
           // group and reads only those basis vectors (CGS2 read the basis four
-          // times per step, this reads it three times plus the few selected).
-          auto basis_dots = [&]() {  // cco[i][s] = (v_i, w) for i <= j
-            for (int i0 = 0; i0 <= j; i0 += kRed) {
+          // times per step, this reads it three times plus the few
+          // selected).  (w', w') is summed along with c, and is the new vector's
+          // norm when nothing is selected.
+          // kFly vectors' loads are in flight at a time (past the last vector, the
+          // last again): one at a time, each waited out an L2 latency.
+          constexpr int kFly = TPW > 2 ? 2 : 4;
+          // cco[i][s] = (v_i, w) for i <= j, and (w, w) at i = j + 1
+          auto basis_dots = [&](bool norm) {
+            const int nd = j + 1 + (norm ? 1 : 0);
+            const double ww = norm ? pdot(Wv, Wv) : 0.0;
+            for (int i0 = 0; i0 < nd; i0 += kRed) {
               double p[kRed];
 #pragma unroll
-              for (int c = 0; c < kRed; ++c) {
-                p[c] = 0.0;
-                if (i0 + c <= j) {
-                  Vec<TPW> vi;
-                  vld(vi, wbas + (size_t)(i0 + c) * L::V, l);
-                  p[c] = pdot(vi, Wv);
-                }
-              }
-              gsum<kRed>(p, red, l);
-              if (owner) {
+              for (int c0 = 0; c0 < kRed; c0 += kFly) {
+                if (i0 + c0 <= j) {
+                  Vec<TPW> vi[kFly];
 #pragma unroll
-                for (int c = 0; c < kRed; ++c)
-                  if (i0 + c <= j) cco[(i0 + c) * kG + l.sl] = p[c];
+                  for (int c = 0; c < kFly; ++c) vld(vi[c], wbas + (size_t)min(i0 + c0 + c, j) * L::V, l);
+#pragma unroll
+                  for (int c = 0; c < kFly; ++c) p[c0 + c] = pdot(vi[c], Wv);
+                }
+#pragma unroll
+                for (int c = 0; c < kFly; ++c)
+                  if (i0 + c0 + c > j) p[c0 + c] = ww;
+              }
+              gsum_to<NW>(p, min(kRed, nd - i0), red, cco + (size_t)i0 * kG, l);
+            }
+          };
+          // w -= sum_i cco[i] v_i over i <= j, or over the vectors flagged in need
+          auto basis_update = [&](bool flagged) {
+            for (int i0 = 0; i0 <= j; i0 += kFly) {
+              if (flagged) {
+                for (int i = i0; i <= min(i0 + kFly - 1, j); ++i) {
+                  if (!need[i]) continue;  // uniform across the block
+                  const double c = cco[i * kG + l.sl];
+                  Vec<TPW> vi;
+                  vld(vi, wbas + (size_t)i * L::V, l);
+#pragma unroll
+                  for (int t = 0; t < TPW; ++t) Wv.t[t] -= c * vi.t[t];
+                }
+                continue;
+              }
+              Vec<TPW> vi[kFly];
+#pragma unroll
+              for (int c = 0; c < kFly; ++c) vld(vi[c], wbas + (size_t)min(i0 + c, j) * L::V, l);
+#pragma unroll
+              for (int c = 0; c < kFly; ++c) {
+                if (i0 + c > j) break;
+                const double y = cco[(i0 + c) * kG + l.sl];
+#pragma unroll
+                for (int t = 0; t < TPW; ++t) Wv.t[t] -= y * vi[c].t[t];
               }
             }
           };
-          basis_dots();
-          __syncthreads();
-          for (int e = threadIdx.x; e < (j + 1) * kG; e += kT) hco[e] += cco[e];
-          for (int i = 0; i <= j; ++i) {
-            const double c = cco[i * kG + l.sl];
-            Vec<TPW> vi;
-            vld(vi, wbas + (size_t)i * L::V, l);
-#pragma unroll
-            for (int t = 0; t < TPW; ++t) Wv.t[t] -= c * vi.t[t];
-          }
-          __syncthreads();
-          basis_dots();
-          {
-            double s2[1] = {pdot(Wv, Wv)};
-            gsum<1>(s2, red, l);
-            if (owner) thr[l.sl] = kVisc1dOrthTol * sqrt(s2[0]);
-          }
-          __syncthreads();
+          basis_dots(false);
+          for (int e = threadIdx.x; e < (j + 1) * kG; e += kT) hco[e] = cco[e];
+          basis_update(false);
+          basis_dots(true);
+          double s[1] = {cco[(j + 1) * kG + l.sl]};
           // keep c_i[s] only where it fails the test (NaN fails); vector i is
           // read when any system keeps it
-          for (int i = threadIdx.x; i <= j; i += kT) {
-            int any = 0;
-            for (int q = 0; q < kG; ++q) {
-              const double c = cco[i * kG + q];
-              if (fabs(c) <= thr[q]) cco[i * kG + q] = 0.0;
-              else any = 1;
+          bool second = false;
+          for (int e0 = 0; e0 < (j + 1) * kG; e0 += kT) {
+            const int e = e0 + (int)threadIdx.x;
+            bool keep = false;
+            if (e < (j + 1) * kG) {
+              keep = !(fabs(cco[e]) <= kVisc1dOrthTol * sqrt(s[0]));
+              if (!keep) cco[e] = 0.0;
             }
-            need[i] = any;
+            const unsigned long long kept = __ballot(keep);
+            if (l.sl == 0 && e < (j + 1) * kG) need[e / kG] = (kept >> (l.lq * kG)) & 0xffffull ? 1 : 0;
+            second |= kept != 0;
           }
-          __syncthreads();
-          for (int i = 0; i <= j; ++i) {
-            if (!need[i]) continue;  // uniform across the block
-            const double c = cco[i * kG + l.sl];
-            Vec<TPW> vi;
-            vld(vi, wbas + (size_t)i * L::V, l);
-#pragma unroll
-            for (int t = 0; t < TPW; ++t) Wv.t[t] -= c * vi.t[t];
+          if (__syncthreads_or(second)) {
+            basis_update(true);
+            for (int e = threadIdx.x; e < (j + 1) * kG; e += kT) hco[e] += cco[e];
+            s[0] = pdot(Wv, Wv);
+            gsum<1, NW>(s, rd, l);
           }
-          for (int e = threadIdx.x; e < (j + 1) * kG; e += kT) hco[e] += cco[e];
-          __syncthreads();
-          double s[1] = {pdot(Wv, Wv)};
-          gsum<1>(s, red, l);
           const double hn = sqrt(s[0]);
 #pragma unroll
           for (int t = 0; t < TPW; ++t)
@@ -742,11 +813,22 @@ __global__ __launch_bounds__(kT, (KIND == K_GMRES || TPW > 4) ? 1 : 2) void k_vi
           if (owner && !park) {
             // previous rotations on the new column, then the new rotation
             double hj = hco[l.sl];
-            for (int i = 0; i < j; ++i) {
-              const double hb = hco[(i + 1) * kG + l.sl];
-              const double c = wcs[i * kG + l.sl], sg = wsn[i * kG + l.sl];
-              wH[((size_t)j * (m + 1) + i) * kG + l.sl] = c * hj + sg * hb;
-              hj = -sg * hj + c * hb;
+            for (int i0 = 0; i0 < j; i0 += kAhead) {  // kAhead rotations loaded at a time
+              double cv[kAhead], sv[kAhead];
+#pragma unroll
+              for (int q = 0; q < kAhead; ++q) {
+                const int i = min(i0 + q, j - 1);
+                cv[q] = wcs[i * kG + l.sl];
+                sv[q] = wsn[i * kG + l.sl];
+              }
+#pragma unroll
+              for (int q = 0; q < kAhead; ++q) {
+                const int i = i0 + q;
+                if (i >= j) break;
+                const double hb = hco[(i + 1) * kG + l.sl];
+                wH[((size_t)j * (m + 1) + i) * kG + l.sl] = cv[q] * hj + sv[q] * hb;
+                hj = -sv[q] * hj + cv[q] * hb;
+              }
             }
             const double rr = hypot(hj, hn);
             const double c = rr > 0.0 ? hj / rr : 1.0, sg = rr > 0.0 ? hn / rr : 0.0;
@@ -766,7 +848,7 @@ __global__ __launch_bounds__(kT, (KIND == K_GMRES || TPW > 4) ? 1 : 2) void k_vi
             park = stop_s[l.sl] != 0;
           }
           jend = j + 1;
-          if (!__syncthreads_or(!park)) break;
+          if (!__any(!park)) break;
         }
         // back-solve H y = g (y into cco), then x += M^-1 (V y)
         if (owner) {
@@ -774,7 +856,15 @@ __global__ __launch_bounds__(kT, (KIND == K_GMRES || TPW > 4) ? 1 : 2) void k_vi
             double yi = 0.0;
             if (i < k) {
               double t = wg[i * kG + l.sl];
-              for (int q = i + 1; q < k; ++q) t -= wH[((size_t)q * (m + 1) + i) * kG + l.sl] * cco[q * kG + l.sl];
+              for (int q0 = i + 1; q0 < k; q0 += kAhead) {
+                double hv[kAhead];
+#pragma unroll
+                for (int q = 0; q < kAhead; ++q)
+                  hv[q] = wH[((size_t)min(q0 + q, k - 1) * (m + 1) + i) * kG + l.sl];
+#pragma unroll
+                for (int q = 0; q < kAhead; ++q)
+                  if (q0 + q < k) t -= hv[q] * cco[(q0 + q) * kG + l.sl];
+              }
               const double d = wH[((size_t)i * (m + 1) + i) * kG + l.sl];
               yi = d != 0.0 ? t / d : 0.0;
             }
@@ -812,29 +902,30 @@ __global__ __launch_bounds__(kT, (KIND == K_GMRES || TPW > 4) ? 1 : 2) void k_vi
 
 namespace {
 
-template <int TPW, int OP>
+template <int TPW, int NW, int OP>
 hipError_t launch_tpw(const Visc1dArgs& a, hipStream_t st) {
-  using L = Lay<TPW>;
+  using L = Lay<TPW, NW>;
+  constexpr int kT = 64 * NW;
   const int kind = a.mode != VISC1D_SOLVE    ? K_APPLY
                    : a.solver == VISC1D_RMR ? K_RMR
                    : a.solver == VISC1D_CG  ? K_CG
                                             : K_GMRES;
   const int m = kind == K_GMRES ? a.restart : 0;
-  const size_t lds = (size_t)(L::NB + kRed * 4 * kG + 2 * (m + 1) * kG + kG) * sizeof(double) +
+  const size_t lds = (size_t)(L::NB + ((m ? kRed : 0) + 4) * NW * kG + 2 * (m + 1) * kG) * sizeof(double) +
                      (2 * kG + m + 1) * sizeof(int);
-  const void* fn = kind == K_APPLY ? reinterpret_cast<const void*>(&k_visc1d<TPW, K_APPLY, OP>)
-                   : kind == K_RMR ? reinterpret_cast<const void*>(&k_visc1d<TPW, K_RMR, OP>)
-                   : kind == K_CG  ? reinterpret_cast<const void*>(&k_visc1d<TPW, K_CG, OP>)
-                                   : reinterpret_cast<const void*>(&k_visc1d<TPW, K_GMRES, OP>);
+  const void* fn = kind == K_APPLY ? reinterpret_cast<const void*>(&k_visc1d<TPW, NW, K_APPLY, OP>)
+                   : kind == K_RMR ? reinterpret_cast<const void*>(&k_visc1d<TPW, NW, K_RMR, OP>)
+                   : kind == K_CG  ? reinterpret_cast<const void*>(&k_visc1d<TPW, NW, K_CG, OP>)
+                                   : reinterpret_cast<const void*>(&k_visc1d<TPW, NW, K_GMRES, OP>);
   if (lds > 65536) {
     const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
   const dim3 grid((a.batch + kG - 1) / kG);
-  if (kind == K_APPLY) hipLaunchKernelGGL((k_visc1d<TPW, K_APPLY, OP>), grid, dim3(kT), lds, st, a);
-  else if (kind == K_RMR) hipLaunchKernelGGL((k_visc1d<TPW, K_RMR, OP>), grid, dim3(kT), lds, st, a);
-  else if (kind == K_CG) hipLaunchKernelGGL((k_visc1d<TPW, K_CG, OP>), grid, dim3(kT), lds, st, a);
-  else hipLaunchKernelGGL((k_visc1d<TPW, K_GMRES, OP>), grid, dim3(kT), lds, st, a);
+  if (kind == K_APPLY) hipLaunchKernelGGL((k_visc1d<TPW, NW, K_APPLY, OP>), grid, dim3(kT), lds, st, a);
+  else if (kind == K_RMR) hipLaunchKernelGGL((k_visc1d<TPW, NW, K_RMR, OP>), grid, dim3(kT), lds, st, a);
+  else if (kind == K_CG) hipLaunchKernelGGL((k_visc1d<TPW, NW, K_CG, OP>), grid, dim3(kT), lds, st, a);
+  else hipLaunchKernelGGL((k_visc1d<TPW, NW, K_GMRES, OP>), grid, dim3(kT), lds, st, a);
   return hipGetLastError();
 }
 

@@ -233,3 +233,28 @@ def test_bench_configuration_sampled():
             assert rel2(u[k, 1:-1], orc["x"]) < 1e-9, (solver, k, rel2(u[k, 1:-1], orc["x"]))
             assert abs(rr[k] / orc["rel_residual"] - 1.0) < 1e-6, (solver, k, rr[k], orc["rel_residual"])
     h.close()
+
+
+# every count of row tiles at which the split over wavefronts changes, with
+# unknowns that end inside a tile, on its edge and one past it
+@pytest.mark.parametrize("basis,n", [("fourier", 30), ("cheb", 67), ("fourier", 130), ("cheb", 195), ("fourier", 258),
+                                     ("cheb", 322), ("fourier", 324), ("fourier", 384), ("cheb", 387),
+                                     ("fourier", 448), ("cheb", 452), ("fourier", 498)])
+def test_solve_at_the_edges_of_the_row_tiles(basis, n):
+    """All three solvers; GMRES also in cycles that end on and beside the 16
+    sums that are reduced together.  A solve that reports convergence has an
+    oracle-evaluated residual of 1e-10 (1% for its rounding)."""
+    from paper_2403_06654_amd.api import Visc1d
+    print(f"case visc1d tiles {basis} n={n}", flush=True)
+    a = 1e-3
+    x, rho, systems = _case(basis, n, [1.5, 3.0, 5.0], a)
+    b = np.random.default_rng(n).standard_normal(rho.shape)
+    h = Visc1d(basis, n, a)
+    for solver, restart in (("rmr", 30), ("gmres", 128), ("gmres", 15), ("gmres", 16), ("gmres", 17)):
+        u, it, rr, info = h.solve(to_dev(rho), to_dev(b), solver=solver, restart=restart, max_iter=4000)
+        assert info["status"] == 0, (solver, restart, info)
+        u = to_host(u)
+        for k, (A, V) in enumerate(systems):
+            r = rel2(A @ _inner(basis, u[k]), _inner(basis, b[k]))
+            assert r <= 1.01e-10, (solver, restart, k, r)
+    h.close()
