@@ -27,6 +27,7 @@
 #include <initializer_list>
 
 #include "fft_core.hpp"
+#include "gs_device.hpp"
 
 #include "passes.hpp"
 #include "spectral.hpp"
@@ -94,7 +95,7 @@ struct Col512 {
 // wall grid 7.6 -> 5.5.  Larger fields keep the shapes below, which are chosen
 // for bandwidth: with the limit at 2^20 slots a 64 x 128 x 256 FP32+refine
 // solve took 3481 us instead of 3417 (128^3 FP64 K: 1888 instead of 1953).
-constexpr size_t kSmallField = 131072;
+constexpr size_t kSmallField = kFoldElems;
 
 constexpr int col_groups(int mode) {
   return mode == COL_P_FIRST || mode == COL_P_LAST ? 2 : mode == COL_P_MIDINV || mode == COL_P_MIDFWD ? 3 : 1;
@@ -109,9 +110,10 @@ struct ColSmall {
 // lengths that the small configuration is built for
 constexpr bool col_has_small(int L, int mode) { return L <= 256 || (col_groups(mode) <= 2 && L <= 1024); }
 
-template <int L, typename R, int MODE, bool SM = false>
+template <int L, typename R, int MODE, bool SM = false, bool GS = false>
 struct ColCfg {
-  static constexpr int NG = SM ? col_groups(MODE) : 1;
+  // (GS: a Helmholtz pass gets a second group for the dots)
+  static constexpr int NG = SM ? (GS && MODE == COL_H_LAST ? 2 : col_groups(MODE)) : 1;
   static constexpr bool E8 = sizeof(R) == 8 && L < 512 && MODE != COL_P_LAST && MODE != COL_P_MIDFWD;
   static constexpr int E = SM ? ColSmall<L>::E
                               : L == 512 ? Col512<R, MODE>::E : E8 ? (L >= 8 ? 8 : L) : (L >= 16 ? 16 : L);
@@ -212,9 +214,74 @@ __device__ __forceinline__ KSys* block_sys() {
   return (KSys*)(seg + offsetof(Args, sys)) + blockIdx.y;
 }
 
-template <int L, typename R, int MODE, bool SM>
-__global__ __launch_bounds__((ColCfg<L, R, MODE, SM>::NT)) void k_col(ColArgs a, const C2<R>* __restrict__ twtab) {
-  using Cf = ColCfg<L, R, MODE, SM>;
+// Gram-Schmidt work of a small field's first or last pass (GsCarry): a step
+// then is the operator's passes and one update kernel.  On their own, the dots
+// and the check each were a launch of 4 to 7 us that mostly waited for its first
+// loads; here
+//   - the last pass forms the dots with its result while it still holds it: its
+//     groups of wavefronts share the vectors, and the first few each are
+//     loaded before the transform;
+//   - every block of the first pass reduces the check dots for itself while its
+//     column is on the way, and one more block takes the rotations, so that
+//     their serial chain runs beside the transforms.
+// Solves, before -> now (1481 / 15024 us with neither this nor the small kernels):
+// 32^3 FP64 897 -> 747 us, 24 served 2D requests 11.7 -> 11.5 ms.
+struct ColGs {
+  int nv;      // last pass: vectors of the dots; first pass: vectors of the step to finish
+  int nb;      // first pass: blocks that left the check dots
+  double tol, scale;
+  struct Sys {
+    DevState* st;
+    double* partial;
+    const void* V[kMaxVec];
+  } sys[kMaxBatch];
+};
+struct ColGsKernArgs {  // the kernel-argument segment of k_col_gs
+  ColArgs a;
+  const void* tw;
+  ColGs gs;
+};
+typedef __attribute__((address_space(4))) const ColGs KGs;
+__device__ __forceinline__ KGs* kern_gs() {
+  typedef __attribute__((address_space(4))) const char KChar;
+  return (KGs*)((KChar*)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(ColGsKernArgs, gs));
+}
+
+// val[0..K) = the sums of nb <= kFoldBlocks block partials, by all the block's
+// wavefronts (fold_reduce with K and the block size known at run time): up to
+// nine values of a wavefront have their loads in flight together.
+template <int NW>
+__device__ __forceinline__ void fold_sums(const double* partial, int nb, int K, double scale, double* val) {
+  constexpr int PW = 9, Q = kFoldBlocks / 64;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int i0 = w; i0 < K; i0 += NW * PW) {
+    double v[PW];
+#pragma unroll
+    for (int p = 0; p < PW; ++p) {
+      v[p] = 0.0;
+      const int i = i0 + NW * p;
+      if (i < K) {
+        const double* src = partial + (size_t)i * kRedBlocks;
+        double t[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) t[q] = lane + 64 * q < nb ? src[lane + 64 * q] : 0.0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) v[p] += t[q];
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < PW; ++p) {
+      const double t = wave_sum(v[p]);
+      if (lane == 0 && i0 + NW * p < K) val[i0 + NW * p] = t * scale;
+    }
+  }
+}
+
+template <int L, typename R, int MODE, bool SM, bool GS>
+__device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restrict__ twtab) {
+  using Cf = ColCfg<L, R, MODE, SM, GS>;
+  constexpr bool CHECK = GS && MODE == COL_P_FIRST, DOTS = GS && (MODE == COL_P_LAST || MODE == COL_H_LAST);
+  static_assert(!GS || (SM && (CHECK || DOTS)), "Gram-Schmidt work of small fields' first and last passes");
   constexpr int E = Cf::E, T = Cf::T, TC = Cf::TC, NTG = Cf::NTG, NG = Cf::NG, NT = Cf::NT;
   using S = Sched<L, E>;
   constexpr int R0 = S::template first_radix<false>();
@@ -240,12 +307,60 @@ __global__ __launch_bounds__((ColCfg<L, R, MODE, SM>::NT)) void k_col(ColArgs a,
   const int grp = NG > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / NTG) : 0;
   const int tid = NG > 1 ? threadIdx.x - grp * NTG : threadIdx.x;
   const int c = tid % TC, t = tid / TC;
-  const int ob = blockIdx.x / a.ntile, tile = blockIdx.x % a.ntile;
+  // CHECK: the block past the tiles takes the rotations
+  const bool rotations = CHECK && (int)blockIdx.x == a.ntile;
+  const int ob = CHECK ? 0 : blockIdx.x / a.ntile, tile = CHECK ? blockIdx.x : blockIdx.x % a.ntile;
   const int col = tile * TC + c;
-  const bool ok = col < a.inner;
+  const bool ok = col < a.inner && !rotations;
   const size_t base = (size_t)ob * L * a.inner + col;
   LdsCol<R> lds{lds_raw + (NG > 1 ? grp * TC * L : 0), c, TC};
   C2<R> reg[E];
+
+  // DOTS: this group's vectors, i = grp + NG q for q < nq, VB at a time (four
+  // spill where 512 threads share the registers with M v)
+  constexpr int VB = MODE == COL_H_LAST && L == 512 && sizeof(R) == 8 ? 2 : 4;
+  __shared__ double dsum[DOTS ? NT / 64 : 1][DOTS ? kMaxVec / 2 : 1];
+  C2<R> vb[DOTS ? VB : 1][E];
+  KGs* gs = GS ? kern_gs() : nullptr;
+  const int nv = GS ? gs->nv : 0, nq = DOTS ? (nv - grp + NG - 1) / NG : 0;
+  auto load_vectors = [&](int q0) {
+#pragma unroll
+    for (int b = 0; b < VB; ++b)
+      if (q0 + b < nq)
+        col_load<L, E, R1>(vb[DOTS ? b : 0], (const C2<R>*)gs->sys[blockIdx.y].V[grp + NG * (q0 + b)], base, a.inner, t,
+                           ok);
+  };
+  auto dots = [&]() {  // reg: this thread's part of the result, in every group
+    const double w = (col & (a.g.M - 1)) == 0 ? 1.0 : 2.0;  // as spec_w
+    const int wave = threadIdx.x >> 6;
+    for (int q0 = 0; q0 < nq; q0 += VB) {
+      if (q0) load_vectors(q0);
+#pragma unroll
+      for (int b = 0; b < VB; ++b) {
+        if (q0 + b >= nq) continue;
+        double d = 0.0;
+#pragma unroll
+        for (int s = 0; s < E; ++s)
+          d += (double)vb[DOTS ? b : 0][s].x * (double)reg[s].x + (double)vb[DOTS ? b : 0][s].y * (double)reg[s].y;
+        d = wave_sum(w * d);
+        if ((threadIdx.x & 63) == 0) dsum[DOTS ? wave : 0][DOTS ? q0 + b : 0] = d;
+      }
+    }
+    __syncthreads();
+    const int i = threadIdx.x;
+    if (i < nv) {
+      constexpr int WG = NTG / 64 > 0 ? NTG / 64 : 1;  // wavefronts per group
+      double d = 0.0;
+#pragma unroll
+      for (int q = 0; q < WG; ++q) d += dsum[DOTS ? (i % NG) * WG + q : 0][DOTS ? i / NG : 0];
+      gs->sys[blockIdx.y].partial[(size_t)i * kRedBlocks + blockIdx.x] = d;
+    }
+  };
+  if constexpr (DOTS) load_vectors(0);
+  // CHECK: coefficients of the second pass, the scale of the result
+  __shared__ double cval[CHECK ? kMaxVec + 2 : 1], ccl[CHECK ? kMaxVec : 1], cinv;
+  __shared__ int again;
+  double vscale = 1.0;
 
   if constexpr (SM) {
     // every load that does not depend on another one, then the halt flag
@@ -257,21 +372,71 @@ __global__ __launch_bounds__((ColCfg<L, R, MODE, SM>::NT)) void k_col(ColArgs a,
     const void* src = NG == 3 ? (MODE == COL_P_MIDINV ? (grp == 2 ? in1 : in0) : (grp == 0 ? in0 : grp == 1 ? in1 : in2))
                       : MODE == COL_P_LAST && grp == 1 ? in1 : in0;
     col_load<L, E, R0>(reg, (const C2<R>*)src, base, a.inner, t, ok);
+    GsState state{};
+    DevState* st = CHECK ? gs->sys[blockIdx.y].st : nullptr;
+    if (CHECK && threadIdx.x < 64) state = gs_state(st, nv, rotations);
     if (gate && *gate) return;
 #pragma unroll
     for (int i = 0; i < NTW; ++i)
       if (i * NT + (int)threadIdx.x < L) tw_lds[i * NT + threadIdx.x] = twr[i];
+    if constexpr (CHECK) {
+      fold_sums<NT / 64>(gs->sys[blockIdx.y].partial + kFoldHalf, gs->nb, nv + 1, gs->scale, cval);
+      __syncthreads();
+      if (threadIdx.x < 64) {
+        const GsCheck k = gs_check(state, cval, nv, gs->tol);
+        if (rotations) {
+          gs_end(st, state, k, cval, nv);
+        } else {
+          if ((int)threadIdx.x < nv) ccl[threadIdx.x] = k.csel * k.v;
+          if (threadIdx.x == 0) {
+            again = !k.orth;
+            cinv = k.hn > 0.0 ? 1.0 / k.hn : 0.0;
+          }
+        }
+      }
+      if (rotations) return;
+    }
   } else {
     for (int i = threadIdx.x; i < L; i += blockDim.x) tw_lds[i] = twtab[L + i];
   }
   __syncthreads();
   const C2<R>* tw = tw_lds;
+  // CHECK: the second pass on this tile.  Both groups hold the column and form
+  // the same values; group 0 writes them back after its transform, when both
+  // have consumed their loads (a block that sees the halt flag of the rotations
+  // leaves the vector as it is: the vector that ends a cycle is never read).
+  C2<R> kept[CHECK ? E : 1];
+  if constexpr (CHECK) {
+    static_assert(S::npass > 1, "a barrier between the loads and the stores");
+    vscale = cinv;
+    if (again) {
+      double xr[E], xi[E];
+#pragma unroll
+      for (int s = 0; s < E; ++s) {
+        xr[s] = reg[s].x;
+        xi[s] = reg[s].y;
+      }
+      for (int i = 0; i < nv; ++i) {
+        const double ci = ccl[i];
+        if (ci == 0.0) continue;
+        C2<R> v[E];
+        col_load<L, E, R0>(v, (const C2<R>*)gs->sys[blockIdx.y].V[i], base, a.inner, t, ok);
+#pragma unroll
+        for (int s = 0; s < E; ++s) {
+          xr[s] -= ci * (double)v[s].x;
+          xi[s] -= ci * (double)v[s].y;
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < E; ++s) kept[s] = reg[s] = C2<R>{R(xr[s]), R(xi[s])};
+    }
+  }
 
-  if constexpr (SM && NG > 1) {
+  if constexpr (SM && NG > 1 && MODE != COL_H_LAST) {
     // one transform per group; every group meets the same barriers
     if constexpr (MODE == COL_P_FIRST) {
       const int ky = col / a.g.M, kx = col % a.g.M;
-      const R sc = in_scale_of<R>(iscale);
+      const R sc = CHECK ? R(vscale) : in_scale_of<R>(iscale);
 #pragma unroll
       for (int s = 0; s < E; ++s) {
         const int kz = pat_index<L, E, R0>(t, s);
@@ -281,6 +446,9 @@ __global__ __launch_bounds__((ColCfg<L, R, MODE, SM>::NT)) void k_col(ColArgs a,
       }
       fft_line<L, E, +1, false>(reg, lds, tw, t);
       col_store<L, E, R1>(reg, (C2<R>*)(grp ? out1 : out0), base, a.inner, t, ok);
+      if constexpr (CHECK) {
+        if (again && grp == 0) col_store<L, E, R0>(kept, (C2<R>*)in0, base, a.inner, t, ok);
+      }
     } else if constexpr (MODE == COL_P_MIDINV) {
       // in place (out0 = in0, out2 = in1): both readers of in0 have consumed
       // their loads before the first exchange's barrier
@@ -314,6 +482,19 @@ __global__ __launch_bounds__((ColCfg<L, R, MODE, SM>::NT)) void k_col(ColArgs a,
         col_store<L, E, R1>(reg, (C2<R>*)out0, base, a.inner, t, ok);
       } else if (!LAST && grp == 2) {
         col_store<L, E, R1>(reg, (C2<R>*)out1, base, a.inner, t, ok);
+      }
+      if constexpr (DOTS) {  // the result to the other group through group 0's tile
+        const LdsCol<R> mine{lds_raw, c, TC};
+        if (grp == 0) {
+#pragma unroll
+          for (int s = 0; s < E; ++s) mine.st(pat_index<L, E, R1>(t, s), reg[s]);
+        }
+        __syncthreads();
+        if (grp != 0) {
+#pragma unroll
+          for (int s = 0; s < E; ++s) reg[s] = mine.ld(pat_index<L, E, R1>(t, s));
+        }
+        dots();
       }
     }
     return;
@@ -378,6 +559,19 @@ __global__ __launch_bounds__((ColCfg<L, R, MODE, SM>::NT)) void k_col(ColArgs a,
       col_store<L, E, R1>(reg, (C2<R>*)out1, base, a.inner, t, ok);
     }
   } else if constexpr (MODE == COL_H_FIRST || MODE == COL_H_LAST) {
+    if constexpr (DOTS) {
+      if (grp != 0) {  // the second group meets the transform's barriers and takes its part of the dots
+#pragma unroll
+        for (int i = 0; i < 2 * (S::npass - 1); ++i) __syncthreads();
+        __syncthreads();
+        __syncthreads();
+        const LdsCol<R> res{lds_raw, c, TC};
+#pragma unroll
+        for (int s = 0; s < E; ++s) reg[s] = res.ld(pat_index<L, E, R1>(t, s));
+        dots();
+        return;
+      }
+    }
     constexpr bool FIRST = MODE == COL_H_FIRST;
     constexpr int RP = FIRST ? R0 : R1;  // pattern in which v is needed
     const int ky = col / a.g.M, kx = col % a.g.M;
@@ -426,8 +620,26 @@ __global__ __launch_bounds__((ColCfg<L, R, MODE, SM>::NT)) void k_col(ColArgs a,
 #pragma unroll
       for (int s = 0; s < E; ++s) reg[s] = reg[s] + mv[s];
       col_store<L, E, R1>(reg, (C2<R>*)out0, base, a.inner, t, ok);
+      if constexpr (DOTS) {
+        __syncthreads();  // the tile's last exchange has been read
+#pragma unroll
+        for (int s = 0; s < E; ++s) lds.st(pat_index<L, E, R1>(t, s), reg[s]);
+        __syncthreads();
+        dots();
+      }
     }
   }
+}
+
+template <int L, typename R, int MODE, bool SM>
+__global__ __launch_bounds__((ColCfg<L, R, MODE, SM>::NT)) void k_col(ColArgs a, const C2<R>* __restrict__ twtab) {
+  col_pass<L, R, MODE, SM, false>(a, twtab);
+}
+template <int L, typename R, int MODE>
+__global__ __launch_bounds__((ColCfg<L, R, MODE, true, true>::NT)) void k_col_gs(ColArgs a,
+                                                                               const C2<R>* __restrict__ twtab,
+                                                                               ColGs) {
+  col_pass<L, R, MODE, true, true>(a, twtab);
 }
 
 // --------------------------------------------------------- row kernels
@@ -817,6 +1029,62 @@ static void launch_col_L(const ColArgs& a, const void* tw, hipStream_t st) {
   launch_col_S<R, MODE, L, false>(a, tw, st);
 }
 
+// Lengths whose first and last pass carry Gram-Schmidt work (a 1024-point tile
+// already fills a block's registers).
+constexpr int kGsLength = 512;
+bool op_carries_gs(const Geom& g, int kind) {
+  (void)kind;
+  return small_field(g) && !g.cheb && g.nz > 1 && g.nz <= kGsLength;
+}
+// the Helmholtz passes read mirror elements of their input, which another block's second pass may be writing
+bool op_carries_check(const Geom& g, int kind) { return kind == OP_PRESSURE && op_carries_gs(g, kind); }
+
+template <typename F>
+static void for_gs_length(int L, F&& f) {
+  switch (L) {
+    case 16: f(std::integral_constant<int, 16>{}); break;
+    case 32: f(std::integral_constant<int, 32>{}); break;
+    case 64: f(std::integral_constant<int, 64>{}); break;
+    case 128: f(std::integral_constant<int, 128>{}); break;
+    case 256: f(std::integral_constant<int, 256>{}); break;
+    case 512: f(std::integral_constant<int, 512>{}); break;
+    default: fprintf(stderr, "vdsolve: unsupported column length %d\n", L);
+  }
+}
+int op_dot_blocks(const Geom& g) {
+  int n = 0;
+  for_gs_length(g.nz, [&](auto len) {
+    constexpr int TC = ColSmall<decltype(len)::value>::TC;
+    n = (g.ny * g.M + TC - 1) / TC;
+  });
+  return n;
+}
+
+// A first (CHECK) or last pass with the Gram-Schmidt work of c.
+template <typename R, int MODE>
+static void launch_col_gs(int len, const ColArgs& a0, const GsCarry& c, const void* tw, hipStream_t st) {
+  constexpr bool CHECK = MODE == COL_P_FIRST;
+  ColArgs a = a0;
+  as_systems(a);
+  ColGs gs{};
+  gs.nv = CHECK ? c.nv - 1 : c.nv;
+  gs.nb = c.check_blocks;
+  gs.tol = orth_tol<R>();
+  gs.scale = a.g.ntot_inv;
+  for (int k = 0; k < a.nb; ++k) {
+    gs.sys[k].st = c.st[k];
+    gs.sys[k].partial = c.partial[k];
+    for (int i = 0; i < gs.nv; ++i) gs.sys[k].V[i] = c.V[k].p[i];
+  }
+  for_gs_length(len, [&](auto l) {
+    constexpr int L = decltype(l)::value;
+    using Cf = ColCfg<L, R, MODE, true, true>;
+    a.ntile = (a.inner + Cf::TC - 1) / Cf::TC;
+    hipLaunchKernelGGL((k_col_gs<L, R, MODE>), dim3(a.ntile + (CHECK ? 1 : 0), a.nb), dim3(Cf::NT), 0, st, a,
+                       (const C2<R>*)tw, gs);
+  });
+}
+
 template <typename R, int MODE>
 static void launch_col(int L, const ColArgs& a, const void* tw, hipStream_t st) {
   switch (L) {
@@ -829,6 +1097,17 @@ static void launch_col(int L, const ColArgs& a, const void* tw, hipStream_t st) 
     case 1024: launch_col_L<R, MODE, 1024>(a, tw, st); break;
     default: fprintf(stderr, "vdsolve: unsupported column length %d\n", L);
   }
+}
+
+template <typename R>
+static void first_pass(const Geom& g, const ColArgs& a, const GsCarry* gs, const void* tw, hipStream_t st) {
+  if (gs && gs->check) launch_col_gs<R, COL_P_FIRST>(g.nz, a, *gs, tw, st);
+  else launch_col<R, COL_P_FIRST>(g.nz, a, tw, st);
+}
+template <typename R, int MODE>
+static void last_pass(const Geom& g, const ColArgs& a, const GsCarry* gs, const void* tw, hipStream_t st) {
+  if (gs) launch_col_gs<R, MODE>(g.nz, a, *gs, tw, st);
+  else launch_col<R, MODE>(g.nz, a, tw, st);
 }
 
 // Blocks of a looping row pass (eight per CU on 256 CUs), per system.
@@ -939,7 +1218,7 @@ void op_apply(const Geom& g, const OpParams& p, const void* v, void* y, const Op
     a.in[0] = v;
     a.out[0] = t0;
     a.out[1] = t1;
-    VD_T0(0) launch_col<R, COL_P_FIRST>(g.nz, a, twtab, st); VD_T1()
+    VD_T0(0) first_pass<R>(g, a, p.gs, twtab, st); VD_T1()
     RowArgs r = row_args(g, &p);
     r.coef = coef;
     r.cscale = g.ntot_inv;
@@ -975,7 +1254,7 @@ void op_apply(const Geom& g, const OpParams& p, const void* v, void* y, const Op
     d.in[0] = t0;
     d.in[1] = t1;
     d.out[0] = y;
-    VD_T0(4) launch_col<R, COL_P_LAST>(g.nz, d, twtab, st); VD_T1()
+    VD_T0(4) last_pass<R, COL_P_LAST>(g, d, p.gs, twtab, st); VD_T1()
   } else {
     if (g.nz == 1) {
       RowArgs r = row_args(g, &p);
@@ -1023,7 +1302,7 @@ void op_apply(const Geom& g, const OpParams& p, const void* v, void* y, const Op
     d.in[0] = t0;
     d.in[1] = v;
     d.out[0] = y;
-    VD_T0(9) launch_col<R, COL_H_LAST>(g.nz, d, twtab, st); VD_T1()
+    VD_T0(9) last_pass<R, COL_H_LAST>(g, d, p.gs, twtab, st); VD_T1()
   }
 #undef VD_T0
 #undef VD_T1
@@ -1089,7 +1368,7 @@ void op_apply_batch(const Geom& g, const OpParams& p, const OpBatch& b, const vo
     d.outer = 1;
     d.inner = (int)zin;
     for (int k = 0; k < nb; ++k) d.sys[k] = sys_of(k, {b.t[k][0], b.v[k]}, {b.y[k]}, true);
-    timed(9, 3.0 * nb, [&] { launch_col<R, COL_H_LAST>(g.nz, d, twtab, st); });
+    timed(9, 3.0 * nb, [&] { last_pass<R, COL_H_LAST>(g, d, p.gs, twtab, st); });
     return;
   }
   // pressure (2D and 3D grids): the passes of op_apply, system k on
@@ -1098,7 +1377,7 @@ void op_apply_batch(const Geom& g, const OpParams& p, const OpBatch& b, const vo
   a.outer = 1;
   a.inner = (int)zin;
   for (int k = 0; k < nb; ++k) a.sys[k] = sys_of(k, {b.v[k]}, {b.t[k][0], b.t[k][1]}, true);
-  timed(0, 3.0 * nb, [&] { launch_col<R, COL_P_FIRST>(g.nz, a, twtab, st); });
+  timed(0, 3.0 * nb, [&] { first_pass<R>(g, a, p.gs, twtab, st); });
   RowArgs r = row_args(g, &p);
   r.gate = nullptr;
   r.in_scale = nullptr;
@@ -1131,7 +1410,7 @@ void op_apply_batch(const Geom& g, const OpParams& p, const OpBatch& b, const vo
   d.outer = 1;
   d.inner = (int)zin;
   for (int k = 0; k < nb; ++k) d.sys[k] = sys_of(k, {b.t[k][0], b.t[k][1]}, {b.y[k]}, false);
-  timed(4, 3.0 * nb, [&] { launch_col<R, COL_P_LAST>(g.nz, d, twtab, st); });
+  timed(4, 3.0 * nb, [&] { last_pass<R, COL_P_LAST>(g, d, p.gs, twtab, st); });
 }
 
 template <typename R>

@@ -19,11 +19,31 @@ struct Geom {
   int cheb;             // z is a Chebyshev-Gauss-Lobatto axis (2D, ny = 1): x transforms only
 };
 
-enum OpKind { OP_PRESSURE = 0, OP_HELMHOLTZ = 1 };
-
 // Independent systems solved together in one set of launches (the
 // components of a velocity solve).
 constexpr int kMaxBatch = 3;
+constexpr int kMaxVec = 34;  // Krylov vectors per multi-dot / multi-update
+struct VecPtrs {
+  const void* p[kMaxVec];
+};
+struct DevState;
+
+enum OpKind { OP_PRESSURE = 0, OP_HELMHOLTZ = 1 };
+
+// Parts of a GMRES step that the operator's passes carry on small fields
+// (op_carries_gs), system k of a launch with its own state and partials.  The
+// last pass forms the dots of its result with V[k][0..nv).  With check, the first
+// pass takes the orthogonality check, the second pass and the rotations of the
+// step before, whose result is the input v = V[k][nv - 1] and whose
+// check dots came from check_blocks blocks, and scales its input by the new norm.
+struct GsCarry {
+  int nv = 0;
+  bool check = false;
+  int check_blocks = 0;
+  DevState* st[kMaxBatch] = {};
+  double* partial[kMaxBatch] = {};
+  VecPtrs V[kMaxBatch] = {};
+};
 
 struct OpParams {
   int kind;                  // OpKind
@@ -32,6 +52,7 @@ struct OpParams {
   int precond;               // apply the constant-density inverse to the input first
   const double* in_scale;    // optional device scalar multiplying the input
   const int* gate = nullptr; // optional device flag: when nonzero every pass returns at once
+  const GsCarry* gs = nullptr;  // optional Gram-Schmidt work of the passes (gate: the states' halt flags)
 };
 
 // Work buffers of one operator application (spectral, same precision as the
@@ -69,6 +90,13 @@ struct Prof {
   void drop();
   void release();
 };
+
+// Whether the passes of this grid's operator carry the dots of a step, whether
+// they also take the check of the step before, and the number of blocks whose
+// partials the dots leave.
+bool op_carries_gs(const Geom& g, int kind);
+bool op_carries_check(const Geom& g, int kind);
+int op_dot_blocks(const Geom& g);
 
 // y = A (M^-1 (s v)) in spectral space.  R = float or double.
 template <typename R>

@@ -302,6 +302,21 @@ struct SolveOut {
   int reorth = 0;
 };
 
+// The Gram-Schmidt work that the operator passes of step j carry (states,
+// partials and vectors left to the caller), and what is left to the vector kernels.
+// A profile that times the dots gets them as a launch of their own.
+bool carries_gs(const vd_grid* G, const Geom& g, int kind) {
+  return op_carries_gs(g, kind) && !(G->prof.on && ((G->prof.mask >> 10) & 1u));
+}
+GsCarry carry_of(const Geom& g, int j, bool check) {
+  GsCarry c;
+  c.nv = j + 1;
+  c.check = check && j > 0;
+  c.check_blocks = gs_update_blocks(g);
+  return c;
+}
+GsParts parts_of(const Geom& g, bool last, bool check) { return GsParts{op_dot_blocks(g), last || !check}; }
+
 template <typename R>
 struct Krylov {
   vd_grid* G;
@@ -334,8 +349,10 @@ struct Krylov {
     }
   }
 
-  void apply(const void* v, void* y, bool with_prec, const double* in_scale = nullptr, const int* gate = nullptr) {
+  void apply(const void* v, void* y, bool with_prec, const double* in_scale = nullptr, const int* gate = nullptr,
+             const GsCarry* gs = nullptr) {
     OpParams p = cfg.op;
+    p.gs = gs;
     p.precond = with_prec ? cfg.op.precond : 0;
     p.in_scale = in_scale;
     p.gate = gate;
@@ -394,12 +411,26 @@ struct Krylov {
   }
 
   // Arnoldi step j: V[j+1] = A M^-1 v_j, Gram-Schmidt against V[0..j] and
-  // the Givens rotations of column j.  gate: the device halt flag, or none.
-  void arnoldi_step(const std::vector<void*>& V, int j, const int* gate) {
-    apply(V[j], V[j + 1], true, &G->dst->vs[j], gate);
+  // the Givens rotations of column j.  gate: the device halt flag.  On small
+  // fields the operator's last pass forms the dots and, where another step
+  // follows (not last), the first pass of that step takes the check and the
+  // rotations (step j's state is then posted by step j + 1's first launch).
+  void arnoldi_step(const std::vector<void*>& V, int j, bool last, const int* gate) {
     VecPtrs P{};
     for (int i = 0; i <= j; ++i) P.p[i] = V[i];
-    gs_orthogonalize<R>(g, V[j + 1], P, j + 1, G->dst, G->partial, G->st, &G->prof);
+    GsParts parts;
+    GsCarry c;
+    const bool carry = carries_gs(G, g, cfg.op.kind);
+    if (carry) {
+      const bool check = op_carries_check(g, cfg.op.kind);
+      c = carry_of(g, j, check);
+      c.st[0] = G->dst;
+      c.partial[0] = G->partial;
+      c.V[0] = P;
+      parts = parts_of(g, last, check);
+    }
+    apply(V[j], V[j + 1], true, &G->dst->vs[j], gate, carry ? &c : nullptr);
+    gs_orthogonalize<R>(g, V[j + 1], P, j + 1, G->dst, G->partial, G->st, &G->prof, parts);
   }
   SolveOut gmres(const void* b, void* x, double bnorm) {
     SolveOut o;
@@ -427,7 +458,7 @@ struct Krylov {
       gmres_init(G->dst, beta, m, bnorm, cfg.rtol, jlast, run, G->st);  // v_0 = V[0] / beta via the scale vs[0]
       // the step count k of this cycle: its basis size for the back-solve
       StepState t;
-      const int k = run_queued(jlast, run, t, bnorm, [&](int j, const int* gate) { arnoldi_step(V, j, gate); });
+      const int k = run_queued(jlast, run, t, bnorm, [&](int j, const int* gate) { arnoldi_step(V, j, j == jlast, gate); });
       o.iters += k;
       o.reorth += t.nreorth;
       if (t.bad) { o.status = VD_EBREAKDOWN; return o; }
@@ -769,8 +800,9 @@ struct KrylovBatch {
   // y_q = A M^-1 v_q (with_prec) or A v_q for the systems sys[0..ob.nb) of
   // ob (v, y, in_scale and gate filled in), each with its own work fields,
   // coefficients and preconditioner constant
-  void apply_set(OpBatch& ob, const int* sys, bool with_prec) {
+  void apply_set(OpBatch& ob, const int* sys, bool with_prec, const GsCarry* gs = nullptr) {
     OpParams p = cfg.op;
+    p.gs = gs;
     p.precond = with_prec ? cfg.op.precond : 0;
     for (int q = 0; q < ob.nb; ++q) {
       const int k = sys[q];
@@ -788,6 +820,14 @@ struct KrylovBatch {
       pq.rho0 = ob.rho0[q];
       pq.in_scale = ob.in_scale[q];
       pq.gate = ob.gate[q];
+      GsCarry one;
+      if (gs) {
+        one = *gs;
+        one.st[0] = gs->st[q];
+        one.partial[0] = gs->partial[q];
+        one.V[0] = gs->V[q];
+        pq.gs = &one;
+      }
       OpWork w{};
       for (int i = 0; i < 3; ++i) w.t[i] = ob.t[q][i];
       op_apply<R>(g, pq, ob.v[q], ob.y[q], w, ob.coef[q], tw, G->st, &G->prof);
@@ -818,8 +858,8 @@ struct KrylovBatch {
     if (G->prof.on) G->prof.flush();
   }
 
-  // Arnoldi step j of the systems sys[0..ns)
-  void step(int j, const int* sys, int ns) {
+  // Arnoldi step j of the systems sys[0..ns) (last: as Krylov::arnoldi_step)
+  void step(int j, bool last, const int* sys, int ns) {
     OpBatch ob{};
     ob.nb = ns;
     void* w[kMaxBatch];
@@ -838,8 +878,21 @@ struct KrylovBatch {
       ds[q] = dst[k];
       ps[q] = part[k];
     }
-    apply_set(ob, sys, true);
-    gs_orthogonalize_batch<R>(g, w, V, j + 1, ds, ps, ns, G->st, &G->prof);
+    GsParts parts;
+    GsCarry c;
+    const bool carry = carries_gs(G, g, cfg.op.kind);
+    if (carry) {
+      const bool check = op_carries_check(g, cfg.op.kind);
+      c = carry_of(g, j, check);
+      for (int q = 0; q < ns; ++q) {
+        c.st[q] = ds[q];
+        c.partial[q] = ps[q];
+        c.V[q] = V[q];
+      }
+      parts = parts_of(g, last, check);
+    }
+    apply_set(ob, sys, true, carry ? &c : nullptr);
+    gs_orthogonalize_batch<R>(g, w, V, j + 1, ds, ps, ns, G->st, &G->prof, parts);
   }
   // Steps 0..jlast of a cycle of the systems sys[0..ns), queued one step ahead
   // of the host like Krylov::run_queued; each system stops at its own halt
@@ -849,12 +902,12 @@ struct KrylovBatch {
                   std::vector<double>* hist, double hist_bnorm) {
     Prof& pf = G->prof;
     if (pf.on) pf.flush();
-    step(0, sys, ns);
+    step(0, jlast == 0, sys, ns);
     size_t mark = pf.pending.size();
     bool stopped[kMaxBatch] = {};
     int nstop = 0;
     for (int j = 0; j <= jlast; ++j) {
-      if (j < jlast) step(j + 1, sys, ns);
+      if (j < jlast) step(j + 1, j + 1 == jlast, sys, ns);
       for (int q = 0; q < ns; ++q) {
         if (stopped[q]) continue;
         const StepState tt = end[q] = next_step(mail[sys[q]], j, run[q], G->st);

@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
+#include "gs_device.hpp"
 #include "spectral.hpp"
 #include "vecops.hpp"
 
@@ -24,30 +25,6 @@ size_t nred_partial() { return (size_t)kRedBlocks * kRedStride; }
 static int nblk(size_t n) {
   size_t b = (n + 1023) / 1024;
   return (int)(b < 1 ? 1 : (b > (size_t)kRedBlocks ? kRedBlocks : b));
-}
-
-// v plus the value that the DPP pattern CTRL brings to this lane (0 where it
-// brings none, and in the rows that ROWS leaves out)
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double add_dpp(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, true);
-  return v + __hiloint2double(hi, lo);
-}
-// Sum over the wavefront (all 64 lanes active), returned in every lane: row
-// shifts by 1, 2, 4, 8 leave each 16-lane row's sum in its last lane, two row
-// broadcasts carry them to lane 63.  A fixed tree on the vector ALU: the same
-// tree through LDS permutes costs two LDS round trips per step, which the
-// latency-bound reductions of small fields feel.
-__device__ __forceinline__ double wave_sum(double v) {
-  v = add_dpp<0x111, 0xf>(v);  // row_shr:1
-  v = add_dpp<0x112, 0xf>(v);  // row_shr:2
-  v = add_dpp<0x114, 0xf>(v);  // row_shr:4
-  v = add_dpp<0x118, 0xf>(v);  // row_shr:8
-  v = add_dpp<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
-  v = add_dpp<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
-                          __builtin_amdgcn_readlane(__double2loint(v), 63));
 }
 
 // Reduce acc[0..K) across a 256-thread block; value i of block b goes to
@@ -101,22 +78,6 @@ __device__ __forceinline__ void reduce_values(const double* __restrict__ partial
     const double v = sum_partials(partial + (size_t)i * kRedBlocks, nblk);
     if (lane == 0) out[i] = v * scale;
   }
-}
-
-// Values to the host (one thread).  The release orders them, and everything
-// else this thread has written, before seq for any observer of the system.
-__device__ __forceinline__ void post_mail(Mail* m, double a, double b, unsigned long long flags,
-                                          unsigned long long seq) {
-  __hip_atomic_store(&m->v[0], a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  __hip_atomic_store(&m->v[1], b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  __hip_atomic_store(&m->flags, flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  __hip_atomic_store(&m->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-// The state after step j of a cycle or run (bad and halt as just decided).
-__device__ __forceinline__ void post_step(DevState* st, int j, double resid, double nrm2, bool bad, bool halt,
-                                          int nreorth) {
-  post_mail(st->mail + MAIL_STEP + (j & 1), resid, nrm2,
-            (bad ? 1ull : 0ull) | (halt ? 2ull : 0ull) | ((unsigned long long)nreorth << 2), st->run + j + 1);
 }
 
 // Scalar steps of CG and RMR, taken by one thread on the reduced values
@@ -299,29 +260,6 @@ void mdot(const Geom& g, const void* x, const VecPtrs& V, int nv, bool want_norm
 //           because |c| << ||w'||.  It reads only the vectors in S.
 // Pass 3 exits at once when not needed, so the common step costs two
 // passes over the basis.
-//
-// Choice of tol: the Arnoldi relation A V_j = V_{j+1} H_j holds to rounding
-// whatever the orthogonality, so the computed least-squares residual
-// |beta e1 - H y| differs from the true one |V_{j+1}(beta e1 - H y)| only by
-// the factor |V_{j+1}| <= sqrt(1 + (j+1) delta), delta the largest cosine
-// between basis vectors.  Orthogonality must therefore stay far from 1
-// (else the basis degenerates and convergence stalls), not below the solve
-// tolerance.  tol = 1e-8 (FP64) keeps that factor within 2e-7 of 1 for 32
-// vectors; 1e-4 (FP32 inner solves, target 1e-5) within 0.2%.  A tighter
-// tol only makes the second pass fire whenever the operator is close to the
-// identity (velocity solves), where |w'| << |w| magnifies the rounding of the
-// first-pass dots.
-template <typename R>
-constexpr double orth_tol() { return sizeof(R) == 8 ? 1e-8 : 1e-4; }
-
-// leading dimension of the column-major Hessenberg matrix
-__device__ __forceinline__ int ldh() { return kMaxRestart + 1; }
-
-__device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-  return v;
-}
 
 // The scalar steps below run in the block that finishes the cross-block
 // reduction of the pass before them (one launch instead of two).  Reduced
@@ -344,112 +282,19 @@ __global__ __launch_bounds__(1024) void k_gs_prep(DevStates S, int nv, int nb, d
   }
 }
 
-// Orthogonality check of the first pass, taken by one wavefront with lane i on
-// basis vector i (val: the reduced dots (V_i, w') and, at nv, ||w'||^2).
-struct GsCheck {
-  double h, v;   // this lane's first-pass coefficient and vector scale
-  double csel;   // its second-pass coefficient (0: the vector passed the test)
-  double hn;     // norm of the orthogonalised vector
-  bool orth;     // no second pass needed
-  bool finite;
-};
-__device__ __forceinline__ GsCheck gs_check(const DevState* st, const double* val, int nv, double tol) {
-  const int lane = threadIdx.x & 63;
-  GsCheck k;
-  double c = 0.0;
-  k.h = k.v = 0.0;
-  if (lane < nv) {
-    k.v = st->vs[lane];
-    k.h = st->hcol[lane];
-    c = k.v * val[lane];
-  }
-  const double n2 = val[nv];
-  const double thr = tol * sqrt(n2);
-  k.orth = n2 > 0.0 && wave_max(fabs(c)) <= thr;
-  // The second pass subtracts only the components that fail the test: the
-  // others already meet the tolerance accepted when no second pass runs.
-  // (n2 <= 0 selects every nonzero component.)
-  k.csel = (!k.orth && lane < nv && !(fabs(c) <= thr)) ? c : 0.0;
-  const double h2 = n2 - wave_sum(k.csel * k.csel);
-  // wave_max drops NaN, and a NaN norm would read as a lucky breakdown
-  k.finite = isfinite(n2) && isfinite(wave_sum(c * c));
-  k.hn = k.orth ? sqrt(n2) : (h2 > 0.0 ? sqrt(h2) : 0.0);
-  return k;
-}
-
-// The Givens rotations of GMRES on the new Hessenberg column j = nv - 1 (the
-// second pass, if any, changes only w, not H) and the stopping test of the
-// host loop, taken here so that the next step, when already queued, exits at
-// its gates.  One full wavefront; hc, csl, snl: its LDS scratch.
-__device__ __forceinline__ void gs_givens(DevState* st, const GsCheck& k, int nv, double* hc, double* csl,
-                                          double* snl) {
-  const int lane = threadIdx.x & 63, j = nv - 1;
-  if (lane < j) {
-    csl[lane] = st->cs[lane];
-    snl[lane] = st->sn[lane];
-  }
-  if (lane < nv) hc[lane] = k.h + k.csel;  // Hessenberg column before rotation
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  if (lane != 0) return;
-  const double hn = k.hn;
-  const int nreorth = st->nreorth + (k.orth ? 0 : 1);
-  st->reorth = k.orth ? 0 : 1;
-  st->nreorth = nreorth;
-  st->hn = hn;
-  st->vs[nv] = hn > 0.0 ? 1.0 / hn : 0.0;
-  // previous rotations, in order, then the new one
-  double* H = st->H;
-  const int ld = ldh();
-  double a = hc[0];
-  for (int i = 0; i < j; ++i) {
-    const double b = hc[i + 1];
-    H[i + j * ld] = csl[i] * a + snl[i] * b;
-    a = -snl[i] * a + csl[i] * b;
-  }
-  const double rr = hypot(a, hn);
-  double cr = 1.0, sr = 0.0;
-  if (rr > 0.0) {
-    cr = a / rr;
-    sr = hn / rr;
-  }
-  st->cs[j] = cr;
-  st->sn[j] = sr;
-  H[j + j * ld] = rr;
-  H[j + 1 + j * ld] = 0.0;
-  const double gj = st->g[j];
-  st->g[j + 1] = -sr * gj;
-  st->g[j] = cr * gj;
-  const double resid = fabs(sr * gj);
-  st->resid = resid;
-  const bool bad = st->bad || !k.finite || !isfinite(rr) || !isfinite(sr * gj);
-  const bool halt = bad || resid / st->stop_bnorm <= st->stop_rtol || j >= st->jlast;
-  if (bad) st->bad = 1;
-  if (halt) st->halt = 1;
-  post_step(st, j, resid, 0.0, bad, halt, nreorth);
-}
-
 __global__ __launch_bounds__(1024) void k_gs_check(DevStates S, int nv, double tol, int nb, double scale) {
   DevState* st = S.st[blockIdx.y];
   const double* __restrict__ partial = S.partial[blockIdx.y];
   __shared__ double val[kMaxVec + 2];
-  __shared__ double hc[kMaxVec + 1], csl[kMaxRestart], snl[kMaxRestart];
   if (st->halt) {  // a step queued past the end of the cycle: no second pass either
     if (threadIdx.x == 0) st->reorth = 0;
     return;
   }
+  const GsState gs = gs_state(st, nv, true);
   reduce_values(partial, nb, nv + 1, scale, val);
   __syncthreads();
   if (threadIdx.x >= 64) return;  // one wavefront from here on
-  const int lane = threadIdx.x;
-  const GsCheck k = gs_check(st, val, nv, tol);
-  if (lane <= nv) st->red[lane] = val[lane];
-  if (lane < nv) {
-    st->ccol[lane] = k.csel;
-    st->coef[lane] = k.csel * k.v;
-  }
-  gs_givens(st, k, nv, hc, csl, snl);
+  gs_end(st, gs, gs_check(gs, val, nv, tol), val, nv);
 }
 
 template <typename R, int NV>
@@ -546,16 +391,15 @@ __global__ __launch_bounds__(256) void k_gs_reorth(SysSet<R> S, int nv, size_t n
 // with the second pass inside k_gs_finish (block 0 writes the state).  Larger
 // fields keep the kernels above: they are bound by the basis stream, and their
 // up to 1024 partials per value are too many to reduce in every block.
-// The dots and the check dots alternate between two halves of each partial
-// row, because blocks of one launch read the first while others write the second.
+// Of an FP64 or FP32 pressure step on a Fourier grid only the update is left here:
+// the operator's last pass forms the dots and the next step's first pass takes
+// the check (op_carries_gs).  The dots and the check dots alternate between two
+// halves of each partial row, because blocks of one launch read the first while others write the second.
 // Measured per launch, before -> now (rocprofv3, median over a solve):
 //   32^3 FP64, 9-16 vectors: dots 14.6 -> 4.3 us, update with k_gs_prep 12.2 +
 //     3.8 -> 5.7 us, check with second pass 4.6 + 1.7 -> 6.1 us;
 //   101 x 64 slots FP32, 5-8 vectors: 9.1 -> 3.8, 7.6 + 1.8 -> 5.0 and
 //     3.9 + 1.8 -> 4.6 us.
-constexpr size_t kFoldElems = 131072;
-constexpr int kFoldBlocks = 256;
-constexpr int kFoldHalf = kRedBlocks / 2;
 static bool folds(size_t n) { return n <= kFoldElems; }
 static int fold_blocks(size_t n) { return (int)std::min<size_t>((n + 255) / 256, kFoldBlocks); }
 
@@ -639,7 +483,7 @@ __global__ __launch_bounds__(256 * H) void k_mdot_s(SysSet<R> S, int nv, size_t 
 // w' = w - sum_i h_i v_i with its check dots; the dots of k_mdot_s are reduced
 // here.  Every split forms its part of the sum; they meet in LDS.
 template <typename R, int NVH, int H>
-__global__ __launch_bounds__(256 * H) void k_gs_update_s(SysSet<R> S, int nv, size_t n, int M, double scale) {
+__global__ __launch_bounds__(256 * H) void k_gs_update_s(SysSet<R> S, int nv, size_t n, int M, double scale, int nbd) {
   const int sy = blockIdx.y;
   DevState* st = S.st[sy];
   if (st->halt) return;
@@ -663,7 +507,7 @@ __global__ __launch_bounds__(256 * H) void k_gs_update_s(SysSet<R> S, int nv, si
       if (i < nvh) vv[i] = ldg((const C2<R>*)V[i] + e);
   };
   load(b0 + te);  // the first elements' loads overlap the reduction
-  fold_reduce<NVH * H, 4 * H>(partial, gridDim.x, nv, scale, val);
+  fold_reduce<NVH * H, 4 * H>(partial, nbd, nv, scale, val);  // nbd blocks formed the dots
   if ((int)threadIdx.x < NVH * H) {
     const int i = threadIdx.x;
     double c = 0.0;
@@ -723,13 +567,14 @@ __global__ __launch_bounds__(256) void k_gs_finish(SysSet<R> S, int nv, size_t n
   const int sy = blockIdx.y;
   DevState* st = S.st[sy];
   __shared__ double val[NV + 1], cl[NV];
-  __shared__ double hc[kMaxVec + 1], csl[kMaxRestart], snl[kMaxRestart];
   __shared__ int again;
   if (st->halt) return;
+  GsState gs{};
+  if (threadIdx.x < 64) gs = gs_state(st, nv, blockIdx.x == 0);
   fold_reduce<NV + 1, 4>(S.partial[sy] + kFoldHalf, gridDim.x, nv + 1, scale, val);
   GsCheck k{};
   if (threadIdx.x < 64) {
-    k = gs_check(st, val, nv, tol);
+    k = gs_check(gs, val, nv, tol);
     if ((int)threadIdx.x < nv) cl[threadIdx.x] = k.csel * k.v;
     if (threadIdx.x == 0) again = !k.orth;
   }
@@ -751,31 +596,30 @@ __global__ __launch_bounds__(256) void k_gs_finish(SysSet<R> S, int nv, size_t n
       stg(x + e, C2<R>{R(xr), R(xi)});
     }
   }
-  if (blockIdx.x != 0 || threadIdx.x >= 64) return;
-  const int lane = threadIdx.x;
-  if (lane <= nv) st->red[lane] = val[lane];
-  if (lane < nv) {
-    st->ccol[lane] = k.csel;
-    st->coef[lane] = k.csel * k.v;
-  }
-  gs_givens(st, k, nv, hc, csl, snl);
+  if (blockIdx.x == 0 && threadIdx.x < 64) gs_end(st, gs, k, val, nv);
 }
 
 template <typename R, int NVH, int H>
-static void launch_gs_small(const Geom& g, const SysSet<R>& S, int nsys, int nv, hipStream_t s, Prof* prof) {
+static void launch_gs_small(const Geom& g, const SysSet<R>& S, int nsys, int nv, const GsParts& parts, hipStream_t s,
+                            Prof* prof) {
   const size_t n = nspec(g);
   const dim3 gr(fold_blocks(n), nsys);
   const bool pr = prof && prof->on;
   const double fb = (double)n * sizeof(C2<R>) * nsys;
-  if (pr) prof->begin(10, s, (nv + 1) * fb);
-  hipLaunchKernelGGL((k_mdot_s<R, NVH, H>), gr, dim3(256 * H), 0, s, S, nv, n, g.M);
-  if (pr) prof->end(s);
+  if (parts.dot_blocks == 0) {
+    if (pr) prof->begin(10, s, (nv + 1) * fb);
+    hipLaunchKernelGGL((k_mdot_s<R, NVH, H>), gr, dim3(256 * H), 0, s, S, nv, n, g.M);
+    if (pr) prof->end(s);
+  }
   if (pr) prof->begin(11, s, (nv + 2) * fb);
-  hipLaunchKernelGGL((k_gs_update_s<R, NVH, H>), gr, dim3(256 * H), 0, s, S, nv, n, g.M, g.ntot_inv);
+  hipLaunchKernelGGL((k_gs_update_s<R, NVH, H>), gr, dim3(256 * H), 0, s, S, nv, n, g.M, g.ntot_inv,
+                     parts.dot_blocks ? parts.dot_blocks : (int)gr.x);
   if (pr) prof->end(s);
-  hipLaunchKernelGGL((k_gs_finish<R, NVH * H < kMaxVec ? NVH * H : kMaxVec>), gr, dim3(256), 0, s, S, nv, n,
-                     orth_tol<R>(), g.ntot_inv);
+  if (parts.finish)
+    hipLaunchKernelGGL((k_gs_finish<R, NVH * H < kMaxVec ? NVH * H : kMaxVec>), gr, dim3(256), 0, s, S, nv, n,
+                       orth_tol<R>(), g.ntot_inv);
 }
+int gs_update_blocks(const Geom& g) { return fold_blocks(nspec(g)); }
 
 template <typename R, int NV>
 static void launch_gs(const Geom& g, const SysSet<R>& S, int nsys, int nv, int second, hipStream_t s) {
@@ -788,13 +632,14 @@ static void launch_gs(const Geom& g, const SysSet<R>& S, int nsys, int nv, int s
 // step (nv basis vectors each); each system's kernels return at once once
 // its own halt flag is set.
 template <typename R>
-static void gs_orthogonalize_set(const Geom& g, const SysSet<R>& S, int nsys, int nv, hipStream_t s, Prof* prof) {
+static void gs_orthogonalize_set(const Geom& g, const SysSet<R>& S, int nsys, int nv, const GsParts& parts,
+                                 hipStream_t s, Prof* prof) {
   if (folds(nspec(g))) {
-    if (nv <= 4) launch_gs_small<R, 4, 1>(g, S, nsys, nv, s, prof);
-    else if (nv <= 8) launch_gs_small<R, 8, 1>(g, S, nsys, nv, s, prof);
-    else if (nv <= 16) launch_gs_small<R, 8, 2>(g, S, nsys, nv, s, prof);
-    else if (nv <= 24) launch_gs_small<R, 8, 3>(g, S, nsys, nv, s, prof);
-    else launch_gs_small<R, 9, 4>(g, S, nsys, nv, s, prof);
+    if (nv <= 4) launch_gs_small<R, 4, 1>(g, S, nsys, nv, parts, s, prof);
+    else if (nv <= 8) launch_gs_small<R, 8, 1>(g, S, nsys, nv, parts, s, prof);
+    else if (nv <= 16) launch_gs_small<R, 8, 2>(g, S, nsys, nv, parts, s, prof);
+    else if (nv <= 24) launch_gs_small<R, 8, 3>(g, S, nsys, nv, parts, s, prof);
+    else launch_gs_small<R, 9, 4>(g, S, nsys, nv, parts, s, prof);
     return;
   }
   const bool pr = prof && prof->on;
@@ -823,14 +668,14 @@ static void gs_orthogonalize_set(const Geom& g, const SysSet<R>& S, int nsys, in
 
 template <typename R>
 void gs_orthogonalize(const Geom& g, void* w, const VecPtrs& V, int nv, DevState* st, double* partial,
-                      hipStream_t s, Prof* prof) {
+                      hipStream_t s, Prof* prof, const GsParts& parts) {
   // the dot pass is gated by the system's halt flag like the other kernels
-  gs_orthogonalize_set<R>(g, one_system<R>(w, V, st, partial, &st->halt), 1, nv, s, prof);
+  gs_orthogonalize_set<R>(g, one_system<R>(w, V, st, partial, &st->halt), 1, nv, parts, s, prof);
 }
 
 template <typename R>
 void gs_orthogonalize_batch(const Geom& g, void* const* w, const VecPtrs* V, int nv, DevState* const* st,
-                            double* const* partial, int nsys, hipStream_t s, Prof* prof) {
+                            double* const* partial, int nsys, hipStream_t s, Prof* prof, const GsParts& parts) {
   SysSet<R> S{};
   for (int k = 0; k < nsys; ++k) {
     S.x[k] = (C2<R>*)w[k];
@@ -839,7 +684,7 @@ void gs_orthogonalize_batch(const Geom& g, void* const* w, const VecPtrs* V, int
     S.partial[k] = partial[k];
     S.gate[k] = &st[k]->halt;
   }
-  gs_orthogonalize_set<R>(g, S, nsys, nv, s, prof);
+  gs_orthogonalize_set<R>(g, S, nsys, nv, parts, s, prof);
 }
 
 // ------------------------------------------------------------- lincomb
@@ -1439,9 +1284,9 @@ void kcoef_finish(const double* rho, const double* lap_psi, double* kc64, float*
   template void lincomb<R>(const Geom&, void*, const VecPtrs&, int, const double*, hipStream_t);               \
   template void scale<R>(const Geom&, void*, const double*, double, hipStream_t);                              \
   template void gs_orthogonalize<R>(const Geom&, void*, const VecPtrs&, int, DevState*, double*, hipStream_t,  \
-                                    Prof*);                                                                    \
+                                    Prof*, const GsParts&);                                                                    \
   template void gs_orthogonalize_batch<R>(const Geom&, void* const*, const VecPtrs*, int, DevState* const*,   \
-                                          double* const*, int, hipStream_t, Prof*);                          \
+                                          double* const*, int, hipStream_t, Prof*, const GsParts&);                          \
   template void sub_norm<R>(const Geom&, const void*, const void*, void*, double*, double*, hipStream_t,       \
                             const Post&);                                                                      \
   template void precond_axpy<R>(const Geom&, const OpParams&, void*, const void*, const double*, double,       \

@@ -14,12 +14,7 @@
 
 namespace vd {
 
-constexpr int kMaxVec = 34;       // vectors per multi-dot / multi-update
 constexpr int kRedBlocks = 1024;  // partial sums per reduction (4 blocks per CU)
-
-struct VecPtrs {
-  const void* p[kMaxVec];
-};
 
 // What a kernel tells the waiting host: written by the kernel straight into
 // pinned host memory, values first, then seq with a system-scope release.  The
@@ -88,9 +83,17 @@ void mdot(const Geom& g, const void* x, const VecPtrs& V, int nv, bool want_norm
 // Hessenberg column in st->hcol (+ st->ccol), ||w|| in st->hn and
 // vs[nv] = 1 / ||w||, and applies the Givens rotations to column nv - 1
 // (st->resid = new residual estimate).
+// On small fields a caller may take parts of it elsewhere: with dot_blocks, that
+// many blocks have already written the dots' partials; without finish, the
+// check, the second pass and the rotations are left to the next operator pass.
+struct GsParts {
+  int dot_blocks = 0;
+  bool finish = true;
+};
 template <typename R>
 void gs_orthogonalize(const Geom& g, void* w, const VecPtrs& V, int nv, DevState* st, double* partial,
-                      hipStream_t s, Prof* prof = nullptr);
+                      hipStream_t s, Prof* prof = nullptr, const GsParts& parts = GsParts{});
+int gs_update_blocks(const Geom& g);  // block partials of the check dots (small fields)
 
 // The same step for nsys <= kMaxBatch independent systems together (one
 // launch per pass for all of them; system k: w[k], V[k], st[k], partial[k];
@@ -99,7 +102,8 @@ void gs_orthogonalize(const Geom& g, void* w, const VecPtrs& V, int nv, DevState
 // when it is orthogonalised alone.
 template <typename R>
 void gs_orthogonalize_batch(const Geom& g, void* const* w, const VecPtrs* V, int nv, DevState* const* st,
-                            double* const* partial, int nsys, hipStream_t s, Prof* prof = nullptr);
+                            double* const* partial, int nsys, hipStream_t s, Prof* prof = nullptr,
+                            const GsParts& parts = GsParts{});
 
 // Device states and reduction partials of a set of systems (single-block
 // scalar kernels index them by blockIdx.y).

@@ -45,6 +45,48 @@ def test_gmres_around_the_small_field_limit(shape, precision):
         assert abs(info["iterations"] - ref["iterations"]) <= 1
 
 
+# Gram-Schmidt work inside the operator's passes: the shortest, the longest (512) and
+# the first length (1024) that does not carry it, partial tiles, one to several blocks
+@pytest.mark.parametrize("shape", [(16, 16), (512, 32), (1024, 32), (16, 16, 16), (128, 16, 32), (256, 64), (32, 64, 64)])
+@pytest.mark.parametrize("precision", ["fp64", "fp32_refine"])
+def test_steps_carried_by_the_passes(shape, precision):
+    """Restarted solves (the last step of a cycle finishes by itself), a budget
+    that ends a cycle early and the first step alone, for the pressure passes
+    (dots and check) and the Helmholtz passes (dots).  The oracle's operator
+    gives a true residual of 1e-10 (1% for its own rounding); the FP64 counts
+    differ from the oracle's by at most one step per cycle."""
+    from paper_2403_06654_amd.api import Grid
+    rho = smooth_density(shape, 5, 1.0, RATIO)
+    f = workloads.band_limited(shape, min(shape) // 4, seed=4)
+    b, _ = operators.project_range(-f, operators.nullspace_basis(shape))
+    g = Grid(shape)
+    g.set_density(to_dev(rho))
+    p, info = g.solve_pressure(to_dev(f), restart=20, precision=precision)
+    x = to_host(p)
+    assert info["status"] == 0
+    assert np.linalg.norm(operators.apply_pressure(x, rho) - b) <= 1.01e-10 * np.linalg.norm(b)
+    if precision == "fp64":
+        ref = krylov.gmres(lambda y: operators.apply_pressure(y, rho), b,
+                           lambda r: operators.precond_pressure(r, float(rho.mean())), restart=20, rtol=1e-10,
+                           max_iter=500)
+        assert abs(info["iterations"] - ref["iterations"]) <= 1 + ref["iterations"] // 20
+        for cut in (1, 7):
+            q, c = g.solve_pressure(to_dev(f), restart=20, max_iter=cut)
+            assert c["status"] == 1 and c["iterations"] == cut
+    # a nearly constant density: the step's result almost lies in the basis, so
+    # the check asks for second passes, which the first pass of the next step takes
+    near = 1.0 + (1e-9 if precision == "fp64" else 2e-4) * smooth_density(shape, 5, 1.0, 2.0)
+    g.set_density(to_dev(near))
+    p, info = g.solve_pressure(to_dev(f), restart=20, precision=precision)
+    assert info["status"] == 0 and info["iterations"] > 1 and info["gs_second_passes"] > 0
+    assert np.linalg.norm(operators.apply_pressure(to_host(p), near) - b) <= 1.01e-10 * np.linalg.norm(b)
+    g.set_density(to_dev(rho))
+    w, wi = g.solve_helmholtz(to_dev(f), 0.05, precision=precision)
+    res = operators.apply_helmholtz(to_host(w), rho, 0.05) - f
+    g.close()
+    assert wi["status"] == 0 and np.linalg.norm(res) <= 1.01e-10 * np.linalg.norm(f)
+
+
 # every column length on either side of the limit, the limit itself, and a y
 # length (512) that the small configuration is not built for beside z and x
 # lengths that it is; tolerances as for the other operator parity tests
