@@ -54,20 +54,23 @@ __device__ __forceinline__ double wave_sum(double v) {
                           __builtin_amdgcn_readlane(__double2loint(v), 63));
 }
 
-// Values to the host (one thread).  The release orders them, and everything
-// else this thread has written, before seq for any observer of the system.
+// Values to the host (one thread).
 __device__ __forceinline__ void post_mail(Mail* m, double a, double b, unsigned long long flags,
                                           unsigned long long seq) {
+  const unsigned long long c = mail_check((unsigned long long)__double_as_longlong(a),
+                                          (unsigned long long)__double_as_longlong(b), flags, seq);
   __hip_atomic_store(&m->v[0], a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   __hip_atomic_store(&m->v[1], b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   __hip_atomic_store(&m->flags, flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  __hip_atomic_store(&m->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(&m->check, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(&m->seq, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-// The state after step j of a cycle or run (bad and halt as just decided).
-__device__ __forceinline__ void post_step(DevState* st, int j, double resid, double nrm2, bool bad, bool halt,
-                                          int nreorth) {
-  post_mail(st->mail + MAIL_STEP + (j & 1), resid, nrm2,
-            (bad ? 1ull : 0ull) | (halt ? 2ull : 0ull) | ((unsigned long long)nreorth << 2), st->run + j + 1);
+// The state after step j of a cycle or run (bad and halt as just decided); mail
+// and run: the state's.
+__device__ __forceinline__ void post_step(Mail* mail, unsigned long long run, int j, double resid, double nrm2,
+                                          bool bad, bool halt, int nreorth) {
+  post_mail(mail + MAIL_STEP + (j & 1), resid, nrm2,
+            (bad ? 1ull : 0ull) | (halt ? 2ull : 0ull) | ((unsigned long long)nreorth << 2), run + j + 1);
 }
 
 // leading dimension of the column-major Hessenberg matrix
@@ -111,6 +114,8 @@ struct GsState {
   double v = 0, h = 0, cs = 0, sn = 0;
   double g = 0, stop_bnorm = 0, stop_rtol = 0;
   int nreorth = 0, bad = 0, jlast = 0;
+  Mail* mail = nullptr;
+  unsigned long long run = 0;
 };
 __device__ __forceinline__ GsState gs_state(const DevState* st, int nv, bool rotations) {
   const int lane = threadIdx.x & 63;
@@ -130,6 +135,8 @@ __device__ __forceinline__ GsState gs_state(const DevState* st, int nv, bool rot
     s.nreorth = st->nreorth;
     s.bad = st->bad;
     s.jlast = st->jlast;
+    s.mail = st->mail;
+    s.run = st->run;
   }
   return s;
 }
@@ -193,7 +200,7 @@ __device__ __forceinline__ void gs_givens(DevState* st, const GsState& s, const 
   const bool halt = bad || resid / s.stop_bnorm <= s.stop_rtol || j >= s.jlast;
   if (bad) st->bad = 1;
   if (halt) st->halt = 1;
-  post_step(st, j, resid, 0.0, bad, halt, nreorth);
+  post_step(s.mail, s.run, j, resid, 0.0, bad, halt, nreorth);
 }
 
 // End of the orthogonality check, by one full wavefront: the reduced values and

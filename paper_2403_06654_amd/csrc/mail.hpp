@@ -10,13 +10,23 @@
 
 namespace vd {
 
+// Whether mailbox m holds the whole of post number seq.  The words arrive in any
+// order; one that is still the last post's does not fit the check.
+inline bool mail_here(const Mail* m, unsigned long long seq) {
+  if (__atomic_load_n(&m->seq, __ATOMIC_ACQUIRE) != seq) return false;
+  unsigned long long w[2];
+  for (int i = 0; i < 2; ++i) w[i] = __atomic_load_n((const unsigned long long*)&m->v[i], __ATOMIC_ACQUIRE);
+  const unsigned long long flags = __atomic_load_n(&m->flags, __ATOMIC_ACQUIRE);
+  return __atomic_load_n(&m->check, __ATOMIC_ACQUIRE) == mail_check(w[0], w[1], flags, seq);
+}
+
 // Waits until mailbox m holds post number seq, which work already on stream st
 // will post.  Polls the pinned memory; every few ten microseconds it also asks
 // the stream, so that a device error, or a stream that has ended without
 // posting, ends the wait (false).
 inline bool wait_mail(const Mail* m, unsigned long long seq, hipStream_t st) {
   for (unsigned spin = 1;; ++spin) {
-    if (__atomic_load_n(&m->seq, __ATOMIC_ACQUIRE) == seq) return true;
+    if (mail_here(m, seq)) return true;
 #if defined(__x86_64__)
     __builtin_ia32_pause();
 #endif
@@ -28,7 +38,7 @@ inline bool wait_mail(const Mail* m, unsigned long long seq, hipStream_t st) {
       std::this_thread::yield();
       continue;
     }
-    return q == hipSuccess && __atomic_load_n(&m->seq, __ATOMIC_ACQUIRE) == seq;
+    return q == hipSuccess && mail_here(m, seq);
   }
 }
 

@@ -247,33 +247,31 @@ __device__ __forceinline__ KGs* kern_gs() {
   return (KGs*)((KChar*)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(ColGsKernArgs, gs));
 }
 
-// val[0..K) = the sums of nb <= kFoldBlocks block partials, by all the block's
-// wavefronts (fold_reduce with K and the block size known at run time): up to
-// nine values of a wavefront have their loads in flight together.
+// val[0..K) = the sums of nb <= kFoldBlocks block partials, by all NW wavefronts
+// of the block.  Four lanes sum a value, with up to 16 loads each in flight: with
+// one or two wavefronts a tree over all lanes for every value, one value after
+// another, took longer than the loads.
 template <int NW>
 __device__ __forceinline__ void fold_sums(const double* partial, int nb, int K, double scale, double* val) {
-  constexpr int PW = 9, Q = kFoldBlocks / 64;
-  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  for (int i0 = w; i0 < K; i0 += NW * PW) {
-    double v[PW];
+  constexpr int Q = 16;
+  const int q = threadIdx.x & 3;
+  for (int i = threadIdx.x >> 2; i < K; i += 16 * NW) {
+    const double* src = partial + (size_t)i * kRedBlocks;
+    double s = 0.0;
+    for (int b0 = q; b0 < nb; b0 += 4 * Q) {
+      double t[Q];
 #pragma unroll
-    for (int p = 0; p < PW; ++p) {
-      v[p] = 0.0;
-      const int i = i0 + NW * p;
-      if (i < K) {
-        const double* src = partial + (size_t)i * kRedBlocks;
-        double t[Q];
+      for (int m = 0; m < Q; ++m) t[m] = b0 + 4 * m < nb ? src[b0 + 4 * m] : 0.0;
 #pragma unroll
-        for (int q = 0; q < Q; ++q) t[q] = lane + 64 * q < nb ? src[lane + 64 * q] : 0.0;
+      for (int h = Q / 2; h > 0; h >>= 1) {
 #pragma unroll
-        for (int q = 0; q < Q; ++q) v[p] += t[q];
+        for (int m = 0; m < h; ++m) t[m] += t[m + h];
       }
+      s += t[0];
     }
-#pragma unroll
-    for (int p = 0; p < PW; ++p) {
-      const double t = wave_sum(v[p]);
-      if (lane == 0 && i0 + NW * p < K) val[i0 + NW * p] = t * scale;
-    }
+    s = add_dpp<0xb1, 0xf>(s);  // lanes q ^ 1
+    s = add_dpp<0x4e, 0xf>(s);  // lanes q ^ 2
+    if (q == 0) val[i] = s * scale;
   }
 }
 
@@ -361,6 +359,7 @@ __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restri
   __shared__ double cval[CHECK ? kMaxVec + 2 : 1], ccl[CHECK ? kMaxVec : 1], cinv;
   __shared__ int again;
   double vscale = 1.0;
+  R mult[SM && MODE == COL_P_FIRST ? E : 1];
 
   if constexpr (SM) {
     // every load that does not depend on another one, then the halt flag
@@ -372,6 +371,12 @@ __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restri
     const void* src = NG == 3 ? (MODE == COL_P_MIDINV ? (grp == 2 ? in1 : in0) : (grp == 0 ? in0 : grp == 1 ? in1 : in2))
                       : MODE == COL_P_LAST && grp == 1 ? in1 : in0;
     col_load<L, E, R0>(reg, (const C2<R>*)src, base, a.inner, t, ok);
+    if constexpr (MODE == COL_P_FIRST) {  // divisions, while the loads are on their way
+      const int ky = col / a.g.M, kx = col % a.g.M;
+#pragma unroll
+      for (int s = 0; s < E; ++s)
+        mult[s] = a.precond ? mult_press<R>(kx, ky, pat_index<L, E, R0>(t, s), a.g, rho0) : R(1);
+    }
     GsState state{};
     DevState* st = CHECK ? gs->sys[blockIdx.y].st : nullptr;
     if (CHECK && threadIdx.x < 64) state = gs_state(st, nv, rotations);
@@ -435,14 +440,11 @@ __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restri
   if constexpr (SM && NG > 1 && MODE != COL_H_LAST) {
     // one transform per group; every group meets the same barriers
     if constexpr (MODE == COL_P_FIRST) {
-      const int ky = col / a.g.M, kx = col % a.g.M;
       const R sc = CHECK ? R(vscale) : in_scale_of<R>(iscale);
 #pragma unroll
       for (int s = 0; s < E; ++s) {
-        const int kz = pat_index<L, E, R0>(t, s);
-        const R m = a.precond ? mult_press<R>(kx, ky, kz, a.g, rho0) : R(1);
-        reg[s] = cscale(reg[s], m * sc);
-        if (grp == 1) reg[s] = cik(reg[s], kprime_of<R>(kz, L, R(a.g.sz)));
+        reg[s] = cscale(reg[s], mult[s] * sc);
+        if (grp == 1) reg[s] = cik(reg[s], kprime_of<R>(pat_index<L, E, R0>(t, s), L, R(a.g.sz)));
       }
       fft_line<L, E, +1, false>(reg, lds, tw, t);
       col_store<L, E, R1>(reg, (C2<R>*)(grp ? out1 : out0), base, a.inner, t, ok);

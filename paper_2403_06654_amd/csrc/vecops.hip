@@ -81,11 +81,22 @@ __device__ __forceinline__ void reduce_values(const double* __restrict__ partial
 }
 
 // Scalar steps of CG and RMR, taken by one thread on the reduced values
-// (passed in: see k_reduce).
-__device__ __forceinline__ void cg_beta_step(DevState* st, double rzn) {  // beta = (r, M r)_new / (r, M r)
-  st->beta = st->rz != 0.0 ? rzn / st->rz : 0.0;
+// (passed in: see k_reduce) and on the state as it was loaded ahead of them.
+struct RecState {
+  double rz, stop_bnorm, stop_rtol;
+  int step, bad, jlast;
+  Mail* mail;
+  unsigned long long run;
+};
+__device__ __forceinline__ RecState rec_state(const DevState* st) {
+  return RecState{st->rz, st->stop_bnorm, st->stop_rtol, st->step, st->bad, st->jlast, st->mail, st->run};
+}
+__device__ __forceinline__ void cg_beta_step(DevState* st, const RecState& s, double rzn) {
+  // beta = (r, M r)_new / (r, M r)
+  const double beta = s.rz != 0.0 ? rzn / s.rz : 0.0;
+  st->beta = beta;
   st->rz = rzn;
-  if (!isfinite(st->beta)) st->bad = 1;
+  if (!isfinite(beta)) st->bad = 1;
 }
 __device__ __forceinline__ void rmr_alpha_step(DevState* st, double rw, double ww) {  // alpha = (r, w) / (w, w)
   st->alpha = ww > 0.0 ? rw / ww : 0.0;
@@ -95,14 +106,14 @@ __device__ __forceinline__ void rmr_alpha_step(DevState* st, double rw, double w
 // square, also in st->nrm2), the host loop's test taken on the device: a
 // non-finite scalar, the tolerance, or the last step of the run sets halt.
 // step counts the steps.
-__device__ __forceinline__ bool rec_check_step(DevState* st, double n2) {
-  const int j = st->step;
+__device__ __forceinline__ bool rec_check_step(DevState* st, const RecState& s, double n2) {
+  const int j = s.step;
   st->step = j + 1;
   const double rn = n2 < 0.0 ? 0.0 : sqrt(n2);
-  const bool bad = st->bad != 0;
-  const bool halt = bad || !(n2 == n2) || rn / st->stop_bnorm <= st->stop_rtol || j >= st->jlast;
+  const bool bad = s.bad != 0;
+  const bool halt = bad || !(n2 == n2) || rn / s.stop_bnorm <= s.stop_rtol || j >= s.jlast;
   if (halt) st->halt = 1;
-  post_step(st, j, rn, n2, bad, halt, 0);
+  post_step(s.mail, s.run, j, rn, n2, bad, halt, 0);
   return halt;
 }
 
@@ -118,6 +129,8 @@ __global__ __launch_bounds__(1024) void k_reduce(const double* __restrict__ part
   if (gate && *gate) return;
   __shared__ double val[2];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  RecState rs{};
+  if (post != POST_NONE) rs = rec_state(st);
   for (int i = w; i < K; i += 16) {
     const double v = sum_partials(partial + (size_t)i * kRedBlocks, nblk) * scale;
     if (lane == 0) {
@@ -128,13 +141,13 @@ __global__ __launch_bounds__(1024) void k_reduce(const double* __restrict__ part
   if (post == POST_NONE) return;
   __syncthreads();
   if (threadIdx.x) return;
-  if (post == POST_CG_BETA) cg_beta_step(st, val[0]);
+  if (post == POST_CG_BETA) cg_beta_step(st, rs, val[0]);
   else if (post == POST_RMR_ALPHA) rmr_alpha_step(st, val[0], val[1]);
-  else if (post == POST_REC_CHECK) rec_check_step(st, val[0]);
+  else if (post == POST_REC_CHECK) rec_check_step(st, rs, val[0]);
   else if (post == POST_CG_STEP) {
-    if (!rec_check_step(st, val[0])) cg_beta_step(st, val[1]);
+    if (!rec_check_step(st, rs, val[0])) cg_beta_step(st, rs, val[1]);
   }
-  else if (post == POST_MAIL) post_mail(st->mail + MAIL_VALUE, val[0], 0.0, 0, seq);
+  else if (post == POST_MAIL) post_mail(rs.mail + MAIL_VALUE, val[0], 0.0, 0, seq);
 }
 
 // gate (here and below): optional device flag; when nonzero the launch does

@@ -16,16 +16,28 @@ namespace vd {
 
 constexpr int kRedBlocks = 1024;  // partial sums per reduction (4 blocks per CU)
 
-// What a kernel tells the waiting host: written by the kernel straight into
-// pinned host memory, values first, then seq with a system-scope release.  The
-// host polls seq for the number it expects (each is used once per mailbox).
-// A step whose state went to the host as a copy of its own, with an event to
-// wait for, cost about 10 us of the stream per Krylov step.
+// What a kernel tells the waiting host, written straight into pinned host memory.
+// The host polls seq for the number it expects (each is used once per mailbox)
+// and takes the values when check fits all of them: the words may arrive in any
+// order, so a step's kernel neither waits between its stores nor writes back its
+// L2 for the host.  A step whose state went to the host as a copy of its own,
+// with an event to wait for, cost about 10 us of the stream per Krylov step.
 struct alignas(64) Mail {
-  double v[3];
+  double v[2];
   unsigned long long flags;  // bit 0: bad, bit 1: halt, above: second passes of this cycle
   unsigned long long seq;
+  unsigned long long check;  // mail_check of the four
 };
+__host__ __device__ inline unsigned long long mail_check(unsigned long long a, unsigned long long b,
+                                                         unsigned long long flags, unsigned long long seq) {
+  unsigned long long h = 0x9e3779b97f4a7c15ull;
+  const unsigned long long w[4] = {a, b, flags, seq};
+  for (int i = 0; i < 4; ++i) {
+    h = (h ^ w[i]) * 0xff51afd7ed558ccdull;
+    h ^= h >> 32;
+  }
+  return h;
+}
 // mailboxes of a solver state: two for the Krylov steps in turn, one for
 // single reduced values
 enum { MAIL_STEP = 0, MAIL_VALUE = 2, kMails = 3 };
