@@ -54,6 +54,24 @@ __device__ __forceinline__ double wave_sum(double v) {
                           __builtin_amdgcn_readlane(__double2loint(v), 63));
 }
 
+// Sum of one value's nblk <= kRedBlocks block partials by one wavefront, in a
+// fixed order: lanes stride over them, then the wavefront's tree.  Every lane
+// issues all its loads before the first addition.  A loop that added each
+// partial as it arrived paid up to sixteen dependent load latencies: on 1024
+// partials of 9-16 values k_gs_prep took 6.8 us (4.5 now) and k_gs_check 9.4 us
+// (5.2 now).
+__device__ __forceinline__ double sum_partials(const double* __restrict__ p, int nblk) {
+  constexpr int Q = kRedBlocks / 64;
+  const int lane = threadIdx.x & 63;
+  double v[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) v[q] = lane + 64 * q < nblk ? p[lane + 64 * q] : 0.0;
+  double s = v[0];
+#pragma unroll
+  for (int q = 1; q < Q; ++q) s += v[q];
+  return wave_sum(s);
+}
+
 // Values to the host (one thread).
 __device__ __forceinline__ void post_mail(Mail* m, double a, double b, unsigned long long flags,
                                           unsigned long long seq) {
@@ -71,6 +89,44 @@ __device__ __forceinline__ void post_step(Mail* mail, unsigned long long run, in
                                           bool bad, bool halt, int nreorth) {
   post_mail(mail + MAIL_STEP + (j & 1), resid, nrm2,
             (bad ? 1ull : 0ull) | (halt ? 2ull : 0ull) | ((unsigned long long)nreorth << 2), run + j + 1);
+}
+
+// Scalar steps of CG and RMR, taken by one thread on the reduced values
+// (passed in: see k_reduce) and on the state as it was loaded ahead of them.
+struct RecState {
+  double rz, stop_bnorm, stop_rtol;  // rz: of the step that ends
+  int step, bad, jlast;
+  Mail* mail;
+  unsigned long long run;
+};
+__device__ __forceinline__ RecState rec_state(const DevState* st, int slot = 0) {
+  return RecState{st->rz[slot], st->stop_bnorm, st->stop_rtol, st->step, st->bad, st->jlast, st->mail, st->run};
+}
+__device__ __forceinline__ double cg_beta(double rz, double rzn) { return rz != 0.0 ? rzn / rz : 0.0; }
+__device__ __forceinline__ void cg_beta_step(DevState* st, const RecState& s, double rzn, int slot = 0) {
+  // beta = (r, M r)_new / (r, M r)
+  const double beta = cg_beta(s.rz, rzn);
+  st->beta = beta;
+  st->rz[slot] = rzn;
+  if (!isfinite(beta)) st->bad = 1;
+}
+__device__ __forceinline__ void rmr_alpha_step(DevState* st, double rw, double ww) {  // alpha = (r, w) / (w, w)
+  st->alpha = ww > 0.0 ? rw / ww : 0.0;
+  if (!isfinite(st->alpha)) st->bad = 1;
+}
+// Stopping test of a CG or RMR step on its recursive residual (n2 = its
+// square, also in st->nrm2), the host loop's test taken on the device: a
+// non-finite scalar, the tolerance, or the last step of the run sets halt.
+// step counts the steps.
+__device__ __forceinline__ bool rec_check_step(DevState* st, const RecState& s, double n2) {
+  const int j = s.step;
+  st->step = j + 1;
+  const double rn = n2 < 0.0 ? 0.0 : sqrt(n2);
+  const bool bad = s.bad != 0;
+  const bool halt = bad || !(n2 == n2) || rn / s.stop_bnorm <= s.stop_rtol || j >= s.jlast;
+  if (halt) st->halt = 1;
+  post_step(s.mail, s.run, j, rn, n2, bad, halt, 0);
+  return halt;
 }
 
 // leading dimension of the column-major Hessenberg matrix

@@ -236,15 +236,36 @@ struct ColGs {
     const void* V[kMaxVec];
   } sys[kMaxBatch];
 };
-struct ColGsKernArgs {  // the kernel-argument segment of k_col_gs
+// CG and RMR work of the first or last pass (RecCarry), for fields of any size:
+// the direction's update, a pass of its own over three fields, takes one field
+// more in the first pass, which reads the direction anyway; the dots of the last
+// pass' result, two fields, take at most one; and the reduction with the stopping
+// test runs beside the first pass in one more block.  128^3 FP64, us a step: k_cg_p
+// 10.6 + z-first 8.6 -> 15.3, z-last 10.8 + dots 6.7 -> 11.7, reduction 4.0 -> 0; K
+// form by CG 1780 -> 1676 us a solve.
+struct ColRec {
+  int cg, precond;
+  int nb, slot;
+  double scale;
+  DevState* st;
+  double* partial;
+  const void* r;
+  void* p;
+};
+// What a launch carries beside the transforms.
+enum Carry { CARRY_NONE = 0, CARRY_GS, CARRY_REC };
+template <typename T>
+struct ColCarryKernArgs {  // the kernel-argument segment of k_col_gs and k_col_rec
   ColArgs a;
   const void* tw;
-  ColGs gs;
+  T carry;
 };
 typedef __attribute__((address_space(4))) const ColGs KGs;
-__device__ __forceinline__ KGs* kern_gs() {
+template <typename T>
+__device__ __forceinline__ auto* kern_carry() {
   typedef __attribute__((address_space(4))) const char KChar;
-  return (KGs*)((KChar*)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(ColGsKernArgs, gs));
+  typedef __attribute__((address_space(4))) const T KT;
+  return (KT*)((KChar*)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(ColCarryKernArgs<T>, carry));
 }
 
 // val[0..K) = the sums of nb <= kFoldBlocks block partials, by all NW wavefronts
@@ -275,8 +296,26 @@ __device__ __forceinline__ void fold_sums(const double* partial, int nb, int K, 
   }
 }
 
-template <int L, typename R, int MODE, bool SM, bool GS>
+// M^-1 r at kz = pat_index(t, s) of a thread's column, all E points: r and, where
+// the Helmholtz inverse needs it, r at the mirror have been loaded.
+template <int L, int E, int RPAT, bool HELM, typename R>
+__device__ __forceinline__ C2<R> precond_point(int s, C2<R> r, C2<R> rm, int kx, int ky, int t, const ColArgs& a,
+                                               double rho0) {
+  const int kz = pat_index<L, E, RPAT>(t, s);
+  if constexpr (HELM) {
+    const HelmMult<R> h = mult_helm<R>(kx, ky, kz, a.g, rho0, a.nu, false);
+    return kx ? cscale(r, h.g0) : diag_packed(r, rm, h.g0, h.gN);
+  } else {
+    return cscale(r, mult_press<R>(kx, ky, kz, a.g, rho0));
+  }
+}
+
+template <int L, typename R, int MODE, bool SM, int CARRY>
 __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restrict__ twtab) {
+  constexpr bool GS = CARRY == CARRY_GS, REC = CARRY == CARRY_REC;
+  constexpr bool ENDS = REC && (MODE == COL_P_FIRST || MODE == COL_H_FIRST);
+  constexpr bool DOT = REC && (MODE == COL_P_LAST || MODE == COL_H_LAST);
+  static_assert(!REC || ENDS || DOT, "CG and RMR work of first and last passes");
   using Cf = ColCfg<L, R, MODE, SM, GS>;
   constexpr bool CHECK = GS && MODE == COL_P_FIRST, DOTS = GS && (MODE == COL_P_LAST || MODE == COL_H_LAST);
   static_assert(!GS || (SM && (CHECK || DOTS)), "Gram-Schmidt work of small fields' first and last passes");
@@ -306,8 +345,9 @@ __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restri
   const int tid = NG > 1 ? threadIdx.x - grp * NTG : threadIdx.x;
   const int c = tid % TC, t = tid / TC;
   // CHECK: the block past the tiles takes the rotations
-  const bool rotations = CHECK && (int)blockIdx.x == a.ntile;
-  const int ob = CHECK ? 0 : blockIdx.x / a.ntile, tile = CHECK ? blockIdx.x : blockIdx.x % a.ntile;
+  // (ENDS: the stopping test)
+  const bool rotations = (CHECK || ENDS) && (int)blockIdx.x == a.ntile;
+  const int ob = CHECK || ENDS ? 0 : blockIdx.x / a.ntile, tile = CHECK || ENDS ? blockIdx.x : blockIdx.x % a.ntile;
   const int col = tile * TC + c;
   const bool ok = col < a.inner && !rotations;
   const size_t base = (size_t)ob * L * a.inner + col;
@@ -319,7 +359,7 @@ __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restri
   constexpr int VB = MODE == COL_H_LAST && L == 512 && sizeof(R) == 8 ? 2 : 4;
   __shared__ double dsum[DOTS ? NT / 64 : 1][DOTS ? kMaxVec / 2 : 1];
   C2<R> vb[DOTS ? VB : 1][E];
-  KGs* gs = GS ? kern_gs() : nullptr;
+  KGs* gs = GS ? kern_carry<ColGs>() : nullptr;
   const int nv = GS ? gs->nv : 0, nq = DOTS ? (nv - grp + NG - 1) / NG : 0;
   auto load_vectors = [&](int q0) {
 #pragma unroll
@@ -355,6 +395,93 @@ __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restri
     }
   };
   if constexpr (DOTS) load_vectors(0);
+  // ENDS: the end of the step before.  The first wavefront sums the partials of
+  // (r, M^-1 r) for beta, in the last block also those of |r|^2 for the test; rz
+  // alternates between two entries, because blocks still read the old one.
+  auto* rec = kern_carry<ColRec>();  // used with REC only
+  __shared__ double cbeta;
+  const bool upd = ENDS && rec->cg;
+  auto end_step = [&]() {
+    if (threadIdx.x >= 64 || !(rec->cg || rotations)) return;
+    DevState* st = rec->st;
+    const double* part = rec->partial + 2 * kRedBlocks;
+    RecState s{};
+    double old = 0.0;
+    if (rotations) s = rec_state(st, rec->slot);
+    if (rec->cg) old = st->rz[rec->slot];
+    const double rzn = rec->cg ? sum_partials(part + kRedBlocks, rec->nb) * rec->scale : 0.0;
+    if (rotations) {
+      const double n2 = sum_partials(part, rec->nb) * rec->scale;
+      if (threadIdx.x == 0) {
+        st->red[0] = n2;
+        st->red[1] = rzn;
+        if (!rec_check_step(st, s, n2) && rec->cg) cg_beta_step(st, s, rzn, rec->slot ^ 1);
+      }
+    } else if (threadIdx.x == 0) {
+      cbeta = cg_beta(old, rzn);
+    }
+  };
+  // p = M^-1 r + beta p on this thread's points (x: p), with r loaded before
+  constexpr bool HELM = MODE == COL_H_FIRST;
+  C2<R> rr[ENDS ? E : 1], rm[ENDS && HELM ? E : 1];
+  auto load_r = [&]() {
+    if (!upd) return;
+    const C2<R>* r = (const C2<R>*)rec->r;
+    col_load<L, E, R0>(rr, r, base, a.inner, t, ok);
+    if constexpr (ENDS && HELM) {
+      const int ky = col / a.g.M;
+      if (col % a.g.M == 0 && rec->precond && ok) {
+#pragma unroll
+        for (int s = 0; s < E; ++s)
+          rm[s] = ldg(r + (size_t)((a.g.ny - ky) % a.g.ny) * a.g.M + (size_t)((L - pat_index<L, E, R0>(t, s)) % L) * a.inner);
+      }
+    }
+  };
+  auto new_p = [&](C2<R>* x) {
+    const double b = cbeta;
+    const int ky = col / a.g.M, kx = col % a.g.M;
+#pragma unroll
+    for (int s = 0; s < E; ++s) {
+      C2<R> z = rr[ENDS ? s : 0];
+      if (rec->precond)
+        z = precond_point<L, E, R0, HELM>(s, z, rm[ENDS && HELM ? s : 0], kx, ky, t, a, rho0);
+      x[s] = ok ? C2<R>{R(z.x + b * x[s].x), R(z.y + b * x[s].y)} : C2<R>{R(0), R(0)};
+    }
+  };
+  // DOT: (y, p), and for RMR |y|^2, of the result y that group 0 holds; p's points
+  // in the same pattern
+  __shared__ double rsum[DOT ? NT / 64 : 1][2];
+  C2<R> pv[DOT ? E : 1];
+  auto load_p = [&]() {
+    if (grp == 0) col_load<L, E, R1>(pv, (const C2<R>*)rec->p, base, a.inner, t, ok);
+  };
+  auto rec_dots = [&](const C2<R>* y) {
+    double d = 0.0, n = 0.0;
+    if (grp == 0) {
+      const double w = (col & (a.g.M - 1)) == 0 ? 1.0 : 2.0;  // as spec_w
+#pragma unroll
+      for (int s = 0; s < E; ++s) {
+        d += w * ((double)pv[DOT ? s : 0].x * (double)y[s].x + (double)pv[DOT ? s : 0].y * (double)y[s].y);
+        n += w * ((double)y[s].x * (double)y[s].x + (double)y[s].y * (double)y[s].y);
+      }
+      d = wave_sum(d);
+      n = wave_sum(n);
+      if ((threadIdx.x & 63) == 0) {
+        rsum[DOT ? threadIdx.x >> 6 : 0][0] = d;
+        rsum[DOT ? threadIdx.x >> 6 : 0][1] = n;
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x < (rec->cg ? 1 : 2)) {
+      constexpr int WG = NTG / 64;
+      double v = rsum[0][threadIdx.x];
+#pragma unroll
+      for (int q = 1; q < WG; ++q) v += rsum[DOT ? q : 0][threadIdx.x];
+      rec->partial[(size_t)threadIdx.x * kRedBlocks + blockIdx.x] = v;
+    }
+  };
+  if constexpr (SM && ENDS) load_r();
+  if constexpr (SM && DOT) load_p();
   // CHECK: coefficients of the second pass, the scale of the result
   __shared__ double cval[CHECK ? kMaxVec + 2 : 1], ccl[CHECK ? kMaxVec : 1], cinv;
   __shared__ int again;
@@ -404,13 +531,24 @@ __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restri
   } else {
     for (int i = threadIdx.x; i < L; i += blockDim.x) tw_lds[i] = twtab[L + i];
   }
+  if constexpr (ENDS) {
+    end_step();
+    if (rotations) return;
+  }
   __syncthreads();
   const C2<R>* tw = tw_lds;
   // CHECK: the second pass on this tile.  Both groups hold the column and form
   // the same values; group 0 writes them back after its transform, when both
   // have consumed their loads (a block that sees the halt flag of the rotations
   // leaves the vector as it is: the vector that ends a cycle is never read).
-  C2<R> kept[CHECK ? E : 1];
+  C2<R> kept[CHECK || (SM && ENDS) ? E : 1];
+  if constexpr (SM && ENDS) {
+    if (upd) {
+      new_p(reg);
+#pragma unroll
+      for (int s = 0; s < E; ++s) kept[s] = reg[s];
+    }
+  }
   if constexpr (CHECK) {
     static_assert(S::npass > 1, "a barrier between the loads and the stores");
     vscale = cinv;
@@ -451,6 +589,9 @@ __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restri
       if constexpr (CHECK) {
         if (again && grp == 0) col_store<L, E, R0>(kept, (C2<R>*)in0, base, a.inner, t, ok);
       }
+      if constexpr (ENDS) {
+        if (upd && grp == 0) col_store<L, E, R0>(kept, (C2<R>*)rec->p, base, a.inner, t, ok);
+      }
     } else if constexpr (MODE == COL_P_MIDINV) {
       // in place (out0 = in0, out2 = in1): both readers of in0 have consumed
       // their loads before the first exchange's barrier
@@ -485,6 +626,7 @@ __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restri
       } else if (!LAST && grp == 2) {
         col_store<L, E, R1>(reg, (C2<R>*)out1, base, a.inner, t, ok);
       }
+      if constexpr (DOT) rec_dots(reg);
       if constexpr (DOTS) {  // the result to the other group through group 0's tile
         const LdsCol<R> mine{lds_raw, c, TC};
         if (grp == 0) {
@@ -515,6 +657,13 @@ __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restri
     const int ky = col / a.g.M, kx = col % a.g.M;
     const R sc = in_scale_of<R>(iscale);
     col_load<L, E, R0>(reg, (const C2<R>*)in0, base, a.inner, t, ok);
+    if constexpr (ENDS) {
+      if (upd) {
+        load_r();
+        new_p(reg);
+        col_store<L, E, R0>(reg, (C2<R>*)rec->p, base, a.inner, t, ok);
+      }
+    }
     C2<R> r2[E];
 #pragma unroll
     for (int s = 0; s < E; ++s) {
@@ -555,6 +704,10 @@ __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restri
       acc[s] = LAST ? C2<R>{-(acc[s].x + d.x), -(acc[s].y + d.y)} : acc[s] + d;
     }
     col_store<L, E, R1>(acc, (C2<R>*)out0, base, a.inner, t, ok);
+    if constexpr (DOT) {
+      load_p();
+      rec_dots(acc);
+    }
     if constexpr (!LAST) {
       col_load<L, E, R0>(reg, (const C2<R>*)in2, base, a.inner, t, ok);
       fft_line<L, E, -1, false>(reg, lds, tw, t);
@@ -583,8 +736,18 @@ __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restri
     if constexpr (SM && FIRST) {
 #pragma unroll
       for (int s = 0; s < E; ++s) mv[s] = reg[s];
+      if constexpr (ENDS) {
+        if (upd) col_store<L, E, R0>(kept, (C2<R>*)rec->p, base, a.inner, t, ok);
+      }
     } else {
       col_load<L, E, RP>(mv, v, base, a.inner, t, ok);
+      if constexpr (ENDS) {
+        if (upd) {
+          load_r();
+          new_p(mv);
+          col_store<L, E, R0>(mv, (C2<R>*)rec->p, base, a.inner, t, ok);
+        }
+      }
     }
     const bool need_mirror = (kx == 0) && (a.precond || !FIRST);
     const int kym = (a.g.ny - ky) % a.g.ny;
@@ -622,6 +785,10 @@ __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restri
 #pragma unroll
       for (int s = 0; s < E; ++s) reg[s] = reg[s] + mv[s];
       col_store<L, E, R1>(reg, (C2<R>*)out0, base, a.inner, t, ok);
+      if constexpr (DOT) {
+        if constexpr (!SM) load_p();
+        rec_dots(reg);
+      }
       if constexpr (DOTS) {
         __syncthreads();  // the tile's last exchange has been read
 #pragma unroll
@@ -635,13 +802,18 @@ __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restri
 
 template <int L, typename R, int MODE, bool SM>
 __global__ __launch_bounds__((ColCfg<L, R, MODE, SM>::NT)) void k_col(ColArgs a, const C2<R>* __restrict__ twtab) {
-  col_pass<L, R, MODE, SM, false>(a, twtab);
+  col_pass<L, R, MODE, SM, CARRY_NONE>(a, twtab);
 }
 template <int L, typename R, int MODE>
 __global__ __launch_bounds__((ColCfg<L, R, MODE, true, true>::NT)) void k_col_gs(ColArgs a,
                                                                                const C2<R>* __restrict__ twtab,
                                                                                ColGs) {
-  col_pass<L, R, MODE, true, true>(a, twtab);
+  col_pass<L, R, MODE, true, CARRY_GS>(a, twtab);
+}
+template <int L, typename R, int MODE, bool SM>
+__global__ __launch_bounds__((ColCfg<L, R, MODE, SM>::NT)) void k_col_rec(ColArgs a, const C2<R>* __restrict__ twtab,
+                                                                         ColRec) {
+  col_pass<L, R, MODE, SM, CARRY_REC>(a, twtab);
 }
 
 // --------------------------------------------------------- row kernels
@@ -1087,6 +1259,42 @@ static void launch_col_gs(int len, const ColArgs& a0, const GsCarry& c, const vo
   });
 }
 
+bool op_carries_rec(const Geom& g) { return !g.cheb && g.nz > 1 && g.nz <= kGsLength; }
+template <typename R>
+int op_rec_blocks(const Geom& g, int kind) {
+  int n = 0;
+  for_gs_length(g.nz, [&](auto len) {
+    constexpr int L = decltype(len)::value;
+    const int tc = small_field(g) ? ColSmall<L>::TC
+                   : kind == OP_PRESSURE ? ColCfg<L, R, COL_P_LAST>::TC : ColCfg<L, R, COL_H_LAST>::TC;
+    n = (g.ny * g.M + tc - 1) / tc;
+  });
+  return n <= kRedBlocks ? n : 0;
+}
+template int op_rec_blocks<double>(const Geom&, int);
+template int op_rec_blocks<float>(const Geom&, int);
+
+// A first or last pass with the CG or RMR work of c.
+template <typename R, int MODE>
+static void launch_col_rec(int len, const ColArgs& a0, const RecCarry& c, const void* tw, hipStream_t st) {
+  constexpr bool FIRST = MODE == COL_P_FIRST || MODE == COL_H_FIRST;
+  ColArgs a = a0;
+  as_systems(a);
+  const ColRec rec{c.cg ? 1 : 0, c.precond ? 1 : 0, c.nb, c.slot, a.g.ntot_inv, c.st, c.partial, c.r, c.p};
+  for_gs_length(len, [&](auto l) {
+    constexpr int L = decltype(l)::value;
+    auto go = [&](auto sm) {
+      constexpr bool SM = decltype(sm)::value;
+      using Cf = ColCfg<L, R, MODE, SM>;
+      a.ntile = (a.inner + Cf::TC - 1) / Cf::TC;
+      hipLaunchKernelGGL((k_col_rec<L, R, MODE, SM>), dim3(a.ntile + (FIRST ? 1 : 0), a.nb), dim3(Cf::NT), 0, st, a,
+                         (const C2<R>*)tw, rec);
+    };
+    if (small_field(a.g)) go(std::true_type{});
+    else go(std::false_type{});
+  });
+}
+
 template <typename R, int MODE>
 static void launch_col(int L, const ColArgs& a, const void* tw, hipStream_t st) {
   switch (L) {
@@ -1101,14 +1309,21 @@ static void launch_col(int L, const ColArgs& a, const void* tw, hipStream_t st) 
   }
 }
 
-template <typename R>
-static void first_pass(const Geom& g, const ColArgs& a, const GsCarry* gs, const void* tw, hipStream_t st) {
-  if (gs && gs->check) launch_col_gs<R, COL_P_FIRST>(g.nz, a, *gs, tw, st);
-  else launch_col<R, COL_P_FIRST>(g.nz, a, tw, st);
+template <typename R, int MODE>
+static void first_pass(const Geom& g, const OpParams& p, const ColArgs& a, const void* tw, hipStream_t st) {
+  if constexpr (MODE == COL_P_FIRST) {
+    if (p.gs && p.gs->check) {
+      launch_col_gs<R, MODE>(g.nz, a, *p.gs, tw, st);
+      return;
+    }
+  }
+  if (p.rec && p.rec->ends) launch_col_rec<R, MODE>(g.nz, a, *p.rec, tw, st);
+  else launch_col<R, MODE>(g.nz, a, tw, st);
 }
 template <typename R, int MODE>
-static void last_pass(const Geom& g, const ColArgs& a, const GsCarry* gs, const void* tw, hipStream_t st) {
-  if (gs) launch_col_gs<R, MODE>(g.nz, a, *gs, tw, st);
+static void last_pass(const Geom& g, const OpParams& p, const ColArgs& a, const void* tw, hipStream_t st) {
+  if (p.gs) launch_col_gs<R, MODE>(g.nz, a, *p.gs, tw, st);
+  else if (p.rec && p.rec->dots) launch_col_rec<R, MODE>(g.nz, a, *p.rec, tw, st);
   else launch_col<R, MODE>(g.nz, a, tw, st);
 }
 
@@ -1220,7 +1435,7 @@ void op_apply(const Geom& g, const OpParams& p, const void* v, void* y, const Op
     a.in[0] = v;
     a.out[0] = t0;
     a.out[1] = t1;
-    VD_T0(0) first_pass<R>(g, a, p.gs, twtab, st); VD_T1()
+    VD_T0(0) first_pass<R, COL_P_FIRST>(g, p, a, twtab, st); VD_T1()
     RowArgs r = row_args(g, &p);
     r.coef = coef;
     r.cscale = g.ntot_inv;
@@ -1256,7 +1471,7 @@ void op_apply(const Geom& g, const OpParams& p, const void* v, void* y, const Op
     d.in[0] = t0;
     d.in[1] = t1;
     d.out[0] = y;
-    VD_T0(4) last_pass<R, COL_P_LAST>(g, d, p.gs, twtab, st); VD_T1()
+    VD_T0(4) last_pass<R, COL_P_LAST>(g, p, d, twtab, st); VD_T1()
   } else {
     if (g.nz == 1) {
       RowArgs r = row_args(g, &p);
@@ -1273,7 +1488,7 @@ void op_apply(const Geom& g, const OpParams& p, const void* v, void* y, const Op
     a.inner = (int)zin;
     a.in[0] = v;
     a.out[0] = t0;
-    VD_T0(5) launch_col<R, COL_H_FIRST>(g.nz, a, twtab, st); VD_T1()
+    VD_T0(5) first_pass<R, COL_H_FIRST>(g, p, a, twtab, st); VD_T1()
     if (g.ny > 1) {
       ColArgs b = col_args_fft(g, p);
       b.outer = g.nz;
@@ -1304,7 +1519,7 @@ void op_apply(const Geom& g, const OpParams& p, const void* v, void* y, const Op
     d.in[0] = t0;
     d.in[1] = v;
     d.out[0] = y;
-    VD_T0(9) last_pass<R, COL_H_LAST>(g, d, p.gs, twtab, st); VD_T1()
+    VD_T0(9) last_pass<R, COL_H_LAST>(g, p, d, twtab, st); VD_T1()
   }
 #undef VD_T0
 #undef VD_T1
@@ -1350,7 +1565,7 @@ void op_apply_batch(const Geom& g, const OpParams& p, const OpBatch& b, const vo
     a.outer = 1;
     a.inner = (int)zin;
     for (int k = 0; k < nb; ++k) a.sys[k] = sys_of(k, {b.v[k]}, {b.t[k][0]}, true);
-    timed(5, 2.0 * nb, [&] { launch_col<R, COL_H_FIRST>(g.nz, a, twtab, st); });
+    timed(5, 2.0 * nb, [&] { first_pass<R, COL_H_FIRST>(g, p, a, twtab, st); });
     ColArgs c = col(true);
     c.outer = g.nz;
     c.inner = g.M;
@@ -1370,7 +1585,7 @@ void op_apply_batch(const Geom& g, const OpParams& p, const OpBatch& b, const vo
     d.outer = 1;
     d.inner = (int)zin;
     for (int k = 0; k < nb; ++k) d.sys[k] = sys_of(k, {b.t[k][0], b.v[k]}, {b.y[k]}, true);
-    timed(9, 3.0 * nb, [&] { last_pass<R, COL_H_LAST>(g, d, p.gs, twtab, st); });
+    timed(9, 3.0 * nb, [&] { last_pass<R, COL_H_LAST>(g, p, d, twtab, st); });
     return;
   }
   // pressure (2D and 3D grids): the passes of op_apply, system k on
@@ -1379,7 +1594,7 @@ void op_apply_batch(const Geom& g, const OpParams& p, const OpBatch& b, const vo
   a.outer = 1;
   a.inner = (int)zin;
   for (int k = 0; k < nb; ++k) a.sys[k] = sys_of(k, {b.v[k]}, {b.t[k][0], b.t[k][1]}, true);
-  timed(0, 3.0 * nb, [&] { first_pass<R>(g, a, p.gs, twtab, st); });
+  timed(0, 3.0 * nb, [&] { first_pass<R, COL_P_FIRST>(g, p, a, twtab, st); });
   RowArgs r = row_args(g, &p);
   r.gate = nullptr;
   r.in_scale = nullptr;
@@ -1412,7 +1627,7 @@ void op_apply_batch(const Geom& g, const OpParams& p, const OpBatch& b, const vo
   d.outer = 1;
   d.inner = (int)zin;
   for (int k = 0; k < nb; ++k) d.sys[k] = sys_of(k, {b.t[k][0], b.t[k][1]}, {b.y[k]}, false);
-  timed(4, 3.0 * nb, [&] { last_pass<R, COL_P_LAST>(g, d, p.gs, twtab, st); });
+  timed(4, 3.0 * nb, [&] { last_pass<R, COL_P_LAST>(g, p, d, twtab, st); });
 }
 
 template <typename R>

@@ -45,6 +45,22 @@ struct GsCarry {
   VecPtrs V[kMaxBatch] = {};
 };
 
+// Parts of a CG or RMR step that the operator's passes carry (op_carries_rec).  With
+// dots, the last pass forms (y, p) (p: the direction, RMR: the residual) and for RMR
+// |y|^2.  With ends, the first pass takes the end of the step before, whose
+// rec_step left nb block partials: the stopping test, and for CG beta and the new
+// direction p = M^-1 r + beta p, which is then the pass's input (in place).
+struct RecCarry {
+  bool cg = false, dots = false, ends = false;
+  bool precond = false;  // M^-1 of CG's direction (the pass itself applies none)
+  int nb = 0;
+  int slot = 0;          // DevState::rz entry of the step before
+  DevState* st = nullptr;
+  double* partial = nullptr;
+  const void* r = nullptr;
+  void* p = nullptr;
+};
+
 struct OpParams {
   int kind;                  // OpKind
   double rho0;               // constant density of the preconditioner
@@ -53,6 +69,7 @@ struct OpParams {
   const double* in_scale;    // optional device scalar multiplying the input
   const int* gate = nullptr; // optional device flag: when nonzero every pass returns at once
   const GsCarry* gs = nullptr;  // optional Gram-Schmidt work of the passes (gate: the states' halt flags)
+  const RecCarry* rec = nullptr;  // optional CG or RMR work of the passes
 };
 
 // Work buffers of one operator application (spectral, same precision as the
@@ -97,6 +114,11 @@ struct Prof {
 bool op_carries_gs(const Geom& g, int kind);
 bool op_carries_check(const Geom& g, int kind);
 int op_dot_blocks(const Geom& g);
+// The same for CG and RMR steps (single systems), and the blocks whose partials
+// the dots leave (0: more than a reduction takes, the passes carry no dots).
+bool op_carries_rec(const Geom& g);
+template <typename R>
+int op_rec_blocks(const Geom& g, int kind);
 
 // y = A (M^-1 (s v)) in spectral space.  R = float or double.
 template <typename R>

@@ -350,9 +350,10 @@ struct Krylov {
   }
 
   void apply(const void* v, void* y, bool with_prec, const double* in_scale = nullptr, const int* gate = nullptr,
-             const GsCarry* gs = nullptr) {
+             const GsCarry* gs = nullptr, const RecCarry* rec = nullptr) {
     OpParams p = cfg.op;
     p.gs = gs;
+    p.rec = rec;
     p.precond = with_prec ? cfg.op.precond : 0;
     p.in_scale = in_scale;
     p.gate = gate;
@@ -508,6 +509,26 @@ struct Krylov {
     return done;
   }
 
+  // What the operator passes of step j of a CG or RMR run carry, and what is left
+  // to rec_step.
+  bool carry_rec(bool is_cg, int j, int jlast, const void* r, void* p, RecCarry* c, RecParts* parts) {
+    if (!op_carries_rec(g)) return false;
+    parts->dot_blocks = op_rec_blocks<R>(g, cfg.op.kind);
+    parts->slot = j & 1;
+    parts->finish = j == jlast;
+    c->cg = is_cg;
+    c->dots = parts->dot_blocks > 0;
+    c->ends = j > 0;
+    c->precond = cfg.op.precond != 0;
+    c->nb = rec_step_blocks(g);
+    c->slot = (j - 1) & 1;
+    c->st = G->dst;
+    c->partial = G->partial;
+    c->r = r;
+    c->p = p;
+    return true;
+  }
+
   SolveOut cg(const void* b, void* x, double bnorm) {
     if (dense_prec()) return cg_eigen(b, x, bnorm);
     SolveOut o;
@@ -531,10 +552,13 @@ struct Krylov {
       else ck(hipMemcpyAsync(p, r, G->nspec * elem_bytes(prec), hipMemcpyDeviceToDevice, G->st));
       StepState t;
       o.iters += run_queued(jlast, run, t, bnorm, [&](int j, const int* gate) {
-        if (j > 0) cg_p<R>(g, gated(gate), p, r, G->dst, G->st);  // p = M^-1 r + beta p
-        apply(p, q, false, nullptr, gate);
-        dot_partials<R>(g, q, p, false, G->partial, G->st, gate);
-        rec_step<R>(g, cfg.op, false, x, r, rn, p, q, G->dst, G->partial, G->st);
+        RecCarry c;
+        RecParts parts;
+        const bool carry = carry_rec(true, j, jlast, r, p, &c, &parts);
+        if (j > 0 && !carry) cg_p<R>(g, gated(gate), p, r, G->dst, G->st);  // p = M^-1 r + beta p
+        apply(p, q, false, nullptr, gate, nullptr, carry ? &c : nullptr);
+        if (!c.dots) dot_partials<R>(g, q, p, false, G->partial, G->st, gate);
+        rec_step<R>(g, cfg.op, false, x, r, rn, p, q, G->dst, G->partial, G->st, parts);
         std::swap(r, rn);
       });
       if (t.bad || !(t.nrm2 == t.nrm2)) { o.status = VD_EBREAKDOWN; return o; }
@@ -611,11 +635,14 @@ struct Krylov {
       const unsigned long long run = new_run(G, jlast);
       rec_init(G->dst, bnorm, cfg.rtol, jlast, run, G->st);
       StepState t;
-      o.iters += run_queued(jlast, run, t, bnorm, [&](int, const int* gate) {
-        apply(r, w, true, nullptr, gate);  // w = A M^-1 r
+      o.iters += run_queued(jlast, run, t, bnorm, [&](int j, const int* gate) {
+        RecCarry c;
+        RecParts parts;
+        const bool carry = carry_rec(false, j, jlast, nullptr, r, &c, &parts);
+        apply(r, w, true, nullptr, gate, nullptr, carry ? &c : nullptr);  // w = A M^-1 r
         if (!dense_prec()) {
-          dot_partials<R>(g, w, r, true, G->partial, G->st, gate);
-          rec_step<R>(g, cfg.op, true, x, r, rn, nullptr, w, G->dst, G->partial, G->st);
+          if (!c.dots) dot_partials<R>(g, w, r, true, G->partial, G->st, gate);
+          rec_step<R>(g, cfg.op, true, x, r, rn, nullptr, w, G->dst, G->partial, G->st, parts);
           std::swap(r, rn);
           return;
         }

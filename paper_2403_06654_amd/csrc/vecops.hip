@@ -52,24 +52,6 @@ __device__ __forceinline__ void block_store(const double* acc, int k_used, doubl
 // powers of two), so the kx = 0 test is a mask, not a 64-bit division
 __device__ __forceinline__ double spec_w(size_t e, int M) { return (e & (size_t)(M - 1)) == 0 ? 1.0 : 2.0; }
 
-// Sum of one value's nblk <= kRedBlocks block partials by one wavefront, in a
-// fixed order: lanes stride over them, then the wavefront's tree.  Every lane
-// issues all its loads before the first addition.  A loop that added each
-// partial as it arrived paid up to sixteen dependent load latencies: on 1024
-// partials of 9-16 values k_gs_prep took 6.8 us (4.5 now) and k_gs_check 9.4 us
-// (5.2 now).
-__device__ __forceinline__ double sum_partials(const double* __restrict__ p, int nblk) {
-  constexpr int Q = kRedBlocks / 64;
-  const int lane = threadIdx.x & 63;
-  double v[Q];
-#pragma unroll
-  for (int q = 0; q < Q; ++q) v[q] = lane + 64 * q < nblk ? p[lane + 64 * q] : 0.0;
-  double s = v[0];
-#pragma unroll
-  for (int q = 1; q < Q; ++q) s += v[q];
-  return wave_sum(s);
-}
-
 // One wave per output value (a 1024-thread block).  No block-wide barrier.
 __device__ __forceinline__ void reduce_values(const double* __restrict__ partial, int nblk, int K, double scale,
                                               double* __restrict__ out) {
@@ -78,43 +60,6 @@ __device__ __forceinline__ void reduce_values(const double* __restrict__ partial
     const double v = sum_partials(partial + (size_t)i * kRedBlocks, nblk);
     if (lane == 0) out[i] = v * scale;
   }
-}
-
-// Scalar steps of CG and RMR, taken by one thread on the reduced values
-// (passed in: see k_reduce) and on the state as it was loaded ahead of them.
-struct RecState {
-  double rz, stop_bnorm, stop_rtol;
-  int step, bad, jlast;
-  Mail* mail;
-  unsigned long long run;
-};
-__device__ __forceinline__ RecState rec_state(const DevState* st) {
-  return RecState{st->rz, st->stop_bnorm, st->stop_rtol, st->step, st->bad, st->jlast, st->mail, st->run};
-}
-__device__ __forceinline__ void cg_beta_step(DevState* st, const RecState& s, double rzn) {
-  // beta = (r, M r)_new / (r, M r)
-  const double beta = s.rz != 0.0 ? rzn / s.rz : 0.0;
-  st->beta = beta;
-  st->rz = rzn;
-  if (!isfinite(beta)) st->bad = 1;
-}
-__device__ __forceinline__ void rmr_alpha_step(DevState* st, double rw, double ww) {  // alpha = (r, w) / (w, w)
-  st->alpha = ww > 0.0 ? rw / ww : 0.0;
-  if (!isfinite(st->alpha)) st->bad = 1;
-}
-// Stopping test of a CG or RMR step on its recursive residual (n2 = its
-// square, also in st->nrm2), the host loop's test taken on the device: a
-// non-finite scalar, the tolerance, or the last step of the run sets halt.
-// step counts the steps.
-__device__ __forceinline__ bool rec_check_step(DevState* st, const RecState& s, double n2) {
-  const int j = s.step;
-  st->step = j + 1;
-  const double rn = n2 < 0.0 ? 0.0 : sqrt(n2);
-  const bool bad = s.bad != 0;
-  const bool halt = bad || !(n2 == n2) || rn / s.stop_bnorm <= s.stop_rtol || j >= s.jlast;
-  if (halt) st->halt = 1;
-  post_step(s.mail, s.run, j, rn, n2, bad, halt, 0);
-  return halt;
 }
 
 // The final reduction, optionally followed (same launch, after a block
@@ -832,7 +777,7 @@ void dot_partials(const Geom& g, const void* x, const void* v, bool want_norm, d
 // Thread 0 of block 0 keeps the state.  Ends with a block barrier.
 template <bool RMR>
 __device__ __forceinline__ double step_alpha(DevState* st, const double* __restrict__ partial, int nb,
-                                             double scale) {
+                                             double scale, int slot) {
   __shared__ double sh[2];
   const int w = threadIdx.x >> 6;
   if (w < (RMR ? 2 : 1)) {
@@ -846,7 +791,7 @@ __device__ __forceinline__ double step_alpha(DevState* st, const double* __restr
     a = sh[1] > 0.0 ? sh[0] / sh[1] : 0.0;
     bad = !isfinite(a);
   } else {  // rz / (p, A p)
-    a = sh[0] != 0.0 ? st->rz / sh[0] : 0.0;
+    a = sh[0] != 0.0 ? st->rz[slot] / sh[0] : 0.0;
     bad = !isfinite(a) || sh[0] <= 0.0;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -866,9 +811,9 @@ __global__ __launch_bounds__(256) void k_rec_step(C2<R>* __restrict__ x, const C
                                                   C2<R>* __restrict__ rnew, const C2<R>* __restrict__ p,
                                                   const C2<R>* __restrict__ q, DevState* st, Geom g, int kind,
                                                   double rho0, double nu, size_t n, double* partial, int nb,
-                                                  double scale) {
+                                                  double scale, int slot) {
   if (st->halt) return;
-  const double a = step_alpha<RMR>(st, partial, nb, scale);
+  const double a = step_alpha<RMR>(st, partial, nb, scale, slot);
   double acc[2] = {0.0, 0.0};
   for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (size_t)gridDim.x * 256) {
     const C2<R> xv = ldg(x + e), rv = ldg(r + e), qv = ldg(q + e);
@@ -902,17 +847,21 @@ __global__ __launch_bounds__(256) void k_rec_step(C2<R>* __restrict__ x, const C
   }
   block_store<2>(acc, RMR ? 1 : 2, partial + 2 * kRedBlocks + blockIdx.x);
 }
+int rec_step_blocks(const Geom& g) { return nblk(nspec(g)); }
 template <typename R>
 void rec_step(const Geom& g, const OpParams& op, bool rmr, void* x, const void* r, void* rnew, const void* p,
-              const void* q, DevState* st, double* partial, hipStream_t s) {
+              const void* q, DevState* st, double* partial, hipStream_t s, const RecParts& parts) {
   const size_t n = nspec(g);
-  const int nb = nblk(n), kind = op.precond ? op.kind : -1;
+  const int nb = nblk(n), kind = op.precond ? op.kind : -1, nbd = parts.dot_blocks ? parts.dot_blocks : nb;
   if (rmr)
     hipLaunchKernelGGL((k_rec_step<R, true>), dim3(nb), dim3(256), 0, s, (C2<R>*)x, (const C2<R>*)r, (C2<R>*)rnew,
-                       (const C2<R>*)p, (const C2<R>*)q, st, g, kind, op.rho0, op.nu, n, partial, nb, g.ntot_inv);
+                       (const C2<R>*)p, (const C2<R>*)q, st, g, kind, op.rho0, op.nu, n, partial, nbd, g.ntot_inv,
+                       parts.slot);
   else
     hipLaunchKernelGGL((k_rec_step<R, false>), dim3(nb), dim3(256), 0, s, (C2<R>*)x, (const C2<R>*)r, (C2<R>*)rnew,
-                       (const C2<R>*)p, (const C2<R>*)q, st, g, kind, op.rho0, op.nu, n, partial, nb, g.ntot_inv);
+                       (const C2<R>*)p, (const C2<R>*)q, st, g, kind, op.rho0, op.nu, n, partial, nbd, g.ntot_inv,
+                       parts.slot);
+  if (!parts.finish) return;
   reduce(partial + 2 * kRedBlocks, nb, rmr ? 1 : 2, g.ntot_inv, st->red, s, &st->halt,
          Post{rmr ? POST_REC_CHECK : POST_CG_STEP, st});
 }
@@ -929,7 +878,7 @@ __global__ __launch_bounds__(256) void k_eig_step(C2<R>* __restrict__ xt, C2<R>*
                                                   const C2<R>* __restrict__ qq, DevState* st, EigDiag d, size_t n,
                                                   int M, double* partial, int nb, double scale) {
   if (st->halt) return;
-  const double a = step_alpha<false>(st, partial, nb, scale);
+  const double a = step_alpha<false>(st, partial, nb, scale, 0);
   double acc[2] = {0.0, 0.0};
   for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (size_t)gridDim.x * 256) {
     const C2<R> xv = ldg(xt + e), pv = ldg(pt + e), rv = ldg(r + e), tv = ldg(rt + e), qv = ldg(qq + e),
@@ -1308,7 +1257,7 @@ void kcoef_finish(const double* rho, const double* lap_psi, double* kc64, float*
                            const Post&);                                                                       \
   template void dot_partials<R>(const Geom&, const void*, const void*, bool, double*, hipStream_t, const int*); \
   template void rec_step<R>(const Geom&, const OpParams&, bool, void*, const void*, void*, const void*,        \
-                            const void*, DevState*, double*, hipStream_t);                                     \
+                            const void*, DevState*, double*, hipStream_t, const RecParts&);                                     \
   template void eig_step<R>(const Geom&, const EigDiag&, void*, void*, void*, const void*, const void*,        \
                             DevState*, double*, hipStream_t);                                                  \
   template void eig_p<R>(const Geom&, const EigDiag&, void*, const void*, bool, DevState*, double*,            \

@@ -56,7 +56,8 @@ struct DevState {
   double hn;                 // norm of the newest orthogonalised vector
   int reorth;                // second Gram-Schmidt pass ran for this step
   int nreorth;               // second passes of the current cycle
-  double alpha, beta, rz, rz_new;
+  double alpha, beta;
+  double rz[2];              // CG: (r, M^-1 r); carried steps alternate between the two
   // Krylov stopping test, evaluated on the device after each step (GMRES:
   // resid / stop_bnorm <= stop_rtol on the Givens estimate; CG and RMR: on
   // the recursive residual), a non-finite scalar, or step jlast of the cycle
@@ -160,9 +161,18 @@ void dot_partials(const Geom& g, const void* x, const void* v, bool want_norm, d
 //   rnew = r - alpha q           (q: w for RMR; rnew must be another buffer)
 // with the new |r|^2 (red[0]), for CG also (r, M^-1 r) (red[1]), the stopping
 // test and CG's beta.  Gated by st->halt.
+// Where the operator's passes carry parts of the step (RecCarry): dot_blocks left
+// the dots' partials, slot holds rz, and without finish the test and beta are
+// left to the next step's first pass.
+struct RecParts {
+  int dot_blocks = 0;
+  int slot = 0;
+  bool finish = true;
+};
 template <typename R>
 void rec_step(const Geom& g, const OpParams& op, bool rmr, void* x, const void* r, void* rnew, const void* p,
-              const void* q, DevState* st, double* partial, hipStream_t s);
+              const void* q, DevState* st, double* partial, hipStream_t s, const RecParts& parts = RecParts{});
+int rec_step_blocks(const Geom& g);  // block partials that rec_step leaves
 // CG on a Chebyshev grid with its dense preconditioner V D V^T, in the basis V
 // (rt = V^T r, p = V pt, x accumulated as V xt; qq: q and V^T q, one after the
 // other; lam, scale, sx: D as in the contraction's epilogue): after

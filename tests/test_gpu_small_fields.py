@@ -87,6 +87,39 @@ def test_steps_carried_by_the_passes(shape, precision):
     assert wi["status"] == 0 and np.linalg.norm(res) <= 1.01e-10 * np.linalg.norm(f)
 
 
+# CG and RMR work inside the first and last pass, for both operators: each z length
+# from the shortest to the longest that carries it (512) and the first that does not,
+# on small fields and above their limit, partial tiles, and fields whose last pass
+# has more blocks than a reduction takes (its dots then are a launch of their own)
+@pytest.mark.parametrize("shape", [(16, 16), (512, 64), (1024, 16), (16, 16, 16), (64, 32, 64), (128, 16, 16),
+                                   (256, 16, 32), (16, 128, 256), (32, 128, 128), (128, 64, 64), (64, 1024, 32),
+                                   (512, 1024), (16, 512, 512)])
+@pytest.mark.parametrize("precision", ["fp64", "fp32_refine"])
+def test_cg_and_rmr_carried_by_the_passes(shape, precision):
+    """The oracle's operator gives every returned field a true residual of 1e-10
+    (1% for its own rounding); a second solve returns the same bits; a budget
+    ends the run after that many steps."""
+    from paper_2403_06654_amd.api import Grid
+    rho = smooth_density(shape, 6, 1.0, 2.0)
+    f = workloads.band_limited(shape, min(shape) // 4, seed=5)
+    b, _ = operators.project_range(-f, operators.nullspace_basis(shape))
+    g = Grid(shape)
+    g.set_density(to_dev(rho))
+    fd = to_dev(f)
+    for solver in ("cg", "rmr"):
+        p, info = g.solve_pressure(fd, solver=solver, precision=precision)
+        again, _ = g.solve_pressure(fd, solver=solver, precision=precision)
+        x = to_host(p)
+        assert info["status"] == 0 and np.array_equal(x, to_host(again))
+        assert np.linalg.norm(operators.apply_pressure(x, rho) - b) <= 1.01e-10 * np.linalg.norm(b)
+        _, cut = g.solve_pressure(fd, solver=solver, max_iter=3)
+        assert cut["status"] == 1 and cut["iterations"] == 3
+        w, wi = g.solve_helmholtz(fd, 0.05, solver=solver, precision=precision)
+        res = operators.apply_helmholtz(to_host(w), rho, 0.05) - f
+        assert wi["status"] == 0 and np.linalg.norm(res) <= 1.01e-10 * np.linalg.norm(f)
+    g.close()
+
+
 # every column length on either side of the limit, the limit itself, and a y
 # length (512) that the small configuration is not built for beside z and x
 # lengths that it is; tolerances as for the other operator parity tests
