@@ -224,8 +224,8 @@ __device__ __forceinline__ KSys* block_sys() {
 //   - every block of the first pass reduces the check dots for itself while its
 //     column is on the way, and one more block takes the rotations, so that
 //     their serial chain runs beside the transforms.
-// Solves, before -> now (1481 / 15024 us with neither this nor the small kernels):
-// 32^3 FP64 897 -> 747 us, 24 served 2D requests 11.7 -> 11.5 ms.
+// 32^3 FP64, us a launch, on their own -> here: dots 4.1 + z-last 3.8 -> 6.0, check
+// 7.0 + z-first 4.3 -> 6.3; solve 897 -> 677 us, 24 served 2D requests 11.7 -> 11.2 ms.
 struct ColGs {
   int nv;      // last pass: vectors of the dots; first pass: vectors of the step to finish
   int nb;      // first pass: blocks that left the check dots
