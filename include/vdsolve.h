@@ -386,7 +386,10 @@ vd_status vd_ns_set_state(vd_ns* h, const double* u, const double* rho, const do
  * (requires s > 0). */
 vd_status vd_ns_init_taylor_green(vd_ns* h);
 /* Advance nsteps steps; info (may be NULL) describes the last one.
- * Returns the worse of the last step's solve statuses. */
+ * Returns the worse of the last step's solve statuses.  A step that cannot be
+ * taken (VD_EDOMAIN: its mid-step density is not positive; VD_EBREAKDOWN) ends
+ * the call: the handle then holds the state, the time and the history of the
+ * last completed step, and info is not written. */
 vd_status vd_ns_step(vd_ns* h, int nsteps, vd_ns_info* info);
 /* Copy the state out (device arrays; any may be NULL). */
 vd_status vd_ns_get_state(vd_ns* h, double* u, double* rho, double* p, double* t);

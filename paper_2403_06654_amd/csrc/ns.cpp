@@ -375,9 +375,9 @@ double viscous_residual(vd_ns* h, const double* b, const double* x, double* r) {
 }
 
 // Right-preconditioned GMRES(m) on A x = x - dt/2 zeta(rho^(n+1/2), x) = b
-// (stacks of three spectra); x holds the initial guess.  The steps are queued
-// one ahead of the host, as in vdsolve.cpp.
-void solve_viscous(vd_ns* h, const double* b, double* x, int& iters, int& status, double& relres) {
+// (stacks of three spectra) from the initial guess x0, which is kept.  The steps
+// are queued one ahead of the host, as in vdsolve.cpp.
+void solve_viscous(vd_ns* h, const double* b, const double* x0, double* x, int& iters, int& status, double& relres) {
   const size_t n3 = 3 * h->N;
   const int m = h->prm.restart;
   const double rtol = h->prm.visc_rtol;
@@ -404,16 +404,15 @@ void solve_viscous(vd_ns* h, const double* b, double* x, int& iters, int& status
     timed(h, 2, vb * (2.0 * j + 5.0),
           [&] { gs_orthogonalize<double>(h->g3, vec(j + 1), P, j + 1, h->dst, h->part, h->st); });
   };
-  double beta = viscous_residual(h, b, x, vec(0));
+  const double* cur = x0;  // the iterate: x from the first cycle's end on
+  double beta = viscous_residual(h, b, cur, vec(0));
   while (true) {
     relres = beta / bn;
-    if (!(beta == beta)) {
-      status = VD_EBREAKDOWN;
-      return;
-    }
-    if (relres <= rtol) return;
-    if (iters >= h->prm.max_iter) {
-      status = VD_NOT_CONVERGED;
+    const bool ok = relres <= rtol;
+    if (!(beta == beta)) status = VD_EBREAKDOWN;
+    else if (!ok && iters >= h->prm.max_iter) status = VD_NOT_CONVERGED;
+    if (ok || status != VD_OK) {
+      if (cur != x) ck(hipMemcpyAsync(x, cur, n3 * sizeof(double), hipMemcpyDeviceToDevice, h->st));
       return;
     }
     const int jlast = std::min(m, h->prm.max_iter - iters) - 1;
@@ -438,8 +437,9 @@ void solve_viscous(vd_ns* h, const double* b, double* x, int& iters, int& status
     for (int i = 0; i < k; ++i) P.p[i] = vec(i);
     lincomb<double>(h->g3, h->z3, P, k, h->dst->coef, h->st);
     for (int c = 0; c < 3; ++c)
-      precond_axpy<double>(h->g, op, x + c * h->N, h->z3 + c * h->N, nullptr, 1.0, h->st);
-    beta = viscous_residual(h, b, x, vec(0));
+      precond_axpy<double>(h->g, op, x + c * h->N, h->z3 + c * h->N, nullptr, 1.0, h->st, cur + c * h->N);
+    cur = x;
+    beta = viscous_residual(h, b, cur, vec(0));
   }
 }
 
@@ -472,8 +472,9 @@ void manufactured(vd_ns* h, double t) {
   lin(h, h->Sh, N, {{1.0, h->Sh}, {1.0, h->z3}, {-1.0 / (h->prm.re * h->prm.sc), lap}});
 }
 
-// phi from the spectrum of div(u*) / dt, into phih
-vd_status solve_pressure(vd_ns* h, double* div, vd_solve_info* pi) {
+// phi (a spectrum) from the spectrum of div(u*) / dt, with the last step's as the
+// initial guess
+vd_status solve_pressure(vd_ns* h, const double* div, double* phih, vd_solve_info* pi) {
   vd_solve_opts o;
   vd_default_opts(&o);
   o.solver = h->prm.pres_solver;
@@ -484,7 +485,7 @@ vd_status solve_pressure(vd_ns* h, double* div, vd_solve_info* pi) {
   o.use_x0 = 1;
   vd_status ps = VD_OK;
   if (h->prm.pres_form == VD_FORM_L) {
-    timed(h, 1, 0.0, [&] { ps = grid_solve_pressure_spec(h->grid, div, h->phih, &o, pi); });
+    timed(h, 1, 0.0, [&] { ps = grid_solve_pressure_spec(h->grid, div, h->phih, phih, &o, pi); });
     return ps;
   }
   // the modified form changes the unknown in physical space
@@ -492,10 +493,15 @@ vd_status solve_pressure(vd_ns* h, double* div, vd_solve_info* pi) {
   inv(h, div, f);
   inv(h, h->phih, phi);
   timed(h, 1, 0.0, [&] { ps = vd_solve_pressure(h->grid, f, phi, &o, pi); });
-  if (ps >= 0) fwd(h, phi, h->phih);
+  if (ps >= 0) fwd(h, phi, phih);
   return ps;
 }
 
+// One step.  Everything that can refuse it (a mid-step density that is not
+// positive, a breakdown of the pressure solve) works in scratch: the state, the
+// advection terms, the last phi and the time change together at the end, so a
+// step that throws leaves the state of the last completed one, and is the same
+// step when it is tried again.
 void step_once(vd_ns* h) {
   const size_t N = h->N;
   const double dt = h->prm.dt, re = h->prm.re, sc = h->prm.sc;
@@ -544,31 +550,34 @@ void step_once(vd_ns* h) {
   z.nout = h->nu[0];
   zeta(h, z, true, false);
   fwd_columns(h, h->bh, 3);
-  std::swap(h->nu[0], h->nu[1]);  // the current terms become the previous ones
-  std::swap(h->nrh[0], h->nrh[1]);
-  h->have_prev = true;
+  double* us = h->x3h;
   int vit = 0, vst = 0;
   double vres = 0;
-  solve_viscous(h, h->bh, h->uh, vit, vst, vres);  // uh: u^n to u*
+  solve_viscous(h, h->bh, h->uh, us, vit, vst, vres);
   // 5. pressure equation
-  ns_div(h->g, h->uh, h->ns, 1.0 / dt, h->z3, h->st);
+  ns_div(h->g, us, h->ns, 1.0 / dt, h->z3, h->st);
   if (vd_set_density(h->grid, h->rh) != VD_OK) throw Err{VD_EDOMAIN};
   vd_solve_info pi{};
-  const vd_status ps = solve_pressure(h, h->z3, &pi);
+  double* phi = h->Sh;  // the mass source has been used
+  const vd_status ps = solve_pressure(h, h->z3, phi, &pi);
   if (ps < 0 && ps != VD_NOT_CONVERGED) throw Err{ps};
-  // 6. projection
-  scalar_rows(h, h->phih);
-  grad_over_rho(h, h->x3h, false);
-  lin(h, h->uh, 3 * N, {{1.0, h->uh}, {-dt, h->x3h}});
+  // 6. projection (from here on the step cannot be refused)
+  scalar_rows(h, phi);
+  grad_over_rho(h, h->z3, false);
+  lin(h, h->uh, 3 * N, {{1.0, us}, {-dt, h->z3}});
   // 7. pressure update: p += phi - (div grad)^-1 div(dt/2 rho zeta(rho, grad(phi) / rho))
-  vector_rows(h, h->x3h);
+  vector_rows(h, h->z3);
   z = zeta_args(h, 0.0, 0.5 * dt, h->q3);
   z.wconst = 1.0 / re;  // rho times 1 / (rho Re)
   zeta(h, z, false, false);
   fwd_columns(h, h->q3, 3);
-  ns_pressure(h->g, h->q3, h->ns, h->phih, h->ph, h->st);
-  // rho^(n+1) becomes the state
+  ns_pressure(h->g, h->q3, h->ns, phi, h->ph, h->st);
+  std::swap(h->phih, h->Sh);
+  // rho^(n+1) becomes the state, the current advection terms the previous ones
   std::swap(h->rhoh, h->rho1h);
+  std::swap(h->nu[0], h->nu[1]);
+  std::swap(h->nrh[0], h->nrh[1]);
+  h->have_prev = true;
   h->t += dt;
   ++h->steps;
   h->last.t = h->t;
@@ -729,9 +738,11 @@ vd_status vd_ns_init_taylor_green(vd_ns* h) {
 vd_status vd_ns_step(vd_ns* h, int nsteps, vd_ns_info* info) {
   if (!h || nsteps < 0) return VD_EINVAL;
   if (!h->have_state) return VD_EINVAL;
+  int done = 0;
   try {
-    for (int k = 0; k < nsteps; ++k) {
+    while (done < nsteps) {
       step_once(h);
+      ++done;
       if (h->prof) {
         ck(hipStreamSynchronize(h->st));
         prof_flush(h);
@@ -743,6 +754,14 @@ vd_status vd_ns_step(vd_ns* h, int nsteps, vd_ns_info* info) {
     if (h->prof) prof_flush(h);
   } catch (const Err& e) {
     hipGetLastError();
+    if (done > 0) {  // the state is that of the last completed step
+      try {
+        state_to_physical(h);
+        ck(hipStreamSynchronize(h->st));
+      } catch (const Err&) {
+        hipGetLastError();
+      }
+    }
     return e.s;
   }
   if (info) *info = h->last;
@@ -804,7 +823,7 @@ vd_status vd_ns_project(vd_ns* h, const double* rho, const double* u, double* ou
     o.rtol = h->prm.pres_rtol;
     o.max_iter = h->prm.max_iter;
     double* phi = h->z3 + N;
-    ps = grid_solve_pressure_spec(h->grid, h->z3, phi, &o, info);
+    ps = grid_solve_pressure_spec(h->grid, h->z3, nullptr, phi, &o, info);
     if (ps < 0 && ps != VD_NOT_CONVERGED) return ps;
     ns_recip(rho, h->prm.re, h->cirr, N, h->st);
     scalar_rows(h, phi);

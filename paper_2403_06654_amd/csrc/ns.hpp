@@ -17,9 +17,9 @@ const Geom& grid_geom(const vd_grid* G);
 const void* grid_twiddles(const vd_grid* G);
 
 // vd_solve_pressure (direct form, Fourier grid) from and to packed spectra on
-// the grid's stream: p also holds the initial guess if opts->use_x0.
-vd_status grid_solve_pressure_spec(vd_grid* G, const void* fhat, void* phat, const vd_solve_opts* opts,
-                                   vd_solve_info* info);
+// the grid's stream; x0hat: the initial guess if opts->use_x0.
+vd_status grid_solve_pressure_spec(vd_grid* G, const void* fhat, const void* x0hat, void* phat,
+                                   const vd_solve_opts* opts, vd_solve_info* info);
 
 // A stack is nf fields one after another, `stride` slots (one packed field)
 // apart.  Grids are n^3, n a power of two in [16, 512].  gate (optional): a

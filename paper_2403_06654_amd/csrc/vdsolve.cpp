@@ -1506,6 +1506,7 @@ struct SolveCtx {
   const double* f;
   double* x;
   bool spec = false;  // f and x are packed spectra (pressure, direct form, Fourier grid)
+  const double* x0 = nullptr;  // and so is the initial guess, which x does not hold
   vd_solve_opts o;
   vd_solve_info info;
 };
@@ -1636,7 +1637,7 @@ static vd_status solve_impl(vd_grid* G, void* c) {
       rho_sqrt_mul(G->rho, x, t, true, 1.0, G->nreal, G->st);
       fwd_transform(G->g, t, x64, nullptr, G->tw64, G->st);
     } else if (s->o.use_x0) {
-      if (s->spec) ck(hipMemcpyAsync(x64, x, G->nspec * 16, hipMemcpyDeviceToDevice, G->st));
+      if (s->spec) ck(hipMemcpyAsync(x64, s->x0, G->nspec * 16, hipMemcpyDeviceToDevice, G->st));
       else fwd_transform(G->g, x, x64, nullptr, G->tw64, G->st);
       if (G->g.cheb) c2_project(G->g, x64, G->dsmall + 1, G->st);
       else if (s->kind == VD_OP_PRESSURE) project_range(G->g, x64, G->dsmall + 1, G->st);
@@ -1692,7 +1693,8 @@ static vd_status reject(vd_solve_info* info, vd_status s) {
 }
 
 static vd_status solve_common(vd_grid* G, int kind, double nu, int ncomp, const double* f, double* x,
-                              const vd_solve_opts* opts, vd_solve_info* info, bool spec = false) {
+                              const vd_solve_opts* opts, vd_solve_info* info, bool spec = false,
+                              const double* x0 = nullptr) {
   if (!G || !f || !x || ncomp < 1) return reject(info, VD_EINVAL);
   if (!G->has_rho) return reject(info, VD_EINVAL);
   SolveCtx c{};
@@ -1702,6 +1704,7 @@ static vd_status solve_common(vd_grid* G, int kind, double nu, int ncomp, const 
   c.f = f;
   c.x = x;
   c.spec = spec;
+  c.x0 = x0;
   if (opts) c.o = *opts;
   else vd_default_opts(&c.o);
   if (!opts_ok(c.o)) return reject(info, VD_EINVAL);
@@ -1932,8 +1935,8 @@ vd_status vd_profile_read(vd_grid* G, double* ms, long long* count, double* byte
 
 }  // extern "C"
 
-vd_status vd::grid_solve_pressure_spec(vd_grid* G, const void* fhat, void* phat, const vd_solve_opts* opts,
-                                       vd_solve_info* info) {
+vd_status vd::grid_solve_pressure_spec(vd_grid* G, const void* fhat, const void* x0hat, void* phat,
+                                       const vd_solve_opts* opts, vd_solve_info* info) {
   if (G && (G->g.cheb || (opts && opts->formulation != VD_FORM_L))) return reject(info, VD_ENOTSUP);
-  return solve_common(G, VD_OP_PRESSURE, 0.0, 1, (const double*)fhat, (double*)phat, opts, info, true);
+  return solve_common(G, VD_OP_PRESSURE, 0.0, 1, (const double*)fhat, (double*)phat, opts, info, true, (const double*)x0hat);
 }

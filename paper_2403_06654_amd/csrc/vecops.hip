@@ -726,22 +726,22 @@ void sub_norm(const Geom& g, const void* b, const void* q, void* r, double* part
 }
 
 template <typename R>
-__global__ __launch_bounds__(256) void k_precond_axpy(C2<R>* __restrict__ x, const C2<R>* __restrict__ z, Geom g,
-                                                      int kind, double rho0, double nu, const double* ad, double ah,
+__global__ __launch_bounds__(256) void k_precond_axpy(C2<R>* x, const C2<R>* x_from, const C2<R>* __restrict__ z,
+                                                      Geom g, int kind, double rho0, double nu, const double* ad, double ah,
                                                       size_t n, const int* __restrict__ gate) {
   if (gate && *gate) return;
   const double a = (ad ? *ad : 1.0) * ah;
   for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (size_t)gridDim.x * 256) {
     C2<R> mz = precond_at<R>(z, e, g, kind, rho0, nu);
-    C2<R> xv = ldg(x + e);
+    C2<R> xv = ldg(x_from + e);
     stg(x + e, C2<R>{R(xv.x + a * mz.x), R(xv.y + a * mz.y)});
   }
 }
 template <typename R>
 void precond_axpy(const Geom& g, const OpParams& p, void* x, const void* z, const double* a_dev, double a_host,
-                  hipStream_t s) {
-  hipLaunchKernelGGL((k_precond_axpy<R>), dim3(nblk(nspec(g))), dim3(256), 0, s, (C2<R>*)x, (const C2<R>*)z, g,
-                     p.precond ? p.kind : -1, p.rho0, p.nu, a_dev, a_host, nspec(g), p.gate);
+                  hipStream_t s, const void* x_from) {
+  hipLaunchKernelGGL((k_precond_axpy<R>), dim3(nblk(nspec(g))), dim3(256), 0, s, (C2<R>*)x,
+                     (const C2<R>*)(x_from ? x_from : x), (const C2<R>*)z, g, p.precond ? p.kind : -1, p.rho0, p.nu, a_dev, a_host, nspec(g), p.gate);
 }
 
 template <typename R>
@@ -1252,7 +1252,7 @@ void kcoef_finish(const double* rho, const double* lap_psi, double* kc64, float*
   template void sub_norm<R>(const Geom&, const void*, const void*, void*, double*, double*, hipStream_t,       \
                             const Post&);                                                                      \
   template void precond_axpy<R>(const Geom&, const OpParams&, void*, const void*, const double*, double,       \
-                                hipStream_t);                                                                  \
+                                hipStream_t, const void*);                                                     \
   template void dot_rMr<R>(const Geom&, const OpParams&, const void*, double*, double*, hipStream_t,           \
                            const Post&);                                                                       \
   template void dot_partials<R>(const Geom&, const void*, const void*, bool, double*, hipStream_t, const int*); \

@@ -140,10 +140,11 @@ void sub_norm(const Geom& g, const void* b, const void* q, void* r, double* part
 
 // Gates: the kernels below that take OpParams honour p.gate; the others take
 // an explicit gate.  A nonzero *gate makes the launch do nothing.
-// x += a M^-1 z   (a = (*a_dev) * a_host; M^-1 diagonal, Helmholtz kx = 0 mirrored)
+// x += a M^-1 z   (a = (*a_dev) * a_host; M^-1 diagonal, Helmholtz kx = 0 mirrored), or
+// x = x_from + a M^-1 z
 template <typename R>
 void precond_axpy(const Geom& g, const OpParams& p, void* x, const void* z, const double* a_dev,
-                  double a_host, hipStream_t s);
+                  double a_host, hipStream_t s, const void* x_from = nullptr);
 
 // (r, M^-1 r) reduced into out[0]
 template <typename R>

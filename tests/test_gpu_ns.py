@@ -209,3 +209,52 @@ def test_steps_at_every_tile_shape_match_the_oracle(n, restart):
         fs.step(st, dt, re, sc, s=None)
     for got, want in zip(out[0], (st.u, st.rho, st.p)):
         _close(got, want, 1e-9)
+
+
+@pytest.mark.parametrize("form", ["L", "K"])
+def test_a_refused_step_leaves_the_last_completed_one(form):
+    """A density that the Adams-Bashforth step of a long time step amplifies:
+    the mid-step density is positive in the first two steps (minimum 0.6) and
+    negative in the third (-0.7, oracle), which is refused.  Wherever the call
+    ended, the handle holds what two steps give, bit for bit; trying again is
+    refused again; and a state set afterwards steps as on a new handle."""
+    from paper_2403_06654_amd.api import FractionalStep, VdError
+    n, kw = 16, dict(re=50.0, sc=1000.0, dt=1.2, pres_form=form)
+    X, _, _ = fs.mesh(n)
+    u0 = to_dev(np.stack([np.ones_like(X), 0 * X, 0.1 * np.sin(X)]))
+    rho0, p0 = to_dev(2.4 + np.cos(X)), to_dev(0 * X)
+
+    def start(rho):
+        ns = FractionalStep(n, **kw)
+        ns.set_state(u0, rho, p0, 0.25)
+        return ns
+
+    def fields(ns):
+        return [to_host(x) for x in ns.state()[:3]]
+
+    ref = start(rho0)
+    ref.step(2)
+    want, t2 = fields(ref), ref.state()[3]
+    ref.close()
+    safe = start(to_dev(4.0 + np.cos(X)))
+    safe.step(1)
+    after = fields(safe)
+    safe.close()
+    for calls in ((5,), (2, 1), (1, 4)):
+        ns = start(rho0)
+        for k, c in enumerate(calls):
+            if k + 1 < len(calls):
+                ns.step(c)
+                continue
+            for _ in range(2):
+                with pytest.raises(VdError) as e:
+                    ns.step(c)
+                assert e.value.status == -3
+                assert ns.state()[3] == t2
+                for a, b in zip(fields(ns), want):
+                    assert np.array_equal(a, b)
+        ns.set_state(u0, to_dev(4.0 + np.cos(X)), p0, 0.25)
+        ns.step(1)
+        for a, b in zip(fields(ns), after):
+            assert np.array_equal(a, b)
+        ns.close()
