@@ -57,8 +57,8 @@ struct vd_ns {
   bool spec = false;  // the spectra hold the state (else they are built from the physical fields)
   double t = 0;
   int steps = 0;
-  // coefficients of a density: its values, gradient (3), Hessian (00 01 02 11 12 22), 1 / (rho Re)
-  double *rh = nullptr, *cg = nullptr, *ch = nullptr, *cirr = nullptr;
+  // coefficients of a density: its values, gradient (3), Hessian (00 01 02 11 12 22), 1 / rho
+  double *rh = nullptr, *cg = nullptr, *ch = nullptr, *cir = nullptr;
   // scratch: spectra of rho^(n+1) and rho^(n+1/2); rows of three components
   // (stacks T, Tz, Tl, Ty) and of a scalar's gradient (3); stacks of three
   double *rho1h = nullptr, *rhh = nullptr;
@@ -239,6 +239,9 @@ void vector_rows(vd_ns* h, const double* spec, bool precond = false, const doubl
   timed(h, 0, fields_bytes(h, 21.0), [&] { ns_y_pass(y, 3, false, h->tw, h->st); });
 }
 
+// x pass of a u + b zeta(rho, u).  1 / Re goes into b, not into the field 1 / rho,
+// which the pressure gradient takes too: at a Re that overflows times rho (flows
+// without viscosity) only the viscous term may vanish.
 NsZetaArgs zeta_args(const vd_ns* h, double a, double b, double* out) {
   NsZetaArgs z{};
   z.y0 = h->T;
@@ -249,13 +252,12 @@ NsZetaArgs zeta_args(const vd_ns* h, double a, double b, double* out) {
   z.n = h->N;
   z.gr = h->cg;
   z.h = h->ch;
-  z.irr = h->cirr;
+  z.ir = h->cir;
   z.a = a;
-  z.b = b;
+  z.b = b / h->prm.re;
   z.inv_sc = 1.0 / h->prm.sc;
   z.norm = h->g.ntot_inv;
   z.sx = h->g.sx;
-  z.re = h->prm.re;
   z.out = out;
   return z;
 }
@@ -272,7 +274,7 @@ void viscous_apply(vd_ns* h, const double* x, double* out, bool precond, const d
   fwd_columns(h, out, 3, gate);
 }
 
-// density values, gradient, Hessian and 1 / (rho Re) of a density spectrum
+// density values, gradient, Hessian and 1 / rho of a density spectrum
 void coefficients(vd_ns* h, const double* spec) {
   const size_t N = h->N;
   NsZArgs z{};
@@ -301,13 +303,12 @@ void coefficients(vd_ns* h, const double* spec) {
   c.y2 = y.y2;
   c.y3 = y.y3;
   c.rho = h->rh;
-  c.irr = h->cirr;
+  c.ir = h->cir;
   c.gr = h->cg;
   c.h = h->ch;
   c.n = N;
   c.norm = h->g.ntot_inv;
   c.sx = h->g.sx;
-  c.re = h->prm.re;
   timed(h, 0, fields_bytes(h, 17.0), [&] { ns_coef_pass(h->g, c, h->tw, h->st); });
 }
 
@@ -326,17 +327,16 @@ void advect_scalar(vd_ns* h, double* out) {
   fwd_columns(h, out, 1);
 }
 
-// grad(q) / rho from q's gradient rows (pr) and cirr: a stack of three, spectra
+// grad(q) / rho from q's gradient rows (pr) and cir: a stack of three, spectra
 // or (phys) physical
 void grad_over_rho(vd_ns* h, double* out, bool phys) {
   NsGradArgs a{};
   a.q0 = h->pr;
   a.qy = h->pr + h->N;
   a.qz = h->pr + 2 * h->N;
-  a.irr = h->cirr;
+  a.ir = h->cir;
   a.norm = h->g.ntot_inv;
   a.sx = h->g.sx;
-  a.re = h->prm.re;
   a.stride = h->ns;
   a.out = out;
   timed(h, 0, fields_bytes(h, 7.0), [&] { ns_grad_pass(h->g, a, phys, h->tw, h->st); });
@@ -568,7 +568,7 @@ void step_once(vd_ns* h) {
   // 7. pressure update: p += phi - (div grad)^-1 div(dt/2 rho zeta(rho, grad(phi) / rho))
   vector_rows(h, h->z3);
   z = zeta_args(h, 0.0, 0.5 * dt, h->q3);
-  z.wconst = 1.0 / re;  // rho times 1 / (rho Re)
+  z.unit = true;  // rho times 1 / rho
   zeta(h, z, false, false);
   fwd_columns(h, h->q3, 3);
   ns_pressure(h->g, h->q3, h->ns, phi, h->ph, h->st);
@@ -666,7 +666,7 @@ vd_status vd_ns_create(vd_ns** out, int n, const vd_ns_params* prm, hipStream_t 
     h->rh = dalloc(h, N);
     h->cg = dalloc(h, 3 * N);
     h->ch = dalloc(h, 6 * N);
-    h->cirr = dalloc(h, N);
+    h->cir = dalloc(h, N);
     h->rho1h = dalloc(h, N);
     h->rhh = dalloc(h, N);
     h->T = dalloc(h, 3 * N);
@@ -825,7 +825,7 @@ vd_status vd_ns_project(vd_ns* h, const double* rho, const double* u, double* ou
     double* phi = h->z3 + N;
     ps = grid_solve_pressure_spec(h->grid, h->z3, nullptr, phi, &o, info);
     if (ps < 0 && ps != VD_NOT_CONVERGED) return ps;
-    ns_recip(rho, h->prm.re, h->cirr, N, h->st);
+    ns_recip(rho, h->cir, N, h->st);
     scalar_rows(h, phi);
     grad_over_rho(h, h->q3, true);
     lin(h, out, 3 * N, {{1.0, u}, {-1.0, h->q3}});

@@ -54,17 +54,18 @@ void ns_y_pass(const NsYArgs& a, int nf, bool hess, const void* tw, hipStream_t 
 // x pass of zeta (eq. VDINSE.zeta) on three components' rows (y0, yy, yz, yl:
 // stacks t0, y1, t1, t2 of the y pass):
 //   out_i = a u_i + b W (Lap u_i + (sum_j u_j h_ij + sum_j gr_j d_j u_i) inv_sc),
-// W = irr = 1 / (rho Re), or wconst if not zero; with rhs also
+// W = ir = 1 / rho, or 1 with unit (b takes 1 / Re); with rhs also
 //   + ca n_i + cp nprev_i + cg d_i p / rho + ce ext_i,  n_i = (u . grad) u_i,
 // p0, py, pz the rows of p's gradient (grad_rows), n_i written to nout; nprev,
-// ext and nout are optional.  gr, h, irr, nprev, ext, nout: physical.  out: rows
+// ext and nout are optional.  gr, h, ir, nprev, ext, nout: physical.  out: rows
 // transformed along x, or physical.
 struct NsZetaArgs {
   const void *y0, *yy, *yz, *yl;
   size_t stride;  // slots per field
   size_t n;       // grid points
-  const double *gr, *h, *irr;
-  double a, b, inv_sc, wconst = 0, norm, sx, re = 0;
+  const double *gr, *h, *ir;
+  double a, b, inv_sc, norm, sx;
+  bool unit = false;
   const void *p0 = nullptr, *py = nullptr, *pz = nullptr;
   const double *nprev = nullptr, *ext = nullptr;
   double ca = 0, cp = 0, cg = 0, ce = 0;
@@ -75,12 +76,12 @@ struct NsZetaArgs {
 void ns_zeta_pass(const Geom& g, const NsZetaArgs& a, bool rhs, bool phys, const void* tw, hipStream_t st);
 
 // x pass of a density's coefficients from the hess passes' rows: rho,
-// irr = 1 / (rho Re), gradient gr (3) and Hessian h (00 01 02 11 12 22).
+// ir = 1 / rho, gradient gr (3) and Hessian h (00 01 02 11 12 22).
 struct NsCoefArgs {
   const void *y0, *t1, *t2, *y1, *y2, *y3;
-  double *rho, *irr, *gr, *h;
+  double *rho, *ir, *gr, *h;
   size_t n;
-  double norm, sx, re;
+  double norm, sx;
 };
 void ns_coef_pass(const Geom& g, const NsCoefArgs& a, const void* tw, hipStream_t st);
 
@@ -95,12 +96,12 @@ struct NsAdvArgs {
 };
 void ns_advect_pass(const Geom& g, const NsAdvArgs& a, const void* tw, hipStream_t st);
 
-// x pass of grad(q) / rho (irr = 1 / (rho Re)), a stack of three; rows
+// x pass of grad(q) / rho (ir = 1 / rho), a stack of three; rows
 // transformed along x, or physical.
 struct NsGradArgs {
   const void *q0, *qy, *qz;
-  const double* irr;
-  double norm, sx, re;
+  const double* ir;
+  double norm, sx;
   size_t stride;
   void* out;
 };
@@ -138,8 +139,8 @@ struct LinArgs {
 };
 void ns_lincomb(const LinArgs& a, hipStream_t st);
 
-// out = 1 / (c x)
-void ns_recip(const double* x, double c, double* out, size_t n, hipStream_t st);
+// out = 1 / x
+void ns_recip(const double* x, double* out, size_t n, hipStream_t st);
 
 // eq. VDINSE.solexact on the n^3 grid of [0, 2 pi)^3 at time t: u (3 fields
 // one after another), p, rho, and when non-null the time derivatives du (3

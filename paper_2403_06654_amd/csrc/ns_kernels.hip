@@ -34,9 +34,8 @@ __global__ __launch_bounds__(kT) void k_lincomb(LinArgs a) {
   }
 }
 
-__global__ __launch_bounds__(kT) void k_recip(const double* __restrict__ x, double c, double* __restrict__ out,
-                                              size_t n) {
-  for (size_t e = blockIdx.x * (size_t)kT + threadIdx.x; e < n; e += (size_t)gridDim.x * kT) out[e] = 1.0 / (c * x[e]);
+__global__ __launch_bounds__(kT) void k_recip(const double* __restrict__ x, double* __restrict__ out, size_t n) {
+  for (size_t e = blockIdx.x * (size_t)kT + threadIdx.x; e < n; e += (size_t)gridDim.x * kT) out[e] = 1.0 / x[e];
 }
 
 __global__ __launch_bounds__(kT) void k_tg(int n, double t, double s, double* __restrict__ u, double* __restrict__ p,
@@ -87,8 +86,8 @@ void ns_lincomb(const LinArgs& a, hipStream_t st) {
   hipLaunchKernelGGL(k_lincomb, dim3(grid_of(a.n)), dim3(kT), 0, st, a);
 }
 
-void ns_recip(const double* x, double c, double* out, size_t n, hipStream_t st) {
-  hipLaunchKernelGGL(k_recip, dim3(grid_of(n)), dim3(kT), 0, st, x, c, out, n);
+void ns_recip(const double* x, double* out, size_t n, hipStream_t st) {
+  hipLaunchKernelGGL(k_recip, dim3(grid_of(n)), dim3(kT), 0, st, x, out, n);
 }
 
 void ns_tg_fields(int n, double t, double s, double* u, double* p, double* rho, double* du, double* drho,

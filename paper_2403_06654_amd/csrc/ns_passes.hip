@@ -329,7 +329,7 @@ __device__ __forceinline__ void row_store(const Cd* X, void* p, unsigned off) {
 
 // x pass of zeta (eq. VDINSE.zeta), wavefront i on component i:
 //   out_i = a u_i + b W (Lap u_i + (sum_j u_j h_ij + sum_j g_j d_j u_i) / Sc)
-// with W = 1 / (rho Re) (irr), or wconst where that is not zero; and, for the
+// with W = 1 / rho (ir), or 1 (unit; b holds 1 / Re); and, for the
 // right-hand side of a step (RHS), n_i = (u . grad) u_i written to nout and
 //   out_i += ca n_i + cp nprev_i + cg d_i p / rho + ce ext_i.
 // The rows of out are transformed along x, or (PHYS) physical.
@@ -397,8 +397,8 @@ __global__ __launch_bounds__(192) void k_ns_zeta_x(NsZetaArgs a, const Cd* __res
   F.to_real(X, reg);
 #pragma unroll
   for (int s = 0; s < E; ++s) {
-    const Cd q = ldb(a.irr, off, F.pair(s));
-    const double wx = a.wconst != 0.0 ? a.wconst : q.x, wy = a.wconst != 0.0 ? a.wconst : q.y;
+    const Cd q = ldb(a.ir, off, F.pair(s));
+    const double wx = a.unit ? 1.0 : q.x, wy = a.unit ? 1.0 : q.y;
     reg[s] = Cd{a.a * u[s].x + a.b * wx * (reg[s].x * a.norm + a.inv_sc * acc[s].x),
                 a.a * u[s].y + a.b * wy * (reg[s].y * a.norm + a.inv_sc * acc[s].y)};
   }
@@ -413,8 +413,8 @@ __global__ __launch_bounds__(192) void k_ns_zeta_x(NsZetaArgs a, const Cd* __res
 #pragma unroll
     for (int s = 0; s < E; ++s) {
       const int m = F.pair(s);
-      const Cd q = ldb(a.irr, off, m);
-      const double c = a.cg * a.re * a.norm;  // 1 / rho = Re irr
+      const Cd q = ldb(a.ir, off, m);
+      const double c = a.cg * a.norm;
       reg[s].x += a.ca * adv[s].x + c * q.x * gp[s].x;
       reg[s].y += a.ca * adv[s].y + c * q.y * gp[s].y;
       if (a.nprev) {
@@ -439,7 +439,7 @@ __global__ __launch_bounds__(192) void k_ns_zeta_x(NsZetaArgs a, const Cd* __res
   }
 }
 
-// x pass of a density's coefficients: rho, 1 / (rho Re), its gradient and its
+// x pass of a density's coefficients: rho, 1 / rho, its gradient and its
 // Hessian (00 01 02 11 12 22), physical; the derivatives by wavefront: along x
 // (and xx), along y (and xy, yy, yz), along z (and xz, zz).
 template <int L>
@@ -469,7 +469,7 @@ __global__ __launch_bounds__(192) void k_ns_coef_x(NsCoefArgs a, const Cd* __res
     for (int s = 0; s < E; ++s) {
       const Cd r = cscale(reg[s], a.norm);
       stb(a.rho, off, F.pair(s), r);
-      stb(a.irr, off, F.pair(s), Cd{1.0 / (a.re * r.x), 1.0 / (a.re * r.y)});
+      stb(a.ir, off, F.pair(s), Cd{1.0 / r.x, 1.0 / r.y});
     }
     dx(1);
     emit(a.gr);
@@ -532,7 +532,7 @@ __global__ __launch_bounds__(192) void k_ns_advect_x(NsAdvArgs a, const Cd* __re
 }
 
 // x pass of grad(q) / rho: wavefront d writes component d, its rows transformed
-// along x or (PHYS) physical (irr = 1 / (rho Re)).
+// along x or (PHYS) physical (ir = 1 / rho).
 template <int L, bool PHYS>
 __global__ __launch_bounds__(192) void k_ns_gradq_x(NsGradArgs a, const Cd* __restrict__ twtab) {
   VD_NS_ROWS((const int*)nullptr)
@@ -543,11 +543,10 @@ __global__ __launch_bounds__(192) void k_ns_gradq_x(NsGradArgs a, const Cd* __re
     for (int s = 0; s < E; ++s) X[s] = cik(X[s], (double)(t + s * T) * a.sx);
   }
   F.to_real(X, reg);
-  const double c = a.norm * a.re;
 #pragma unroll
   for (int s = 0; s < E; ++s) {
-    const Cd q = ldb(a.irr, off, F.pair(s));
-    reg[s] = Cd{c * q.x * reg[s].x, c * q.y * reg[s].y};
+    const Cd q = ldb(a.ir, off, F.pair(s));
+    reg[s] = Cd{a.norm * q.x * reg[s].x, a.norm * q.y * reg[s].y};
   }
   Cd* out = (Cd*)a.out + (size_t)wv * a.stride;  // a field is as large physical as packed
   if constexpr (PHYS) {

@@ -258,3 +258,44 @@ def test_a_refused_step_leaves_the_last_completed_one(form):
         for a, b in zip(fields(ns), after):
             assert np.array_equal(a, b)
         ns.close()
+
+
+def test_projection_without_viscosity():
+    """P_rho does not depend on Re, nor on a constant factor of rho: not at a
+    Reynolds number that overflows when it is multiplied by the density either.
+    (Both sides solve the same system to 1e-13; tolerance as above.)"""
+    from paper_2403_06654_amd.api import FractionalStep
+    n = 16
+    X, Y, Z = fs.mesh(n)
+    rho = 3.0 + np.sin(X) * np.cos(2 * Y) + 0.5 * np.sin(Z)
+    w = np.random.default_rng(1).standard_normal((3, n, n, n))
+    out = []
+    for re, scale in ((1.0, 1.0), (1e306, 1e3)):
+        ns = FractionalStep(n, re=re, pres_rtol=1e-13)
+        pw, info = ns.project(to_dev(scale * rho), to_dev(w))
+        assert info["status"] == 0
+        out.append(to_host(pw))
+        ns.close()
+    _close(out[1], out[0], 1e-10)
+
+
+def test_a_step_without_viscosity():
+    """Steps at such a Reynolds number against the oracle's at Re = 1e11, where
+    the viscous terms are below 1e-10 of the fields."""
+    from paper_2403_06654_amd.api import FractionalStep
+    n, dt, scale = 16, 0.05, 1e3
+    X, Y, Z = fs.mesh(n)
+    u0 = np.stack([np.sin(X) * np.cos(Y) + 0.3 * np.cos(2 * Z), -np.cos(X) * np.sin(Y), 0.2 * np.sin(X + Y)])
+    rho0 = scale * (3.0 + np.sin(X) * np.cos(Y) + 0.5 * np.sin(Z))
+    p0 = scale * np.cos(X) * np.cos(2 * Y) * np.cos(Z)
+    u0 = fs.projection(u0, rho0)
+    ns = FractionalStep(n, re=1e306, sc=1.0, dt=dt, s=0.0)
+    ns.set_state(to_dev(u0), to_dev(rho0), to_dev(p0), 0.0)
+    ns.step(2)
+    u, rho, p, _ = ns.state()
+    ns.close()
+    st = fs.State(u0, rho0, p0, 0.0)
+    for _ in range(2):
+        fs.step(st, dt, 1e11, 1.0, s=None)
+    for got, want in ((u, st.u), (rho, st.rho), (p, st.p)):
+        _close(to_host(got), want, 1e-8)
