@@ -64,12 +64,12 @@ struct EpiArgs {
 // is issued before the halt flag is read, batches are short (KU k-steps), and
 // where a 16 x 16 tiling would not fit the chip at once anyway (kGemmTiles) a
 // wave computes two column tiles from one 16 B load of B per k-step and lane:
-// lane li then holds columns 2 li and 2 li + 1.
-// Measured per launch (FP64, N = 512, back-to-back launches with HIP events; TN = 1
-// with KU = 5 / TN = 1, KU = 3 / TN = 2, KU = 3), us: M = 257, K = 257: 5.4 / 5.2 /
-// 5.3; M = 514, K = 257: 7.8 / 7.4 / 6.8; M = 257, K = 514: 8.9 / 8.2 / 8.4;
-// M = 514, K = 514: 13.3 / 12.3 / 11.2.  4 and 16 waves, 32 x 32 tiles per wave and
-// tiles staged in LDS (22-26 us at M = K = 514) are slower.
+// lane li then holds columns 2 li and 2 li + 1.  4 and 16 waves, 32 x 32 tiles per
+// wave and tiles staged in LDS (22-26 us at M = K = 514) are slower.
+// Whatever the tile, an element is the same sum: a wave's k-steps go to two chains
+// in turn, and the chains of all waves are added in FP64.  (FP32 products, relative
+// error at K = 257 / 514 / 1026: 7.8e-8 / 1.06e-7 / 1.47e-7; with one chain per
+// column tile 1.06e-7 / 1.47e-7 / 2.05e-7, for 2 to 3% of the TN = 2 launch.)
 // AT: A is stored transposed ([K][M]), so a load of 16 consecutive rows is
 // one contiguous run.
 constexpr int kGemmWaves = 8, kGemmKU = 3;
@@ -87,7 +87,8 @@ __global__ __launch_bounds__(64 * kGemmWaves) void k_gemm(const R* __restrict__ 
   const int li = lane & 15, lk = lane >> 4;
   const int ra = r0 + li, cb = c0 + TN * li;
   const bool rin = ra < M, cin = cb < N;  // TN = 2: N is even
-  typename MF::V acc[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};  // a chain per column tile, or alternate k-steps
+  // two chains per column tile, alternate k-steps of this wave, added in FP64
+  typename MF::V acc[TN][2] = {};
   R a[KU], b[KU][TN];
   auto load = [&](int s0) {
 #pragma unroll
@@ -106,28 +107,28 @@ __global__ __launch_bounds__(64 * kGemmWaves) void k_gemm(const R* __restrict__ 
   };
   load(w);
   if (e.gate && *e.gate) return;
-  for (int s0 = w;;) {
+  static_assert(KU % 2 == 1, "the chains change places from batch to batch");
+  int s0 = w;
+  bool more = true;
+  while (more) {
 #pragma unroll
-    for (int u = 0; u < KU; ++u) {
+    for (int h = 0; h < 2; ++h) {
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int t = TN == 2 ? j : u & 1;
-        acc[t] = MF::mac(a[u], b[u][j], acc[t]);
+      for (int u = 0; u < KU; ++u) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[j][(h + u) & 1] = MF::mac(a[u], b[u][j], acc[j][(h + u) & 1]);
       }
+      s0 += W * KU;
+      more = 4 * s0 < K;
+      if (!more) break;
+      load(s0);
     }
-    s0 += W * KU;
-    if (4 * s0 >= K) break;
-    load(s0);
   }
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     double* o = part[w] + MF::row(lk, r) * LD + TN * li;
-    if constexpr (TN == 2) {
-      o[0] = (double)acc[0][r];
-      o[1] = (double)acc[1][r];
-    } else {
-      o[0] = (double)acc[0][r] + (double)acc[1][r];
-    }
+#pragma unroll
+    for (int j = 0; j < TN; ++j) o[j] = (double)acc[j][0][r] + (double)acc[j][1][r];
   }
   __syncthreads();
   if (threadIdx.x >= 16 * TS) return;

@@ -189,3 +189,20 @@ def test_contraction_tiles(M, N, K, shift):
     Bd32.copy_(torch.from_numpy(B))
     C32 = dense_matmul(torch.from_numpy(A.astype(np.float32)).cuda(), Bd32, precision="fp32").cpu().numpy()
     assert rel2(C32.astype(np.float64), A @ B) < 2e-6
+
+
+@pytest.mark.parametrize("M,N,K", [(514, 512, 257), (1026, 1024, 513), (600, 520, 1026), (1000, 514, 37)])
+def test_contraction_sums_do_not_depend_on_the_tile(M, N, K):
+    """A wide product takes two column tiles per wavefront, a narrow one a single
+    tile: an element is the same sum in both, in the same order, so that the
+    partial sums (and the FP32 rounding of them) do not grow with the width."""
+    import torch
+    from paper_2403_06654_amd.api import dense_matmul
+    gen = torch.Generator(device="cuda").manual_seed(M + K)
+    for precision, dtype in (("fp64", torch.float64), ("fp32", torch.float32)):
+        A = torch.randn((M, K), dtype=dtype, device="cuda", generator=gen)
+        B = torch.randn((K, N), dtype=dtype, device="cuda", generator=gen)
+        C = dense_matmul(A, B, precision=precision)
+        for c in range(0, N, 34):  # at most 3 column tiles: 195 tiles of 16 x 16
+            part = dense_matmul(A, B[:, c:c + 34].contiguous(), precision=precision)
+            assert bool((C[:, c:c + 34] == part).all()), (precision, c)
