@@ -62,7 +62,7 @@ struct EpiArgs {
 // by its loads, their latency and their number, not by MFMA or HBM (at
 // M = K = 514 the loads alone take 11.5 of 13.3 us).  So the first batch of loads
 // is issued before the halt flag is read, batches are short (KU k-steps), and
-// where a 16 x 16 tiling would not fit the chip at once anyway (kGemmTiles) a
+// where there are enough 16 x 16 tiles (kGemmTiles) a
 // wave computes two column tiles from one 16 B load of B per k-step and lane:
 // lane li then holds columns 2 li and 2 li + 1.  4 and 16 waves, 32 x 32 tiles per
 // wave and tiles staged in LDS (22-26 us at M = K = 514) are slower.
@@ -73,7 +73,15 @@ struct EpiArgs {
 // AT: A is stored transposed ([K][M]), so a load of 16 consecutive rows is
 // one contiguous run.
 constexpr int kGemmWaves = 8, kGemmKU = 3;
-constexpr int kGemmTiles = 512;  // two 16 x 16 tiles per CU
+// Two column tiles above three 16 x 16 tiles per CU.  A block of two takes 1.5 times
+// as long as a block of one: at 513 to 768 tiles that is two rounds of the CUs
+// against three, which gains nothing, and beyond it does gain.  Measured, us per
+// launch (TN = 1 / TN = 2, N = 512): M = 257, K = 257 (544 tiles) 5.4 / 5.6 in FP64,
+// 4.2 / 4.5 in FP32; M = 257, K = 514 8.6 / 8.9 and 6.4 / 7.0; M = 385, K = 385 (800
+// tiles) 8.2 / 7.3 and 6.3 / 5.8; M = K = 514 (1056 tiles) 12.7 / 12.0 and 9.7 / 9.7;
+// M = K = 770 23.8 / 20.4 and 16.4 / 16.3.  (257 to 512 tiles, one round against two,
+// gains 3% in FP64 (-9 to 11%) and nothing in FP32; they keep the single tile.)
+constexpr int kGemmTiles = 768;
 
 template <typename R, bool AT, int TN>
 __global__ __launch_bounds__(64 * kGemmWaves) void k_gemm(const R* __restrict__ A, int lda, const R* __restrict__ B,

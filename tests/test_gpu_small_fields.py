@@ -191,7 +191,8 @@ def test_contraction_tiles(M, N, K, shift):
     assert rel2(C32.astype(np.float64), A @ B) < 2e-6
 
 
-@pytest.mark.parametrize("M,N,K", [(514, 512, 257), (1026, 1024, 513), (600, 520, 1026), (1000, 514, 37)])
+@pytest.mark.parametrize("M,N,K", [(514, 512, 257), (1026, 1024, 513), (600, 520, 1026), (1000, 514, 37),
+                                   (384, 512, 40), (385, 512, 40)])
 def test_contraction_sums_do_not_depend_on_the_tile(M, N, K):
     """A wide product takes two column tiles per wavefront, a narrow one a single
     tile: an element is the same sum in both, in the same order, so that the
