@@ -1610,7 +1610,9 @@ static vd_status solve_impl(vd_grid* G, void* c) {
   for (int comp = 0; comp < s->ncomp; ++comp) {
     const double* f = s->f + (size_t)comp * G->nreal;
     double* x = s->x + (size_t)comp * G->nreal;
-    bool removed = false;  // the projection writes the removed norm to dsmall[0]
+    // The projection writes the removed norm to dsmall[0], to be read after the
+    // stream has been waited for: a mailbox post orders nothing but its own words.
+    bool removed = false;
     if (G->g.cheb) {  // weak form: b = -I^T W I f, nullspace constant in z
       void* tmp = buf(G, 64, B_TMP);
       fwd_transform(G->g, f, tmp, nullptr, G->tw64, G->st);
@@ -1644,8 +1646,7 @@ static vd_status solve_impl(vd_grid* G, void* c) {
     } else {
       ck(hipMemsetAsync(x64, 0, G->nspec * 16, G->st));
     }
-    double bnorm = host_norm_of(G, b64);  // waits for its reduction, so for the projection before it
-    if (removed) s->info.rhs_null_norm = std::fmax(s->info.rhs_null_norm, G->dsmall[0]);
+    double bnorm = host_norm_of(G, b64);
     int refin = 0;
     std::vector<double> hist;
     const bool want_hist = comp == 0 && s->o.history_cap > 0;
@@ -1669,6 +1670,7 @@ static vd_status solve_impl(vd_grid* G, void* c) {
     }
     ck(hipStreamSynchronize(G->st));
     ck(hipGetLastError());
+    if (removed) s->info.rhs_null_norm = std::fmax(s->info.rhs_null_norm, G->dsmall[0]);
     s->info.iterations += so.iters;
     s->info.refinements += refin;
     s->info.gs_second_passes += so.reorth;
@@ -1765,8 +1767,8 @@ static vd_status pressure_batch_impl(vd_grid* G0, void* c) {
       ck(hipMemsetAsync(x64[k], 0, G->nspec * 16, G->st));
     }
     bnorm[k] = host_norm_of(G, b64[k]);
-    s->infos[k].rhs_null_norm = G->dsmall[0];
     ck(hipStreamSynchronize(G->st));  // the batch runs on the first grid's stream
+    s->infos[k].rhs_null_norm = G->dsmall[0];
   }
   op.rho0 = S.rho0[0];
   SolveOut so[kMaxBatch];

@@ -207,3 +207,38 @@ def test_contraction_sums_do_not_depend_on_the_tile(M, N, K):
         for c in range(0, N, 34):  # at most 3 column tiles: 195 tiles of 16 x 16
             part = dense_matmul(A, B[:, c:c + 34].contiguous(), precision=precision)
             assert bool((C[:, c:c + 34] == part).all()), (precision, c)
+
+
+@pytest.mark.parametrize("cheb", [False, True])
+def test_removed_norms_belong_to_their_solve(cheb):
+    """rhs_null_norm of solves one after another on one grid, and of two grids
+    solved together: each the norm that its own right-hand side lost, none the
+    one of the solve before.  (Fourier grid: the mean, c sqrt(N) in Euclidean
+    norm; Chebyshev grid: compared with a grid that solves it alone.)"""
+    from paper_2403_06654_amd.api import Grid
+    shape, kw = ((33, 32), dict(lengths=(2.0, 2.0), cheb=True)) if cheb else ((16, 32), {})
+    rho = to_dev(smooth_density(shape, 3))
+    f = np.random.default_rng(5).standard_normal(shape) if cheb else workloads.band_limited(shape, 4, seed=5)
+    f -= f.mean()
+    means = [3.0 * 0.5 ** k for k in range(12)]
+
+    def alone(c):
+        g = Grid(shape, **kw)
+        g.set_density(rho)
+        _, info = g.solve_pressure(to_dev(f + c), rtol=1e-6)
+        g.close()
+        return info["rhs_null_norm"]
+
+    want = [alone(c) if cheb else c * np.sqrt(f.size) for c in means]
+    grids = [Grid(shape, **kw) for _ in range(2)]
+    for g in grids:
+        g.set_density(rho)
+    for c, w in zip(means, want):
+        _, info = grids[0].solve_pressure(to_dev(f + c), rtol=1e-6)
+        assert info["rhs_null_norm"] == (w if cheb else pytest.approx(w, rel=1e-9))
+    for (c, d), (w, v) in zip(zip(means, means[::-1]), zip(want, want[::-1])):
+        _, infos = Grid.solve_pressure_batch(grids, [to_dev(f + c), to_dev(f + d)], rtol=1e-6)
+        for info, x in zip(infos, (w, v)):
+            assert info["rhs_null_norm"] == (x if cheb else pytest.approx(x, rel=1e-9))
+    for g in grids:
+        g.close()
