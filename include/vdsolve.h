@@ -219,8 +219,10 @@ size_t vd_workspace_bytes_helmholtz(const vd_grid_desc* desc, const vd_solve_opt
  * events on the grid's stream while enabled.  Classes 0..4: the pressure
  * operator's z-first, y-inverse, x, y-forward and z-last passes; 5..9: the
  * same passes of the Helmholtz operator; 10: the GMRES Gram-Schmidt dot
- * pass; 11: the GMRES Gram-Schmidt update pass.  ms[c] = total
- * milliseconds, count[c] = launches, bytes[c] = algorithmic bytes those
+ * pass (on small grids the operator's last pass forms the dots: class 10 then
+ * counts them, and their time and bytes are that pass's); 11: the GMRES
+ * Gram-Schmidt update pass.  Timing changes neither the kernels that run nor any
+ * bit of a result.  ms[c] = total milliseconds, count[c] = launches, bytes[c] = algorithmic bytes those
  * launches read and wrote (3D grids), for c < nclass (<= 12); any output
  * pointer may be NULL.  Reading resets the totals.  `classes` is a bit mask
  * of the classes to time (bit c = class c; -1 times all, 0 disables); each

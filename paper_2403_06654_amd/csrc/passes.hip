@@ -1206,12 +1206,11 @@ static void launch_col_L(const ColArgs& a, const void* tw, hipStream_t st) {
 // Lengths whose first and last pass carry Gram-Schmidt work (a 1024-point tile
 // already fills a block's registers).
 constexpr int kGsLength = 512;
-bool op_carries_gs(const Geom& g, int kind) {
-  (void)kind;
+bool op_carries_gs(const Geom& g) {
   return small_field(g) && !g.cheb && g.nz > 1 && g.nz <= kGsLength;
 }
 // the Helmholtz passes read mirror elements of their input, which another block's second pass may be writing
-bool op_carries_check(const Geom& g, int kind) { return kind == OP_PRESSURE && op_carries_gs(g, kind); }
+bool op_carries_check(const Geom& g, int kind) { return kind == OP_PRESSURE && op_carries_gs(g); }
 
 template <typename F>
 static void for_gs_length(int L, F&& f) {
@@ -1407,14 +1406,21 @@ static RowArgs row_args(const Geom& g, const OpParams* p) {
 
 // Fields each pass reads plus writes (3D): pressure P1..P5, Helmholtz P1..P5.
 constexpr double kPassFields[10] = {3, 5, 7, 5, 3, 2, 2, 3, 2, 3};
+// and those that a first or last pass adds for the Krylov step that it carries
+// (the second pass of Gram-Schmidt, which few steps take, left out)
+static double first_carry_fields(const OpParams& p) { return p.rec && p.rec->ends && p.rec->cg ? 2 : 0; }
+static double last_carry_fields(const OpParams& p) {
+  return p.gs ? p.gs->nv : p.rec && p.rec->dots ? 1 : 0;
+}
 
 template <typename R>
 void op_apply(const Geom& g, const OpParams& p, const void* v, void* y, const OpWork& w, const void* coef,
               const void* twtab, hipStream_t st, Prof* prof) {
   const bool pr = prof && prof->on;
   const double fb = (double)g.nz * g.ny * g.M * sizeof(C2<R>);  // one field
-#define VD_T0(c) \
-  if (pr) prof->begin(c, st, kPassFields[c] * fb);
+#define VD_TC(c, carry) \
+  if (pr) prof->begin(c, st, (kPassFields[c] + (carry)) * fb);
+#define VD_T0(c) VD_TC(c, 0)
 #define VD_T1() \
   if (pr) prof->end(st);
   const size_t zin = (size_t)g.ny * g.M;  // inner size of the z pass
@@ -1435,7 +1441,7 @@ void op_apply(const Geom& g, const OpParams& p, const void* v, void* y, const Op
     a.in[0] = v;
     a.out[0] = t0;
     a.out[1] = t1;
-    VD_T0(0) first_pass<R, COL_P_FIRST>(g, p, a, twtab, st); VD_T1()
+    VD_TC(0, first_carry_fields(p)) first_pass<R, COL_P_FIRST>(g, p, a, twtab, st); VD_T1()
     RowArgs r = row_args(g, &p);
     r.coef = coef;
     r.cscale = g.ntot_inv;
@@ -1471,7 +1477,7 @@ void op_apply(const Geom& g, const OpParams& p, const void* v, void* y, const Op
     d.in[0] = t0;
     d.in[1] = t1;
     d.out[0] = y;
-    VD_T0(4) last_pass<R, COL_P_LAST>(g, p, d, twtab, st); VD_T1()
+    VD_TC(4, last_carry_fields(p)) last_pass<R, COL_P_LAST>(g, p, d, twtab, st); VD_T1()
   } else {
     if (g.nz == 1) {
       RowArgs r = row_args(g, &p);
@@ -1488,7 +1494,7 @@ void op_apply(const Geom& g, const OpParams& p, const void* v, void* y, const Op
     a.inner = (int)zin;
     a.in[0] = v;
     a.out[0] = t0;
-    VD_T0(5) first_pass<R, COL_H_FIRST>(g, p, a, twtab, st); VD_T1()
+    VD_TC(5, first_carry_fields(p)) first_pass<R, COL_H_FIRST>(g, p, a, twtab, st); VD_T1()
     if (g.ny > 1) {
       ColArgs b = col_args_fft(g, p);
       b.outer = g.nz;
@@ -1519,9 +1525,10 @@ void op_apply(const Geom& g, const OpParams& p, const void* v, void* y, const Op
     d.in[0] = t0;
     d.in[1] = v;
     d.out[0] = y;
-    VD_T0(9) last_pass<R, COL_H_LAST>(g, p, d, twtab, st); VD_T1()
+    VD_TC(9, last_carry_fields(p)) last_pass<R, COL_H_LAST>(g, p, d, twtab, st); VD_T1()
   }
 #undef VD_T0
+#undef VD_TC
 #undef VD_T1
 }
 
@@ -1585,7 +1592,7 @@ void op_apply_batch(const Geom& g, const OpParams& p, const OpBatch& b, const vo
     d.outer = 1;
     d.inner = (int)zin;
     for (int k = 0; k < nb; ++k) d.sys[k] = sys_of(k, {b.t[k][0], b.v[k]}, {b.y[k]}, true);
-    timed(9, 3.0 * nb, [&] { last_pass<R, COL_H_LAST>(g, p, d, twtab, st); });
+    timed(9, (3.0 + last_carry_fields(p)) * nb, [&] { last_pass<R, COL_H_LAST>(g, p, d, twtab, st); });
     return;
   }
   // pressure (2D and 3D grids): the passes of op_apply, system k on
@@ -1627,7 +1634,7 @@ void op_apply_batch(const Geom& g, const OpParams& p, const OpBatch& b, const vo
   d.outer = 1;
   d.inner = (int)zin;
   for (int k = 0; k < nb; ++k) d.sys[k] = sys_of(k, {b.t[k][0], b.t[k][1]}, {b.y[k]}, false);
-  timed(4, 3.0 * nb, [&] { last_pass<R, COL_P_LAST>(g, p, d, twtab, st); });
+  timed(4, (3.0 + last_carry_fields(p)) * nb, [&] { last_pass<R, COL_P_LAST>(g, p, d, twtab, st); });
 }
 
 template <typename R>

@@ -83,7 +83,9 @@ struct OpWork {
 // 0 z-first, 1 y-inverse, 2 x, 3 y-forward, 4 z-last of the pressure
 // operator; 5..9 the same passes of the Helmholtz operator; 10 the
 // Gram-Schmidt dot pass (k_mdot), 11 the Gram-Schmidt update pass
-// (k_gs_update).
+// (k_gs_update).  Where an operator pass forms the dots (GsCarry), class 10 only
+// counts them (tally): their time and bytes are that pass's, as in a run that
+// is not timed.
 struct Prof {
   static constexpr int kClasses = 12;
   bool on = false;
@@ -99,6 +101,7 @@ struct Prof {
   hipEvent_t cur_a = nullptr;
   void begin(int cls, hipStream_t s, double nbytes = 0);
   void end(hipStream_t s);
+  void tally(int cls);  // count an occurrence that has no launch of its own
   void flush();  // accumulate completed pairs (call after a stream sync)
   // accumulate the oldest n pairs only (their end events must have completed)
   void flush_front(size_t n);
@@ -111,7 +114,7 @@ struct Prof {
 // Whether the passes of this grid's operator carry the dots of a step, whether
 // they also take the check of the step before, and the number of blocks whose
 // partials the dots leave.
-bool op_carries_gs(const Geom& g, int kind);
+bool op_carries_gs(const Geom& g);
 bool op_carries_check(const Geom& g, int kind);
 int op_dot_blocks(const Geom& g);
 // The same for CG and RMR steps (single systems), and the blocks whose partials

@@ -71,11 +71,18 @@ void Prof::end(hipStream_t s) {
   pending.push_back(Pair{cur, cur_bytes, cur_a, b});
   cur = -1;
 }
+void Prof::tally(int cls) {
+  if ((mask >> cls) & 1u) pending.push_back(Pair{cls, 0.0, nullptr, nullptr});
+}
 void Prof::flush() { flush_front(pending.size()); }
 void Prof::flush_front(size_t n) {
   n = std::min(n, pending.size());
   for (size_t i = 0; i < n; ++i) {
     const Pair& p = pending[i];
+    if (!p.a) {
+      cnt[p.cls] += 1;
+      continue;
+    }
     float ms_ = 0.f;
     if (hipEventSynchronize(p.b) == hipSuccess && hipEventElapsedTime(&ms_, p.a, p.b) == hipSuccess) {
       ms[p.cls] += ms_;
@@ -89,6 +96,7 @@ void Prof::flush_front(size_t n) {
 }
 void Prof::drop() {
   for (const Pair& p : pending) {
+    if (!p.a) continue;
     spare.push_back(p.a);
     spare.push_back(p.b);
   }
@@ -304,10 +312,6 @@ struct SolveOut {
 
 // The Gram-Schmidt work that the operator passes of step j carry (states,
 // partials and vectors left to the caller), and what is left to the vector kernels.
-// A profile that times the dots gets them as a launch of their own.
-bool carries_gs(const vd_grid* G, const Geom& g, int kind) {
-  return op_carries_gs(g, kind) && !(G->prof.on && ((G->prof.mask >> 10) & 1u));
-}
 GsCarry carry_of(const Geom& g, int j, bool check) {
   GsCarry c;
   c.nv = j + 1;
@@ -421,7 +425,7 @@ struct Krylov {
     for (int i = 0; i <= j; ++i) P.p[i] = V[i];
     GsParts parts;
     GsCarry c;
-    const bool carry = carries_gs(G, g, cfg.op.kind);
+    const bool carry = op_carries_gs(g);
     if (carry) {
       const bool check = op_carries_check(g, cfg.op.kind);
       c = carry_of(g, j, check);
@@ -907,7 +911,7 @@ struct KrylovBatch {
     }
     GsParts parts;
     GsCarry c;
-    const bool carry = carries_gs(G, g, cfg.op.kind);
+    const bool carry = op_carries_gs(g);
     if (carry) {
       const bool check = op_carries_check(g, cfg.op.kind);
       c = carry_of(g, j, check);

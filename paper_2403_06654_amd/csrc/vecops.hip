@@ -568,6 +568,8 @@ static void launch_gs_small(const Geom& g, const SysSet<R>& S, int nsys, int nv,
     if (pr) prof->begin(10, s, (nv + 1) * fb);
     hipLaunchKernelGGL((k_mdot_s<R, NVH, H>), gr, dim3(256 * H), 0, s, S, nv, n, g.M);
     if (pr) prof->end(s);
+  } else if (pr) {
+    prof->tally(10);
   }
   if (pr) prof->begin(11, s, (nv + 2) * fb);
   hipLaunchKernelGGL((k_gs_update_s<R, NVH, H>), gr, dim3(256 * H), 0, s, S, nv, n, g.M, g.ntot_inv,

@@ -242,3 +242,33 @@ def test_removed_norms_belong_to_their_solve(cheb):
             assert info["rhs_null_norm"] == (x if cheb else pytest.approx(x, rel=1e-9))
     for g in grids:
         g.close()
+
+
+@pytest.mark.parametrize("shape,kind", [((32, 32, 32), "pressure"), ((64, 32), "pressure"), ((16, 32, 64), "helmholtz"),
+                                        ((32, 32, 32), "cg")])
+@pytest.mark.parametrize("precision", ["fp64", "fp32_refine"])
+def test_a_profile_changes_no_bit(shape, kind, precision):
+    """A timed solve runs the launches of a plain one: the same bits whatever
+    classes are timed, with the dots that an operator pass forms counted."""
+    from paper_2403_06654_amd.api import Grid
+    rho, f = smooth_density(shape, 7, 1.0, 6.0), workloads.band_limited(shape, 4, seed=8)
+    g = Grid(shape)
+    g.set_density(to_dev(rho))
+    fd = to_dev(np.stack([f, np.roll(f, 3, axis=0)])) if kind == "helmholtz" else to_dev(f)
+
+    def solve():
+        if kind == "helmholtz":
+            return g.solve_helmholtz(fd, 0.02, precision=precision)
+        return g.solve_pressure(fd, solver="cg" if kind == "cg" else "gmres", precision=precision)
+
+    want, plain = solve()
+    for classes in (True, 1 << 10, 1 << 11, (1 << 4) | (1 << 9)):
+        g.profile_read()
+        g.profile_enable(classes)
+        x, info = solve()
+        ms, cnt, _ = g.profile_read()
+        g.profile_enable(False)
+        assert bool((x == want).all()) and info["iterations"] == plain["iterations"]
+        if kind == "pressure" and (classes is True or classes == 1 << 10):
+            assert cnt[10] == plain["iterations"] and ms[10] == 0.0
+    g.close()
