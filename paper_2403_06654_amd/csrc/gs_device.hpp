@@ -72,6 +72,17 @@ __device__ __forceinline__ double sum_partials(const double* __restrict__ p, int
   return wave_sum(s);
 }
 
+// The halt flag where a block of the same launch may set it: one thread of a block
+// reads it, and the whole block goes by what it saw (through LDS, at a barrier).
+// Wavefronts that each read it could part: some would return, and the others would
+// go on past a barrier without what the first were to write for them.
+__device__ __forceinline__ int halt_now(const int* flag) {
+  return flag ? __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+}
+__device__ __forceinline__ void set_halt(DevState* st) {
+  __hip_atomic_store(&st->halt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Values to the host (one thread).
 __device__ __forceinline__ void post_mail(Mail* m, double a, double b, unsigned long long flags,
                                           unsigned long long seq) {
@@ -124,7 +135,7 @@ __device__ __forceinline__ bool rec_check_step(DevState* st, const RecState& s, 
   const double rn = n2 < 0.0 ? 0.0 : sqrt(n2);
   const bool bad = s.bad != 0;
   const bool halt = bad || !(n2 == n2) || rn / s.stop_bnorm <= s.stop_rtol || j >= s.jlast;
-  if (halt) st->halt = 1;
+  if (halt) set_halt(st);
   post_step(s.mail, s.run, j, rn, n2, bad, halt, 0);
   return halt;
 }
@@ -255,7 +266,7 @@ __device__ __forceinline__ void gs_givens(DevState* st, const GsState& s, const 
   const bool bad = s.bad || !k.finite || !isfinite(rr) || !isfinite(sr * s.g);
   const bool halt = bad || resid / s.stop_bnorm <= s.stop_rtol || j >= s.jlast;
   if (bad) st->bad = 1;
-  if (halt) st->halt = 1;
+  if (halt) set_halt(st);
   post_step(s.mail, s.run, j, resid, 0.0, bad, halt, nreorth);
 }
 

@@ -328,7 +328,10 @@ __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restri
   // path for a launch of one system and a batch)
   KSys* sy = block_sys<ColArgs>();
   const int* gate = sy->gate;
-  if (!SM && gate && *gate) return;  // the flag is written before the launch
+  // CHECK, ENDS: this launch's own extra block may set the flag (halt_now); in the
+  // others it was written before the launch
+  constexpr bool OWN = CHECK || ENDS;
+  if (!SM && !OWN && gate && *gate) return;
   const void* in0 = sy->in[0];
   const void* in1 = sy->in[1];
   const void* in2 = sy->in[2];
@@ -350,6 +353,11 @@ __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restri
   const int ob = CHECK || ENDS ? 0 : blockIdx.x / a.ntile, tile = CHECK || ENDS ? blockIdx.x : blockIdx.x % a.ntile;
   const int col = tile * TC + c;
   const bool ok = col < a.inner && !rotations;
+  // A block that sees the flag leaves its tile as it is: what follows a halted step
+  // reads neither the direction and the vector that this pass would complete nor
+  // its results.
+  __shared__ int halted;
+  if (OWN && rotations && gate && *gate) return;  // halted by an earlier launch
   const size_t base = (size_t)ob * L * a.inner + col;
   LdsCol<R> lds{lds_raw + (NG > 1 ? grp * TC * L : 0), c, TC};
   C2<R> reg[E];
@@ -507,13 +515,18 @@ __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restri
     GsState state{};
     DevState* st = CHECK ? gs->sys[blockIdx.y].st : nullptr;
     if (CHECK && threadIdx.x < 64) state = gs_state(st, nv, rotations);
-    if (gate && *gate) return;
+    if constexpr (OWN) {
+      if (threadIdx.x == 0) halted = halt_now(gate);
+    } else {
+      if (gate && *gate) return;
+    }
 #pragma unroll
     for (int i = 0; i < NTW; ++i)
       if (i * NT + (int)threadIdx.x < L) tw_lds[i * NT + threadIdx.x] = twr[i];
     if constexpr (CHECK) {
       fold_sums<NT / 64>(gs->sys[blockIdx.y].partial + kFoldHalf, gs->nb, nv + 1, gs->scale, cval);
       __syncthreads();
+      if (halted) return;
       if (threadIdx.x < 64) {
         const GsCheck k = gs_check(state, cval, nv, gs->tol);
         if (rotations) {
@@ -529,6 +542,7 @@ __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restri
       if (rotations) return;
     }
   } else {
+    if (OWN && threadIdx.x == 0) halted = halt_now(gate);
     for (int i = threadIdx.x; i < L; i += blockDim.x) tw_lds[i] = twtab[L + i];
   }
   if constexpr (ENDS) {
@@ -536,11 +550,11 @@ __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restri
     if (rotations) return;
   }
   __syncthreads();
+  if (ENDS && halted) return;
   const C2<R>* tw = tw_lds;
   // CHECK: the second pass on this tile.  Both groups hold the column and form
   // the same values; group 0 writes them back after its transform, when both
-  // have consumed their loads (a block that sees the halt flag of the rotations
-  // leaves the vector as it is: the vector that ends a cycle is never read).
+  // have consumed their loads.
   C2<R> kept[CHECK || (SM && ENDS) ? E : 1];
   if constexpr (SM && ENDS) {
     if (upd) {

@@ -518,18 +518,19 @@ __global__ __launch_bounds__(256 * H) void k_gs_update_s(SysSet<R> S, int nv, si
 
 // The orthogonality check in every block, the second pass over the vectors
 // that failed it, and in block 0 the Givens rotations and the stopping test.
-// (A block that starts after block 0 has set halt skips its part of the second
+// (A block that sees the halt flag of block 0 skips its part of the second
 // pass: the vector that ends a cycle is never read.)
 template <typename R, int NV>
 __global__ __launch_bounds__(256) void k_gs_finish(SysSet<R> S, int nv, size_t n, double tol, double scale) {
   const int sy = blockIdx.y;
   DevState* st = S.st[sy];
   __shared__ double val[NV + 1], cl[NV];
-  __shared__ int again;
-  if (st->halt) return;
+  __shared__ int again, halted;
   GsState gs{};
   if (threadIdx.x < 64) gs = gs_state(st, nv, blockIdx.x == 0);
-  fold_reduce<NV + 1, 4>(S.partial[sy] + kFoldHalf, gridDim.x, nv + 1, scale, val);
+  if (threadIdx.x == 0) halted = halt_now(&st->halt);
+  fold_reduce<NV + 1, 4>(S.partial[sy] + kFoldHalf, gridDim.x, nv + 1, scale, val);  // ends with a barrier
+  if (halted) return;
   GsCheck k{};
   if (threadIdx.x < 64) {
     k = gs_check(gs, val, nv, tol);

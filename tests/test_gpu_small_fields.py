@@ -272,3 +272,28 @@ def test_a_profile_changes_no_bit(shape, kind, precision):
         if kind == "pressure" and (classes is True or classes == 1 << 10):
             assert cnt[10] == plain["iterations"] and ms[10] == 0.0
     g.close()
+
+
+@pytest.mark.parametrize("shape,solver", [((32, 32, 32), "gmres"), ((64, 64), "gmres"), ((32, 32, 32), "cg"),
+                                          ((16, 128, 128), "cg"), ((64, 128, 64), "cg"), ((32, 32, 32), "rmr"),
+                                          ((64, 128, 64), "rmr")])
+def test_a_run_that_halts_leaves_nothing_behind(shape, solver):
+    """Solves of growing length on one grid, each ended on the device while the
+    next step is queued (by tolerance and by the iteration limit), give the bits
+    of a grid that solves each alone: what the blocks of the halting launch left
+    of the next step is not read again."""
+    from paper_2403_06654_amd.api import Grid
+    rho, f = smooth_density(shape, 9, 1.0, 3.0), workloads.band_limited(shape, 4, seed=10)
+    rd, fd = to_dev(rho), to_dev(f)
+    runs = [dict(rtol=10.0 ** -k) for k in (1, 2, 4, 7, 10)] + [dict(max_iter=m) for m in (1, 2, 5)]
+    g = Grid(shape)
+    g.set_density(rd)
+    for opts in runs:
+        h = Grid(shape)
+        h.set_density(rd)
+        want, iw = h.solve_pressure(fd, solver=solver, **opts)
+        h.close()
+        for _ in range(3):
+            p, info = g.solve_pressure(fd, solver=solver, **opts)
+            assert info["iterations"] == iw["iterations"] and bool((p == want).all())
+    g.close()
