@@ -143,18 +143,20 @@ __device__ __forceinline__ bool rec_check_step(DevState* st, const RecState& s, 
 // leading dimension of the column-major Hessenberg matrix
 __device__ __forceinline__ int ldh() { return kMaxRestart + 1; }
 
+// The larger of v and the value that the DPP pattern CTRL brings to this lane (v
+// itself where it brings none, and in the rows that ROWS leaves out)
 template <int CTRL, int ROWS>
 __device__ __forceinline__ double max_dpp(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, true);
+  const int vl = __double2loint(v), vh = __double2hiint(v);
+  const int lo = __builtin_amdgcn_update_dpp(vl, vl, CTRL, ROWS, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(vh, vh, CTRL, ROWS, 0xf, false);
   return fmax(v, __hiloint2double(hi, lo));
 }
 __device__ __forceinline__ double lane_value(double v, int lane) {  // lane: the same in the whole wavefront
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
                           __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
-// Largest of the wavefront's values, which are not negative (lanes that a DPP
-// pattern leaves out count as 0); a NaN is dropped.
+// Largest of the wavefront's values (all 64 lanes active); a NaN is dropped.
 __device__ __forceinline__ double wave_max(double v) {
   v = max_dpp<0x111, 0xf>(v);
   v = max_dpp<0x112, 0xf>(v);
