@@ -377,7 +377,7 @@ typedef struct {
 
 void vd_ns_default_params(vd_ns_params* p);
 /* VD_EINVAL for bad sizes or parameters; VD_ENOMEM.  The handle holds
- * 65 + 3 (restart + 1) fields of n^3 doubles (2.7 GB at 128^3 with
+ * 64 + 3 (restart + 1) fields of n^3 doubles (2.6 GB at 128^3 with
  * restart 30, 21 GB at 256^3) and a pressure grid. */
 vd_status vd_ns_create(vd_ns** out, int n, const vd_ns_params* prm, hipStream_t stream);
 vd_status vd_ns_destroy(vd_ns* h);

@@ -123,17 +123,11 @@ void ns_div(const Geom& g, const void* v, size_t stride, double c, void* out, hi
 // p += phi - (div grad)^-1 div v
 void ns_pressure(const Geom& g, const void* v, size_t stride, const void* phi, void* p, hipStream_t st);
 
-// out = (sum_t c_t in_t + (sum_t cd_t dv_t) / den) * mul (up to 6 and 3
-// terms; mul optional); out may alias an input.
+// out = sum_t c_t in_t (up to 3 terms); out may alias an input.
 struct LinArgs {
   int nt = 0;
-  const double* in[6] = {};
-  double c[6] = {};
-  int nd = 0;
-  const double* dv[3] = {};
-  double cd[3] = {};
-  const double* den = nullptr;
-  const double* mul = nullptr;
+  const double* in[3] = {};
+  double c[3] = {};
   double* out = nullptr;
   size_t n = 0;
 };

@@ -24,12 +24,6 @@ __global__ __launch_bounds__(kT) void k_lincomb(LinArgs a) {
   for (size_t e = blockIdx.x * (size_t)kT + threadIdx.x; e < a.n; e += (size_t)gridDim.x * kT) {
     double s = 0.0;
     for (int t = 0; t < a.nt; ++t) s += a.c[t] * a.in[t][e];
-    if (a.nd > 0) {
-      double q = 0.0;
-      for (int t = 0; t < a.nd; ++t) q += a.cd[t] * a.dv[t][e];
-      s += q / a.den[e];
-    }
-    if (a.mul) s *= a.mul[e];
     a.out[e] = s;
   }
 }
