@@ -357,7 +357,8 @@ __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restri
   // reads neither the direction and the vector that this pass would complete nor
   // its results.
   __shared__ int halted;
-  if (OWN && rotations && gate && *gate) return;  // halted by an earlier launch
+  int seen = 0;  // thread 0's reading, on its way until the block's first barrier
+  if (OWN && threadIdx.x == 0) seen = halt_now(gate);
   const size_t base = (size_t)ob * L * a.inner + col;
   LdsCol<R> lds{lds_raw + (NG > 1 ? grp * TC * L : 0), c, TC};
   C2<R> reg[E];
@@ -420,7 +421,7 @@ __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restri
     const double rzn = rec->cg ? sum_partials(part + kRedBlocks, rec->nb) * rec->scale : 0.0;
     if (rotations) {
       const double n2 = sum_partials(part, rec->nb) * rec->scale;
-      if (threadIdx.x == 0) {
+      if (threadIdx.x == 0 && !seen) {
         st->red[0] = n2;
         st->red[1] = rzn;
         if (!rec_check_step(st, s, n2) && rec->cg) cg_beta_step(st, s, rzn, rec->slot ^ 1);
@@ -515,16 +516,13 @@ __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restri
     GsState state{};
     DevState* st = CHECK ? gs->sys[blockIdx.y].st : nullptr;
     if (CHECK && threadIdx.x < 64) state = gs_state(st, nv, rotations);
-    if constexpr (OWN) {
-      if (threadIdx.x == 0) halted = halt_now(gate);
-    } else {
-      if (gate && *gate) return;
-    }
+    if (!OWN && gate && *gate) return;
 #pragma unroll
     for (int i = 0; i < NTW; ++i)
       if (i * NT + (int)threadIdx.x < L) tw_lds[i * NT + threadIdx.x] = twr[i];
     if constexpr (CHECK) {
       fold_sums<NT / 64>(gs->sys[blockIdx.y].partial + kFoldHalf, gs->nb, nv + 1, gs->scale, cval);
+      if (threadIdx.x == 0) halted = seen;
       __syncthreads();
       if (halted) return;
       if (threadIdx.x < 64) {
@@ -542,12 +540,12 @@ __device__ __forceinline__ void col_pass(const ColArgs& a, const C2<R>* __restri
       if (rotations) return;
     }
   } else {
-    if (OWN && threadIdx.x == 0) halted = halt_now(gate);
     for (int i = threadIdx.x; i < L; i += blockDim.x) tw_lds[i] = twtab[L + i];
   }
   if constexpr (ENDS) {
     end_step();
     if (rotations) return;
+    if (threadIdx.x == 0) halted = seen;
   }
   __syncthreads();
   if (ENDS && halted) return;
