@@ -23,7 +23,7 @@ import sys
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 sys.path.insert(0, ROOT)
 
-from paper_2403_06654_amd.traffic import class_patterns  # noqa: E402
+from paper_2403_06654_amd.traffic import class_name, class_patterns  # noqa: E402
 
 GATE_US = 10.0
 
@@ -39,7 +39,8 @@ def class_durations(trace, patterns):
     out = {}
     for name, pat in patterns.items():
         rx = re.compile(pat)
-        d = [(int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3 for r in trace if rx.match(r["Kernel_Name"])]
+        d = [(int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3 for r in trace
+             if rx.match(class_name(r["Kernel_Name"]))]
         work = [x for x in d if x >= GATE_US]
         out[name] = (work, len(d) - len(work))
     return out
@@ -96,8 +97,9 @@ def render(prof_dir, bench_line, n, title, command, top=20):
 
 
 def gemm_shapes(trace):
-    """The Chebyshev contractions (k_gemm) by launch shape: one 16 x 16 tile
-    of C per block, so the grid gives M (rows, 16 per block row) and N."""
+    """The Chebyshev contractions (k_gemm) by launch shape: one tile of C per
+    block, 16 rows and 16 or 32 columns (the kernel's last template argument:
+    column tiles of 16), so the grid gives M and N."""
     groups = {}
     for r in trace:
         name = r["Kernel_Name"]

@@ -34,3 +34,32 @@ def test_class_patterns_follow_the_grid():
     import re
     assert re.match(p5["gmres gram-schmidt dots (k_mdot)"], "void vd::k_mdot<double, 16>(x)")
     assert not re.match(p5["gmres gram-schmidt dots (k_mdot)"], "void vd::k_mdot<double, 1>(x)")
+
+
+def test_every_class_is_a_kernel_of_the_library():
+    """The classes of both grids that counter passes are taken on match a kernel
+    of the built library each, in the configuration of large fields and no other."""
+    import re
+    import shutil
+    import subprocess
+    import pytest
+    from paper_2403_06654_amd import build
+    if shutil.which("nm") is None:
+        pytest.skip("nm is not installed")
+    out = subprocess.run(["nm", "-C", build.OUT], capture_output=True, text=True, check=True).stdout
+    names = {"void vd::" + m for m in re.findall(r"vd::__device_stub__(k_[a-z0-9_]+<.*)", out)}
+    assert names
+    for n in (256, 512):
+        for cls, pat in traffic.class_patterns(n).items():
+            hits = [x for x in names if re.match(pat, traffic.class_name(x))]
+            assert hits, (n, cls)
+            assert not any(x.split("(")[0].endswith(", true>") for x in hits), (n, cls, hits)
+
+
+def test_counters_of_passes_in_the_large_field_configuration():
+    row = "void vd::k_row<128, double, 2, false>(vd::RowArgs, ...)"
+    small = "void vd::k_row<128, double, 2, true>(vd::RowArgs, ...)"
+    F = [_row("__amd_rocclr_copyBuffer", 1048576), _row(row, 400.0), _row(small, 7.0)]
+    W = [_row("__amd_rocclr_copyBuffer", 1048576), _row(row, 200.0), _row(small, 7.0)]
+    out = traffic.summarize(F, W, "abc")
+    assert out["per_launch_bytes"] == {"pressure x pass (k_row ROW_P)": 600 * 1024}
