@@ -732,11 +732,15 @@ SolveOut solve_spectral(vd_grid* G, const vd_solve_opts& o, const OpParams& op, 
 // Device state, partials and mailboxes of system k (k = 0: the grid's own).
 void ensure_systems(vd_grid* G, int n) {
   for (int k = 1; k < n; ++k) {
-    if (G->dstx[k]) continue;
-    ck(hipMalloc(&G->dstx[k], sizeof(DevState)));
-    ck(hipMalloc(&G->partialx[k], nred_partial() * sizeof(double)));
+    if (G->mailx[k]) continue;  // made last: an earlier call may have run out of memory before
+    if (!G->dstx[k]) ck(hipMalloc(&G->dstx[k], sizeof(DevState)));
+    if (!G->partialx[k]) ck(hipMalloc(&G->partialx[k], nred_partial() * sizeof(double)));
     ck(hipMemsetAsync(G->dstx[k], 0, sizeof(DevState), G->st));
-    ck(make_mail(&G->mailx[k], G->dstx[k], G->st));
+    Mail* mail = nullptr;
+    const hipError_t e = make_mail(&mail, G->dstx[k], G->st);
+    if (e != hipSuccess && mail) hipHostFree(mail);
+    ck(e);
+    G->mailx[k] = mail;
   }
 }
 DevState* sys_dst(vd_grid* G, int k) { return k ? G->dstx[k] : G->dst; }
