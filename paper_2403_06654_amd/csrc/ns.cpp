@@ -376,7 +376,12 @@ double viscous_residual(vd_ns* h, const double* b, const double* x, double* r) {
 
 // Right-preconditioned GMRES(m) on A x = x - dt/2 zeta(rho^(n+1/2), x) = b
 // (stacks of three spectra) from the initial guess x0, which is kept.  The steps
-// are queued one ahead of the host, as in vdsolve.cpp.
+// are queued one ahead of the host, as in vdsolve.cpp, and take the second
+// Gram-Schmidt pass where the check asks for it (a cosine above 1e-8, orth_tol), not
+// always: the stopping test is on the true residual, and over 32^3 to 128^3, Re = 1
+// to 500, restart 10 and 30 and up to 44 steps a solve, solves with two passes
+// always took the same steps to the same residuals (three digits) and to fields
+// within 3e-13.
 void solve_viscous(vd_ns* h, const double* b, const double* x0, double* x, int& iters, int& status, double& relres) {
   const size_t n3 = 3 * h->N;
   const int m = h->prm.restart;

@@ -94,7 +94,8 @@ struct Col512 {
 // x 6.2 -> 4.2, y-forward 7.9 -> 3.8, z-last 6.4 -> 4.0; x pass of a 257 x 512
 // wall grid 7.6 -> 5.5.  Larger fields keep the shapes below, which are chosen
 // for bandwidth: with the limit at 2^20 slots a 64 x 128 x 256 FP32+refine
-// solve took 3481 us instead of 3417 (128^3 FP64 K: 1888 instead of 1953).
+// solve took 3481 us instead of 3417.  (128^3 FP64 K took 1888 instead of 1953: the
+// best limit depends on the type and lies between, where it is not measured.)
 constexpr size_t kSmallField = kFoldElems;
 
 constexpr int col_groups(int mode) {

@@ -8,7 +8,8 @@
 //
 // Methods (Sec. 3.1 solver list):
 //   GMRES(m)  right preconditioned (x = M^-1 V y), classical Gram-Schmidt
-//             applied twice, Givens rotations, restart every m steps; the
+//             with a measured orthogonality check and a second pass where
+//             it fails, Givens rotations, restart every m steps; the
 //             true FP64 residual gates termination at the end of a cycle.
 //   CG        preconditioned conjugate gradient on the symmetric operators.
 //   RMR       Richardson iteration with the minimal-residual step length:

@@ -2,8 +2,8 @@
 //
 // Sec. 3.1, eq. VDINSE.Vrho: V_rho u = u - (a / rho)(D2 u + rho'' u + rho' D1 u)
 // = b, right-preconditioned by V^-1 = (I - a D2)^-1 (eq. VDINSE.V), solved by
-// GMRES(m) (classical Gram-Schmidt applied twice) or the Richardson
-// minimal-residual iteration.
+// GMRES(m) (classical Gram-Schmidt with a measured check, and a second pass where
+// it fails), CG or the Richardson minimal-residual iteration.
 //
 // Every system of a batch shares the differentiation matrices and V^-1, so a
 // matrix-vector product over a group of 16 systems is a dense product
@@ -678,7 +678,7 @@ __global__ __launch_bounds__(64 * NW, (kVisc1dWaves<TPW, NW, KIND>)) void k_visc
       vld(X, wx, l);
       scatter(X, true);
     } else {
-      // right-preconditioned GMRES(m), classical Gram-Schmidt applied twice
+      // right-preconditioned GMRES(m), classical Gram-Schmidt with a measured check
       double* wbas = W + 5 * L::V;                 // [m + 1] tiled basis vectors
       double* wH = wbas + (size_t)(m + 1) * L::V;  // [m][m + 1][kG]: column j, row i
       double* wcs = wH + (size_t)(m + 1) * m * kG; // [m][kG]
