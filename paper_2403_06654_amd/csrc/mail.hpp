@@ -11,7 +11,9 @@
 namespace vd {
 
 // Whether mailbox m holds the whole of post number seq.  The words arrive in any
-// order; one that is still the last post's does not fit the check.
+// order; one that is still the last post's does not fit the check.  A post orders
+// nothing but its own words: whatever else a kernel stores to pinned memory is
+// read after the stream has been waited for.
 inline bool mail_here(const Mail* m, unsigned long long seq) {
   if (__atomic_load_n(&m->seq, __ATOMIC_ACQUIRE) != seq) return false;
   unsigned long long w[2];
