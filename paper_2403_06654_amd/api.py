@@ -151,6 +151,10 @@ def lib():
     if _LIB is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(f"{LIB_PATH} is missing: build it with `python -m paper_2403_06654_amd.build`")
+        # torch first: it brings a HIP runtime of its own, which the library then
+        # uses too.  In the other order a process holds two runtimes, and the
+        # library's allocations fail once torch has set up the device.
+        import torch  # noqa: F401
         L = ctypes.CDLL(LIB_PATH)
         for name, (res, args) in _SIGS.items():
             fn = getattr(L, name)

@@ -5,6 +5,8 @@ import ctypes
 import math
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -27,6 +29,15 @@ def test_library_exports_every_declared_symbol():
     for n in names:
         assert hasattr(L, n), n
     assert set(names) == set(api._SIGS), "binding and header disagree"
+
+
+def test_one_hip_runtime_whichever_is_loaded_first():
+    """The library opened before torch is imported must share torch's HIP runtime."""
+    code = ("from paper_2403_06654_amd import api; api.lib(); import torch; "
+            "print(len({l.split()[-1] for l in open('/proc/self/maps') if 'libamdhip64' in l}))")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr
+    assert int(r.stdout) == 1
 
 
 def test_defaults():
